@@ -283,117 +283,163 @@ __global__ __launch_bounds__(kBlock) void k_validate(const ItemDev* items, int32
 
 // ----------------------------------------------------------------------------- scans
 
-// Exclusive scans (u32 in, u64 out, out[n] = total) by reduce / spine / down-sweep.
-__global__ __launch_bounds__(kBlock) void k_scan_reduce(const uint32_t* in0, const uint32_t* in1,
-                                                        const uint64_t* n_dev, uint64_t n_max,
-                                                        uint64_t* bsum, uint64_t nb_cap) {
-  __shared__ uint64_t red[kNW + 1];
+// Exclusive scans (u32 in, u64 out, out[n] = total) in chunks of kScanBlock
+// entries, four consecutive entries per thread (16-byte loads and stores).
+// Two launches: the chunk sums, then the down-sweep, whose workgroups add up
+// the sums before their own chunk. Arrays of more than kSpineBlocks chunks
+// take a launch between the two that scans the sums.
+// Latency-bound at the sizes most calls have (20 to 100 chunks: about 5 us a
+// launch, of which 4 are the launch itself), so what counts is the number of
+// launches and of dependent steps; at 4,096 chunks it moves 24 bytes per entry.
+constexpr int kScanThreads = 1024;
+static_assert(kScanBlock == 4 * kScanThreads, "four entries per thread");
+// Up to here a down-sweep workgroup reads at most four sums per thread.
+constexpr uint64_t kSpineBlocks = 4 * (uint64_t)kScanThreads;
+
+typedef uint32_t scan4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint64_t scan2 __attribute__((ext_vector_type(2)));  // 16-byte aligned
+
+__device__ __forceinline__ scan4 scan_load(const uint32_t* in, uint64_t t0, uint64_t n) {
+  scan4 v = scan4{0u, 0u, 0u, 0u};
+  if (t0 + 4 <= n) {
+    v = *(const GMEM scan4*)gm(in + t0);
+  } else {
+    if (t0 < n) v.x = gm(in)[t0];
+    if (t0 + 1 < n) v.y = gm(in)[t0 + 1];
+    if (t0 + 2 < n) v.z = gm(in)[t0 + 2];
+  }
+  return v;
+}
+__device__ __forceinline__ uint64_t scan_sum(scan4 v) {
+  return (uint64_t)v.x + v.y + ((uint64_t)v.z + v.w);
+}
+// The prefixes of entries t0..t0+3 (out is 16-byte aligned, t0 a multiple of 4).
+__device__ __forceinline__ void scan_store(uint64_t* out, uint64_t t0, uint64_t n, scan4 v, uint64_t ex) {
+  const uint64_t e1 = ex + v.x, e2 = e1 + v.y, e3 = e2 + v.z;
+  if (t0 + 4 <= n) {
+    GMEM scan2* const o = (GMEM scan2*)gm(out + t0);
+    o[0] = scan2{ex, e1};
+    o[1] = scan2{e2, e3};
+  } else {
+    if (t0 < n) gm(out)[t0] = ex;
+    if (t0 + 1 < n) gm(out)[t0 + 1] = e1;
+    if (t0 + 2 < n) gm(out)[t0 + 2] = e2;
+  }
+  if (t0 < n && n <= t0 + 4) gm(out)[n] = e3 + v.w;  // (entries past n are zero)
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const uint32_t* in0, const uint32_t* in1,
+                                                              const uint64_t* n_dev, uint64_t n_max,
+                                                              uint64_t* bsum, uint64_t nb_cap) {
+  __shared__ uint64_t red[2][kScanThreads / kWave];
   const uint64_t n = n_dev ? min(*n_dev, n_max) : n_max;
   const uint64_t lo = (uint64_t)blockIdx.x * kScanBlock;
   if (lo >= n) return;
-  const uint64_t hi = min(n, lo + kScanBlock);
-  uint64_t s0 = 0, s1 = 0;
-  for (uint64_t i = lo + threadIdx.x; i < hi; i += kBlock) {
-    s0 += in0[i];
-    if (in1) s1 += in1[i];
-  }
-  uint64_t t0, t1;
-  block_excl_scan<kNW>(s0, red, t0);
-  block_excl_scan<kNW>(s1, red, t1);
+  const uint64_t t0 = lo + 4 * (uint64_t)threadIdx.x;
+  const scan4 v0 = scan_load(in0, t0, n);
+  scan4 v1 = scan4{0u, 0u, 0u, 0u};
+  if (in1) v1 = scan_load(in1, t0, n);
+  uint64_t t, u;
+  block_excl_scan<kScanThreads / kWave>(scan_sum(v0), red[0], t);
+  block_excl_scan<kScanThreads / kWave>(scan_sum(v1), red[1], u);
   if (threadIdx.x == 0) {
-    bsum[blockIdx.x] = t0;
-    bsum[nb_cap + blockIdx.x] = t1;
+    bsum[blockIdx.x] = t;
+    bsum[nb_cap + blockIdx.x] = u;
   }
 }
 
-__global__ __launch_bounds__(1024) void k_scan_spine(const uint64_t* n_dev, uint64_t n_max,
-                                                     uint64_t* bsum, uint64_t nb_cap,
-                                                     uint64_t* out0, uint64_t* out1) {
-  __shared__ uint64_t red[1024 / kWave + 1];
+__global__ __launch_bounds__(kScanThreads) void k_scan_spine(const uint64_t* n_dev, uint64_t n_max,
+                                                             uint64_t* bsum, uint64_t nb_cap, int narr) {
+  __shared__ uint64_t red[kScanThreads / kWave];
   const uint64_t n = n_dev ? min(*n_dev, n_max) : n_max;
   const uint64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  for (int arr = 0; arr < (out1 ? 2 : 1); ++arr) {
+  for (int arr = 0; arr < narr; ++arr) {
     uint64_t* b = bsum + (uint64_t)arr * nb_cap;
     uint64_t carry = 0;
-    for (uint64_t base = 0; base < nb; base += 1024) {
+    for (uint64_t base = 0; base < nb; base += kScanThreads) {
       const uint64_t i = base + threadIdx.x;
       const uint64_t v = i < nb ? b[i] : 0;
       uint64_t tot;
-      const uint64_t ex = block_excl_scan<1024 / kWave>(v, red, tot);
+      const uint64_t ex = block_excl_scan<kScanThreads / kWave>(v, red, tot);
       if (i < nb) b[i] = carry + ex;
       carry += tot;
     }
-    if (threadIdx.x == 0) (arr == 0 ? out0 : out1)[n] = carry;
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_down(const uint32_t* in0, uint64_t* out0,
-                                                      const uint32_t* in1, uint64_t* out1,
-                                                      const uint64_t* n_dev, uint64_t n_max,
-                                                      const uint64_t* bsum, uint64_t nb_cap) {
-  __shared__ uint64_t red[kNW + 1];
-  constexpr int kPer = kScanBlock / kBlock;
+// spined: bsum holds the prefixes of the chunk sums, else the sums.
+__global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in0, uint64_t* out0,
+                                                            const uint32_t* in1, uint64_t* out1,
+                                                            const uint64_t* n_dev, uint64_t n_max,
+                                                            const uint64_t* bsum, uint64_t nb_cap,
+                                                            int spined) {
+  __shared__ uint64_t red[2][kScanThreads / kWave];
   const uint64_t n = n_dev ? min(*n_dev, n_max) : n_max;
   const uint64_t lo = (uint64_t)blockIdx.x * kScanBlock;
-  if (lo >= n) return;
+  if (lo >= n) {
+    if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+      out0[0] = 0;
+      if (out1) out1[0] = 0;
+    }
+    return;
+  }
+  const uint64_t t0 = lo + 4 * (uint64_t)threadIdx.x;
   for (int arr = 0; arr < (in1 ? 2 : 1); ++arr) {
-    const uint32_t* in = arr ? in1 : in0;
-    uint64_t* out = arr ? out1 : out0;
-    const uint64_t base = bsum[(uint64_t)arr * nb_cap + blockIdx.x];
-    const uint64_t t0 = lo + (uint64_t)threadIdx.x * kPer;
-    uint32_t v[kPer];
-    uint64_t s = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      v[j] = (t0 + j < n) ? in[t0 + j] : 0u;
-      s += v[j];
+    const scan4 v = scan_load(arr ? in1 : in0, t0, n);
+    const uint64_t* const b = bsum + (uint64_t)arr * nb_cap;
+    uint64_t base;
+    if (spined) {
+      base = b[blockIdx.x];
+    } else {
+      uint64_t part = 0;
+      for (uint64_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) part += b[i];
+      block_excl_scan<kScanThreads / kWave>(part, red[0], base);
     }
     uint64_t tot;
-    uint64_t ex = block_excl_scan<kNW>(s, red, tot) + base;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      if (t0 + j < n) out[t0 + j] = ex;
-      ex += v[j];
-    }
+    const uint64_t ex = block_excl_scan<kScanThreads / kWave>(scan_sum(v), red[1], tot) + base;
+    scan_store(arr ? out1 : out0, t0, n, v, ex);
   }
 }
 
-// The three kernels above in one workgroup, for arrays of at most
-// kSmallScan entries: the carry runs through the kScanBlock chunks in order,
-// which costs less than two more launches while the array is this short.
-constexpr uint64_t kSmallScan = 4 * (uint64_t)kScanBlock;
+// Both steps in one workgroup, for arrays of at most kSmallScan entries: the
+// carry runs through the kScanBlock chunks in order, the next chunk's loads
+// issued before the current one is scanned, which costs less than another
+// launch while the array is this short.
+constexpr uint64_t kSmallScan = 2 * (uint64_t)kScanBlock;
 
-__global__ __launch_bounds__(1024) void k_scan_small(const uint32_t* in0, uint64_t* out0,
-                                                     const uint32_t* in1, uint64_t* out1,
-                                                     const uint64_t* n_dev, uint64_t n_max) {
-  __shared__ uint64_t red[1024 / kWave + 1];
-  constexpr int kPer = kScanBlock / 1024;
+__global__ __launch_bounds__(kScanThreads) void k_scan_small(const uint32_t* in0, uint64_t* out0,
+                                                             const uint32_t* in1, uint64_t* out1,
+                                                             const uint64_t* n_dev, uint64_t n_max) {
+  __shared__ uint64_t red[2][kScanThreads / kWave];
   const uint64_t n = n_dev ? min(*n_dev, n_max) : n_max;
-  for (int arr = 0; arr < (out1 ? 2 : 1); ++arr) {
-    const uint32_t* in = arr ? in1 : in0;
-    uint64_t* out = arr ? out1 : out0;
-    uint64_t carry = 0;
-    for (uint64_t lo = 0; lo < n; lo += kScanBlock) {
-      const uint64_t t0 = lo + (uint64_t)threadIdx.x * kPer;
-      uint32_t v[kPer];
-      uint64_t sum = 0;
-#pragma unroll
-      for (int j = 0; j < kPer; ++j) {
-        v[j] = (in && t0 + j < n) ? in[t0 + j] : 0u;
-        sum += v[j];
-      }
-      uint64_t tot;
-      uint64_t ex = block_excl_scan<1024 / kWave>(sum, red, tot) + carry;
-      if (in) {
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-          if (t0 + j < n) out[t0 + j] = ex;
-          ex += v[j];
-        }
-      }
-      carry += tot;
+  const uint64_t t0 = 4 * (uint64_t)threadIdx.x;
+  scan4 c0 = scan4{0u, 0u, 0u, 0u}, c1 = c0;
+  if (in0) c0 = scan_load(in0, t0, n);
+  if (in1) c1 = scan_load(in1, t0, n);
+  uint64_t carry0 = 0, carry1 = 0;
+  for (uint64_t lo = 0; lo < n; lo += kScanBlock) {
+    scan4 n0 = scan4{0u, 0u, 0u, 0u}, n1 = n0;
+    if (lo + kScanBlock < n) {
+      if (in0) n0 = scan_load(in0, lo + kScanBlock + t0, n);
+      if (in1) n1 = scan_load(in1, lo + kScanBlock + t0, n);
     }
-    if (threadIdx.x == 0) out[n] = carry;
+    uint64_t tot;
+    if (in0) {
+      const uint64_t ex = block_excl_scan<kScanThreads / kWave>(scan_sum(c0), red[0], tot) + carry0;
+      scan_store(out0, lo + t0, n, c0, ex);
+      carry0 += tot;
+    }
+    if (in1) {
+      const uint64_t ex = block_excl_scan<kScanThreads / kWave>(scan_sum(c1), red[1], tot) + carry1;
+      scan_store(out1, lo + t0, n, c1, ex);
+      carry1 += tot;
+    }
+    c0 = n0;
+    c1 = n1;
+  }
+  if (n == 0 && threadIdx.x == 0) {
+    out0[0] = 0;
+    if (out1) out1[0] = 0;
   }
 }
 
@@ -2498,22 +2544,20 @@ hipError_t launch_validate(const ItemDev* items, uint32_t n_items, uint64_t max_
 hipError_t launch_scan(const uint32_t* in0, uint64_t* out0, const uint32_t* in1, uint64_t* out1,
                        const uint64_t* n_dev, uint64_t n_max, uint64_t* block_sums, hipStream_t s) {
   if (n_max <= G::kSmallScan) {
-    hipLaunchKernelGGL(G::k_scan_small, dim3(1), dim3(1024), 0, s, in0, out0, in1, out1, n_dev,
-                       n_max);
+    hipLaunchKernelGGL(G::k_scan_small, dim3(1), dim3(G::kScanThreads), 0, s, in0, out0, in1, out1,
+                       n_dev, n_max);
     return hipGetLastError();
   }
   const uint64_t nb = (n_max + kScanBlock - 1) / kScanBlock;
   const uint64_t cap = nb + 1;
-  if (nb) {
-    hipLaunchKernelGGL(G::k_scan_reduce, grid1(nb), dim3(G::kBlock), 0, s, in0, in1, n_dev, n_max,
-                       block_sums, cap);
-  }
-  hipLaunchKernelGGL(G::k_scan_spine, dim3(1), dim3(1024), 0, s, n_dev, n_max, block_sums, cap, out0,
-                     out1);
-  if (nb) {
-    hipLaunchKernelGGL(G::k_scan_down, grid1(nb), dim3(G::kBlock), 0, s, in0, out0, in1, out1, n_dev,
-                       n_max, block_sums, cap);
-  }
+  const int spined = nb > G::kSpineBlocks ? 1 : 0;
+  hipLaunchKernelGGL(G::k_scan_reduce, grid1(nb), dim3(G::kScanThreads), 0, s, in0, in1, n_dev,
+                     n_max, block_sums, cap);
+  if (spined)
+    hipLaunchKernelGGL(G::k_scan_spine, dim3(1), dim3(G::kScanThreads), 0, s, n_dev, n_max,
+                       block_sums, cap, in1 ? 2 : 1);
+  hipLaunchKernelGGL(G::k_scan_down, grid1(nb), dim3(G::kScanThreads), 0, s, in0, out0, in1, out1,
+                     n_dev, n_max, block_sums, cap, spined);
   return hipGetLastError();
 }
 

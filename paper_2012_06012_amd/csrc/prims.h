@@ -33,14 +33,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
   return v;
 }
 
-// Inclusive wave scan of a 64-bit value (cross-lane shuffles).
+// Inclusive wave scan of a 64-bit value: the same DPP steps on both words.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRows, 0xf, false);
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
 __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-  const uint32_t l = lane_id();
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint64_t u = __shfl_up(v, o, kWave);
-    if (l >= (uint32_t)o) v += u;
-  }
+  v += dpp_u64<0x111, 0xf>(v);  // row_shr:1
+  v += dpp_u64<0x112, 0xf>(v);  // row_shr:2
+  v += dpp_u64<0x114, 0xf>(v);  // row_shr:4
+  v += dpp_u64<0x118, 0xf>(v);  // row_shr:8
+  v += dpp_u64<0x142, 0xa>(v);  // row_bcast:15
+  v += dpp_u64<0x143, 0xc>(v);  // row_bcast:31
   return v;
 }
 
@@ -50,30 +56,27 @@ __device__ __forceinline__ uint64_t wave_incl_scan(uint64_t v) { return wave_inc
 template <class T>
 __device__ __forceinline__ T wave_bcast(T v, int lane) { return __shfl(v, lane, kWave); }
 
-// Exclusive scan over a workgroup of NW waves. `scratch` holds NW + 1 values.
-// Every thread of the workgroup must call it. Returns the exclusive prefix;
-// `total` receives the workgroup total.
+// Exclusive scan over a workgroup of NW waves. `scratch` holds at least NW
+// values. Every thread of the workgroup must call it. Returns the exclusive
+// prefix; `total` receives the workgroup total. Every thread adds up the wave
+// totals itself (broadcast LDS reads in flight together): no serial pass by
+// one thread and a barrier less.
 template <int NW, class T>
 __device__ __forceinline__ T block_excl_scan(T v, T* scratch, T& total) {
   const T inc = wave_incl_scan(v);
   const int w = threadIdx.x / kWave;
   if (lane_id() == kWave - 1) scratch[w] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T a = 0;
+  T before = 0, all = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      T t = scratch[i];
-      scratch[i] = a;
-      a += t;
-    }
-    scratch[NW] = a;
+  for (int i = 0; i < NW; ++i) {
+    const T t = scratch[i];
+    if (i < w) before += t;
+    all += t;
   }
+  total = all;
   __syncthreads();
-  total = scratch[NW];
-  const T r = inc - v + scratch[w];
-  __syncthreads();
-  return r;
+  return inc - v + before;
 }
 
 // Lanes of the wave whose `digit` equals the calling lane's digit, among the
