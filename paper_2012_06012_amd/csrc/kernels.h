@@ -131,6 +131,10 @@ hipError_t launch_validate(const ItemDev* items, uint32_t n_items, uint64_t max_
 hipError_t launch_scan(const uint32_t* in0, uint64_t* out0, const uint32_t* in1, uint64_t* out1,
                        const uint64_t* n_dev, uint64_t n_max, uint64_t* block_sums,
                        hipStream_t s);
+// out[k] = w * (in[0] + ... + in[k-1]) for k = 0..n, as offsets of width ow
+// (4 or 8); block_sums as for launch_scan.
+hipError_t launch_scan_offsets(const uint32_t* in, uint64_t n, uint32_t w, int ow, void* out,
+                               uint64_t* block_sums, hipStream_t s);
 // Per-cell sort key and carried value of a view operation (LocalTranspose or
 // ViewSwap, Section 3) on one item whose bounds are already on the device.
 struct ViewArgs {

@@ -401,6 +401,43 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_down(const uint32_t* in0,
   }
 }
 
+// The down-sweep of mgt_counts_to_offsets: the prefixes times w go straight to
+// the caller's offsets of width ow (element aligned), out[n] = total.
+__global__ __launch_bounds__(kScanThreads) void k_scan_offsets(const uint32_t* in, uint64_t n, uint64_t w,
+                                                               int ow, void* out, const uint64_t* bsum,
+                                                               int spined) {
+  typedef uint64_t off2 __attribute__((ext_vector_type(2), aligned(8)));
+  __shared__ uint64_t red[2][kScanThreads / kWave];
+  const uint64_t t0 = (uint64_t)blockIdx.x * kScanBlock + 4 * (uint64_t)threadIdx.x;
+  const scan4 v = scan_load(in, t0, n);
+  uint64_t base = 0;
+  if (spined) {
+    base = bsum[blockIdx.x];
+  } else if (blockIdx.x) {
+    uint64_t part = 0;
+    for (uint64_t i = threadIdx.x; i < blockIdx.x; i += kScanThreads) part += bsum[i];
+    block_excl_scan<kScanThreads / kWave>(part, red[0], base);
+  }
+  uint64_t tot;
+  const uint64_t ex = block_excl_scan<kScanThreads / kWave>(scan_sum(v), red[1], tot) + base;
+  const uint64_t e0 = ex * w, e1 = e0 + v.x * w, e2 = e1 + v.y * w, e3 = e2 + v.z * w;
+  if (t0 + 4 <= n) {
+    if (ow == 4) {
+      *(GMEM scan4*)gm((uint32_t*)out + t0) = scan4{(uint32_t)e0, (uint32_t)e1, (uint32_t)e2, (uint32_t)e3};
+    } else {
+      GMEM off2* const o = (GMEM off2*)gm((uint64_t*)out + t0);
+      o[0] = off2{e0, e1};
+      o[1] = off2{e2, e3};
+    }
+  } else {
+    if (t0 < n) st_off(out, t0, (int64_t)e0, ow);
+    if (t0 + 1 < n) st_off(out, t0 + 1, (int64_t)e1, ow);
+    if (t0 + 2 < n) st_off(out, t0 + 2, (int64_t)e2, ow);
+  }
+  // (entries past n are zero, so the last prefix is the total)
+  if ((t0 < n && n <= t0 + 4) || (n == 0 && t0 == 0)) st_off(out, n, (int64_t)(e3 + v.w * w), ow);
+}
+
 // Both steps in one workgroup, for arrays of at most kSmallScan entries: the
 // carry runs through the kScanBlock chunks in order, the next chunk's loads
 // issued before the current one is scanned, which costs less than another
@@ -2558,6 +2595,21 @@ hipError_t launch_scan(const uint32_t* in0, uint64_t* out0, const uint32_t* in1,
                        block_sums, cap, in1 ? 2 : 1);
   hipLaunchKernelGGL(G::k_scan_down, grid1(nb), dim3(G::kScanThreads), 0, s, in0, out0, in1, out1,
                      n_dev, n_max, block_sums, cap, spined);
+  return hipGetLastError();
+}
+
+hipError_t launch_scan_offsets(const uint32_t* in, uint64_t n, uint32_t w, int ow, void* out,
+                               uint64_t* block_sums, hipStream_t s) {
+  const uint64_t nb = n ? (n + kScanBlock - 1) / kScanBlock : 1;
+  const int spined = nb > G::kSpineBlocks ? 1 : 0;
+  if (nb > 1)  // one chunk needs no sums
+    hipLaunchKernelGGL(G::k_scan_reduce, grid1(nb), dim3(G::kScanThreads), 0, s, in, nullptr, nullptr,
+                       n, block_sums, nb + 1);
+  if (spined)
+    hipLaunchKernelGGL(G::k_scan_spine, dim3(1), dim3(G::kScanThreads), 0, s, nullptr, n, block_sums,
+                       nb + 1, 1);
+  hipLaunchKernelGGL(G::k_scan_offsets, grid1(nb), dim3(G::kScanThreads), 0, s, in, n, (uint64_t)w, ow,
+                     out, block_sums, spined);
   return hipGetLastError();
 }
 

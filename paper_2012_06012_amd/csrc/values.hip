@@ -31,52 +31,178 @@ __device__ __forceinline__ void st_o(void* p, uint64_t i, uint64_t v, int ow) {
 __device__ __forceinline__ uint64_t gtid() { return (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ uint64_t gstride() { return (uint64_t)gridDim.x * blockDim.x; }
 
-// 1 where a cell starts a run of equal columns inside its row: the first
-// cell, a column change (row starts are added by k_row_heads).
-__global__ __launch_bounds__(kB) void k_heads(const int32_t* col, uint64_t nnz, uint32_t* h) {
-  for (uint64_t k = gtid(); k < nnz; k += gstride())
-    h[k] = (k == 0 || gm(col)[k] != gm(col)[k - 1]) ? 1u : 0u;
+// Coalescing. Heads (cells that start a run of equal columns inside their
+// row) are kept as a bitmap of one 64-bit word per 64 cells, so the flags and
+// their scan move 1/8 byte and 1/16 byte per cell in place of 4 and 8:
+//   k_heads      column changes, one ballot word per wave round (reads col)
+//   k_row_heads  row starts, ORed in
+//   k_head_sums  heads per chunk of kChunkWords words
+//   k_head_pref  heads before every word (the chunk's base is the sum of the
+//                earlier chunks), the number of output cells m and the last
+//                payload offset
+//   k_emit       heads to their slots, run lengths, output row offsets
+// The bound is memory: col twice, the payload offsets once (every line holds
+// a head unless runs are long), the outputs once. 24 M cells in runs of two
+// on average (8-byte offsets): 346 -> 144 us against the form before (4-byte
+// flags, 8-byte slots and a 4-byte array of run starts, all in memory); k_emit
+// takes 81 of them, at 5.7 TB/s.
+constexpr int kChunkWords = 4 * kB;  // words per workgroup of k_head_sums / k_head_pref
+
+__device__ __forceinline__ uint32_t low_bits(uint64_t m, uint32_t l) {  // set bits of m below l
+  return (uint32_t)__popcll(m & ((1ull << l) - 1ull));
+}
+
+__global__ __launch_bounds__(kB) void k_heads(const int32_t* col, uint64_t nnz, uint64_t* words) {
+  const uint32_t lane = lane_id();
+  const uint64_t nw = (nnz + 63) >> 6;
+  const uint64_t waves = gstride() / kWave;
+  constexpr int kRounds = 4;  // words per wave and step, their loads in flight together
+  for (uint64_t w0 = gtid() / kWave * kRounds; w0 < nw; w0 += waves * kRounds) {
+    int32_t c[kRounds], p[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const uint64_t k = min(((w0 + r) << 6) + lane, nnz - 1);
+      c[r] = gm(col)[k];
+      p[r] = gm(col)[k ? k - 1 : 0];
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const uint64_t k = ((w0 + r) << 6) + lane;
+      const uint64_t m = ballot(k < nnz && (k == 0 || c[r] != p[r]));
+      if (lane == 0 && w0 + r < nw) gm(words)[w0 + r] = m;
+    }
+  }
 }
 
 __global__ __launch_bounds__(kB) void k_row_heads(const void* rp, int ow, uint64_t n_rows,
-                                                  uint64_t nnz, uint32_t* h) {
+                                                  uint64_t nnz, uint64_t* words) {
   for (uint64_t i = gtid(); i < n_rows; i += gstride()) {
     const uint64_t a = min(ld_o(rp, i, ow), nnz), b = min(ld_o(rp, i + 1, ow), nnz);
-    if (a < b) h[a] = 1u;
+    if (a < b)
+      __hip_atomic_fetch_or(gm((unsigned long long*)words + (a >> 6)), 1ull << (a & 63),
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// Run heads to their output slot pos[k] (exclusive scan of the head flags;
-// pos[nnz] = number of output cells m).
+// The thread's four words of its chunk, and how many heads they hold.
+__device__ __forceinline__ uint32_t chunk_words(const uint64_t* words, uint64_t nw, uint64_t (&x)[4]) {
+  const uint64_t w0 = (uint64_t)blockIdx.x * kChunkWords + 4 * threadIdx.x;
+  uint32_t c = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    x[j] = w0 + j < nw ? gm(words)[w0 + j] : 0ull;
+    c += (uint32_t)__popcll(x[j]);
+  }
+  return c;
+}
+
+__global__ __launch_bounds__(kB) void k_head_sums(const uint64_t* words, uint64_t nw, uint32_t* sums) {
+  __shared__ uint32_t red[kB / kWave];
+  uint64_t x[4];
+  uint32_t tot;
+  block_excl_scan<kB / kWave>(chunk_words(words, nw, x), red, tot);
+  if (threadIdx.x == 0) sums[blockIdx.x] = tot;
+}
+
+__global__ __launch_bounds__(kB) void k_head_pref(const uint64_t* words, uint64_t nw,
+                                                  const uint32_t* sums, uint32_t* pref,
+                                                  const void* poff, int ow, uint64_t nnz,
+                                                  void* o_poff, int64_t* d_m) {
+  __shared__ uint32_t red[2][kB / kWave];
+  uint64_t x[4];
+  const uint32_t c = chunk_words(words, nw, x);
+  uint32_t part = 0, base, tot;
+  for (uint32_t i = threadIdx.x; i < blockIdx.x; i += kB) part += sums[i];
+  block_excl_scan<kB / kWave>(part, red[0], base);
+  uint32_t ex = block_excl_scan<kB / kWave>(c, red[1], tot) + base;
+  const uint64_t w0 = (uint64_t)blockIdx.x * kChunkWords + 4 * threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (w0 + j <= nw) pref[w0 + j] = ex;  // pref[nw] = m
+    ex += (uint32_t)__popcll(x[j]);
+  }
+  if (w0 <= nw && nw < w0 + 4) {  // the thread that wrote pref[nw] (words past nw are empty)
+    st_o(o_poff, ex, ld_o(poff, nnz, ow), ow);
+    if (d_m) *d_m = (int64_t)ex;
+  }
+}
+
+// Heads before cell k (k <= nnz).
+__device__ __forceinline__ uint32_t heads_before(const uint64_t* words, const uint32_t* pref, uint64_t k) {
+  const uint32_t l = (uint32_t)k & 63u;
+  return gm(pref)[k >> 6] + (l ? low_bits(gm(words)[k >> 6], l) : 0u);
+}
+
+// The cell of head number q < m, searched among the words from w on.
+__device__ uint64_t head_cell(const uint64_t* words, const uint32_t* pref, uint64_t nw, uint64_t w,
+                              uint32_t q) {
+  uint64_t lo = w, hi = nw;  // pref[lo] <= q, the answer's word is in [lo, hi)
+  while (hi - lo > 1) {
+    const uint64_t mid = (lo + hi) >> 1;
+    if (gm(pref)[mid] <= q) lo = mid;
+    else hi = mid;
+  }
+  uint64_t m = gm(words)[lo];
+  for (uint32_t j = q - gm(pref)[lo]; j; --j) m &= m - 1ull;
+  return (lo << 6) + (uint32_t)__ffsll((unsigned long long)m) - 1u;
+}
+
+// The first `cell_blocks` workgroups take the cells, one word per wave round
+// and kRounds words in flight; the others take the row offsets.
 __global__ __launch_bounds__(kB) void k_emit(const int32_t* col, const void* poff, int ow,
-                                             uint64_t nnz, const uint32_t* h, const uint64_t* pos,
-                                             int32_t* o_col, void* o_poff, uint32_t* first,
-                                             int64_t* d_m) {
-  if (gtid() == 0) {
-    const uint64_t m = min(pos[nnz], nnz);
-    first[m] = (uint32_t)nnz;
-    st_o(o_poff, m, ld_o(poff, nnz, ow), ow);
-    if (d_m) *d_m = (int64_t)m;
+                                             uint64_t nnz, const uint64_t* words,
+                                             const uint32_t* pref, uint32_t cell_blocks,
+                                             const void* rp, uint64_t n_rows, int32_t* o_col,
+                                             void* o_poff, uint32_t* o_counts, void* o_rp) {
+  if (blockIdx.x >= cell_blocks) {
+    const uint64_t stride = (uint64_t)(gridDim.x - cell_blocks) * kB;
+    for (uint64_t i = (uint64_t)(blockIdx.x - cell_blocks) * kB + threadIdx.x; i <= n_rows; i += stride)
+      st_o(o_rp, i, heads_before(words, pref, min(ld_o(rp, i, ow), nnz)), ow);
+    return;
   }
-  for (uint64_t k = gtid(); k < nnz; k += gstride()) {
-    if (!h[k]) continue;
-    const uint64_t p = pos[k];
-    gm(o_col)[p] = gm(col)[k];
-    st_o(o_poff, p, ld_o(poff, k, ow), ow);
-    first[p] = (uint32_t)k;
-  }
-}
-
-// Output row offsets (heads before each row start) and run lengths.
-__global__ __launch_bounds__(kB) void k_rows_counts(const void* rp, int ow, uint64_t n_rows,
-                                                    uint64_t nnz, const uint64_t* pos,
-                                                    const uint32_t* first, void* o_rp,
-                                                    uint32_t* o_counts) {
-  const uint64_t m = min(pos[nnz], nnz);
-  const uint64_t n = max(nnz, n_rows + 1);
-  for (uint64_t j = gtid(); j < n; j += gstride()) {
-    if (j < m && o_counts) o_counts[j] = first[j + 1] - first[j];
-    if (j <= n_rows) st_o(o_rp, j, pos[min(ld_o(rp, j, ow), nnz)], ow);
+  const uint32_t lane = lane_id();
+  const uint64_t nw = (nnz + 63) >> 6;
+  constexpr int kRounds = 4;
+  const uint64_t waves = (uint64_t)cell_blocks * (kB / kWave);
+  for (uint64_t w0 = ((uint64_t)blockIdx.x * (kB / kWave) + threadIdx.x / kWave) * kRounds; w0 < nw;
+       w0 += waves * kRounds) {
+    uint64_t m[kRounds + 1];
+    uint32_t p[kRounds];
+#pragma unroll
+    for (int r = 0; r <= kRounds; ++r) {  // (wave-uniform addresses)
+      m[r] = w0 + r < nw ? gm(words)[w0 + r] : 0ull;
+      if (r < kRounds) p[r] = gm(pref)[min(w0 + r, nw)];
+    }
+    int32_t c[kRounds];
+    uint64_t o[kRounds];
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      const uint64_t k = min(((w0 + r) << 6) + lane, nnz - 1);
+      c[r] = 0;
+      o[r] = 0;
+      if ((m[r] >> lane) & 1ull) {
+        c[r] = gm(col)[k];
+        o[r] = ld_o(poff, k, ow);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+      if (!((m[r] >> lane) & 1ull)) continue;
+      const uint64_t k = ((w0 + r) << 6) + lane;
+      const uint32_t q = p[r] + low_bits(m[r], lane);
+      gm(o_col)[q] = c[r];
+      st_o(o_poff, q, o[r], ow);
+      if (o_counts) {
+        // up to the next head: in this word, in the next one, or searched for
+        const uint64_t above = (m[r] >> lane) >> 1;
+        uint64_t next;
+        if (above) next = k + (uint32_t)__ffsll((unsigned long long)above);
+        else if (m[r + 1]) next = ((w0 + r + 1) << 6) + (uint32_t)__ffsll((unsigned long long)m[r + 1]) - 1u;
+        else if (q + 1 < gm(pref)[nw]) next = head_cell(words, pref, nw, w0 + r, q + 1);
+        else next = nnz;
+        gm(o_counts)[q] = (uint32_t)(next - k);
+      }
+    }
   }
 }
 
@@ -90,35 +216,106 @@ __global__ __launch_bounds__(kB) void k_expand_rows(const void* rp, const void* 
     st_o(o_rp, i, ld_o(poff, min(ld_o(rp, i, ow), nnz), ow) / w, ow);
 }
 
-__global__ __launch_bounds__(kB) void k_expand_check(const void* poff, int ow, uint64_t nnz,
-                                                     uint32_t w, int32_t* d_status) {
-  bool bad = false;
-  for (uint64_t k = gtid(); k <= nnz; k += gstride()) bad |= (ld_o(poff, k, ow) % w) != 0;
-  if (bad && d_status) *d_status = MGT_ERANGE;
+// The last cell of [lo, hi) whose payload offset is at most b (lo if none),
+// found by the whole workgroup: each round probes kB evenly spaced cells.
+__device__ __forceinline__ uint64_t coop_last_le(const void* poff, int ow, uint64_t lo, uint64_t hi,
+                                                 uint64_t b) {
+  while (hi - lo > 1) {
+    const uint64_t step = (hi - lo + kB - 1) / kB;
+    const uint64_t p = lo + (uint64_t)threadIdx.x * step;
+    const bool ok = p < hi && ld_o(poff, p, ow) <= b;
+    int c = __syncthreads_count(ok);
+    c = c < 1 ? 1 : c;
+    lo = lo + (uint64_t)(c - 1) * step;
+    hi = min(lo + step, hi);
+  }
+  return lo;
 }
 
-// One output cell per value: the cell holding byte q * w is the last cell
-// whose payload offset is at most q * w.
+// One output cell per value, kExVals values per workgroup: the cell holding
+// byte q * w is the last cell whose payload offset is at most q * w. The
+// workgroup finds its first and last cell once, counts in LDS where the cells
+// between them start, and scans the counts: the payload offsets are read once,
+// in order, where a binary search per value read about 23 of them one after
+// another. A range of more than kExCells cells (long runs of empty cells)
+// is searched per value instead, so no input makes one workgroup walk it.
+// Bound by the latency of its steps (search, walk, scan, store), with 4 + ow
+// bytes stored per value. 24 M values of 6 M cells, 8-byte offsets: 536 -> 172
+// us against the binary search per value.
+// Each workgroup also checks its share of the offsets (status only).
+constexpr int kExVals = 2048;
+constexpr uint64_t kExCells = 8 * kExVals;
+
 __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const void* poff, int ow,
                                                      uint64_t nnz, uint64_t nvals, uint32_t w,
-                                                     int32_t* o_col, void* o_poff) {
-  for (uint64_t q = gtid(); q < nvals; q += gstride()) {
-    const uint64_t b = q * w;
-    uint64_t lo = 0, hi = nnz;
-    while (hi - lo > 1) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (ld_o(poff, mid, ow) <= b) lo = mid;
-      else hi = mid;
+                                                     int32_t* o_col, void* o_poff,
+                                                     int32_t* d_status) {
+  __shared__ uint32_t incl[kExVals];
+  __shared__ uint32_t red[kB / kWave];
+  bool bad = false;
+  {
+    const uint64_t per = (nnz + gridDim.x) / gridDim.x;  // nnz + 1 offsets over the grid, rounded up
+    const uint64_t k1 = min(nnz + 1, (blockIdx.x + 1) * per);
+    for (uint64_t k = blockIdx.x * per + threadIdx.x; k < k1; k += kB) {
+      const uint64_t v = ld_o(poff, k, ow);
+      bad |= (v >> 32) ? (v % w) != 0 : ((uint32_t)v % w) != 0;
     }
-    gm(o_col)[q] = nnz ? gm(col)[lo] : 0;
-    if (o_poff) st_o(o_poff, q, b, ow);
   }
-  if (gtid() == 0 && o_poff) st_o(o_poff, nvals, nvals * w, ow);
-}
-
-__global__ __launch_bounds__(kB) void k_scale_offsets(const uint64_t* ex, uint64_t n, uint32_t w,
-                                                      int ow, void* poff) {
-  for (uint64_t k = gtid(); k <= n; k += gstride()) st_o(poff, k, ex[k] * w, ow);
+  for (uint64_t q0 = (uint64_t)blockIdx.x * kExVals; q0 < nvals; q0 += (uint64_t)gridDim.x * kExVals) {
+    const uint32_t n = (uint32_t)min((uint64_t)kExVals, nvals - q0);
+    const uint64_t b0 = q0 * w, b1 = (q0 + n) * w;
+    const uint64_t c0 = coop_last_le(poff, ow, 0, nnz, b0);
+    const uint64_t c1 = coop_last_le(poff, ow, c0, nnz, b1 - 1);
+    const bool walk = c1 - c0 <= kExCells;  // block-uniform
+    if (walk) {
+      for (uint32_t i = threadIdx.x; i < (uint32_t)kExVals; i += kB) incl[i] = 0;
+      __syncthreads();
+      for (uint64_t k = c0 + 1 + threadIdx.x; k <= c1; k += kB) {
+        const uint64_t o = ld_o(poff, k, ow);
+        const uint64_t d = o > b0 ? o - b0 : 0;
+        // (whole values: d is a multiple of w; clamped for offsets that are not in order)
+        const uint64_t at = (d >> 32) ? d / w : (uint64_t)((uint32_t)d / w);
+        atomicAdd(&incl[min(at, (uint64_t)kExVals - 1)], 1u);
+      }
+      __syncthreads();
+      constexpr int kPer = kExVals / kB;
+      const uint32_t p0 = threadIdx.x * kPer;
+      uint32_t v[kPer], s = 0;
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        v[j] = incl[p0 + j];
+        s += v[j];
+      }
+      uint32_t tot;
+      uint32_t ex = block_excl_scan<kB / kWave>(s, red, tot);
+#pragma unroll
+      for (int j = 0; j < kPer; ++j) {
+        ex += v[j];
+        incl[p0 + j] = ex;
+      }
+      __syncthreads();
+    }
+    for (uint32_t i = threadIdx.x; i < n; i += kB) {
+      const uint64_t q = q0 + i;
+      uint64_t cell;
+      if (walk) {
+        cell = min(c0 + incl[i], nnz - 1);
+      } else {
+        uint64_t lo = c0, hi = c1 + 1;
+        while (hi - lo > 1) {
+          const uint64_t mid = (lo + hi) >> 1;
+          if (ld_o(poff, mid, ow) <= q * w) lo = mid;
+          else hi = mid;
+        }
+        cell = lo;
+      }
+      gm(o_col)[q] = gm(col)[cell];
+      if (o_poff) st_o(o_poff, q, q * w, ow);
+    }
+    __syncthreads();  // incl is reused
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && o_poff) st_o(o_poff, nvals, nvals * w, ow);
+  if (bad && d_status) *d_status = MGT_ERANGE;
 }
 
 inline dim3 grid_for(uint64_t n) {
@@ -127,18 +324,20 @@ inline dim3 grid_for(uint64_t n) {
   return dim3((unsigned)g);
 }
 
-// Workspace layout: head flags (4 B per cell), their scan (8 B per cell + 1),
-// run starts (4 B per cell + 1), scan scratch.
+// Workspace layout: head bitmap (8 bytes per 64 cells), heads before each of
+// its words (4 bytes per 64 cells), heads per chunk, scan scratch.
 struct VlLayout {
-  uint64_t o_h, o_pos, o_first, o_scan, bytes;
+  uint64_t o_words, o_pref, o_sums, o_scan, bytes;
 };
 inline uint64_t up256(uint64_t x) { return (x + 255) & ~(uint64_t)255; }
+inline uint64_t head_chunks(uint64_t nnz) { return ((nnz + 63) / 64) / kChunkWords + 1; }
 inline VlLayout vl_layout(uint64_t nnz) {
+  const uint64_t nw = (nnz + 63) / 64;
   VlLayout y;
-  y.o_h = 0;
-  y.o_pos = up256(4 * nnz);
-  y.o_first = y.o_pos + up256(8 * (nnz + 1));
-  y.o_scan = y.o_first + up256(4 * (nnz + 1));
+  y.o_words = 0;
+  y.o_pref = up256(8 * nw);
+  y.o_sums = y.o_pref + up256(4 * (nw + 1));
+  y.o_scan = y.o_sums + up256(4 * head_chunks(nnz));
   y.bytes = y.o_scan + up256(scan_scratch_bytes(nnz + 1));
   return y;
 }
@@ -175,22 +374,27 @@ int mgt_coalesce(int64_t n_rows, int64_t nnz, int32_t offset_width, const void* 
   const vl::VlLayout y = vl::vl_layout(n);
   if (workspace_bytes < y.bytes) return MGT_ENOMEM;
   uint8_t* W = (uint8_t*)workspace;
-  uint32_t* h = (uint32_t*)(W + y.o_h);
-  uint64_t* pos = (uint64_t*)(W + y.o_pos);
-  uint32_t* first = (uint32_t*)(W + y.o_first);
-  uint64_t* scan = (uint64_t*)(W + y.o_scan);
+  uint64_t* words = (uint64_t*)(W + y.o_words);
+  uint32_t* pref = (uint32_t*)(W + y.o_pref);
+  uint32_t* sums = (uint32_t*)(W + y.o_sums);
   const int ow = offset_width;
+  const uint64_t nw = (n + 63) / 64;
+  const dim3 block(vl::kB);
   if (n) {
-    hipLaunchKernelGGL(vl::k_heads, vl::grid_for(n), dim3(vl::kB), 0, stream, col, n, h);
-    hipLaunchKernelGGL(vl::k_row_heads, vl::grid_for(r), dim3(vl::kB), 0, stream, row_ptr, ow, r,
-                       n, h);
+    hipLaunchKernelGGL(vl::k_heads, vl::grid_for((nw + 3) / 4 * kWave), block, 0, stream, col, n, words);
+    if (r)
+      hipLaunchKernelGGL(vl::k_row_heads, vl::grid_for(r), block, 0, stream, row_ptr, ow, r, n, words);
   }
-  MGT_VL_HIP(hipGetLastError());
-  MGT_VL_HIP(launch_scan(h, pos, nullptr, nullptr, nullptr, n, scan, stream));
-  hipLaunchKernelGGL(vl::k_emit, vl::grid_for(n), dim3(vl::kB), 0, stream, col, payload_off, ow,
-                     n, h, pos, o_col, o_payload_off, first, d_m);
-  hipLaunchKernelGGL(vl::k_rows_counts, vl::grid_for(std::max(n, r + 1)), dim3(vl::kB), 0,
-                     stream, row_ptr, ow, r, n, pos, first, o_row_ptr, o_counts);
+  // (the last chunk also holds the slot past the last word)
+  const dim3 chunks((unsigned)vl::head_chunks(n));
+  if (chunks.x > 1)
+    hipLaunchKernelGGL(vl::k_head_sums, chunks, block, 0, stream, words, nw, sums);
+  hipLaunchKernelGGL(vl::k_head_pref, chunks, block, 0, stream, words, nw, sums, pref, payload_off, ow,
+                     n, o_payload_off, d_m);
+  const uint32_t cells = n ? vl::grid_for((nw + 3) / 4 * kWave).x : 0;
+  const uint32_t rows = vl::grid_for(r + 1).x;
+  hipLaunchKernelGGL(vl::k_emit, dim3(cells + rows), block, 0, stream, col, payload_off, ow, n, words,
+                     pref, cells, row_ptr, r, o_col, o_payload_off, o_counts, o_row_ptr);
   MGT_VL_HIP(hipGetLastError());
   return MGT_OK;
 }
@@ -214,10 +418,12 @@ int mgt_expand(int64_t n_rows, int64_t nnz, int64_t payload_bytes, int32_t offse
   const int ow = offset_width;
   hipLaunchKernelGGL(vl::k_expand_rows, vl::grid_for(r + 1), dim3(vl::kB), 0, stream, row_ptr,
                      payload_off, ow, r, n, w, o_row_ptr, d_status);
-  hipLaunchKernelGGL(vl::k_expand_check, vl::grid_for(n + 1), dim3(vl::kB), 0, stream,
-                     payload_off, ow, n, w, d_status);
-  hipLaunchKernelGGL(vl::k_expand_cells, vl::grid_for(nvals), dim3(vl::kB), 0, stream, col,
-                     payload_off, ow, n, nvals, w, o_col, o_payload_off);
+  // at least one workgroup (for the status), and enough to check the offsets side by side
+  const uint64_t blocks = std::max<uint64_t>((nvals + vl::kExVals - 1) / vl::kExVals,
+                                             (n + 1 + 8 * vl::kB - 1) / (8 * vl::kB));
+  hipLaunchKernelGGL(vl::k_expand_cells, dim3((unsigned)std::min<uint64_t>(blocks, 1u << 20)),
+                     dim3(vl::kB), 0, stream, col, payload_off, ow, n, nvals, w, o_col, o_payload_off,
+                     d_status);
   MGT_VL_HIP(hipGetLastError());
   return MGT_OK;
 }
@@ -233,12 +439,8 @@ int mgt_counts_to_offsets(int64_t nnz, const uint32_t* counts, int32_t value_byt
   const vl::VlLayout y = vl::vl_layout(n);
   if (workspace_bytes < y.bytes) return MGT_ENOMEM;
   uint8_t* W = (uint8_t*)workspace;
-  uint64_t* ex = (uint64_t*)(W + y.o_pos);
-  uint64_t* scan = (uint64_t*)(W + y.o_scan);
-  MGT_VL_HIP(launch_scan(counts, ex, nullptr, nullptr, nullptr, n, scan, stream));
-  hipLaunchKernelGGL(vl::k_scale_offsets, vl::grid_for(n + 1), dim3(vl::kB), 0, stream, ex, n,
-                     (uint32_t)value_bytes, offset_width, payload_off);
-  MGT_VL_HIP(hipGetLastError());
+  MGT_VL_HIP(launch_scan_offsets(counts, n, (uint32_t)value_bytes, offset_width, payload_off,
+                                 (uint64_t*)(W + y.o_scan), stream));
   return MGT_OK;
 }
 
