@@ -216,20 +216,25 @@ __global__ __launch_bounds__(kB) void k_expand_rows(const void* rp, const void* 
     st_o(o_rp, i, ld_o(poff, min(ld_o(rp, i, ow), nnz), ow) / w, ow);
 }
 
-// The last cell of [lo, hi) whose payload offset is at most b (lo if none),
-// found by the whole workgroup: each round probes kB evenly spaced cells.
-__device__ __forceinline__ uint64_t coop_last_le(const void* poff, int ow, uint64_t lo, uint64_t hi,
-                                                 uint64_t b) {
-  while (hi - lo > 1) {
-    const uint64_t step = (hi - lo + kB - 1) / kB;
-    const uint64_t p = lo + (uint64_t)threadIdx.x * step;
-    const bool ok = p < hi && ld_o(poff, p, ow) <= b;
-    int c = __syncthreads_count(ok);
-    c = c < 1 ? 1 : c;
-    lo = lo + (uint64_t)(c - 1) * step;
-    hi = min(lo + step, hi);
+// The last cells of [0, hi) whose payload offsets are at most b0 and at most
+// b1 >= b0 (cell 0 if none), found by the whole workgroup: each round probes kB
+// evenly spaced cells for both, their loads in flight together.
+__device__ __forceinline__ void coop_last_le(const void* poff, int ow, uint64_t hi, uint64_t b0,
+                                             uint64_t b1, uint64_t& c0, uint64_t& c1) {
+  uint64_t lo0 = 0, hi0 = hi, lo1 = 0, hi1 = hi;
+  while (hi0 - lo0 > 1 || hi1 - lo1 > 1) {
+    const uint64_t st0 = (hi0 - lo0 + kB - 1) / kB, st1 = (hi1 - lo1 + kB - 1) / kB;
+    const uint64_t p0 = lo0 + (uint64_t)threadIdx.x * st0, p1 = lo1 + (uint64_t)threadIdx.x * st1;
+    const uint64_t v0 = ld_o(poff, min(p0, hi - 1), ow), v1 = ld_o(poff, min(p1, hi - 1), ow);
+    const int n0 = max(1, __syncthreads_count(p0 < hi0 && v0 <= b0));
+    const int n1 = max(1, __syncthreads_count(p1 < hi1 && v1 <= b1));
+    lo0 += (uint64_t)(n0 - 1) * st0;
+    hi0 = min(lo0 + st0, hi0);
+    lo1 += (uint64_t)(n1 - 1) * st1;
+    hi1 = min(lo1 + st1, hi1);
   }
-  return lo;
+  c0 = lo0;
+  c1 = max(lo0, lo1);
 }
 
 // One output cell per value, kExVals values per workgroup: the cell holding
@@ -240,7 +245,7 @@ __device__ __forceinline__ uint64_t coop_last_le(const void* poff, int ow, uint6
 // another. A range of more than kExCells cells (long runs of empty cells)
 // is searched per value instead, so no input makes one workgroup walk it.
 // Bound by the latency of its steps (search, walk, scan, store), with 4 + ow
-// bytes stored per value. 24 M values of 6 M cells, 8-byte offsets: 536 -> 172
+// bytes stored per value. 24 M values of 6 M cells, 8-byte offsets: 536 -> 129
 // us against the binary search per value.
 // Each workgroup also checks its share of the offsets (status only).
 constexpr int kExVals = 2048;
@@ -264,8 +269,8 @@ __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const v
   for (uint64_t q0 = (uint64_t)blockIdx.x * kExVals; q0 < nvals; q0 += (uint64_t)gridDim.x * kExVals) {
     const uint32_t n = (uint32_t)min((uint64_t)kExVals, nvals - q0);
     const uint64_t b0 = q0 * w, b1 = (q0 + n) * w;
-    const uint64_t c0 = coop_last_le(poff, ow, 0, nnz, b0);
-    const uint64_t c1 = coop_last_le(poff, ow, c0, nnz, b1 - 1);
+    uint64_t c0, c1;
+    coop_last_le(poff, ow, nnz, b0, b1 - 1, c0, c1);
     const bool walk = c1 - c0 <= kExCells;  // block-uniform
     if (walk) {
       for (uint32_t i = threadIdx.x; i < (uint32_t)kExVals; i += kB) incl[i] = 0;
@@ -295,8 +300,11 @@ __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const v
       }
       __syncthreads();
     }
-    for (uint32_t i = threadIdx.x; i < n; i += kB) {
-      const uint64_t q = q0 + i;
+    constexpr int kOut = kExVals / kB;  // values per thread, their columns in flight together
+    int32_t c[kOut];
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+      const uint32_t i = min((uint32_t)(j * kB) + threadIdx.x, n - 1);
       uint64_t cell;
       if (walk) {
         cell = min(c0 + incl[i], nnz - 1);
@@ -304,13 +312,19 @@ __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const v
         uint64_t lo = c0, hi = c1 + 1;
         while (hi - lo > 1) {
           const uint64_t mid = (lo + hi) >> 1;
-          if (ld_o(poff, mid, ow) <= q * w) lo = mid;
+          if (ld_o(poff, mid, ow) <= (q0 + i) * w) lo = mid;
           else hi = mid;
         }
         cell = lo;
       }
-      gm(o_col)[q] = gm(col)[cell];
-      if (o_poff) st_o(o_poff, q, q * w, ow);
+      c[j] = gm(col)[cell];
+    }
+#pragma unroll
+    for (int j = 0; j < kOut; ++j) {
+      const uint32_t i = (uint32_t)(j * kB) + threadIdx.x;
+      if (i >= n) break;
+      gm(o_col)[q0 + i] = c[j];
+      if (o_poff) st_o(o_poff, q0 + i, (q0 + i) * w, ow);
     }
     __syncthreads();  // incl is reused
   }
