@@ -163,6 +163,40 @@ hipError_t launch_finish(const FinishArgs& a, hipStream_t s);
 // Whole-bucket finish of a gathering call with packed records (runs before
 // launch_finish, which then skips the buckets it wrote).
 hipError_t launch_finish_bucket(const FinishArgs& a, hipStream_t s);
+// A small matrix in one launch (two for a partitioned call; see k_direct). Its
+// arguments travel with the launch: no upload, no workspace.
+constexpr uint32_t kDirectCols = 256;   // columns a workgroup may own
+constexpr uint32_t kDirectWgs = 256;    // workgroups that share the columns
+constexpr int32_t kDirectParts = 256;   // partitions whose bounds fit the arguments
+struct DirectArgs {
+  const void* row_ptr;
+  const int32_t* col;
+  const void* poff;
+  const uint8_t* payload;
+  void* t_row_ptr;
+  int32_t* t_col;
+  void* t_poff;               // may be null (fixed-width cells)
+  uint8_t* t_payload;
+  uint32_t* perm;             // may be null
+  int64_t* xfer_cells;        // partitioned calls (n_parts > 0)
+  int64_t* xfer_bytes;
+  int64_t* part_cell_off;
+  int64_t* part_byte_off;
+  int64_t* sdispls;           // may be null
+  int64_t* rdispls;           // may be null
+  int32_t* d_status;          // may be null
+  int64_t n_rows, n_cols;     // < 2^31
+  uint64_t payload_bytes;     // < 2^32
+  uint32_t nnz;               // > 0
+  uint32_t cols_per_wg;       // <= kDirectCols
+  uint32_t n_wg;              // cols_per_wg * n_wg >= n_cols
+  int32_t lg;                 // offsets of 2^lg bytes (2 or 3)
+  int32_t fixed_w;            // bytes of every cell, or -1
+  int32_t n_parts;            // 0: plain call
+  int32_t bounds[kDirectParts + 1];
+};
+static_assert(sizeof(DirectArgs) <= 2048, "kernel argument size");
+hipError_t launch_direct(const DirectArgs& a, hipStream_t s);
 // mgt_symmetrize's stages after the transpose of the stored triangle
 // (symmetric.hip). Every offset array has width ow.
 struct SymArgs {

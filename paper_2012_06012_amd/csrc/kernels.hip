@@ -2468,6 +2468,329 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
   }
 }
 
+// ----------------------------------------------------------------------------- small calls
+
+// A small matrix in one launch, with no upload and no workspace. The passes
+// above need five dependent launches of one latency chain each (44 us for
+// 20 K cells of which the bytes would take 0.2); here every workgroup owns a
+// run of columns and finds everything it needs by itself, reading all column
+// ids and sizes once:
+//   - cells and bytes of the columns before its own (its place in the output),
+//   - its own cells, in input order: each wave takes a contiguous 1/16 of the
+//     input, counts per (column, wave) and lists them in LDS;
+//   - the counts scanned column by column, waves in order, give every wave a
+//     stable place in every column; each wave then places its cells by itself,
+//     64 at a time (ranks among equal columns by ballots), finds their rows in
+//     the row offsets (in LDS up to kDirRows rows) and copies their payload
+//     from the input straight to its final place.
+// The work grows with cells times workgroups, so it pays up to about
+// kDirectCells cells (runtime.cpp: use_direct, where both sides are given). A
+// wave whose cells outgrow its list (kDirList; skewed columns) reads its share
+// of the input again instead.
+constexpr int kDirThreads = 1024;
+constexpr int kDirNW = kDirThreads / kWave;
+constexpr int kDirRows = 8192;   // row offsets kept in LDS
+constexpr int kDirList = 256;    // listed cells per wave
+constexpr int kDirBatch = 8;     // rounds of 64 cells in flight per wave
+
+struct DirectLds {
+  uint32_t cnt[kDirectCols * kDirNW];  // (column, wave): cells, then first output cell
+  uint32_t byt[kDirectCols * kDirNW];  // likewise payload bytes
+  uint32_t rp[kDirRows];
+  uint32_t k[kDirNW][kDirList];        // listed cells: input index, size, payload offset, column
+  uint32_t z[kDirNW][kDirList];
+  uint32_t o[kDirNW][kDirList];
+  uint16_t c[kDirNW][kDirList];
+  uint32_t below[kDirNW], bytes[kDirNW];
+  uint32_t red[kDirNW];
+};
+static_assert(sizeof(DirectLds) <= 128 * 1024, "one workgroup per CU");
+
+// Places the wave's first n <= 64 listed cells.
+__device__ __forceinline__ void direct_place(const DirectArgs& a, DirectLds& L, uint32_t w, uint32_t n,
+                                             uint32_t at, uint32_t nc, uint32_t cell0, uint32_t byte0,
+                                             bool rows_lds, int dbits) {
+  const uint32_t lane = lane_id();
+  const bool act = lane < n;
+  const uint32_t i = at + (act ? lane : 0u);
+  const uint32_t k = L.k[w][i], c = L.c[w][i];
+  const uint32_t z = act ? L.z[w][i] : 0u, o = L.o[w][i];
+  uint8_t* pd[1] = {a.t_payload};
+  const uint8_t* ps[1] = {a.payload + o};
+  const uint32_t pz[1] = {z};
+  // row of the cell: the last row starting at or before it
+  uint32_t lo = 0, hi = (uint32_t)a.n_rows;
+  if (rows_lds) {
+    while (ballot(hi - lo > 1)) {
+      const uint32_t mid = (lo + hi) >> 1;
+      const bool up = L.rp[mid] <= k;
+      if (hi - lo > 1) {
+        lo = up ? mid : lo;
+        hi = up ? hi : mid;
+      }
+    }
+  } else {
+    while (ballot(hi - lo > 1)) {
+      const uint32_t mid = (lo + hi) >> 1;
+      const bool up = ld_lo(a.row_ptr, mid, a.lg) <= k;
+      if (hi - lo > 1) {
+        lo = up ? mid : lo;
+        hi = up ? hi : mid;
+      }
+    }
+  }
+  const uint64_t peers = match_peers(c, act, dbits);
+  const uint32_t rank = popc_below(peers);
+  uint32_t pre = 0;  // bytes of the equal columns in the lanes below
+  uint64_t rem = act ? peers & ((1ull << lane) - 1ull) : 0ull;
+  while (ballot(rem != 0)) {
+    const int b = rem ? __ffsll((unsigned long long)rem) - 1 : (int)lane;
+    const uint32_t zz = (uint32_t)__shfl((int)z, b, kWave);
+    if (rem) pre += zz;
+    rem &= rem - 1ull;
+  }
+  uint32_t pos = 0, bpos = 0;
+  if (act) {
+    const uint32_t e = c * kDirNW + w;
+    pos = cell0 + L.cnt[e] + rank;
+    bpos = byte0 + L.byt[e] + pre;
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (act && rank + 1u == (uint32_t)__popcll(peers)) {  // the column's last cell moves its place on
+    const uint32_t e = c * kDirNW + w;
+    L.cnt[e] += rank + 1u;
+    L.byt[e] += pre + z;
+  }
+  __builtin_amdgcn_wave_barrier();
+  pd[0] = a.t_payload + bpos;
+  PayRegsT<1> P;
+  pay_load(P, pd, ps, pz);
+  if (act) {
+    gm(a.t_col)[pos] = (int32_t)lo;
+    if (a.perm) gm(a.perm)[pos] = k;
+    if (a.t_poff) st_off(a.t_poff, pos, (int64_t)bpos, a.lg == 3 ? 8 : 4);
+  }
+  pay_store(P, pd, ps, pz);
+}
+
+__global__ __launch_bounds__(kDirThreads) void k_direct(DirectArgs a) {
+  __shared__ DirectLds L;
+  const int ow = a.lg == 3 ? 8 : 4;
+  if (blockIdx.x >= a.n_wg) {  // partitioned calls: one more workgroup, for what follows from X and B
+    uint64_t* const red = (uint64_t*)L.cnt;
+    const uint32_t R = (uint32_t)a.n_parts, d = threadIdx.x;
+    uint64_t cells = 0, bytes = 0;
+    if (d < R) {
+#pragma unroll 8
+      for (uint32_t r = 0; r < R; ++r) {
+        if (a.rdispls) a.rdispls[(uint64_t)d * R + r] = (int64_t)cells;
+        cells += (uint64_t)a.xfer_cells[(uint64_t)r * R + d];
+        bytes += (uint64_t)a.xfer_bytes[(uint64_t)r * R + d];
+      }
+    }
+    uint64_t tc, tb;
+    const uint64_t ec = block_excl_scan<kDirNW>(cells, red, tc);
+    const uint64_t eb = block_excl_scan<kDirNW>(bytes, red, tb);
+    if (d < R) {
+      a.part_cell_off[d] = (int64_t)ec;
+      a.part_byte_off[d] = (int64_t)eb;
+    }
+    if (d == 0) {
+      a.part_cell_off[R] = (int64_t)tc;
+      a.part_byte_off[R] = (int64_t)tb;
+    }
+    return;
+  }
+  const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+  const uint32_t n_cols = (uint32_t)a.n_cols;
+  const uint32_t col0 = min(blockIdx.x * a.cols_per_wg, n_cols);
+  const uint32_t nc = min(a.cols_per_wg, n_cols - col0);
+  const uint32_t E = nc * kDirNW;
+  const bool rows_lds = a.n_rows < kDirRows;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.d_status) *a.d_status = MGT_OK;
+    st_off(a.t_row_ptr, n_cols, (int64_t)a.nnz, ow);
+    if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, ow);
+  }
+  if (nc == 0) return;
+  for (uint32_t e = threadIdx.x; e < E; e += kDirThreads) {
+    L.cnt[e] = 0;
+    L.byt[e] = 0;
+  }
+  if (rows_lds)
+    for (uint32_t i = threadIdx.x; i <= (uint32_t)a.n_rows; i += kDirThreads)
+      L.rp[i] = ld_lo(a.row_ptr, i, a.lg);
+  __syncthreads();
+  // this wave's share of the cells
+  const uint32_t per = (((a.nnz + kDirNW - 1) / kDirNW) + kWave - 1) & ~(uint32_t)(kWave - 1);
+  const uint32_t kb = min(w * per, a.nnz), ke = min(kb + per, a.nnz);
+  const uint32_t last = a.nnz - 1;
+  uint32_t nsel = 0, below = 0, bb = 0;
+  for (uint32_t k0 = kb; k0 < ke; k0 += kWave * kDirBatch) {
+    uint32_t c[kDirBatch], p0[kDirBatch], p1[kDirBatch];
+#pragma unroll
+    for (int q = 0; q < kDirBatch; ++q) {
+      const uint32_t k = min(k0 + (uint32_t)q * kWave + lane, last);
+      c[q] = (uint32_t)gm(a.col)[k];
+      if (a.fixed_w < 0) {
+        p0[q] = ld_lo(a.poff, k, a.lg);
+        p1[q] = ld_lo(a.poff, (uint64_t)k + 1, a.lg);
+      } else {
+        p0[q] = k * (uint32_t)a.fixed_w;
+        p1[q] = p0[q] + (uint32_t)a.fixed_w;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kDirBatch; ++q) {
+      const uint32_t k = k0 + (uint32_t)q * kWave + lane;
+      const uint32_t z = p1[q] - p0[q];
+      const bool in = k < ke, lower = in && c[q] < col0;
+      const uint32_t cc = c[q] - col0;
+      const bool sel = in && !lower && cc < nc;
+      below += (uint32_t)__popcll(ballot(lower));
+      bb += lower ? z : 0u;
+      const uint64_t m = ballot(sel);
+      if (m == 0) continue;  // wave-uniform
+      if (sel) {
+        atomicAdd(&L.cnt[cc * kDirNW + w], 1u);
+        atomicAdd(&L.byt[cc * kDirNW + w], z);
+        const uint32_t at = nsel + popc_below(m);
+        if (at < (uint32_t)kDirList) {
+          L.k[w][at] = k;
+          L.z[w][at] = z;
+          L.o[w][at] = p0[q];
+          L.c[w][at] = (uint16_t)cc;
+        }
+      }
+      nsel += (uint32_t)__popcll(m);
+    }
+  }
+  bb = wave_incl_scan_u32(bb);
+  if (lane == kWave - 1) {
+    L.below[w] = below;
+    L.bytes[w] = bb;
+  }
+  __syncthreads();
+  uint32_t cell0 = 0, byte0 = 0;
+#pragma unroll
+  for (int i = 0; i < kDirNW; ++i) {
+    cell0 += L.below[i];
+    byte0 += L.bytes[i];
+  }
+  {  // column-major scan of the counts: every (column, wave)'s first output cell and byte
+    constexpr int kPer = kDirectCols * kDirNW / kDirThreads;
+    const uint32_t e0 = threadIdx.x * kPer;
+    uint32_t v[kPer], u[kPer], s = 0, t = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      v[j] = e0 + j < E ? L.cnt[e0 + j] : 0u;
+      u[j] = e0 + j < E ? L.byt[e0 + j] : 0u;
+      s += v[j];
+      t += u[j];
+    }
+    uint32_t tot;
+    uint32_t ex = block_excl_scan<kDirNW>(s, L.red, tot);
+    uint32_t eb = block_excl_scan<kDirNW>(t, L.red, tot);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (e0 + j < E) {
+        L.cnt[e0 + j] = ex;
+        L.byt[e0 + j] = eb;
+      }
+      ex += v[j];
+      eb += u[j];
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < nc; i += kDirThreads)
+    st_off(a.t_row_ptr, (uint64_t)col0 + i, (int64_t)(cell0 + L.cnt[i * kDirNW]), ow);
+  // (a wave moves its own counters on while another may still read column
+  // starts above: wave 0's, whose first batch waits for this barrier)
+  __syncthreads();
+  const int dbits = ceil_log2(nc);
+  if (nsel <= (uint32_t)kDirList) {
+    for (uint32_t at = 0; at < nsel; at += kWave)
+      direct_place(a, L, w, min((uint32_t)kWave, nsel - at), at, nc, cell0, byte0, rows_lds, dbits);
+    return;
+  }
+  // more cells than the list holds: read the share again, a full batch at a time
+  uint32_t n = 0;
+  for (uint32_t k0 = kb; k0 < ke; k0 += kWave) {
+    const uint32_t k = min(k0 + lane, last);
+    const uint32_t c = (uint32_t)gm(a.col)[k];
+    const bool sel = k0 + lane < ke && c >= col0 && c - col0 < nc;
+    const uint64_t m = ballot(sel);
+    if (m == 0) continue;
+    if (sel) {
+      const uint32_t at = n + popc_below(m);  // under 128
+      const uint32_t p0 = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : k * (uint32_t)a.fixed_w;
+      const uint32_t p1 = a.fixed_w < 0 ? ld_lo(a.poff, (uint64_t)k + 1, a.lg) : p0 + (uint32_t)a.fixed_w;
+      L.k[w][at] = k;
+      L.z[w][at] = p1 - p0;
+      L.o[w][at] = p0;
+      L.c[w][at] = (uint16_t)(c - col0);
+    }
+    n += (uint32_t)__popcll(m);
+    __builtin_amdgcn_wave_barrier();
+    if (n < (uint32_t)kWave) continue;
+    direct_place(a, L, w, kWave, 0, nc, cell0, byte0, rows_lds, dbits);
+    n -= kWave;
+    if (lane < n) {  // the rest to the front
+      L.k[w][lane] = L.k[w][kWave + lane];
+      L.z[w][lane] = L.z[w][kWave + lane];
+      L.o[w][lane] = L.o[w][kWave + lane];
+      L.c[w][lane] = L.c[w][kWave + lane];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (n) direct_place(a, L, w, n, 0, nc, cell0, byte0, rows_lds, dbits);
+}
+
+// X and B of a small partitioned call (Section 2 step 2): one workgroup per
+// source partition histograms the owners of its cells' columns (its rows, so
+// its cells, are consecutive in the input), writes its row of both matrices
+// and of the send displacements. Runs before k_direct.
+__global__ __launch_bounds__(kDirThreads) void k_direct_xfer(DirectArgs a) {
+  __shared__ uint32_t cnt[kDirectParts], byt[kDirectParts];
+  __shared__ int32_t lb[kDirectParts + 1];
+  __shared__ uint32_t red[kDirNW];
+  const uint32_t R = (uint32_t)a.n_parts, s = blockIdx.x, tid = threadIdx.x;
+  if (tid <= R) lb[tid] = a.bounds[tid];
+  if (tid < R) {
+    cnt[tid] = 0;
+    byt[tid] = 0;
+  }
+  __syncthreads();
+  const uint32_t kb = min(ld_lo(a.row_ptr, (uint32_t)lb[s], a.lg), a.nnz);
+  const uint32_t ke = min(ld_lo(a.row_ptr, (uint32_t)lb[s + 1], a.lg), a.nnz);
+  constexpr int kQ = 4;
+  for (uint32_t k0 = kb; k0 < ke; k0 += kDirThreads * kQ) {  // same trip count on all lanes
+    uint32_t c[kQ], p0[kQ], p1[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const uint32_t k = min(k0 + (uint32_t)q * kDirThreads + tid, a.nnz - 1);
+      c[q] = (uint32_t)gm(a.col)[k];
+      p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : 0u;
+      p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, (uint64_t)k + 1, a.lg) : (uint32_t)a.fixed_w;
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const bool act = k0 + (uint32_t)q * kDirThreads + tid < ke;
+      hist_add_runs(act, act ? owner_of(lb, R, (int64_t)c[q]) : 0u, p1[q] - p0[q], cnt, byt);
+    }
+  }
+  __syncthreads();
+  const uint32_t v = tid < R ? cnt[tid] : 0u;
+  uint32_t tot;
+  const uint32_t ex = block_excl_scan<kDirNW>(v, red, tot);
+  if (tid < R) {
+    const uint64_t e = (uint64_t)s * R + tid;
+    a.xfer_cells[e] = (int64_t)v;
+    a.xfer_bytes[e] = (int64_t)byt[tid];
+    if (a.sdispls) a.sdispls[e] = (int64_t)ex;
+  }
+}
+
 // ----------------------------------------------------------------------------- children
 
 __global__ __launch_bounds__(kBlock) void k_children(ChildArgs a) {
@@ -2667,6 +2990,13 @@ hipError_t launch_view_keys(const ViewArgs& a, hipStream_t s) {
 
 hipError_t launch_children(const ChildArgs& a, hipStream_t s) {
   if (a.nseg) hipLaunchKernelGGL(G::k_children, grid1(a.nseg), dim3(G::kBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_direct(const DirectArgs& a, hipStream_t s) {
+  if (a.n_parts > 0)
+    hipLaunchKernelGGL(G::k_direct_xfer, dim3((unsigned)a.n_parts), dim3(G::kDirThreads), 0, s, a);
+  hipLaunchKernelGGL(G::k_direct, dim3(a.n_wg + (a.n_parts > 0 ? 1u : 0u)), dim3(G::kDirThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -837,9 +837,12 @@ int check_io(const mgt_desc& d, uint32_t flags, const void* row_ptr, const int32
 // Records one call into g: the pinned upload buffer and a private stream are
 // made first (nothing is allocated while capturing), then the call is
 // captured on that stream and instantiated.
+int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStream_t s);
+
+// direct: the call is a small one (run_direct), partitioned or not.
 int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
-                 int32_t* d_status, mgt_graph_s* g) {
-  if (hipHostMalloc(&g->staging, upload_bytes(y), hipHostMallocDefault) != hipSuccess) {
+                 int32_t* d_status, mgt_graph_s* g, bool direct = false, bool partitioned = false) {
+  if (!direct && hipHostMalloc(&g->staging, upload_bytes(y), hipHostMallocDefault) != hipSuccess) {
     g->staging = nullptr;
     return MGT_ENOMEM;
   }
@@ -849,7 +852,8 @@ int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
   int st = MGT_OK;
   if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) st = MGT_EHIP;
   if (st == MGT_OK) {
-    st = run(p, items, y, ws, d_status, s, nullptr, g->staging);
+    st = direct ? run_direct(items[0], partitioned, d_status, s)
+                : run(p, items, y, ws, d_status, s, nullptr, g->staging);
     // the capture is ended whatever happened inside it
     if (hipStreamEndCapture(s, &graph) != hipSuccess && st == MGT_OK) st = MGT_EHIP;
   }
@@ -860,6 +864,66 @@ int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
   if (graph) (void)hipGraphDestroy(graph);
   (void)hipStreamDestroy(s);
   return st;
+}
+
+// Small calls take k_direct: one launch that reads every column id in every
+// workgroup, against five dependent launches of the passes. us per call, direct
+// and passes (1-8 floats per cell, 8-byte offsets): 1 K cells 11 and 40, 20 K 15
+// and 45, 50 K 25 and 50, 80 K 33 and 54, 110 K 44 and 56, 150 K 58 and 58;
+// partitioned (R = 13): 20 K 21 and 75, 150 K 69 and 83.
+constexpr int64_t kDirectCells = 150000;
+
+// Whether a single-matrix call runs directly. Calls that ask for the passes'
+// own stages keep them: device-side checks and stage times, a schedule set by
+// the caller or by the environment.
+bool use_direct(const mgt_plan_s* p, const mgt_desc& d, bool partitioned) {
+  if (d.nnz < 1 || d.nnz > kDirectCells) return false;
+  if (d.n_cols > (int64_t)kDirectCols * kDirectWgs || d.payload_bytes >= (1ll << 32)) return false;
+  if (partitioned && d.n_parts > kDirectParts) return false;
+  if (p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING)) return false;
+  if (p->tune.pass_bits != 0 || p->tune.finish_bits != -1 || p->tune.tile != 0) return false;
+  return max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
+         !env_cap("MGT_NO_PACK", 0, 1, 0) && !env_cap("MGT_NO_DIRECT", 0, 1, 0);
+}
+
+int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStream_t s) {
+  const mgt_desc& d = it.d;
+  const ItemDev& v = it.dev;
+  DirectArgs a{};
+  a.row_ptr = v.row_ptr;
+  a.col = v.col;
+  a.poff = v.poff;
+  a.payload = v.payload;
+  a.t_row_ptr = v.t_row_ptr;
+  a.t_col = v.t_col;
+  a.t_poff = v.t_poff;
+  a.t_payload = v.t_payload;
+  a.perm = v.perm;
+  a.xfer_cells = v.xfer_cells;
+  a.xfer_bytes = v.xfer_bytes;
+  a.part_cell_off = v.part_cell_off;
+  a.part_byte_off = v.part_byte_off;
+  a.sdispls = v.sdispls;
+  a.rdispls = v.rdispls;
+  a.d_status = d_status;
+  a.n_rows = d.n_rows;
+  a.n_cols = d.n_cols;
+  a.payload_bytes = (uint64_t)d.payload_bytes;
+  a.nnz = (uint32_t)d.nnz;
+  // about 256 cells per workgroup, enough workgroups for every column
+  const uint64_t cols = (uint64_t)d.n_cols;
+  uint64_t wgs = std::min<uint64_t>({((uint64_t)d.nnz + 255) / 256, cols, kDirectWgs});
+  wgs = std::max<uint64_t>(wgs, (cols + kDirectCols - 1) / kDirectCols);
+  a.cols_per_wg = (uint32_t)((cols + wgs - 1) / wgs);
+  a.n_wg = (uint32_t)((cols + a.cols_per_wg - 1) / a.cols_per_wg);
+  a.lg = d.offset_width == 8 ? 3 : 2;
+  a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
+  if (partitioned) {
+    a.n_parts = d.n_parts;
+    for (int32_t r = 0; r <= d.n_parts; ++r) a.bounds[r] = (int32_t)it.bounds[r];
+  }
+  MGT_HIP(launch_direct(a, s));
+  return MGT_OK;
 }
 
 // no_alloc: the call allocates nothing (no pinned staging, no events, no heap):
@@ -903,8 +967,11 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   if (!partitioned) it.bounds = nullptr;
   Layout y = make_layout(Items(items, 1));
   if (ws_bytes < y.bytes) return MGT_ENOMEM;
-  if (graph) return record_graph(p, Items(items, 1), y, ws, d_status, graph);
+  const bool direct = use_direct(p, d, partitioned);
+  if (graph)
+    return record_graph(p, Items(items, 1), y, ws, d_status, graph, direct, partitioned);
   p->timing.used = 0;
+  if (direct) return run_direct(it, partitioned, d_status, s);
   if (no_alloc) {
     alignas(16) uint8_t up[kNoAllocUpload];
     if (upload_bytes(y) > sizeof(up)) return MGT_EUNSUPPORTED;
