@@ -197,6 +197,48 @@ struct DirectArgs {
 };
 static_assert(sizeof(DirectArgs) <= 2048, "kernel argument size");
 hipError_t launch_direct(const DirectArgs& a, hipStream_t s);
+// A mid-size matrix in two launches (three for a partitioned call; see
+// tiles.hip): tiles sorted by column bucket, then one workgroup per bucket.
+constexpr uint32_t kTileMax = 4096;      // cells of a tile
+constexpr uint32_t kTileTiles = 2048;    // tiles of a call
+constexpr uint32_t kTileBuckets = 2048;  // buckets of a call
+constexpr uint32_t kTileCols = 512;      // columns of a bucket
+constexpr uint32_t kTileCap = 4608;      // cells of a bucket held at once
+struct TileArgs {
+  const void* row_ptr;
+  const int32_t* col;
+  const void* poff;
+  const uint8_t* payload;
+  void* t_row_ptr;
+  int32_t* t_col;
+  void* t_poff;               // may be null (fixed-width cells)
+  uint8_t* t_payload;
+  uint32_t* perm;             // may be null
+  int64_t* xfer_cells;        // partitioned calls (n_parts > 0)
+  int64_t* xfer_bytes;
+  int64_t* part_cell_off;
+  int64_t* part_byte_off;
+  int64_t* sdispls;           // may be null
+  int64_t* rdispls;           // may be null
+  int32_t* d_status;          // may be null
+  uint2* table;               // workspace: [tile][bucket] (start | cells << 16, bytes before)
+  uint32_t* recs;             // workspace: the records, tile by tile
+  uint32_t* bad;              // workspace: a flag per tile (validate)
+  uint64_t nnz, payload_bytes;  // payload_bytes < 2^32
+  int64_t n_rows, n_cols;     // < 2^31
+  uint32_t cpb;               // columns per bucket
+  uint32_t magic;             // 2^32 / cpb rounded up (cpb > 1)
+  uint32_t n_buckets, n_tiles, tile_cells;
+  uint32_t g8;                // n_buckets rounded up to a multiple of 8
+  int32_t lg;                 // offsets of 2^lg bytes (2 or 3)
+  int32_t fixed_w;            // bytes of every cell, or -1
+  int32_t n_parts;            // 0: plain call; <= kDirectParts
+  int32_t validate;
+};
+struct TileBounds {
+  int32_t bounds[kDirectParts + 1];
+};
+hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s);
 // mgt_symmetrize's stages after the transpose of the stored triangle
 // (symmetric.hip). Every offset array has width ow.
 struct SymArgs {

@@ -81,14 +81,62 @@ __device__ __forceinline__ T block_excl_scan(T v, T* scratch, T& total) {
 
 // Lanes of the wave whose `digit` equals the calling lane's digit, among the
 // lanes where `active` holds. `dbits` (wave-uniform) bounds the digit width.
+// A bit costs five vector instructions: the bit as a full mask, its ballot, and
+// one three-input logic operation per half.
 __device__ __forceinline__ uint64_t match_peers(uint32_t digit, bool active, int dbits) {
-  uint64_t m = ballot(active);
+  const uint64_t act = ballot(active);
+  uint32_t lo = (uint32_t)act, hi = (uint32_t)(act >> 32);
   for (int b = 0; b < dbits; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t v = ballot(bit);
-    m &= bit ? v : ~v;
+    const uint32_t s = (uint32_t)((int32_t)(digit << (31 - b)) >> 31);
+    const uint64_t v = ballot(s != 0u);
+    lo &= ~((uint32_t)v ^ s);
+    hi &= ~((uint32_t)(v >> 32) ^ s);
   }
-  return m;
+  return (uint64_t)lo | ((uint64_t)hi << 32);
+}
+
+// Stable ranks of a wave's N rounds of 64 cells among the cells of their digit
+// in the same wave, in cell order (cell r * 64 + lane of the wave; the first
+// `n` of them are there, the others get rank 0). wc: one 16-bit counter per
+// (digit, wave), zero before and the wave's counts after; at[r] is the index of
+// cell r's counter, and the counters of waves 2v and 2v + 1 share an aligned
+// word. The matches of all rounds advance bit by bit together. The counters
+// are read by every lane and added to by each digit's first lane, round by
+// round: a wave's LDS operations execute in order, so the rounds need no wait
+// between them.
+template <int N>
+__device__ __forceinline__ void wave_ranks(uint16_t* wc, const uint32_t (&at)[N], const uint32_t (&digit)[N],
+                                           uint32_t n, int dbits, uint32_t (&rank)[N]) {
+  const uint32_t lane = lane_id();
+  uint32_t lo[N], hi[N];
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    const uint64_t act = ballot((uint32_t)r * kWave + lane < n);
+    lo[r] = (uint32_t)act;
+    hi[r] = (uint32_t)(act >> 32);
+  }
+  for (int b = 0; b < dbits; ++b) {
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const uint32_t s = (uint32_t)((int32_t)(digit[r] << (31 - b)) >> 31);
+      const uint64_t v = ballot(s != 0u);
+      lo[r] &= ~((uint32_t)v ^ s);
+      hi[r] &= ~((uint32_t)(v >> 32) ^ s);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < N; ++r) {
+    rank[r] = 0;
+    if ((uint32_t)r * kWave + lane < n) {
+      const uint32_t below = __builtin_amdgcn_mbcnt_hi(hi[r], __builtin_amdgcn_mbcnt_lo(lo[r], 0u));
+      const uint32_t old = wc[at[r]];
+      if (below == 0)
+        __hip_atomic_fetch_add((uint32_t*)wc + (at[r] >> 1),
+                               (uint32_t)(__popc(lo[r]) + __popc(hi[r])) << (16u * (at[r] & 1u)),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      rank[r] = old + below;
+    }
+  }
 }
 
 // XCD-aware tile order: the hardware deals workgroups round robin over the 8

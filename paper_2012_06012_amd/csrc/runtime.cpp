@@ -410,6 +410,50 @@ int check_desc(const mgt_desc* d, bool need_bounds) {
   return MGT_OK;
 }
 
+// The two-launch form of mid-size calls (tiles.hip): its buckets, tiles and
+// workspace, or ok = false where the passes take the call.
+struct TileGeo {
+  bool ok = false;
+  uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
+  uint64_t o_table = 0, o_recs = 0, o_bad = 0, bytes = 0;
+};
+
+constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
+
+TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune) {
+  TileGeo t;
+  const uint64_t nnz = (uint64_t)std::max<int64_t>(d.nnz, 0), cols = (uint64_t)std::max<int64_t>(d.n_cols, 0);
+  if (nnz < 1 || nnz > (uint64_t)kTileMax * kTileTiles || cols < 1) return t;
+  if (d.payload_bytes >= (1ll << 32) || (d.flags & MGT_DEBUG_TIMING)) return t;
+  if (partitioned && d.n_parts > kDirectParts) return t;
+  if (tune.pass_bits != 0 || tune.finish_bits != -1 || tune.tile != 0) return t;
+  const uint64_t cap = kTileCap;
+  // buckets of at most 4/5 of what a workgroup holds, whole rounds of the
+  // workgroups that run at once; small calls still fill one round
+  uint64_t g = std::max<uint64_t>((5 * nnz + 4 * cap - 1) / (4 * cap), (cols + kTileCols - 1) / kTileCols);
+  if (g > kTileSlots) g = align_up(g, kTileSlots);
+  else g = std::max<uint64_t>(g, std::min<uint64_t>(kTileSlots, (nnz + 255) / 256));
+  g = std::min<uint64_t>(g, cols);
+  if (g > kTileBuckets) return t;
+  t.cpb = (uint32_t)((cols + g - 1) / g);
+  t.n_buckets = (uint32_t)((cols + t.cpb - 1) / t.cpb);
+  if (t.cpb > kTileCols || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
+  uint64_t tiles = (nnz + kTileMax - 1) / kTileMax;
+  if (tiles > kTileSlots) tiles = std::min<uint64_t>(align_up(tiles, kTileSlots), kTileTiles);
+  else tiles = std::max<uint64_t>(tiles, std::min<uint64_t>(kTileSlots, (nnz + 1023) / 1024));
+  t.tile_cells = (uint32_t)std::min<uint64_t>(align_up((nnz + tiles - 1) / tiles, 64), kTileMax);
+  t.n_tiles = (uint32_t)((nnz + t.tile_cells - 1) / t.tile_cells);
+  if (t.n_tiles > kTileTiles) return t;
+  const uint64_t words = (d.flags & MGT_EMIT_PERM) ? 4 : 3;
+  t.o_table = 0;
+  t.o_recs = align_up(8ull * t.n_tiles * t.n_buckets, 256);
+  t.o_bad = t.o_recs + align_up(4 * words * nnz, 256);
+  t.bytes = t.o_bad + align_up(4ull * t.n_tiles, 256);
+  t.ok = max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
+         !env_cap("MGT_NO_PACK", 0, 1, 0) && !env_cap("MGT_NO_TILES", 0, 1, 0);
+  return t;
+}
+
 struct Timing {
   std::vector<hipEvent_t> ev;
   std::vector<const char*> names;
@@ -838,11 +882,14 @@ int check_io(const mgt_desc& d, uint32_t flags, const void* row_ptr, const int32
 // made first (nothing is allocated while capturing), then the call is
 // captured on that stream and instantiated.
 int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStream_t s);
+int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, void* ws,
+              int32_t* d_status, hipStream_t s);
 
-// direct: the call is a small one (run_direct), partitioned or not.
+// direct, tiles: the call takes run_direct or run_tiles, partitioned or not.
 int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
-                 int32_t* d_status, mgt_graph_s* g, bool direct = false, bool partitioned = false) {
-  if (!direct && hipHostMalloc(&g->staging, upload_bytes(y), hipHostMallocDefault) != hipSuccess) {
+                 int32_t* d_status, mgt_graph_s* g, bool direct = false,
+                 const TileGeo* tiles = nullptr, bool partitioned = false) {
+  if (!direct && !tiles && hipHostMalloc(&g->staging, upload_bytes(y), hipHostMallocDefault) != hipSuccess) {
     g->staging = nullptr;
     return MGT_ENOMEM;
   }
@@ -852,8 +899,9 @@ int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
   int st = MGT_OK;
   if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) st = MGT_EHIP;
   if (st == MGT_OK) {
-    st = direct ? run_direct(items[0], partitioned, d_status, s)
-                : run(p, items, y, ws, d_status, s, nullptr, g->staging);
+    st = direct  ? run_direct(items[0], partitioned, d_status, s)
+         : tiles ? run_tiles(items[0], *tiles, partitioned, p->flags, ws, d_status, s)
+                 : run(p, items, y, ws, d_status, s, nullptr, g->staging);
     // the capture is ended whatever happened inside it
     if (hipStreamEndCapture(s, &graph) != hipSuccess && st == MGT_OK) st = MGT_EHIP;
   }
@@ -867,11 +915,11 @@ int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
 }
 
 // Small calls take k_direct: one launch that reads every column id in every
-// workgroup, against five dependent launches of the passes. us per call, direct
-// and passes (1-8 floats per cell, 8-byte offsets): 1 K cells 11 and 40, 20 K 15
-// and 45, 50 K 25 and 50, 80 K 33 and 54, 110 K 44 and 56, 150 K 58 and 58;
-// partitioned (R = 13): 20 K 21 and 75, 150 K 69 and 83.
-constexpr int64_t kDirectCells = 150000;
+// workgroup. us per call, direct, tiles and passes (1-8 floats per cell, 8-byte
+// offsets): 5 K cells 16, 22 and 44; 20 K 16, 24 and 46; 50 K 26, 25 and 51;
+// 100 K 41, 28 and 54; partitioned (R = 37, 23 bytes): 20 K 22, 30 and 104,
+// 50 K 32, 31 and 104.
+constexpr int64_t kDirectCells = 45000;
 
 // Whether a single-matrix call runs directly. Calls that ask for the passes'
 // own stages keep them: device-side checks and stage times, a schedule set by
@@ -926,6 +974,53 @@ int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStrea
   return MGT_OK;
 }
 
+int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, void* ws,
+              int32_t* d_status, hipStream_t s) {
+  const mgt_desc& d = it.d;
+  const ItemDev& v = it.dev;
+  uint8_t* const W = (uint8_t*)ws;
+  TileArgs a{};
+  a.row_ptr = v.row_ptr;
+  a.col = v.col;
+  a.poff = v.poff;
+  a.payload = v.payload;
+  a.t_row_ptr = v.t_row_ptr;
+  a.t_col = v.t_col;
+  a.t_poff = v.t_poff;
+  a.t_payload = v.t_payload;
+  a.perm = v.perm;
+  a.xfer_cells = v.xfer_cells;
+  a.xfer_bytes = v.xfer_bytes;
+  a.part_cell_off = v.part_cell_off;
+  a.part_byte_off = v.part_byte_off;
+  a.sdispls = v.sdispls;
+  a.rdispls = v.rdispls;
+  a.d_status = d_status;
+  a.table = (uint2*)(W + t.o_table);
+  a.recs = (uint32_t*)(W + t.o_recs);
+  a.bad = (uint32_t*)(W + t.o_bad);
+  a.nnz = (uint64_t)d.nnz;
+  a.payload_bytes = (uint64_t)d.payload_bytes;
+  a.n_rows = d.n_rows;
+  a.n_cols = d.n_cols;
+  a.cpb = t.cpb;
+  a.magic = t.cpb > 1 ? (uint32_t)(((1ull << 32) + t.cpb - 1) / t.cpb) : 0u;
+  a.n_buckets = t.n_buckets;
+  a.n_tiles = t.n_tiles;
+  a.tile_cells = t.tile_cells;
+  a.g8 = (t.n_buckets + 7u) & ~7u;
+  a.lg = d.offset_width == 8 ? 3 : 2;
+  a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
+  a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
+  TileBounds b{};
+  if (partitioned) {
+    a.n_parts = d.n_parts;
+    for (int32_t r = 0; r <= d.n_parts; ++r) b.bounds[r] = (int32_t)it.bounds[r];
+  }
+  MGT_HIP(launch_tiles(a, b, s));
+  return MGT_OK;
+}
+
 // no_alloc: the call allocates nothing (no pinned staging, no events, no heap):
 // plans with MGT_DEBUG_TIMING are refused and the descriptor goes up through
 // kernel arguments.
@@ -968,10 +1063,15 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   Layout y = make_layout(Items(items, 1));
   if (ws_bytes < y.bytes) return MGT_ENOMEM;
   const bool direct = use_direct(p, d, partitioned);
+  const TileGeo tg = tile_geo(d, partitioned, p->tune);
+  // (a workspace that only the passes fit keeps them)
+  const bool tiles = !direct && tg.ok && ws_bytes >= tg.bytes;
   if (graph)
-    return record_graph(p, Items(items, 1), y, ws, d_status, graph, direct, partitioned);
+    return record_graph(p, Items(items, 1), y, ws, d_status, graph, direct, tiles ? &tg : nullptr,
+                        partitioned);
   p->timing.used = 0;
   if (direct) return run_direct(it, partitioned, d_status, s);
+  if (tiles) return run_tiles(it, tg, partitioned, p->flags, ws, d_status, s);
   if (no_alloc) {
     alignas(16) uint8_t up[kNoAllocUpload];
     if (upload_bytes(y) > sizeof(up)) return MGT_EUNSUPPORTED;
@@ -989,7 +1089,8 @@ size_t single_ws(const mgt_desc& d, const int64_t* bounds, bool partitioned, con
       make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true, &t);
   items[0].tile = t.tile;
   std::memset(&items[0].dev, 0, sizeof(ItemDev));
-  return make_layout(items).bytes;
+  const TileGeo tg = tile_geo(d, partitioned, t);
+  return std::max<uint64_t>(make_layout(items).bytes, tg.ok ? tg.bytes : 0);
 }
 
 // Workspace estimate for a batch at the limits; mgt_batch_workspace gives the

@@ -1,0 +1,873 @@
+// The two-launch transpose of mid-size matrices: tiles sorted by column bucket,
+// then one workgroup per bucket that collects its cells from every tile.
+//
+//   k_tile_sort   a workgroup sorts a tile of up to kTileMax consecutive cells
+//                 by bucket (a run of `cpb` columns) and writes their records
+//                 in that order, with the tile's row of a table: for every
+//                 bucket, where its cells start in the tile, how many there
+//                 are, and the payload bytes of the tile's earlier buckets.
+//   k_tile_merge  a workgroup adds up its bucket's column of that table (the
+//                 cells and bytes of all earlier buckets: its place in the
+//                 output), collects the bucket's records tile by tile (input
+//                 order), ranks them by column in LDS and writes the outputs
+//                 in final order, each payload read from the input.
+//
+// us per call, this form and the passes (8-byte offsets; 1-8 floats per cell):
+// 100 K cells 28 and 54, 300 K 36 and 65, 1 M 49 and 120, 4 M 151 and 414; 4.3 M
+// cells of 23 bytes over 37 partitions 210 and 850; 6 M cells of 0 to 7 bytes
+// with perm and device checks 214 and 557.
+//
+// Against the passes of kernels.hip: no histogram launches, no scans of
+// (digit, tile) counts and no segment tables between launches; records move
+// once, payloads go from the input to their place. It takes one level of up to
+// kTileBuckets buckets, so it ends where buckets outgrow the LDS of a
+// workgroup. Neither launch needs anything prepared in memory: the arguments
+// travel with the launches.
+//
+// Record of a cell (3 words, a 4th for perm): payload offset (or the payload
+// itself, up to 4 bytes), row, column within the bucket << 22 | size, input
+// index. A size of 2^22 - 1 or more is looked up again in the offsets.
+// (Payloads of up to 8 bytes in a word more were no faster: 4.3 M cells of 8
+// bytes 143 us, against 146 us for 9 bytes read from the input.)
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "../../include/mgt.h"
+#include "kernels.h"
+#include "prims.h"
+
+namespace mgt {
+namespace tl {
+
+constexpr int kTh = 512;                 // threads of both kernels, two or more workgroups per CU
+constexpr int kNW = kTh / kWave;
+constexpr int kSortItems = kTileMax / kTh;  // cells per lane of k_tile_sort
+constexpr int kSortWave = kSortItems * kWave;
+constexpr uint32_t kInline = 4;             // payload bytes a record holds itself
+constexpr uint32_t kSizeMask = (1u << 22) - 1u;  // size field; all ones: look it up
+static_assert(kTileCols <= 1 << 10, "column field of a record");
+
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32u __attribute__((aligned(1)));
+typedef uint16_t u16u __attribute__((aligned(1)));
+typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ int64_t ld_off(const void* p, uint64_t i, int lg) {
+  return lg == 2 ? (int64_t)gm((const int32_t*)p)[i] : gm((const int64_t*)p)[i];
+}
+__device__ __forceinline__ uint32_t ld_lo(const void* p, uint64_t i, int lg) {
+  return *gm((const uint32_t*)((const uint8_t*)p + (i << lg)));
+}
+__device__ __forceinline__ void st_off(void* p, uint64_t i, int64_t v, int lg) {
+  if (lg == 2) gm((int32_t*)p)[i] = (int32_t)v;
+  else gm((int64_t*)p)[i] = v;
+}
+__device__ __forceinline__ int ceil_log2(uint32_t x) { return x <= 1 ? 0 : 32 - __clz(x - 1); }
+
+// The thread index, opaque to the compiler where it is read: indexes derived
+// from it are recomputed there instead of being kept in registers throughout.
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
+// Whether the call's inputs were found invalid (MGT_VALIDATE): k_tile_sort left
+// a flag per tile. Every thread of the workgroup must call it.
+__device__ __forceinline__ bool any_bad(const TileArgs& a) {
+  if (!a.validate) return false;
+  bool bad = false;
+  for (uint32_t t = threadIdx.x; t < a.n_tiles; t += kTh) bad |= gm(a.bad)[t] != 0u;
+  return __syncthreads_or(bad) != 0;
+}
+
+// ----------------------------------------------------------------------------- tile sort
+
+struct SortLds {
+  uint32_t incl[kTileMax];  // row starts per position, then their inclusive scan
+  uint32_t red[kNW];
+};
+// Beside it, sized by the call's buckets: 16-bit (bucket, wave) counts, then
+// first positions; payload bytes per bucket.
+extern __shared__ uint16_t s_dyn[];
+inline uint32_t sort_dyn_bytes(uint32_t n_buckets) { return n_buckets * (2u * kNW + 4u); }
+
+// Row owning cell k: the last row starting at or before it, found by the whole
+// workgroup (each round probes kTh evenly spaced rows).
+__device__ __forceinline__ uint32_t coop_row(const void* rp, int lg, uint64_t n_rows, uint64_t k) {
+  uint64_t lo = 0, hi = n_rows;
+  while (hi - lo > 1) {
+    const uint64_t step = (hi - lo + kTh - 1) / kTh;
+    const uint64_t p = lo + (uint64_t)threadIdx.x * step;
+    const bool ok = p < hi && (uint64_t)ld_off(rp, min(p, n_rows), lg) <= k;
+    int c = __syncthreads_count(ok);
+    c = c < 1 ? 1 : c;
+    lo = lo + (uint64_t)(c - 1) * step;
+    hi = min(lo + step, hi);
+  }
+  return (uint32_t)lo;
+}
+
+// Device-side data checks of this tile's share of the inputs (as k_validate).
+__device__ bool tile_bad(const TileArgs& a, uint32_t t) {
+  bool bad = false;
+  const uint64_t n_rows = (uint64_t)a.n_rows, nnz = a.nnz;
+  const uint64_t pr = (n_rows + a.n_tiles) / a.n_tiles;  // n_rows + 1 offsets, rounded up
+  const uint64_t r1 = min(n_rows + 1, (t + 1) * pr);
+  for (uint64_t i = t * pr + threadIdx.x; i < r1; i += kTh) {
+    const int64_t v = ld_off(a.row_ptr, i, a.lg);
+    if (i == 0 && v != 0) bad = true;
+    if (i == n_rows ? v != (int64_t)nnz : ld_off(a.row_ptr, i + 1, a.lg) < v) bad = true;
+  }
+  const uint64_t k0 = (uint64_t)t * a.tile_cells;
+  const uint64_t k1 = t + 1 == a.n_tiles ? nnz + 1 : min(nnz + 1, k0 + a.tile_cells);
+  for (uint64_t k = k0 + threadIdx.x; k < k1; k += kTh) {
+    if (a.fixed_w < 0) {
+      const int64_t v = ld_off(a.poff, k, a.lg);
+      if (k == 0 && v != 0) bad = true;
+      if (k == nnz) {
+        if (v != (int64_t)a.payload_bytes) bad = true;
+      } else {
+        const int64_t d = ld_off(a.poff, k + 1, a.lg) - v;
+        if (d < 0 || d >= ((int64_t)1 << 32)) bad = true;
+      }
+    }
+    if (k < nnz) {
+      const int32_t c = gm(a.col)[k];
+      if (c < 0 || (int64_t)c >= a.n_cols) bad = true;
+    }
+  }
+  return bad;
+}
+
+// kIdx: the record carries the cell's input index (perm).
+// Bound by the latency of its steps (row search, loads, row expansion, ranks)
+// with three workgroups per CU in flight; the records are stored straight to
+// their place in the tile's own region (up to 80 KB, whole lines by the time
+// they leave the L2).
+template <bool kIdx>
+__global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs a) {
+  constexpr int kWords = kIdx ? 4 : 3;
+  __shared__ SortLds L;
+  uint16_t* const wc = (uint16_t*)__builtin_assume_aligned(s_dyn, 16);
+  uint32_t* const byt = (uint32_t*)(wc + a.n_buckets * kNW);
+  const uint32_t t = blockIdx.x;
+  const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+  const uint64_t k0 = (uint64_t)t * a.tile_cells;
+  const uint32_t n = (uint32_t)min((uint64_t)a.tile_cells, a.nnz - k0);
+  const uint32_t G = a.n_buckets, last = n - 1;
+  // the tile's columns and offsets first, so they fly during the row search
+  uint32_t col[kSortItems], off[kSortItems], end;
+#pragma unroll
+  for (int r = 0; r < kSortItems; ++r) {
+    const uint32_t i = w * kSortWave + r * kWave + lane;
+    col[r] = (uint32_t)gm(a.col)[k0 + min(i, last)];
+    off[r] = a.fixed_w < 0 ? ld_lo(a.poff, k0 + min(i, n), a.lg) : (uint32_t)(k0 + min(i, n)) * (uint32_t)a.fixed_w;
+  }
+  {
+    const uint32_t e = min(w * kSortWave + kSortWave, n);
+    end = a.fixed_w < 0 ? ld_lo(a.poff, k0 + e, a.lg) : (uint32_t)(k0 + e) * (uint32_t)a.fixed_w;
+  }
+  for (uint32_t i = threadIdx.x; i < (uint32_t)kTileMax; i += kTh) L.incl[i] = 0;
+  for (uint32_t i = threadIdx.x; i < (G * kNW + 1) / 2; i += kTh) ((uint32_t*)wc)[i] = 0;
+  for (uint32_t i = threadIdx.x; i < G; i += kTh) byt[i] = 0;
+  if (a.validate) {
+    const bool bad = __syncthreads_or(tile_bad(a, t)) != 0;
+    if (threadIdx.x == 0) gm(a.bad)[t] = bad ? 1u : 0u;
+  }
+  // the transfer matrices of a partitioned call start at zero (k_tile_xfer adds to them)
+  if (a.n_parts > 0)
+    for (uint64_t e = (uint64_t)t * kTh + threadIdx.x; e < (uint64_t)a.n_parts * a.n_parts;
+         e += (uint64_t)a.n_tiles * kTh) {
+      gm(a.xfer_cells)[e] = 0;
+      gm(a.xfer_bytes)[e] = 0;
+    }
+  const uint32_t r0 = coop_row(a.row_ptr, a.lg, (uint64_t)a.n_rows, k0);
+  __syncthreads();
+  // rows of the tile's cells: row starts counted per position, then scanned
+  {
+    const uint64_t kend = k0 + n;
+    bool more = true;
+    for (uint64_t base = (uint64_t)r0 + 1; more; base += kTh) {
+      const uint64_t r = base + threadIdx.x;
+      bool stop = r >= (uint64_t)a.n_rows;
+      if (!stop) {
+        const uint64_t v = (uint64_t)ld_off(a.row_ptr, r, a.lg);
+        if (v >= k0 && v < kend) atomicAdd(&L.incl[v - k0], 1u);
+        stop = v >= kend;
+      }
+      more = !__syncthreads_or(stop);
+    }
+    constexpr int kPer = kTileMax / kTh;
+    const uint32_t p0 = threadIdx.x * kPer;
+    uint32_t v[kPer], s = 0;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      v[q] = L.incl[p0 + q];
+      s += v[q];
+    }
+    uint32_t tot;
+    uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      ex += v[q];
+      L.incl[p0 + q] = ex;
+    }
+    __syncthreads();
+  }
+  uint32_t rank[kSortItems], dig[kSortItems], size[kSortItems];
+#pragma unroll
+  for (int r = 0; r < kSortItems; ++r) {  // each cell's size: the next cell's offset minus its own
+    uint32_t nx = (uint32_t)__shfl_down((int)off[r], 1);
+    const uint32_t wrap = r + 1 < kSortItems
+        ? (uint32_t)__builtin_amdgcn_readlane((int)off[r + 1 < kSortItems ? r + 1 : r], 0) : end;
+    if (lane == kWave - 1) nx = wrap;
+    size[r] = nx - off[r];
+  }
+  const int dbits = ceil_log2(G);
+  // ranks within the tile: stable per (bucket, wave), each wave in cell order
+  uint32_t at[kSortItems];
+#pragma unroll
+  for (int r = 0; r < kSortItems; ++r) {
+    const uint32_t i = w * kSortWave + r * kWave + lane;
+    // (clamped: columns out of range are undefined input, but stay in bounds)
+    const uint32_t c = min(col[r], (uint32_t)a.n_cols - 1u);
+    uint32_t d = a.cpb > 1u ? __umulhi(c, a.magic) : c;
+    if (d * a.cpb > c) --d;  // the reciprocal is rounded up
+    dig[r] = d;
+    at[r] = d * kNW + w;
+    col[r] = c - d * a.cpb;
+    if (i < n && size[r]) atomicAdd(&byt[d], size[r]);
+  }
+  wave_ranks(wc, at, dig, n > w * kSortWave ? n - w * kSortWave : 0u, dbits, rank);
+  __syncthreads();
+  {  // bucket-major scan of the counters, and of the bytes per bucket
+    constexpr int kPer = kTileBuckets / kTh;  // buckets per thread
+    const uint32_t g0 = threadIdx.x * kPer;
+    uint32_t s = 0, sb = 0, b[kPer];
+    v4 c[kPer];  // eight 16-bit counters of a bucket
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      c[q] = v4{0u, 0u, 0u, 0u};
+      b[q] = 0;
+      if (g0 + q < G) {
+        c[q] = *(const v4*)&wc[(g0 + q) * kNW];
+        b[q] = byt[g0 + q];
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s += (c[q][j] & 0xffffu) + (c[q][j] >> 16);
+      sb += b[q];
+    }
+    uint32_t tot;
+    uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
+    uint32_t eb = block_excl_scan<kNW>(sb, L.red, tot);
+    uint2* const row = a.table + (uint64_t)t * G;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (g0 + q < G) {
+        const uint32_t at = ex;
+        v4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t lo = ex;
+          ex += c[q][j] & 0xffffu;
+          o[j] = lo | (ex << 16);
+          ex += c[q][j] >> 16;
+        }
+        *(v4*)&wc[(g0 + q) * kNW] = o;
+        // (start, cells) and the bytes of the tile's earlier buckets
+        gm(row)[g0 + q].x = at | ((ex - at) << 16);
+        gm(row)[g0 + q].y = eb;
+      }
+      eb += b[q];
+    }
+  }
+  __syncthreads();
+  uint32_t* const rec = a.recs + k0 * kWords;
+#pragma unroll
+  for (int r = 0; r < kSortItems; ++r) {
+    const uint32_t i = w * kSortWave + r * kWave + lane;
+    if (i >= n) continue;
+    const uint32_t z = size[r];
+    uint32_t x = off[r];
+    // a small payload goes in place of its offset: the aligned words that hold
+    // it (each holds one of its bytes; nothing is read past the payload array)
+    if (z && z <= kInline && (uint64_t)x + z <= a.payload_bytes) {
+      const uint8_t* const p = a.payload + x;
+      const uint32_t sh = 8u * ((uint32_t)(uintptr_t)p & 3u);
+      const GMEM uint32_t* const q = gm((const uint32_t*)((uintptr_t)p & ~(uintptr_t)3));
+      const uint32_t nb = ((uint32_t)(uintptr_t)p & 3u) + z;
+      const uint32_t w0 = q[0], w1 = nb > 4u ? q[1] : 0u;
+      x = (uint32_t)((((uint64_t)w1 << 32) | w0) >> sh);
+    }
+    const uint32_t row = r0 + L.incl[i];
+    const uint32_t key = (col[r] << 22) | min(z, kSizeMask);
+    const uint32_t p = (uint32_t)wc[dig[r] * kNW + w] + rank[r];
+    GMEM uint32_t* const o = gm(rec + (uint64_t)p * kWords);
+    if constexpr (kWords == 3) {
+      o[0] = x;
+      o[1] = row;
+      o[2] = key;
+    } else {
+      typedef uint32_t r4 __attribute__((ext_vector_type(4), aligned(4)));
+      *(GMEM r4*)o = r4{x, row, key, (uint32_t)k0 + i};
+    }
+  }
+}
+
+// ----------------------------------------------------------------------------- transfer matrices
+
+// X and B of a partitioned call: workgroups (s, j), j < gridDim.y, histogram
+// the owners of the columns of source partition s (its cells are consecutive
+// in the input), every gridDim.y-th chunk each, and add to its row of both.
+__global__ __launch_bounds__(kTh) void k_tile_xfer(TileArgs a, TileBounds b) {
+  __shared__ uint32_t cnt[kDirectParts], byt[kDirectParts];
+  __shared__ int32_t lb[kDirectParts + 1];
+  if (any_bad(a)) return;
+  const uint32_t R = (uint32_t)a.n_parts, s = blockIdx.x, tid = threadIdx.x;
+  for (uint32_t i = tid; i <= R; i += kTh) lb[i] = b.bounds[i];
+  for (uint32_t i = tid; i < R; i += kTh) {
+    cnt[i] = 0;
+    byt[i] = 0;
+  }
+  __syncthreads();
+  const uint64_t kb = min((uint64_t)ld_off(a.row_ptr, (uint32_t)lb[s], a.lg), a.nnz);
+  const uint64_t ke = min((uint64_t)ld_off(a.row_ptr, (uint32_t)lb[s + 1], a.lg), a.nnz);
+  constexpr uint64_t kQ = 4, kChunk = kTh * kQ;
+  for (uint64_t c0 = kb + blockIdx.y * kChunk; c0 < ke; c0 += gridDim.y * kChunk) {
+    uint32_t c[kQ], p0[kQ], p1[kQ];
+#pragma unroll
+    for (uint32_t q = 0; q < kQ; ++q) {
+      const uint64_t k = min(c0 + q * kTh + tid, ke - 1);
+      c[q] = (uint32_t)gm(a.col)[k];
+      p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : 0u;
+      p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, k + 1, a.lg) : (uint32_t)a.fixed_w;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kQ; ++q) {
+      const bool act = c0 + q * kTh + tid < ke;
+      uint32_t lo = 0, hi = R;  // the last partition starting at or before the column
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (lb[mid] <= (int32_t)c[q]) lo = mid;
+        else hi = mid;
+      }
+      // runs of equal owners in consecutive lanes add up first (sorted rows
+      // give a wave few owners), one atomic pair per run
+      const uint32_t d = act ? lo : 0xffffffffu, z = act ? p1[q] - p0[q] : 0u;
+      const uint32_t lane = lane_id();
+      const uint32_t prev = __shfl_up(d, 1, kWave), next = __shfl_down(d, 1, kWave);
+      const uint64_t heads = ballot(lane == 0 || prev != d);
+      const bool tail = lane == kWave - 1 || next != d;
+      const uint32_t incl = wave_incl_scan_u32(z);
+      const int h = 63 - (int)__clzll(heads & ((2ull << lane) - 1ull));
+      const uint32_t base = __shfl(incl - z, h, kWave);
+      if (act && tail) {
+        atomicAdd(&cnt[d], lane - (uint32_t)h + 1u);
+        atomicAdd(&byt[d], incl - base);
+      }
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < R; i += kTh) {
+    if (!cnt[i]) continue;
+    const uint64_t e = (uint64_t)s * R + i;
+    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_cells + e), (unsigned long long)cnt[i],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_bytes + e), (unsigned long long)byt[i],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// Partition offsets and displacements from X and B, by one workgroup.
+__device__ void tile_tails(const TileArgs& a, uint64_t* red) {
+  const uint32_t R = (uint32_t)a.n_parts, d = threadIdx.x;
+  uint64_t cells = 0, bytes = 0, sent = 0;
+  if (d < R) {
+#pragma unroll 8
+    for (uint32_t r = 0; r < R; ++r) {
+      if (a.rdispls) a.rdispls[(uint64_t)d * R + r] = (int64_t)cells;
+      if (a.sdispls) a.sdispls[(uint64_t)d * R + r] = (int64_t)sent;
+      cells += (uint64_t)a.xfer_cells[(uint64_t)r * R + d];
+      bytes += (uint64_t)a.xfer_bytes[(uint64_t)r * R + d];
+      sent += (uint64_t)a.xfer_cells[(uint64_t)d * R + r];
+    }
+  }
+  uint64_t tc, tb;
+  const uint64_t ec = block_excl_scan<kNW>(cells, red, tc);
+  const uint64_t eb = block_excl_scan<kNW>(bytes, red, tb);
+  if (d < R) {
+    a.part_cell_off[d] = (int64_t)ec;
+    a.part_byte_off[d] = (int64_t)eb;
+  }
+  if (d == 0) {
+    a.part_cell_off[R] = (int64_t)tc;
+    a.part_byte_off[R] = (int64_t)tb;
+  }
+}
+
+// ----------------------------------------------------------------------------- bucket merge
+
+constexpr int kMergeItems = kTileCap / kTh;  // cells per lane of a bucket held at once
+constexpr uint32_t kMergeWave = kMergeItems * kWave;
+
+constexpr uint32_t kStage = 2048 + 16;  // payload bytes of 64 cells of up to 32 bytes
+
+struct MergeLds {
+  // output order: row, payload offset (or payload), size then byte prefix. The
+  // tile of every cell, before that, in `row`.
+  uint32_t row[kTileCap], src[kTileCap], bp[kTileCap + 1];
+  union {
+    struct {
+      uint32_t ex[kTileTiles];  // first cell (bucket order) of every tile's run
+      uint16_t st[kTileTiles];  // where the run starts in the tile
+    };
+    alignas(16) uint8_t stage[kNW][kStage];  // after the records are read, single-chunk buckets only
+  };
+  alignas(16) uint16_t wc[kTileCols * kNW];  // (column, wave) counts, then first positions
+  uint32_t red[kNW];
+  uint64_t red64[kNW];
+};
+
+// Writes the z <= 32 low bytes of v to p (any alignment), in at most six pieces.
+template <class P4, class P2, class P1, class PH, class PB>
+__device__ __forceinline__ void put_pieces(P4 p4, P2 p2, P1 p1, PH ph, PB pb, const v4& a, const v4& b,
+                                           uint32_t z) {
+  if (z >= 16u) p4(0u, a);
+  if (z >= 32u) p4(16u, b);
+  const uint32_t o1 = z & 16u;
+  const v4 u = o1 ? b : a;
+  if (z & 8u) p2(o1, u.x, u.y);
+  const uint32_t o2 = z & 24u;
+  const uint32_t s0 = (z & 8u) ? u.z : u.x, s1 = (z & 8u) ? u.w : u.y;
+  if (z & 4u) p1(o2, s0);
+  const uint32_t o3 = z & 28u;
+  const uint32_t s = (z & 4u) ? s1 : s0;
+  if (z & 2u) ph(o3, (uint16_t)s);
+  if (z & 1u) pb(z & 30u, (uint8_t)((z & 2u) ? s >> 16 : s));
+}
+__device__ __forceinline__ void put_lds(uint8_t* d, const v4& a, const v4& b, uint32_t z) {
+  put_pieces([&](uint32_t o, const v4& x) { *(u32x4u*)(d + o) = u32x4u{x.x, x.y, x.z, x.w}; },
+             [&](uint32_t o, uint32_t x, uint32_t y) { *(u32x2u*)(d + o) = u32x2u{x, y}; },
+             [&](uint32_t o, uint32_t x) { *(u32u*)(d + o) = x; },
+             [&](uint32_t o, uint16_t x) { *(u16u*)(d + o) = x; },
+             [&](uint32_t o, uint8_t x) { d[o] = x; }, a, b, z);
+}
+__device__ __forceinline__ void put_global(uint8_t* dst, const v4& a, const v4& b, uint32_t z) {
+  GMEM uint8_t* const d = gm(dst);
+  put_pieces([&](uint32_t o, const v4& x) { *(GMEM u32x4u*)(d + o) = u32x4u{x.x, x.y, x.z, x.w}; },
+             [&](uint32_t o, uint32_t x, uint32_t y) { *(GMEM u32x2u*)(d + o) = u32x2u{x, y}; },
+             [&](uint32_t o, uint32_t x) { *(GMEM u32u*)(d + o) = x; },
+             [&](uint32_t o, uint16_t x) { *(GMEM u16u*)(d + o) = x; },
+             [&](uint32_t o, uint8_t x) { d[o] = x; }, a, b, z);
+}
+// The z <= 32 bytes at src (any alignment) as two 16-byte values: whole 16-byte
+// loads where 32 bytes of the payload array follow, exact pieces at its end.
+__device__ __forceinline__ void get_bytes(const uint8_t* src, bool whole, uint32_t z, v4& a, v4& b) {
+  const GMEM uint8_t* const s = gm(src);
+  a = v4{0u, 0u, 0u, 0u};
+  b = a;
+  if (whole) {
+    const u32x4u x = *(const GMEM u32x4u*)s;
+    a = v4{x.x, x.y, x.z, x.w};
+    if (z > 16u) {
+      const u32x4u y = *(const GMEM u32x4u*)(s + 16);
+      b = v4{y.x, y.y, y.z, y.w};
+    }
+  } else {
+    uint32_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 32; ++j)
+      if ((uint32_t)j < z) v[j >> 2] |= (uint32_t)s[j] << (8 * (j & 3));
+    a = v4{v[0], v[1], v[2], v[3]};
+    b = v4{v[4], v[5], v[6], v[7]};
+  }
+}
+// A payload of over 32 bytes, by one lane.
+__device__ __forceinline__ void copy_long(uint8_t* dst, const uint8_t* src, uint32_t z) {
+  const GMEM uint8_t* s = gm(src);
+  GMEM uint8_t* d = gm(dst);
+  for (; z >= 64u; z -= 64u, s += 64, d += 64) {
+    u32x4u v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ((const GMEM u32x4u*)s)[j];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ((GMEM u32x4u*)d)[j] = v[j];
+  }
+  for (; z >= 16u; z -= 16u, s += 16, d += 16) *(GMEM u32x4u*)d = *(const GMEM u32x4u*)s;
+  for (uint32_t j = 0; j < z; ++j) d[j] = s[j];
+}
+
+// Size of a record's cell: from the offsets where the field cannot hold it
+// (its payload is not inline, so x is its offset: the last cell starting there).
+__device__ __forceinline__ uint32_t rec_size(const TileArgs& a, uint32_t key, uint32_t x) {
+  uint32_t z = key & kSizeMask;
+  if (z == kSizeMask) {
+    if (a.fixed_w >= 0) return (uint32_t)a.fixed_w;
+    uint64_t lo = 0, hi = a.nnz;
+    while (hi - lo > 1) {
+      const uint64_t mid = (lo + hi) >> 1;
+      if (ld_lo(a.poff, mid, a.lg) <= x) lo = mid;
+      else hi = mid;
+    }
+    z = ld_lo(a.poff, lo + 1, a.lg) - x;
+  }
+  return z;
+}
+
+// The tile of every cell of bucket cells [q0, q0 + m), in tl[0..m): the tile
+// runs' starts marked and spread upwards. Ends with a barrier.
+template <int kItems>
+__device__ __forceinline__ void cell_tiles(const uint32_t* ex, const uint32_t* table_len, uint32_t t0,
+                                           uint32_t per, uint32_t T, uint32_t q0, uint32_t m,
+                                           uint32_t* tl, uint32_t* red) {
+  for (uint32_t i = threadIdx.x; i < m; i += kTh) tl[i] = 0;
+  __syncthreads();
+  for (uint32_t j = 0; j < per; ++j) {
+    const uint32_t t = t0 + j;
+    if (t >= T) break;
+    const uint32_t e = ex[t], len = table_len[j];
+    if (len && e + len > q0 && e < q0 + m) tl[max(e, q0) - q0] = t + 1;
+  }
+  __syncthreads();
+  // inclusive maximum: each thread's run, then over the threads
+  uint32_t v[kItems], s = 0;
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t i = threadIdx.x * kItems + j;
+    v[j] = i < m ? tl[i] : 0u;
+    s = max(s, v[j]);
+  }
+  uint32_t inc = s;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const uint32_t u = (uint32_t)__shfl_up((int)inc, o, kWave);
+    if (lane_id() >= (uint32_t)o) inc = max(inc, u);
+  }
+  const uint32_t w = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1) red[w] = inc;
+  __syncthreads();
+  uint32_t run = (uint32_t)__shfl_up((int)inc, 1, kWave);
+  if (lane_id() == 0) run = 0;
+#pragma unroll
+  for (int i = 0; i < kNW; ++i)
+    if ((uint32_t)i < w) run = max(run, red[i]);
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t i = threadIdx.x * kItems + j;
+    run = max(run, v[j]);
+    if (i < m) tl[i] = run;
+  }
+  __syncthreads();
+}
+
+// Two workgroups per CU (80 KB of LDS each), so one's collection and ranking
+// run beside the other's payload reads. Bound by those: each payload that is
+// not inline costs a 128-byte line from the memory-side cache or HBM, and a CU
+// holds about 65 such reads in flight. Buckets run in plain column order within
+// each XCD, so neighbouring buckets share the lines of the table and of the
+// tiles' records in its L2.
+// A bucket of more than kCap cells (skewed columns) is taken in chunks: column
+// totals first, then every chunk's cells to their column's running place.
+template <bool kIdx>
+__global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs a) {
+  constexpr int kItems = kMergeItems;
+  constexpr uint32_t kCap = kTileCap, kWaveCells = kMergeWave;
+  constexpr uint32_t kWords = kIdx ? 4 : 3;
+  __shared__ MergeLds L;
+  const bool bad = any_bad(a);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (a.d_status) *a.d_status = bad ? MGT_ERANGE : MGT_OK;
+    if (!bad) {
+      st_off(a.t_row_ptr, (uint64_t)a.n_cols, (int64_t)a.nnz, a.lg);
+      if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
+    }
+  }
+  if (bad) return;
+  if (blockIdx.x == a.g8) {  // one more workgroup of a partitioned call
+    tile_tails(a, L.red64);
+    return;
+  }
+  const uint32_t g = (uint32_t)xcd_tile(blockIdx.x, a.g8);
+  const uint32_t G = a.n_buckets, T = a.n_tiles;
+  if (g >= G) return;
+  const uint32_t col0 = g * a.cpb, nc = min(a.cpb, (uint32_t)a.n_cols - col0);
+  // the bucket's column of the table: its place in the output, and its runs
+  constexpr int kPerT = kTileTiles / kTh;
+  const uint32_t per = (T + kTh - 1) / kTh, t0 = threadIdx.x * per;
+  uint32_t len[kPerT];
+  uint32_t n, cell0;
+  uint64_t byte0;
+  {
+    uint32_t st[kPerT], sl = 0, sc = 0;
+    uint64_t sb = 0;
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j) {
+      uint2 e = make_uint2(0u, 0u);
+      if ((uint32_t)j < per && t0 + j < T) {
+        e.x = gm(a.table)[(uint64_t)(t0 + j) * G + g].x;
+        e.y = gm(a.table)[(uint64_t)(t0 + j) * G + g].y;
+      }
+      st[j] = e.x & 0xffffu;
+      len[j] = e.x >> 16;
+      sl += len[j];
+      sc += st[j];
+      sb += e.y;
+    }
+    uint32_t e = block_excl_scan<kNW>(sl, L.red, n);
+    block_excl_scan<kNW>(sc, L.red, cell0);
+    block_excl_scan<kNW>(sb, L.red64, byte0);
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j)
+      if ((uint32_t)j < per && t0 + j < T) {
+        L.ex[t0 + j] = e;
+        L.st[t0 + j] = (uint16_t)st[j];
+        e += len[j];
+      }
+  }
+  __syncthreads();
+  if (n == 0) {
+    for (uint32_t c = threadIdx.x; c < nc; c += kTh)
+      st_off(a.t_row_ptr, (uint64_t)col0 + c, (int64_t)cell0, a.lg);
+    return;
+  }
+  const bool multi = n > kCap;  // block-uniform
+  const int dbits = ceil_log2(nc);
+  // chunked buckets: running first cell and byte of every column (bucket
+  // relative), in the last words of `src` and `bp` of the chunk, which a chunk
+  // of kChunk cells leaves free
+  const uint32_t chunk = multi ? kCap - kTileCols : kCap;
+  uint32_t* const run_c = L.src + chunk;
+  uint32_t* const run_b = L.bp + chunk + 1;
+  const uint32_t E = nc * kNW;
+  if (multi) {
+    for (uint32_t c = threadIdx.x; c < nc; c += kTh) {
+      run_c[c] = 0;
+      run_b[c] = 0;
+    }
+    for (uint32_t q0 = 0; q0 < n; q0 += chunk) {
+      const uint32_t m = min(chunk, n - q0);
+      cell_tiles<kItems>(L.ex, len, t0, per, T, q0, m, L.row, L.red);
+      for (uint32_t i = threadIdx.x; i < m; i += kTh) {
+        const uint32_t t = L.row[i] - 1u;
+        const GMEM uint32_t* const r =
+            gm(a.recs + ((uint64_t)t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t])) * kWords);
+        const uint32_t key = r[2], d = min(key >> 22, nc - 1u);
+        atomicAdd(&run_c[d], 1u);
+        atomicAdd(&run_b[d], rec_size(a, key, r[0]));
+      }
+      __syncthreads();
+    }
+    uint32_t v = 0, u = 0, tot;  // nc <= kTileCols == kTh
+    if (threadIdx.x < nc) {
+      v = run_c[threadIdx.x];
+      u = run_b[threadIdx.x];
+    }
+    const uint32_t ev = block_excl_scan<kNW>(v, L.red, tot);
+    const uint32_t eu = block_excl_scan<kNW>(u, L.red, tot);
+    if (threadIdx.x < nc) {
+      run_c[threadIdx.x] = ev;
+      run_b[threadIdx.x] = eu;
+      st_off(a.t_row_ptr, (uint64_t)col0 + threadIdx.x, (int64_t)cell0 + ev, a.lg);
+    }
+  }
+  for (uint32_t q0 = 0; q0 < n; q0 += chunk) {
+    const uint32_t tid = opaque(threadIdx.x);
+    const uint32_t w = tid / kWave, lane = tid % kWave;
+    const uint32_t m = min(chunk, n - q0);
+    __syncthreads();  // the previous chunk's positions have been read
+    cell_tiles<kItems>(L.ex, len, t0, per, T, q0, m, L.row, L.red);
+    uint32_t x[kItems], row[kItems], key[kItems], idx[kIdx ? kItems : 1];
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      const uint32_t i = min(w * kWaveCells + q * kWave + lane, m - 1u);
+      const uint32_t t = L.row[i] - 1u;
+      const GMEM uint32_t* const r =
+          gm(a.recs + ((uint64_t)t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t])) * kWords);
+      x[q] = r[0];
+      row[q] = r[1];
+      key[q] = r[2];
+      if constexpr (kIdx) idx[q] = r[3];
+    }
+    for (uint32_t e = tid; e < (E + 1) / 2; e += kTh) ((uint32_t*)L.wc)[e] = 0;
+    __syncthreads();
+    uint32_t rank[kItems];
+    {
+      uint32_t at[kItems], d[kItems];
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        d[q] = min(key[q] >> 22, nc - 1u);
+        at[q] = d[q] * kNW + w;
+      }
+      wave_ranks(L.wc, at, d, m > w * kWaveCells ? m - w * kWaveCells : 0u, dbits, rank);
+    }
+    __syncthreads();
+    {  // column-major scan of the counters (eight per column, one column per thread)
+      static_assert(kTileCols == kTh, "one column per thread");
+      v4 c = v4{0u, 0u, 0u, 0u};
+      if (tid < nc) c = *(const v4*)&L.wc[tid * kNW];
+      uint32_t s = 0, tot;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s += (c[j] & 0xffffu) + (c[j] >> 16);
+      uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
+      if (tid < nc) {
+        if (!multi) st_off(a.t_row_ptr, (uint64_t)col0 + tid, (int64_t)cell0 + ex, a.lg);
+        v4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t lo = ex;
+          ex += c[j] & 0xffffu;
+          o[j] = lo | (ex << 16);
+          ex += c[j] >> 16;
+        }
+        *(v4*)&L.wc[tid * kNW] = o;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      const uint32_t i = w * kWaveCells + q * kWave + lane;
+      if (i >= m) continue;
+      const uint32_t d = min(key[q] >> 22, nc - 1u);
+      const uint32_t p = (uint32_t)L.wc[d * kNW + w] + rank[q];
+      L.row[p] = row[q];
+      L.src[p] = x[q];
+      L.bp[p] = rec_size(a, key[q], x[q]);
+      if constexpr (kIdx) {
+        uint64_t at = (uint64_t)cell0 + p;
+        if (multi) at = (uint64_t)cell0 + run_c[d] + (p - L.wc[d * kNW]);
+        gm(a.perm)[at] = idx[q];
+      }
+    }
+    __syncthreads();
+    {  // sizes -> exclusive byte prefix in output order
+      uint32_t v[kItems], s = 0, tot;
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        const uint32_t p = tid * kItems + q;
+        v[q] = p < m ? L.bp[p] : 0u;
+        s += v[q];
+      }
+      uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        const uint32_t p = tid * kItems + q;
+        if (p < m) L.bp[p] = ex;
+        ex += v[q];
+      }
+      if (tid == 0) L.bp[m] = tot;
+      __syncthreads();
+    }
+    // outputs in output order, kPay cells per lane with their payloads in flight
+    constexpr int kPay = 3;
+#pragma unroll 1
+    for (int g0 = 0; g0 < kItems; g0 += kPay) {
+      uint32_t z[kPay], b[kPay], o[kPay], r[kPay];
+      v4 va[kPay], vb[kPay];
+      bool shorts = true;
+#pragma unroll
+      for (int q = 0; q < kPay; ++q) {
+        const uint32_t p = (uint32_t)(g0 + q) * kTh + tid;
+        const bool act = g0 + q < kItems && p < m;
+        const uint32_t pc = act ? p : 0u;
+        b[q] = L.bp[pc];
+        z[q] = act ? L.bp[pc + 1] - b[q] : 0u;
+        o[q] = L.src[pc];
+        r[q] = L.row[pc];
+        va[q] = v4{o[q], 0u, 0u, 0u};
+        vb[q] = v4{0u, 0u, 0u, 0u};
+        shorts &= z[q] <= 32u;
+        if (z[q] > kInline && z[q] <= 32u)
+          get_bytes(a.payload + o[q], (uint64_t)o[q] + 32u <= a.payload_bytes, z[q], va[q], vb[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < kPay; ++q) {
+        const uint32_t p = (uint32_t)(g0 + q) * kTh + tid;
+        if (g0 + q >= kItems || p >= m) continue;
+        uint64_t at = (uint64_t)cell0 + p, bt = byte0 + b[q];
+        if (multi) {
+          uint32_t lo = 0, hi = nc;  // the cell's column: the last one starting at or before p
+          while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if ((uint32_t)L.wc[mid * kNW] <= p) lo = mid;
+            else hi = mid;
+          }
+          const uint32_t ds = L.wc[lo * kNW];
+          at = (uint64_t)cell0 + run_c[lo] + (p - ds);
+          bt = byte0 + run_b[lo] + (b[q] - L.bp[ds]);
+          if (z[q] > 32u) copy_long(a.t_payload + bt, a.payload + o[q], z[q]);
+          else if (z[q]) put_global(a.t_payload + bt, va[q], vb[q], z[q]);
+        }
+        gm(a.t_col)[at] = (int32_t)r[q];
+        if (a.t_poff) st_off(a.t_poff, at, (int64_t)bt, a.lg);
+      }
+      if (multi) continue;
+      // a wave's 64 payloads are one run of output bytes: packed in LDS, then
+      // written 16 bytes per lane
+      const bool staged = __all(shorts);
+#pragma unroll
+      for (int q = 0; q < kPay; ++q) {
+        const uint32_t p = (uint32_t)(g0 + q) * kTh + tid;
+        const uint64_t act = ballot(g0 + q < kItems && p < m);  // a prefix of the lanes
+        if (act == 0) continue;                                  // wave-uniform
+        if (!staged) {
+          if (z[q] > 32u) copy_long(a.t_payload + byte0 + b[q], a.payload + o[q], z[q]);
+          else if (z[q]) put_global(a.t_payload + byte0 + b[q], va[q], vb[q], z[q]);
+          continue;
+        }
+        const uint32_t lastl = 63u - (uint32_t)__clzll(act);
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b[q]);
+        const uint32_t rel = b[q] - b0;
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)(rel + z[q]), (int)lastl);
+        uint8_t* const stage = L.stage[w];
+        put_lds(stage + rel, va[q], vb[q], z[q]);
+        __builtin_amdgcn_wave_barrier();
+        uint8_t* const dst = a.t_payload + byte0 + b0;
+        for (uint32_t e = lane * 16u; e < tot; e += kWave * 16u) {
+          const v4 s = *(const v4*)(stage + e);
+          if (e + 16u <= tot) *(GMEM u32x4u*)gm(dst + e) = u32x4u{s.x, s.y, s.z, s.w};
+          else put_global(dst + e, s, s, tot - e);
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    if (multi) {
+      __syncthreads();
+      uint32_t dc = 0, db = 0;
+      if (tid < nc) {
+        const uint32_t i0 = L.wc[tid * kNW], i1 = tid + 1 < nc ? (uint32_t)L.wc[(tid + 1) * kNW] : m;
+        dc = i1 - i0;
+        db = L.bp[i1] - L.bp[i0];
+        run_c[tid] += dc;
+        run_b[tid] += db;
+      }
+    }
+  }
+}
+
+}  // namespace tl
+
+static_assert(sizeof(tl::MergeLds) <= 80 * 1024, "two workgroups per CU");
+
+template <bool kIdx>
+static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStream_t s) {
+  hipLaunchKernelGGL((tl::k_tile_sort<kIdx>), dim3(a.n_tiles), dim3(tl::kTh),
+                     tl::sort_dyn_bytes(a.n_buckets), s, a);
+  if (a.n_parts > 0) {
+    // about 4,096 cells (two rounds of loads) per workgroup: the kernel is one
+    // chain of latencies, and its adds are one per workgroup and partition pair
+    const uint64_t per = std::min<uint64_t>(a.nnz / ((uint64_t)a.n_parts * 4096u) + 1, 65535);
+    hipLaunchKernelGGL(tl::k_tile_xfer, dim3((unsigned)a.n_parts, (unsigned)per), dim3(tl::kTh), 0, s, a, b);
+  }
+  hipLaunchKernelGGL((tl::k_tile_merge<kIdx>), dim3(a.g8 + (a.n_parts > 0 ? 1u : 0u)),
+                     dim3(tl::kTh), 0, s, a);
+}
+
+hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s) {
+  if (a.perm) launch_tile_kernels<true>(a, b, s);
+  else launch_tile_kernels<false>(a, b, s);
+  return hipGetLastError();
+}
+
+}  // namespace mgt

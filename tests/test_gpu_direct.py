@@ -1,5 +1,5 @@
-"""Small calls (up to 150,000 cells: one launch, no workspace) against the
-oracle and against the same call through the passes (MGT_NO_DIRECT=1), at the
+"""Small calls (up to 45,000 cells: one launch, no workspace) against the
+oracle and against the same call by the other forms (MGT_NO_DIRECT=1), at the
 edges of their forms: 64-cell rounds, a wave's list of 256 cells (a hot column
 outgrows it), row offsets in LDS (up to 8,191 rows) or searched in memory, 256
 columns per workgroup, 256 partitions, every payload copy."""
@@ -19,7 +19,7 @@ PART_KEYS = ("xfer_cells", "xfer_bytes", "part_cell_off", "part_byte_off", "sdis
 
 
 def _both(a, monkeypatch, partitioned, perm=True):
-    """The call run directly and through the passes: equal, and equal to the oracle's."""
+    """The call run directly and by the other forms: equal, and equal to the oracle's."""
     outs = []
     for off in (False, True):
         if off:
@@ -58,13 +58,13 @@ def test_cell_counts(nnz, law, ow, monkeypatch):
 @pytest.mark.parametrize("n_rows,n_cols,law", [
     (1, 1, "uniform"), (8190, 300, "uniform"), (8191, 257, "uniform"), (8192, 256, "hot"),
     (40000, 70, "uniform"), (300, 65536, "uniform"), (300, 65535, "ends"), (5, 40000, "hot"),
-    (300, 65537, "uniform"),  # too many columns: the passes
+    (300, 65537, "uniform"),  # too many columns
 ])
 def test_shapes(n_rows, n_cols, law, monkeypatch):
     _both(_matrix(n_rows, n_cols, 30011, law, n_cols, 13, 8), monkeypatch, False)
 
 
-@pytest.mark.parametrize("nnz", [150000, 150001])  # the last direct size, the first of the passes
+@pytest.mark.parametrize("nnz", [45000, 45001])  # the last direct size, the first past it
 def test_largest(nnz, monkeypatch):
     _both(_matrix(4000, 4000, nnz, "uniform", 1, 33, 8, 9), monkeypatch, True)
 
@@ -141,8 +141,9 @@ def test_replays_and_no_allocation(partitioned):
 
 @pytest.mark.parametrize("seed,parts,sort_rows,ow", [(0, 1, True, 8), (1, 4, False, 4), (2, 300, True, 8)])
 def test_passes_on_small_inputs(seed, parts, sort_rows, ow, monkeypatch):
-    """Small calls the passes still take (other sizes of the same call would)."""
+    """Small calls through the passes (device checks, set schedules and other sizes take them)."""
     monkeypatch.setenv("MGT_NO_DIRECT", "1")
+    monkeypatch.setenv("MGT_NO_TILES", "1")
     a = gen.random_small(seed, n_rows=3000, n_cols=3000, deg_mean=11.0, w_lo=0, w_hi=9,
                          sort_rows=sort_rows, offset_width=ow, parts=parts)
     for partitioned in (False, True):
