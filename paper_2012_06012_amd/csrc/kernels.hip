@@ -653,7 +653,7 @@ struct SortLdsT {
   uint32_t src[kSub];       // payload offset relative to the sub-chunk's first byte
   uint32_t bpre[kBytes ? kSub + 1 : 1];  // exclusive prefix of sz in sorted order; bpre[n] = total
   uint16_t dig[kSlim ? 1 : kSub];
-  uint16_t wc[kFan * kNW];  // (digit, wave) counts, then their digit-major exclusive scan
+  alignas(16) uint16_t wc[kFan * kNW];  // (digit, wave) counts, then their digit-major exclusive scan
 };
 using SortLds = SortLdsT<kMaxFanout, true>;
 constexpr int kFanBits = 1 << MGT_GEO_FANBITS;  // fan-out of a bits-mode pass
@@ -674,21 +674,10 @@ __device__ __forceinline__ void sort_sub(LT& L, uint32_t F, int dbits, uint32_t 
   const uint32_t E = F * kNW;
   for (uint32_t e = threadIdx.x; e < E; e += kBlock) L.wc[e] = 0;
   __syncthreads();
-  uint32_t rank[kItems];
+  uint32_t rank[kItems], at[kItems];
 #pragma unroll
-  for (int r = 0; r < kItems; ++r) {
-    const uint32_t i = w * kWaveCells + r * kWave + lane;
-    const bool act = i < n;
-    const uint32_t d = act ? dg[r] : 0u;
-    const uint64_t peers = match_peers(d, act, dbits);
-    rank[r] = 0;
-    if (act) {
-      const uint32_t below = popc_below(peers);
-      const uint32_t old = L.wc[d * kNW + w];
-      if (below == 0) L.wc[d * kNW + w] = (uint16_t)(old + (uint32_t)__popcll(peers));
-      rank[r] = old + below;
-    }
-  }
+  for (int r = 0; r < kItems; ++r) at[r] = dg[r] * kNW + w;
+  wave_ranks(L.wc, at, dg, n > w * kWaveCells ? n - w * kWaveCells : 0u, dbits, rank);
   __syncthreads();
   {
     const uint32_t per = (E + kBlock - 1) / kBlock;
@@ -2051,7 +2040,7 @@ struct BucketLds {
   uint32_t row[kBkCap];              // output order: original row id
   uint32_t src[kBkCap];              // output order: payload offset above the bucket's lowest
   uint32_t bp[kBkCap + 1];           // output order: size, then its exclusive prefix
-  uint16_t wc[kFinishCols * kBkNW];  // (column, wave) counts, then their column-major scan
+  alignas(16) uint16_t wc[kFinishCols * kBkNW];  // (column, wave) counts, then their column-major scan
   uint64_t lo[kBkNW], hi[kBkNW], tot[kBkNW];
   uint32_t red[kBkNW + 1];
   uint32_t next;                     // skip mode: the next bucket left by an earlier launch
@@ -2215,20 +2204,11 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
       if (len == 0) blo = 0;
       if (fits) {
         // stable ranks: per (column, wave) counters, each wave in cell order
-        const int dbits = ceil_log2(nc);
+        uint32_t at[kBkItems];
 #pragma unroll
-        for (int q = 0; q < kBkItems; ++q) {
-          const uint32_t i = w * kBkWaveCells + q * kWave + lane;
-          const bool act = i < len;
-          const uint64_t peers = match_peers(dg[q], act, dbits);
-          rank[q] = 0;
-          if (act) {
-            const uint32_t below = popc_below(peers);
-            const uint32_t old = L.wc[dg[q] * kBkNW + w];
-            if (below == 0) L.wc[dg[q] * kBkNW + w] = (uint16_t)(old + (uint32_t)__popcll(peers));
-            rank[q] = old + below;
-          }
-        }
+        for (int q = 0; q < kBkItems; ++q) at[q] = dg[q] * kBkNW + w;
+        wave_ranks(L.wc, at, dg, len > w * kBkWaveCells ? len - w * kBkWaveCells : 0u,
+                   ceil_log2(nc), rank);
         __syncthreads();
         {  // column-major exclusive scan of the counters: each column's first output cell
           const uint32_t per = (E + kBkBlock - 1) / kBkBlock;
