@@ -8,8 +8,9 @@
 // storage), or the mirrored cells then the stored row (upper storage).
 //
 // Stages: k_sym_count (cells and payload bytes of every row of S) -> exclusive
-// scans -> k_sym_fill (one wave per row copies both parts: column ids,
-// payload offsets, payload bytes) -> k_sym_tail (end offsets, sizes, status).
+// scans -> k_sym_fill (a workgroup per 2,048 cells of S: column ids, payload
+// offsets, payload bytes; others write the row offsets and the tail: end
+// offsets, sizes, status).
 // Offsets are clamped into their arrays before they index anything, so
 // invalid inputs cannot make these kernels access memory out of bounds.
 #include <hip/hip_runtime.h>
@@ -18,6 +19,7 @@
 
 #include "../../include/mgt.h"
 #include "kernels.h"
+#include "payload.h"
 #include "prims.h"
 
 namespace mgt {
@@ -78,65 +80,156 @@ __global__ __launch_bounds__(kB) void k_sym_count(SymArgs a) {
   }
 }
 
-// One wave per row of S: the stored part and the mirrored part, each a run of
-// consecutive output cells whose payloads are one contiguous byte range of
-// their source (the input, or T's payload).
-__global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a) {
-  if (*(volatile int32_t*)a.st != MGT_OK) return;
-  const uint32_t lane = lane_id();
-  const uint64_t waves = (uint64_t)gridDim.x * (kB / kWave);
-  for (uint64_t i = (uint64_t)blockIdx.x * (kB / kWave) + threadIdx.x / kWave; i < a.n; i += waves) {
-    const uint64_t c0 = a.ocnt[i], b0 = a.obyt[i];
-    if (lane == 0) st_o(a.s_row_ptr, i, c0, a.ow);
-    const uint64_t rs = min(ld_o(a.row_ptr, i, a.ow), a.nnz);
-    const uint64_t re = max(rs, min(ld_o(a.row_ptr, i + 1, a.ow), a.nnz));
-    const Range m = mirrored(a, i);
-    const uint64_t ps0 = min(ld_o(a.poff, rs, a.ow), a.pbytes);
-    const uint64_t pm0 = min(ld_o(a.t_poff, m.m0, a.ow), a.pbytes);
-    const uint64_t ps1 = min(ld_o(a.poff, re, a.ow), a.pbytes);
-    const uint64_t pm1 = min(ld_o(a.t_poff, m.m1, a.ow), a.pbytes);
-    const uint64_t bs = ps1 - min(ps0, ps1), bm = pm1 - min(pm0, pm1);
-    // where each part starts in row i of S
-    const uint64_t cs = a.lower ? c0 : c0 + (m.m1 - m.m0), bs0 = a.lower ? b0 : b0 + bm;
-    const uint64_t cm = a.lower ? c0 + (re - rs) : c0, bm0 = a.lower ? b0 + bs : b0;
-    // (the capacity checks only matter for unvalidated inputs whose offsets
-    // decrease: valid inputs fill S exactly)
-    for (uint64_t j = lane; j < re - rs; j += kWave) {
-      const uint64_t k = rs + j;
-      const uint64_t o = min(ld_o(a.poff, k, a.ow), a.pbytes);
-      const uint64_t o1 = max(o, min(ld_o(a.poff, k + 1, a.ow), a.pbytes));
-      const uint64_t ob = bs0 + (o - min(ps0, o));
-      if (cs + j >= a.cap_cells) break;
-      gm(a.s_col)[cs + j] = gm(a.col)[k];
-      st_o(a.s_poff, cs + j, ob, a.ow);
-      if (o1 > o && ob + (o1 - o) <= a.cap_bytes)
-        copy_cell(a.s_payload + ob, a.payload + o, (uint32_t)(o1 - o));
+// S by output cells, kFillCells per workgroup, whatever the rows' lengths: the
+// workgroup finds the row of its first cell, counts in LDS where the rows after
+// it start and scans the counts. Cell j of row i comes from the stored row or
+// from T's row, both read in order, so every access runs along its array; a
+// wave's 64 payloads are one run of output bytes and go out through LDS.
+// Bound by the loads of the rows' fields (about ten per cell, nearly all from
+// the L1). One wave per row, each lane copying its cell, took 272 us on 4 M
+// cells of 8 bytes on average in rows of 32 (8 M cells of S); this takes 134.
+constexpr int kFillCells = 2048;
+constexpr int kFillPer = kFillCells / kB;
+
+__global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a, uint32_t cell_blocks) {
+  __shared__ uint32_t incl[kFillCells];
+  __shared__ alignas(16) uint8_t stage[kB / kWave][kStage];
+  __shared__ uint32_t red[kB / kWave];
+  const int32_t st = *(volatile int32_t*)a.st;
+  const uint32_t w = threadIdx.x / kWave;
+  if (blockIdx.x >= cell_blocks) {  // the row offsets, and the tail
+    const uint64_t stride = (uint64_t)(gridDim.x - cell_blocks) * kB;
+    const uint64_t i0 = (uint64_t)(blockIdx.x - cell_blocks) * kB + threadIdx.x;
+    if (i0 == 0 && a.d_status) *a.d_status = st;
+    if (st != MGT_OK) return;
+    const uint64_t cells = a.n ? min(a.ocnt[a.n], a.cap_cells) : 0;
+    for (uint64_t i = i0; i < a.n; i += stride) st_o(a.s_row_ptr, i, a.ocnt[i], a.ow);
+    if (i0 == 0) {
+      const uint64_t bytes = a.n ? min(a.obyt[a.n], a.cap_bytes) : 0;
+      st_o(a.s_row_ptr, a.n, cells, a.ow);
+      st_o(a.s_poff, cells, bytes, a.ow);
+      if (a.d_sizes) {
+        a.d_sizes[0] = (int64_t)cells;
+        a.d_sizes[1] = (int64_t)bytes;
+      }
     }
-    for (uint64_t j = lane; j < m.m1 - m.m0; j += kWave) {
-      const uint64_t q = m.m0 + j;
-      const uint64_t o = min(ld_o(a.t_poff, q, a.ow), a.pbytes);
-      const uint64_t o1 = max(o, min(ld_o(a.t_poff, q + 1, a.ow), a.pbytes));
-      const uint64_t ob = bm0 + (o - min(pm0, o));
-      if (cm + j >= a.cap_cells) break;
-      gm(a.s_col)[cm + j] = gm(a.t_col)[q];
-      st_o(a.s_poff, cm + j, ob, a.ow);
-      if (o1 > o && ob + (o1 - o) <= a.cap_bytes)
-        copy_cell(a.s_payload + ob, a.t_payload + o, (uint32_t)(o1 - o));
+    return;
+  }
+  if (st != MGT_OK) return;
+  const uint64_t total = min(a.ocnt[a.n], a.cap_cells);
+  const uint64_t q0 = (uint64_t)blockIdx.x * kFillCells;
+  if (q0 >= total) return;
+  const uint32_t m = (uint32_t)min((uint64_t)kFillCells, total - q0);
+  for (uint32_t i = threadIdx.x; i < (uint32_t)kFillCells; i += kB) incl[i] = 0;
+  uint64_t lo = 0, hi = a.n;  // the last row starting at or before q0
+  while (hi - lo > 1) {
+    const uint64_t step = (hi - lo + kB - 1) / kB;
+    const uint64_t p = lo + (uint64_t)threadIdx.x * step;
+    const int c = max(1, __syncthreads_count(p < hi && a.ocnt[min(p, a.n)] <= q0));
+    lo += (uint64_t)(c - 1) * step;
+    hi = min(lo + step, hi);
+  }
+  const uint64_t r0 = lo;
+  __syncthreads();
+  bool more = true;
+  for (uint64_t base = r0 + 1; more; base += kB) {
+    const uint64_t r = base + threadIdx.x;
+    bool stop = r >= a.n;
+    if (!stop) {
+      const uint64_t v = a.ocnt[r];
+      if (v >= q0 && v < q0 + m) atomicAdd(&incl[v - q0], 1u);
+      stop = v >= q0 + m;
+    }
+    more = !__syncthreads_or(stop);
+  }
+  {
+    const uint32_t p0 = threadIdx.x * kFillPer;
+    uint32_t v[kFillPer], s = 0, tot;
+#pragma unroll
+    for (int j = 0; j < kFillPer; ++j) {
+      v[j] = incl[p0 + j];
+      s += v[j];
+    }
+    uint32_t ex = block_excl_scan<kB / kWave>(s, red, tot);
+#pragma unroll
+    for (int j = 0; j < kFillPer; ++j) {
+      ex += v[j];
+      incl[p0 + j] = ex;
     }
   }
-}
-
-__global__ void k_sym_tail(SymArgs a) {
-  const int32_t st = *(volatile int32_t*)a.st;
-  if (a.d_status) *a.d_status = st;
-  if (st != MGT_OK) return;
-  const uint64_t cells = a.n ? min(a.ocnt[a.n], a.cap_cells) : 0;
-  const uint64_t bytes = a.n ? min(a.obyt[a.n], a.cap_bytes) : 0;
-  st_o(a.s_row_ptr, a.n, cells, a.ow);
-  st_o(a.s_poff, cells, bytes, a.ow);
-  if (a.d_sizes) {
-    a.d_sizes[0] = (int64_t)cells;
-    a.d_sizes[1] = (int64_t)bytes;
+  __syncthreads();
+  constexpr int kPay = 2;  // cells per lane whose fields and payloads are in flight together (4: no faster)
+  const uint64_t top = a.nnz;  // (> 0: S has a cell)
+#pragma unroll 1
+  for (int g = 0; g < kFillPer; g += kPay) {
+    uint64_t ob[kPay], so[kPay];
+    uint32_t z[kPay];
+    int32_t col[kPay];
+    const uint8_t* src[kPay];
+    v4 va[kPay], vb[kPay];
+    bool ok = true;
+#pragma unroll
+    for (int e = 0; e < kPay; ++e) {
+      const uint32_t p = (uint32_t)(g + e) * kB + threadIdx.x;
+      const bool act = p < m;
+      const uint64_t i = r0 + incl[act ? p : 0u], q = q0 + (act ? p : 0u);
+      const uint64_t c0 = a.ocnt[i], c1 = a.ocnt[i + 1], b0 = a.obyt[i];
+      const uint64_t rs = min(ld_o(a.row_ptr, i, a.ow), top);
+      const uint64_t re = max(rs, min(ld_o(a.row_ptr, i + 1, a.ow), top));
+      const uint64_t ns = re - rs, nm = c1 - c0 - ns, j = q - c0;
+      // T's row without its diagonal cells: they lead it for lower storage
+      const uint64_t t0 = a.lower ? ld_o(a.t_row_ptr, i + 1, a.ow) - nm : ld_o(a.t_row_ptr, i, a.ow);
+      const uint64_t m0 = min(t0, top);
+      const bool mir = a.lower ? j >= ns : j < nm;
+      const uint64_t first = mir ? m0 : rs;
+      const uint64_t k = min(first + (a.lower ? (mir ? j - ns : j) : (mir ? j : j - nm)), top - 1);
+      const void* const po = mir ? a.t_poff : a.poff;
+      const uint64_t o = min(ld_o(po, k, a.ow), a.pbytes);
+      const uint64_t o1 = max(o, min(ld_o(po, k + 1, a.ow), a.pbytes));
+      const uint64_t of = min(ld_o(po, first, a.ow), o);
+      // bytes of the part that comes first in the row, for cells of the second
+      uint64_t before = 0;
+      if (a.lower ? mir : !mir) {
+        const void* const pf = a.lower ? a.poff : a.t_poff;
+        const uint64_t f0 = a.lower ? rs : m0, f1 = a.lower ? re : min(m0 + nm, top);
+        const uint64_t x = ld_o(pf, f0, a.ow), y = ld_o(pf, f1, a.ow);
+        before = y > x ? y - x : 0;
+      }
+      ob[e] = b0 + before + (o - of);
+      z[e] = act ? (uint32_t)(o1 - o) : 0u;
+      // (only offsets that decrease, in unvalidated inputs, can pass the end)
+      if (ob[e] > a.cap_bytes || z[e] > a.cap_bytes - ob[e]) z[e] = 0;
+      col[e] = gm(mir ? a.t_col : a.col)[k];
+      so[e] = o;
+      src[e] = (mir ? a.t_payload : a.payload) + o;
+      ok &= z[e] <= 32u;
+    }
+#pragma unroll
+    for (int e = 0; e < kPay; ++e) {
+      va[e] = v4{0u, 0u, 0u, 0u};
+      vb[e] = v4{0u, 0u, 0u, 0u};
+      if (z[e] && z[e] <= 32u) get_bytes(src[e], so[e] + 32u <= a.pbytes, z[e], va[e], vb[e]);
+    }
+#pragma unroll
+    for (int e = 0; e < kPay; ++e) {
+      const uint32_t p = (uint32_t)(g + e) * kB + threadIdx.x;
+      if (p < m) {
+        gm(a.s_col)[q0 + p] = col[e];
+        st_o(a.s_poff, q0 + p, ob[e], a.ow);
+      }
+      const uint64_t act = ballot(p < m);  // a prefix of the lanes
+      if (act == 0) continue;              // wave-uniform
+      // the wave's run of output bytes, if its cells lie in it as they should
+      const uint64_t base = wave_bcast(ob[e], 0);
+      const uint64_t end = wave_bcast(ob[e] + z[e], 63 - (int)__clzll(act));
+      const uint64_t rel = ob[e] - base;
+      if (__all(ok && (p >= m || (ob[e] >= base && rel + z[e] <= end - base))) && end - base <= 2048u) {
+        write_run(stage[w], a.s_payload + base, (uint32_t)rel, (uint32_t)(end - base), va[e], vb[e], z[e]);
+      } else if (z[e]) {
+        if (z[e] <= 32u) put_global(a.s_payload + ob[e], va[e], vb[e], z[e]);
+        else copy_long(a.s_payload + ob[e], src[e], z[e]);
+      }
+    }
   }
 }
 
@@ -149,10 +242,12 @@ hipError_t launch_symmetrize(const SymArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(sym::k_sym_count, dim3((unsigned)g), dim3(sym::kB), 0, s, a);
     hipError_t e = launch_scan(a.cnt, a.ocnt, a.byt, a.obyt, nullptr, n, a.scan, s);
     if (e != hipSuccess) return e;
-    const uint64_t gw = std::min<uint64_t>((n + sym::kB / kWave - 1) / (sym::kB / kWave), 65536);
-    hipLaunchKernelGGL(sym::k_sym_fill, dim3((unsigned)gw), dim3(sym::kB), 0, s, a);
   }
-  hipLaunchKernelGGL(sym::k_sym_tail, dim3(1), dim3(1), 0, s, a);
+  // (S holds at most 2 nnz cells; workgroups past its end leave at once)
+  const uint64_t cells = n ? (2 * a.nnz + sym::kFillCells - 1) / sym::kFillCells : 0;
+  const uint64_t rows = std::min<uint64_t>(n / sym::kB + 1, 4096);
+  hipLaunchKernelGGL(sym::k_sym_fill, dim3((unsigned)(cells + rows)), dim3(sym::kB), 0, s, a,
+                     (uint32_t)cells);
   return hipGetLastError();
 }
 

@@ -35,6 +35,7 @@
 
 #include "../../include/mgt.h"
 #include "kernels.h"
+#include "payload.h"
 #include "prims.h"
 
 namespace mgt {
@@ -47,12 +48,6 @@ constexpr int kSortWave = kSortItems * kWave;
 constexpr uint32_t kInline = 4;             // payload bytes a record holds itself
 constexpr uint32_t kSizeMask = (1u << 22) - 1u;  // size field; all ones: look it up
 static_assert(kTileCols <= 1 << 10, "column field of a record");
-
-typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(1)));
-typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(1)));
-typedef uint32_t u32u __attribute__((aligned(1)));
-typedef uint16_t u16u __attribute__((aligned(1)));
-typedef uint32_t v4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int64_t ld_off(const void* p, uint64_t i, int lg) {
   return lg == 2 ? (int64_t)gm((const int32_t*)p)[i] : gm((const int64_t*)p)[i];
@@ -412,8 +407,6 @@ __device__ void tile_tails(const TileArgs& a, uint64_t* red) {
 constexpr int kMergeItems = kTileCap / kTh;  // cells per lane of a bucket held at once
 constexpr uint32_t kMergeWave = kMergeItems * kWave;
 
-constexpr uint32_t kStage = 2048 + 16;  // payload bytes of 64 cells of up to 32 bytes
-
 struct MergeLds {
   // output order: row, payload offset (or payload), size then byte prefix. The
   // tile of every cell, before that, in `row`.
@@ -429,75 +422,6 @@ struct MergeLds {
   uint32_t red[kNW];
   uint64_t red64[kNW];
 };
-
-// Writes the z <= 32 low bytes of v to p (any alignment), in at most six pieces.
-template <class P4, class P2, class P1, class PH, class PB>
-__device__ __forceinline__ void put_pieces(P4 p4, P2 p2, P1 p1, PH ph, PB pb, const v4& a, const v4& b,
-                                           uint32_t z) {
-  if (z >= 16u) p4(0u, a);
-  if (z >= 32u) p4(16u, b);
-  const uint32_t o1 = z & 16u;
-  const v4 u = o1 ? b : a;
-  if (z & 8u) p2(o1, u.x, u.y);
-  const uint32_t o2 = z & 24u;
-  const uint32_t s0 = (z & 8u) ? u.z : u.x, s1 = (z & 8u) ? u.w : u.y;
-  if (z & 4u) p1(o2, s0);
-  const uint32_t o3 = z & 28u;
-  const uint32_t s = (z & 4u) ? s1 : s0;
-  if (z & 2u) ph(o3, (uint16_t)s);
-  if (z & 1u) pb(z & 30u, (uint8_t)((z & 2u) ? s >> 16 : s));
-}
-__device__ __forceinline__ void put_lds(uint8_t* d, const v4& a, const v4& b, uint32_t z) {
-  put_pieces([&](uint32_t o, const v4& x) { *(u32x4u*)(d + o) = u32x4u{x.x, x.y, x.z, x.w}; },
-             [&](uint32_t o, uint32_t x, uint32_t y) { *(u32x2u*)(d + o) = u32x2u{x, y}; },
-             [&](uint32_t o, uint32_t x) { *(u32u*)(d + o) = x; },
-             [&](uint32_t o, uint16_t x) { *(u16u*)(d + o) = x; },
-             [&](uint32_t o, uint8_t x) { d[o] = x; }, a, b, z);
-}
-__device__ __forceinline__ void put_global(uint8_t* dst, const v4& a, const v4& b, uint32_t z) {
-  GMEM uint8_t* const d = gm(dst);
-  put_pieces([&](uint32_t o, const v4& x) { *(GMEM u32x4u*)(d + o) = u32x4u{x.x, x.y, x.z, x.w}; },
-             [&](uint32_t o, uint32_t x, uint32_t y) { *(GMEM u32x2u*)(d + o) = u32x2u{x, y}; },
-             [&](uint32_t o, uint32_t x) { *(GMEM u32u*)(d + o) = x; },
-             [&](uint32_t o, uint16_t x) { *(GMEM u16u*)(d + o) = x; },
-             [&](uint32_t o, uint8_t x) { d[o] = x; }, a, b, z);
-}
-// The z <= 32 bytes at src (any alignment) as two 16-byte values: whole 16-byte
-// loads where 32 bytes of the payload array follow, exact pieces at its end.
-__device__ __forceinline__ void get_bytes(const uint8_t* src, bool whole, uint32_t z, v4& a, v4& b) {
-  const GMEM uint8_t* const s = gm(src);
-  a = v4{0u, 0u, 0u, 0u};
-  b = a;
-  if (whole) {
-    const u32x4u x = *(const GMEM u32x4u*)s;
-    a = v4{x.x, x.y, x.z, x.w};
-    if (z > 16u) {
-      const u32x4u y = *(const GMEM u32x4u*)(s + 16);
-      b = v4{y.x, y.y, y.z, y.w};
-    }
-  } else {
-    uint32_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int j = 0; j < 32; ++j)
-      if ((uint32_t)j < z) v[j >> 2] |= (uint32_t)s[j] << (8 * (j & 3));
-    a = v4{v[0], v[1], v[2], v[3]};
-    b = v4{v[4], v[5], v[6], v[7]};
-  }
-}
-// A payload of over 32 bytes, by one lane.
-__device__ __forceinline__ void copy_long(uint8_t* dst, const uint8_t* src, uint32_t z) {
-  const GMEM uint8_t* s = gm(src);
-  GMEM uint8_t* d = gm(dst);
-  for (; z >= 64u; z -= 64u, s += 64, d += 64) {
-    u32x4u v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = ((const GMEM u32x4u*)s)[j];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) ((GMEM u32x4u*)d)[j] = v[j];
-  }
-  for (; z >= 16u; z -= 16u, s += 16, d += 16) *(GMEM u32x4u*)d = *(const GMEM u32x4u*)s;
-  for (uint32_t j = 0; j < z; ++j) d[j] = s[j];
-}
 
 // Size of a record's cell: from the offsets where the field cannot hold it
 // (its payload is not inline, so x is its offset: the last cell starting there).
@@ -820,16 +744,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs a) {
         const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)b[q]);
         const uint32_t rel = b[q] - b0;
         const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)(rel + z[q]), (int)lastl);
-        uint8_t* const stage = L.stage[w];
-        put_lds(stage + rel, va[q], vb[q], z[q]);
-        __builtin_amdgcn_wave_barrier();
-        uint8_t* const dst = a.t_payload + byte0 + b0;
-        for (uint32_t e = lane * 16u; e < tot; e += kWave * 16u) {
-          const v4 s = *(const v4*)(stage + e);
-          if (e + 16u <= tot) *(GMEM u32x4u*)gm(dst + e) = u32x4u{s.x, s.y, s.z, s.w};
-          else put_global(dst + e, s, s, tot - e);
-        }
-        __builtin_amdgcn_wave_barrier();
+        write_run(L.stage[w], a.t_payload + byte0 + b0, rel, tot, va[q], vb[q], z[q]);
       }
     }
     if (multi) {
