@@ -204,6 +204,7 @@ constexpr uint32_t kTileTiles = 2048;    // tiles of a call
 constexpr uint32_t kTileBuckets = 2048;  // buckets of a call
 constexpr uint32_t kTileCols = 512;      // columns of a bucket
 constexpr uint32_t kTileCap = 4608;      // cells of a bucket held at once
+constexpr uint32_t kTileBins = 4096;     // column runs of a table of uneven buckets
 struct TileArgs {
   const void* row_ptr;
   const int32_t* col;
@@ -224,6 +225,10 @@ struct TileArgs {
   uint2* table;               // workspace: [tile][bucket] (start | cells << 16, bytes before)
   uint32_t* recs;             // workspace: the records, tile by tile
   uint32_t* bad;              // workspace: a flag per tile (validate)
+  uint16_t* lut;              // workspace, or null for buckets of cpb columns each: the bucket
+                              // of every run of 2^lut_shift columns (k_tile_bounds)
+  uint32_t* bcol;             // with lut: every bucket's first column, n_buckets + 1 entries
+  uint32_t lut_shift, tile_target;  // with lut: and the cells a bucket aims for
   uint64_t nnz, payload_bytes;  // payload_bytes < 2^32
   int64_t n_rows, n_cols;     // < 2^31
   uint32_t cpb;               // columns per bucket

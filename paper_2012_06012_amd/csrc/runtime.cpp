@@ -415,12 +415,15 @@ int check_desc(const mgt_desc* d, bool need_bounds) {
 struct TileGeo {
   bool ok = false;
   uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
-  uint64_t o_table = 0, o_recs = 0, o_bad = 0, bytes = 0;
+  bool uneven = false;  // bucket bounds from sampled columns (k_tile_bounds)
+  uint32_t lut_shift = 0, target = 0;
+  uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_lut = 0, o_bcol = 0, bytes = 0;
 };
 
 constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
 
-TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune) {
+// crowded: the caller knows some columns to hold far more cells than others.
+TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool crowded = false) {
   TileGeo t;
   const uint64_t nnz = (uint64_t)std::max<int64_t>(d.nnz, 0), cols = (uint64_t)std::max<int64_t>(d.n_cols, 0);
   if (nnz < 1 || nnz > (uint64_t)kTileMax * kTileTiles || cols < 1) return t;
@@ -438,6 +441,18 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune) {
   t.cpb = (uint32_t)((cols + g - 1) / g);
   t.n_buckets = (uint32_t)((cols + t.cpb - 1) / t.cpb);
   if (t.cpb > kTileCols || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
+  if (crowded && nnz >= 64 * 1024) {
+    // runs of up to 2^lut_shift columns; buckets aim for 3/5 of what a
+    // workgroup holds, the samples' spread on top
+    t.lut_shift = (uint32_t)std::max(0, ceil_log2_u64(cols) - ceil_log2_u64(kTileBins));
+    t.target = (uint32_t)(3 * cap / 5);
+    const uint64_t run = 1ull << t.lut_shift;
+    const uint64_t most = 2 * run <= kTileCols ? nnz / t.target + cols / (kTileCols - run) + 3 : kTileBuckets + 1;
+    if (most <= kTileBuckets) {
+      t.uneven = true;
+      t.n_buckets = (uint32_t)most;
+    }
+  }
   uint64_t tiles = (nnz + kTileMax - 1) / kTileMax;
   if (tiles > kTileSlots) tiles = std::min<uint64_t>(align_up(tiles, kTileSlots), kTileTiles);
   else tiles = std::max<uint64_t>(tiles, std::min<uint64_t>(kTileSlots, (nnz + 1023) / 1024));
@@ -448,7 +463,9 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune) {
   t.o_table = 0;
   t.o_recs = align_up(8ull * t.n_tiles * t.n_buckets, 256);
   t.o_bad = t.o_recs + align_up(4 * words * nnz, 256);
-  t.bytes = t.o_bad + align_up(4ull * t.n_tiles, 256);
+  t.o_lut = t.o_bad + align_up(4ull * t.n_tiles, 256);
+  t.o_bcol = t.o_lut + align_up(2ull * kTileBins, 256);
+  t.bytes = t.uneven ? t.o_bcol + align_up(4ull * (t.n_buckets + 1), 256) : t.o_lut;
   t.ok = max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
          !env_cap("MGT_NO_PACK", 0, 1, 0) && !env_cap("MGT_NO_TILES", 0, 1, 0);
   return t;
@@ -999,6 +1016,12 @@ int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t f
   a.table = (uint2*)(W + t.o_table);
   a.recs = (uint32_t*)(W + t.o_recs);
   a.bad = (uint32_t*)(W + t.o_bad);
+  if (t.uneven) {
+    a.lut = (uint16_t*)(W + t.o_lut);
+    a.bcol = (uint32_t*)(W + t.o_bcol);
+    a.lut_shift = t.lut_shift;
+    a.tile_target = t.target;
+  }
   a.nnz = (uint64_t)d.nnz;
   a.payload_bytes = (uint64_t)d.payload_bytes;
   a.n_rows = d.n_rows;
@@ -1029,7 +1052,7 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
                 void* t_payload_off, uint8_t* t_payload, uint32_t* perm, int64_t* xc, int64_t* xb,
                 int64_t* pco, int64_t* pbo, int64_t* sd, int64_t* rd, void* ws, size_t ws_bytes,
                 int32_t* d_status, hipStream_t s, mgt_graph_s* graph = nullptr,
-                bool no_alloc = false) {
+                bool no_alloc = false, bool crowded = false) {
   if (!p || p->batch || p->view_op >= 0) return MGT_EINVAL;
   if (no_alloc && (p->flags & MGT_DEBUG_TIMING)) return MGT_EINVAL;
   const mgt_desc& d = p->desc;
@@ -1063,7 +1086,7 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   Layout y = make_layout(Items(items, 1));
   if (ws_bytes < y.bytes) return MGT_ENOMEM;
   const bool direct = use_direct(p, d, partitioned);
-  const TileGeo tg = tile_geo(d, partitioned, p->tune);
+  const TileGeo tg = tile_geo(d, partitioned, p->tune, crowded);
   // (a workspace that only the passes fit keeps them)
   const bool tiles = !direct && tg.ok && ws_bytes >= tg.bytes;
   if (graph)
@@ -1492,7 +1515,10 @@ SymLayout sym_layout(const mgt_plan_s* p) {
   const mgt_desc& d = p->desc;
   const uint64_t n = (uint64_t)d.n_rows, nnz = (uint64_t)d.nnz, ow = (uint64_t)d.offset_width;
   SymLayout y{};
-  uint64_t o = align_up(p->ws_plain, 256);
+  // (the transpose of a triangle takes uneven buckets, which a plan made for
+  // any matrix does not count)
+  const TileGeo tg = tile_geo(d, false, p->tune, true);
+  uint64_t o = align_up(std::max<uint64_t>(p->ws_plain, tg.ok ? tg.bytes : 0), 256);
   auto take = [&](uint64_t bytes) {
     const uint64_t at = o;
     o = align_up(o + bytes, 256);
@@ -1590,8 +1616,8 @@ int mgt_symmetrize(mgt_plan_t plan, int32_t triangle, const void* row_ptr, const
   // the stored triangle's transpose (its status word becomes the call's)
   st = single_call(plan, false, row_ptr, col, payload_off, payload, (void*)a.t_row_ptr,
                    (int32_t*)a.t_col, (void*)a.t_poff, (uint8_t*)a.t_payload, nullptr, nullptr,
-                   nullptr, nullptr, nullptr, nullptr, nullptr, workspace, plan->ws_plain, a.st,
-                   stream);
+                   nullptr, nullptr, nullptr, nullptr, nullptr, workspace, y.o_t_row_ptr, a.st,
+                   stream, nullptr, false, true);
   if (st != MGT_OK) return st;
   return launch_symmetrize(a, stream) == hipSuccess ? MGT_OK : MGT_EHIP;
 }

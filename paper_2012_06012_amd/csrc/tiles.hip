@@ -77,6 +77,73 @@ __device__ __forceinline__ bool any_bad(const TileArgs& a) {
   return __syncthreads_or(bad) != 0;
 }
 
+// ----------------------------------------------------------------------------- uneven buckets
+
+// Bucket bounds for inputs known to crowd some columns (the transpose of a
+// stored triangle: the low columns of a lower one). Equal runs of columns would
+// leave a few buckets many times over what a workgroup holds, and the call
+// waiting for them (4 M cells of a lower triangle: k_tile_merge 219 us with
+// equal runs, 108 with these and 18 for this kernel). One workgroup samples the columns, weighs every run of
+// 2^lut_shift columns by its sampled cells over the target and its columns over
+// the column limit, and cuts where the running weight passes a whole number.
+// Its time is the samples' latency, so calls that do not know their columns to
+// be crowded keep equal runs.
+constexpr int kBoundTh = 1024;
+constexpr uint32_t kSamples = 8192;
+
+__global__ __launch_bounds__(kBoundTh) void k_tile_bounds(TileArgs a) {
+  __shared__ uint32_t hist[kTileBins];
+  __shared__ uint64_t red[kBoundTh / kWave];
+  constexpr int kPer = kTileBins / kBoundTh;
+  for (uint32_t i = threadIdx.x; i < kTileBins; i += kBoundTh) hist[i] = 0;
+  __syncthreads();
+  const uint32_t n_cols = (uint32_t)a.n_cols;
+  // kSamples evenly spaced groups of four cells (the call has more than 4 kSamples)
+  typedef uint32_t col4 __attribute__((ext_vector_type(4), aligned(4)));
+  const uint64_t step = a.nnz / kSamples, ns = 4ull * kSamples;
+  constexpr int kQ = kSamples / kBoundTh;
+  col4 c[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q)
+    c[q] = *(const GMEM col4*)gm(a.col + ((uint64_t)q * kBoundTh + threadIdx.x) * step);
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) atomicAdd(&hist[min(c[q][j], n_cols - 1u) >> a.lut_shift], 1u);
+  }
+  __syncthreads();
+  // weights in 2^-32 of a bucket
+  const uint64_t per_cell = (a.nnz << 32) / (ns * a.tile_target);
+  const uint64_t per_col = (1ull << 32) / (kTileCols - (1u << a.lut_shift));
+  const uint32_t b0 = threadIdx.x * kPer;
+  uint64_t v[kPer], s = 0, tot;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint64_t c0 = min((uint64_t)(b0 + q) << a.lut_shift, (uint64_t)n_cols);
+    const uint64_t c1 = min((uint64_t)(b0 + q + 1) << a.lut_shift, (uint64_t)n_cols);
+    v[q] = hist[b0 + q] * per_cell + (c1 - c0) * per_col;
+    s += v[q];
+  }
+  uint64_t ex = block_excl_scan<kBoundTh / kWave>(s, red, tot);
+  const uint32_t last = a.n_buckets - 1;
+  __shared__ uint32_t ends[kBoundTh];  // the bucket of each thread's last run
+  ends[threadIdx.x] = min((uint32_t)((ex + s - v[kPer - 1]) >> 32), last);
+  __syncthreads();
+  uint32_t prev = threadIdx.x ? ends[threadIdx.x - 1] : 0u;
+  if (threadIdx.x == 0) gm(a.bcol)[0] = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const uint32_t d = min((uint32_t)(ex >> 32), last);
+    const uint64_t c0 = min((uint64_t)(b0 + q) << a.lut_shift, (uint64_t)n_cols);
+    gm(a.lut)[b0 + q] = (uint16_t)d;
+    for (uint32_t x = prev + 1; x <= d; ++x) gm(a.bcol)[x] = (uint32_t)c0;  // (skipped buckets are empty)
+    prev = d;
+    ex += v[q];
+  }
+  if (threadIdx.x == kBoundTh - 1)
+    for (uint32_t x = prev + 1; x <= a.n_buckets; ++x) gm(a.bcol)[x] = n_cols;
+}
+
 // ----------------------------------------------------------------------------- tile sort
 
 struct SortLds {
@@ -228,11 +295,18 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs a) {
     const uint32_t i = w * kSortWave + r * kWave + lane;
     // (clamped: columns out of range are undefined input, but stay in bounds)
     const uint32_t c = min(col[r], (uint32_t)a.n_cols - 1u);
-    uint32_t d = a.cpb > 1u ? __umulhi(c, a.magic) : c;
-    if (d * a.cpb > c) --d;  // the reciprocal is rounded up
+    uint32_t d, first;
+    if (a.lut) {  // uniform
+      d = gm(a.lut)[c >> a.lut_shift];
+      first = gm(a.bcol)[d];
+    } else {
+      d = a.cpb > 1u ? __umulhi(c, a.magic) : c;
+      if (d * a.cpb > c) --d;  // the reciprocal is rounded up
+      first = d * a.cpb;
+    }
     dig[r] = d;
     at[r] = d * kNW + w;
-    col[r] = c - d * a.cpb;
+    col[r] = c - first;
     if (i < n && size[r]) atomicAdd(&byt[d], size[r]);
   }
   wave_ranks(wc, at, dig, n > w * kSortWave ? n - w * kSortWave : 0u, dbits, rank);
@@ -516,7 +590,8 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs a) {
   const uint32_t g = (uint32_t)xcd_tile(blockIdx.x, a.g8);
   const uint32_t G = a.n_buckets, T = a.n_tiles;
   if (g >= G) return;
-  const uint32_t col0 = g * a.cpb, nc = min(a.cpb, (uint32_t)a.n_cols - col0);
+  const uint32_t col0 = a.lut ? gm(a.bcol)[g] : g * a.cpb;
+  const uint32_t nc = a.lut ? gm(a.bcol)[g + 1] - col0 : min(a.cpb, (uint32_t)a.n_cols - col0);
   // the bucket's column of the table: its place in the output, and its runs
   constexpr int kPerT = kTileTiles / kTh;
   const uint32_t per = (T + kTh - 1) / kTh, t0 = threadIdx.x * per;
@@ -767,6 +842,7 @@ static_assert(sizeof(tl::MergeLds) <= 80 * 1024, "two workgroups per CU");
 
 template <bool kIdx>
 static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStream_t s) {
+  if (a.lut) hipLaunchKernelGGL(tl::k_tile_bounds, dim3(1), dim3(tl::kBoundTh), 0, s, a);
   hipLaunchKernelGGL((tl::k_tile_sort<kIdx>), dim3(a.n_tiles), dim3(tl::kTh),
                      tl::sort_dyn_bytes(a.n_buckets), s, a);
   if (a.n_parts > 0) {

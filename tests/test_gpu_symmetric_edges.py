@@ -34,6 +34,9 @@ def _triangle(n, nnz, lower, law, w_hi, ow, seed):
     (1, 5, "uniform", 3, 8), (300, 1024, "uniform", 32, 4), (300, 1025, "uniform", 33, 8),
     (2500, 20011, "dense rows", 9, 8), (60000, 9001, "gaps", 16, 4), (5000, 60013, "uniform", 90, 8),
     (5000, 60013, "uniform", 0, 8),
+    # uneven buckets (from 65,536 stored cells): few, crowded and many columns
+    (3, 65536, "uniform", 5, 8), (700, 120011, "dense rows", 9, 4), (40000, 200003, "uniform", 20, 8),
+    (900000, 300007, "gaps", 4, 8), (1 << 20, 66000, "uniform", 7, 8),
 ])
 def test_fill_edges(n, nnz, law, w_hi, ow, lower):
     _compare(_triangle(n, nnz, lower, law, w_hi, ow, nnz), lower, validate=True)
