@@ -243,7 +243,26 @@ struct TileArgs {
 struct TileBounds {
   int32_t bounds[kDirectParts + 1];
 };
+// Single call: the item's arguments travel with the launches. perm decides the
+// record form.
 hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s);
+// Batch: the items' arguments lie in memory, with running totals of their
+// tiles, buckets, and source partitions of partitioned items (n_items + 1
+// entries each).
+struct TileBatch {
+  const TileArgs* items;
+  const uint32_t* tile_base;
+  const uint32_t* bucket_base;
+  const uint32_t* part_base;
+  const int32_t* bounds;      // kDirectParts + 1 per partitioned item, in order
+  const uint32_t* part_item;  // per item: its index among the partitioned ones
+  uint32_t n_items;
+  uint32_t n_tiles, n_buckets, n_parts;  // the totals
+  uint32_t max_buckets;       // of one item
+  uint64_t max_part_cells;    // cells per source partition, the largest item's mean
+  int32_t idx;                // every item has perm
+};
+hipError_t launch_tile_batch(const TileBatch& b, hipStream_t s);
 // mgt_symmetrize's stages after the transpose of the stored triangle
 // (symmetric.hip). Every offset array has width ow.
 struct SymArgs {

@@ -1713,7 +1713,7 @@ __device__ void item_tails(const ItemDev& it, uint32_t i, const int32_t* item_st
                            const int32_t* abort_flag, int ow, int32_t* d_status, uint64_t* red) {
   if (d_status && threadIdx.x == 0) {
     const int32_t st = item_status[i];
-    d_status[i] = (st == MGT_OK && *abort_flag) ? MGT_ECANCELED : st;
+    d_status[it.out_index] = (st == MGT_OK && *abort_flag) ? MGT_ECANCELED : st;
   }
   if (aborted(abort_flag)) return;
   if (threadIdx.x == 0) {

@@ -71,6 +71,7 @@ struct ItemDev {
   int32_t key_bits;           // column bits (plain) / bits of the widest partition
   int32_t part_mode;          // 1: pass 1 splits by destination partition
   int32_t status_index;       // where this item's status word lives
+  int32_t out_index;          // and the caller's (an item of a batch may run beside others)
   int32_t fixed_w;            // payload bytes of every cell when all cells have the same
                               // width (offset arrays unused), else -1
   int32_t pk_shift;           // column bits of packed records, ceil(log2(n_cols)) (<= 28 when

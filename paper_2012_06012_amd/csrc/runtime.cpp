@@ -219,6 +219,7 @@ struct HostItem {
   mgt_desc d;
   Sched s;
   uint32_t tile = 0;  // cells per tile set by the caller (single-matrix calls), 0: sized here
+  int32_t out = -1;   // the item's index in the caller's batch, -1: its index here
   const int64_t* bounds;  // host
   ItemDev dev;
 };
@@ -423,7 +424,9 @@ struct TileGeo {
 constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
 
 // crowded: the caller knows some columns to hold far more cells than others.
-TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool crowded = false) {
+// batch: one of many items, whose workgroups fill the device together.
+TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool crowded = false,
+                 bool batch = false) {
   TileGeo t;
   const uint64_t nnz = (uint64_t)std::max<int64_t>(d.nnz, 0), cols = (uint64_t)std::max<int64_t>(d.n_cols, 0);
   if (nnz < 1 || nnz > (uint64_t)kTileMax * kTileTiles || cols < 1) return t;
@@ -434,7 +437,8 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   // buckets of at most 4/5 of what a workgroup holds, whole rounds of the
   // workgroups that run at once; small calls still fill one round
   uint64_t g = std::max<uint64_t>((5 * nnz + 4 * cap - 1) / (4 * cap), (cols + kTileCols - 1) / kTileCols);
-  if (g > kTileSlots) g = align_up(g, kTileSlots);
+  if (batch) g = std::max<uint64_t>(g, 1);
+  else if (g > kTileSlots) g = align_up(g, kTileSlots);
   else g = std::max<uint64_t>(g, std::min<uint64_t>(kTileSlots, (nnz + 255) / 256));
   g = std::min<uint64_t>(g, cols);
   if (g > kTileBuckets) return t;
@@ -454,7 +458,8 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
     }
   }
   uint64_t tiles = (nnz + kTileMax - 1) / kTileMax;
-  if (tiles > kTileSlots) tiles = std::min<uint64_t>(align_up(tiles, kTileSlots), kTileTiles);
+  if (batch) {
+  } else if (tiles > kTileSlots) tiles = std::min<uint64_t>(align_up(tiles, kTileSlots), kTileTiles);
   else tiles = std::max<uint64_t>(tiles, std::min<uint64_t>(kTileSlots, (nnz + 1023) / 1024));
   t.tile_cells = (uint32_t)std::min<uint64_t>(align_up((nnz + tiles - 1) / tiles, 64), kTileMax);
   t.n_tiles = (uint32_t)((nnz + t.tile_cells - 1) / t.tile_cells);
@@ -585,9 +590,11 @@ size_t upload_bytes(const Layout& y) { return y.o_up_end; }
 // upload_bytes(y) bytes, 16-byte aligned) and copied to the workspace by
 // kernels taking it as arguments (launch_upload), so the call neither
 // allocates nor touches the plan's pinned staging buffer.
+// record_upload: graph_staging is a part of the plan's staging buffer after
+// all, and the completion event is recorded after the copy.
 int run(mgt_plan_s* p, Items items, const Layout& y, void* ws, int32_t* d_status,
         hipStream_t s, const ViewCall* vc = nullptr, void* graph_staging = nullptr,
-        uint8_t* kernel_upload = nullptr) {
+        uint8_t* kernel_upload = nullptr, bool record_upload = false) {
   uint8_t* W = (uint8_t*)ws;
   const int ow = items.empty() ? 8 : items[0].d.offset_width;
   const uint32_t n = y.n_items;
@@ -629,6 +636,7 @@ int run(mgt_plan_s* p, Items items, const Layout& y, void* ws, int32_t* d_status
     d.key_bits = it.s.key_bits;
     d.part_mode = it.s.part_mode;
     d.status_index = (int32_t)i;
+    d.out_index = it.out >= 0 ? it.out : (int32_t)i;
     d.pk_shift = pk_on ? ceil_log2_u64((uint64_t)std::max<int64_t>(it.d.n_cols, 1)) : 0;
     d.fixed_w = (it.d.flags & MGT_FIXED_WIDTH)
                     ? (int32_t)(it.d.nnz > 0 ? it.d.payload_bytes / it.d.nnz : 0)
@@ -683,7 +691,7 @@ int run(mgt_plan_s* p, Items items, const Layout& y, void* ws, int32_t* d_status
     MGT_HIP(launch_upload(W, H, up_bytes, s));
   } else {
     MGT_HIP(hipMemcpyAsync(W, H, up_bytes, hipMemcpyHostToDevice, s));
-    if (!graph_staging) {
+    if (!graph_staging || record_upload) {
       MGT_HIP(hipEventRecord(p->upload_done, s));
       p->upload_pending = true;
     }
@@ -898,15 +906,9 @@ int check_io(const mgt_desc& d, uint32_t flags, const void* row_ptr, const int32
 // Records one call into g: the pinned upload buffer and a private stream are
 // made first (nothing is allocated while capturing), then the call is
 // captured on that stream and instantiated.
-int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStream_t s);
-int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, void* ws,
-              int32_t* d_status, hipStream_t s);
-
-// direct, tiles: the call takes run_direct or run_tiles, partitioned or not.
-int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
-                 int32_t* d_status, mgt_graph_s* g, bool direct = false,
-                 const TileGeo* tiles = nullptr, bool partitioned = false) {
-  if (!direct && !tiles && hipHostMalloc(&g->staging, upload_bytes(y), hipHostMallocDefault) != hipSuccess) {
+template <class Call>
+int record_graph(size_t staging_bytes, mgt_graph_s* g, Call call) {
+  if (staging_bytes && hipHostMalloc(&g->staging, staging_bytes, hipHostMallocDefault) != hipSuccess) {
     g->staging = nullptr;
     return MGT_ENOMEM;
   }
@@ -916,9 +918,7 @@ int record_graph(mgt_plan_s* p, Items items, const Layout& y, void* ws,
   int st = MGT_OK;
   if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) st = MGT_EHIP;
   if (st == MGT_OK) {
-    st = direct  ? run_direct(items[0], partitioned, d_status, s)
-         : tiles ? run_tiles(items[0], *tiles, partitioned, p->flags, ws, d_status, s)
-                 : run(p, items, y, ws, d_status, s, nullptr, g->staging);
+    st = call(s);
     // the capture is ended whatever happened inside it
     if (hipStreamEndCapture(s, &graph) != hipSuccess && st == MGT_OK) st = MGT_EHIP;
   }
@@ -991,11 +991,11 @@ int run_direct(const HostItem& it, bool partitioned, int32_t* d_status, hipStrea
   return MGT_OK;
 }
 
-int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, void* ws,
-              int32_t* d_status, hipStream_t s) {
+// The kernels' arguments of one item, its workspace at W.
+TileArgs tile_args(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, uint8_t* W,
+                   int32_t* d_status) {
   const mgt_desc& d = it.d;
   const ItemDev& v = it.dev;
-  uint8_t* const W = (uint8_t*)ws;
   TileArgs a{};
   a.row_ptr = v.row_ptr;
   a.col = v.col;
@@ -1035,14 +1035,19 @@ int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t f
   a.lg = d.offset_width == 8 ? 3 : 2;
   a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
   a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
+  if (partitioned) a.n_parts = d.n_parts;
+  return a;
+}
+
+int run_tiles(const HostItem& it, const TileGeo& t, bool partitioned, uint32_t flags, void* ws,
+              int32_t* d_status, hipStream_t s) {
   TileBounds b{};
-  if (partitioned) {
-    a.n_parts = d.n_parts;
-    for (int32_t r = 0; r <= d.n_parts; ++r) b.bounds[r] = (int32_t)it.bounds[r];
-  }
-  MGT_HIP(launch_tiles(a, b, s));
+  if (partitioned)
+    for (int32_t r = 0; r <= it.d.n_parts; ++r) b.bounds[r] = (int32_t)it.bounds[r];
+  MGT_HIP(launch_tiles(tile_args(it, t, partitioned, flags, (uint8_t*)ws, d_status), b, s));
   return MGT_OK;
 }
+
 
 // no_alloc: the call allocates nothing (no pinned staging, no events, no heap):
 // plans with MGT_DEBUG_TIMING are refused and the descriptor goes up through
@@ -1090,8 +1095,11 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   // (a workspace that only the passes fit keeps them)
   const bool tiles = !direct && tg.ok && ws_bytes >= tg.bytes;
   if (graph)
-    return record_graph(p, Items(items, 1), y, ws, d_status, graph, direct, tiles ? &tg : nullptr,
-                        partitioned);
+    return record_graph(direct || tiles ? 0 : upload_bytes(y), graph, [&](hipStream_t gs) {
+      if (direct) return run_direct(it, partitioned, d_status, gs);
+      if (tiles) return run_tiles(it, tg, partitioned, p->flags, ws, d_status, gs);
+      return run(p, Items(items, 1), y, ws, d_status, gs, nullptr, graph->staging);
+    });
   p->timing.used = 0;
   if (direct) return run_direct(it, partitioned, d_status, s);
   if (tiles) return run_tiles(it, tg, partitioned, p->flags, ws, d_status, s);
@@ -1125,11 +1133,10 @@ size_t batch_estimate(const mgt_batch_limits& lim) {
   return (size_t)(2 * 16 * cells + 4 * segs * (sizeof(Seg) + 24) + 64ull * (cells / 16) + (1u << 20));
 }
 
-int batch_items(mgt_plan_s* p, const mgt_item* in, int32_t n, std::vector<HostItem>& items) {
+int batch_items(mgt_plan_s* p, const mgt_item* in, int32_t n, std::vector<HostItem>& items, Tune& tune) {
   if (!p || !p->batch || n < 0 || (n > 0 && !in)) return MGT_EINVAL;
   if (n > p->lim.max_items || n > kMaxItems) return MGT_EUNSUPPORTED;
-  Tune tune;  // the plan's schedule setting, read under its lock
-  {
+  {  // the plan's schedule setting, read under its lock
     std::lock_guard<std::mutex> lock(p->mu);
     tune = p->tune;
   }
@@ -1171,21 +1178,157 @@ int batch_items(mgt_plan_s* p, const mgt_item* in, int32_t n, std::vector<HostIt
   if (tn > p->lim.max_total_nnz || tc > p->lim.max_total_cols || tr > p->lim.max_total_rows ||
       tp > p->lim.max_total_parts)
     return MGT_EUNSUPPORTED;
-  // Every item makes as many passes as the item that needs the most (the
-  // layout pads the others with 0-bit passes, which copy their records). An
-  // item whose fewest passes come from a wider finish than its ideal takes
-  // the padded passes' bits instead, keeping finish buckets near 4 * kSub
-  // cells (wider ones outgrow the whole-bucket finish).
+  return MGT_OK;
+}
+
+// Every item makes as many passes as the item that needs the most (the
+// layout pads the others with 0-bit passes, which copy their records). An
+// item whose fewest passes come from a wider finish than its ideal takes
+// the padded passes' bits instead, keeping finish buckets near 4 * kSub
+// cells (wider ones outgrow the whole-bucket finish).
+void pad_passes(std::vector<HostItem>& items, const Tune& tune) {
   int L = 1;
   for (const HostItem& it : items) L = std::max(L, it.s.n_levels);
-  for (int32_t i = 0; i < n && L > 1; ++i) {
-    HostItem& it = items[(size_t)i];
-    if (it.s.n_levels >= L) continue;
-    const mgt_desc& d = in[i].desc;
+  for (HostItem& it : items) {
+    if (L == 1 || it.s.n_levels >= L) continue;
+    const mgt_desc& d = it.d;
     const Sched s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, d.part_bounds,
                                d.n_parts > 1, false, &tune, L);
     if (s.n_levels <= L) it.s = s;
   }
+}
+
+// How a batch runs: items whose size fits the two-launch form take it together,
+// the others make the passes together.
+struct BatchRun {
+  std::vector<HostItem> passes;  // (out: their indexes in the batch)
+  Layout y;                      // of the passes' part, at the start of the workspace
+  std::vector<HostItem> tiles;
+  std::vector<TileGeo> geo;
+  std::vector<uint64_t> at;      // their workspaces
+  uint64_t n_partitioned = 0;
+  uint64_t o_up = 0;             // the tiles' uploaded tables
+  uint64_t o_items = 0, o_tile = 0, o_bucket = 0, o_part = 0, o_pidx = 0, o_bounds = 0, up_bytes = 0;
+  uint64_t bytes = 0;
+};
+
+// tiles_too = false: every item makes the passes.
+void plan_batch(const mgt_plan_s* p, const std::vector<HostItem>& items, const Tune& tune,
+                bool tiles_too, BatchRun& r) {
+  // device checks cancel a whole batch together: the passes' own business
+  tiles_too = tiles_too && !(p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING));
+  for (size_t i = 0; i < items.size(); ++i) {
+    const HostItem& it = items[i];
+    TileGeo g;
+    if (tiles_too) {
+      mgt_desc d = it.d;
+      d.flags |= p->flags & MGT_EMIT_PERM;
+      g = tile_geo(d, d.n_parts > 1, tune, false, true);
+    }
+    (g.ok ? r.tiles : r.passes).push_back(it);
+    if (g.ok) r.geo.push_back(g);
+    (g.ok ? r.tiles : r.passes).back().out = (int32_t)i;
+  }
+  pad_passes(r.passes, tune);
+  uint64_t o = 0;
+  if (!r.passes.empty()) {
+    r.y = make_layout(r.passes);
+    o = align_up(r.y.bytes, 256);
+  }
+  if (!r.tiles.empty()) {
+    const uint64_t n = r.tiles.size();
+    for (const HostItem& it : r.tiles) r.n_partitioned += it.d.n_parts > 1 ? 1 : 0;
+    r.o_up = o;
+    auto take = [&](uint64_t bytes) {
+      const uint64_t at = o - r.o_up;
+      o = align_up(o + bytes, 256);
+      return at;
+    };
+    r.o_items = take(sizeof(TileArgs) * n);
+    r.o_tile = take(4 * (n + 1));
+    r.o_bucket = take(4 * (n + 1));
+    r.o_part = take(4 * (n + 1));
+    r.o_pidx = take(4 * n);
+    r.o_bounds = take(4ull * (kDirectParts + 1) * r.n_partitioned);
+    r.up_bytes = o - r.o_up;
+    for (const TileGeo& g : r.geo) {
+      r.at.push_back(o);
+      o = align_up(o + g.bytes, 256);
+    }
+  }
+  r.bytes = std::max<uint64_t>(o, 256);
+}
+
+uint64_t batch_upload_bytes(const BatchRun& r) {
+  return (r.passes.empty() ? 0 : align_up(upload_bytes(r.y), 256)) + r.up_bytes;
+}
+
+// Launches a batch; H: batch_upload_bytes(r) pinned bytes that stay as they are
+// until the copies ran (a graph's, or the plan's staging buffer, whose
+// completion event is then recorded: record_upload).
+int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream_t s, uint8_t* H,
+              bool record_upload) {
+  uint8_t* const passes_up = H;
+  auto passes = [&] {
+    return run(p, r.passes, r.y, ws, d_status, s, nullptr, passes_up, nullptr, record_upload);
+  };
+  if (r.tiles.empty()) return passes();
+  if (!r.passes.empty()) H += align_up(upload_bytes(r.y), 256);
+  const size_t n = r.tiles.size();
+  uint8_t* const W = (uint8_t*)ws;
+  TileArgs* const items = (TileArgs*)(H + r.o_items);
+  uint32_t* const tb = (uint32_t*)(H + r.o_tile);
+  uint32_t* const bb = (uint32_t*)(H + r.o_bucket);
+  uint32_t* const pb = (uint32_t*)(H + r.o_part);
+  uint32_t* const pi = (uint32_t*)(H + r.o_pidx);
+  int32_t* const bounds = (int32_t*)(H + r.o_bounds);
+  TileBatch b{};
+  uint64_t tiles = 0, buckets = 0, parts = 0, np = 0;
+  for (size_t i = 0; i < n; ++i) {
+    const HostItem& it = r.tiles[i];
+    const bool part = it.d.n_parts > 1;
+    const TileArgs a = tile_args(it, r.geo[i], part, 0, W + r.at[i], d_status ? d_status + it.out : nullptr);
+    std::memcpy(&items[i], &a, sizeof(a));
+    tb[i] = (uint32_t)tiles;
+    bb[i] = (uint32_t)buckets;
+    pb[i] = (uint32_t)parts;
+    pi[i] = (uint32_t)np;
+    tiles += a.n_tiles;
+    buckets += a.n_buckets;
+    b.max_buckets = std::max(b.max_buckets, a.n_buckets);
+    b.idx = a.perm != nullptr;
+    if (part) {
+      for (int32_t q = 0; q <= it.d.n_parts; ++q)
+        bounds[np * (kDirectParts + 1) + q] = (int32_t)it.bounds[q];
+      ++np;
+      parts += (uint64_t)it.d.n_parts;
+      b.max_part_cells = std::max<uint64_t>(b.max_part_cells, (uint64_t)it.d.nnz / (uint64_t)it.d.n_parts);
+    }
+  }
+  tb[n] = (uint32_t)tiles;
+  bb[n] = (uint32_t)buckets;
+  pb[n] = (uint32_t)parts;
+  if (tiles >= (1ull << 31) || buckets + n >= (1ull << 31)) return MGT_EUNSUPPORTED;
+  uint8_t* const U = W + r.o_up;
+  MGT_HIP(hipMemcpyAsync(U, H, r.up_bytes, hipMemcpyHostToDevice, s));
+  if (!r.passes.empty()) {
+    const int st = passes();
+    if (st != MGT_OK) return st;
+  } else if (record_upload) {
+    MGT_HIP(hipEventRecord(p->upload_done, s));
+    p->upload_pending = true;
+  }
+  b.items = (const TileArgs*)(U + r.o_items);
+  b.tile_base = (const uint32_t*)(U + r.o_tile);
+  b.bucket_base = (const uint32_t*)(U + r.o_bucket);
+  b.part_base = (const uint32_t*)(U + r.o_part);
+  b.part_item = (const uint32_t*)(U + r.o_pidx);
+  b.bounds = (const int32_t*)(U + r.o_bounds);
+  b.n_items = (uint32_t)n;
+  b.n_tiles = (uint32_t)tiles;
+  b.n_buckets = (uint32_t)buckets;
+  b.n_parts = (uint32_t)parts;
+  MGT_HIP(launch_tile_batch(b, s));
   return MGT_OK;
 }
 
@@ -1398,28 +1541,48 @@ int mgt_batch_plan(const mgt_batch_limits* lim, mgt_plan_t* out, size_t* workspa
 int mgt_batch_workspace(mgt_plan_t plan, const mgt_item* items, int32_t n_items, size_t* bytes) {
   if (!bytes) return MGT_EINVAL;
   std::vector<HostItem> hi;
-  int st = batch_items(plan, items, n_items, hi);
+  Tune tune;
+  int st = batch_items(plan, items, n_items, hi, tune);
   if (st != MGT_OK) return st;
-  *bytes = n_items ? make_layout(hi).bytes : 256;
+  if (n_items == 0) {
+    *bytes = 256;
+    return MGT_OK;
+  }
+  // what the batch takes as it runs, and at least what the passes would
+  BatchRun r, all;
+  plan_batch(plan, hi, tune, true, r);
+  plan_batch(plan, hi, tune, false, all);
+  *bytes = std::max(r.bytes, all.bytes);
   return MGT_OK;
 }
 
 int mgt_batch_submit(mgt_plan_t plan, const mgt_item* items, int32_t n_items, void* workspace,
                      size_t workspace_bytes, int32_t* d_status, hipStream_t stream, hipEvent_t done) {
   std::vector<HostItem> hi;
-  int st = batch_items(plan, items, n_items, hi);
+  Tune tune;
+  int st = batch_items(plan, items, n_items, hi, tune);
   if (st != MGT_OK) return st;
   if (n_items == 0) {
     if (done && hipEventRecord(done, stream) != hipSuccess) return MGT_EHIP;
     return MGT_OK;
   }
   if (!workspace || ((uintptr_t)workspace & 255u)) return MGT_EINVAL;
-  Layout y = make_layout(hi);
-  if (workspace_bytes < y.bytes) return MGT_ENOMEM;
+  BatchRun r;
+  plan_batch(plan, hi, tune, true, r);
+  if (workspace_bytes < r.bytes && !r.tiles.empty()) {  // a workspace that only the passes fit
+    r = BatchRun();
+    plan_batch(plan, hi, tune, false, r);
+  }
+  if (workspace_bytes < r.bytes) return MGT_ENOMEM;
   std::lock_guard<std::mutex> lock(plan->mu);
   plan->timing.used = 0;
-  st = run(plan, hi, y, workspace, d_status, stream);
+  st = ensure_staging(plan, batch_upload_bytes(r));
   if (st != MGT_OK) return st;
+  st = run_batch(plan, r, workspace, d_status, stream, (uint8_t*)plan->staging, true);
+  if (st != MGT_OK) {  // (a copy queued before the failure may still read the staging buffer)
+    if (hipEventRecord(plan->upload_done, stream) == hipSuccess) plan->upload_pending = true;
+    return st;
+  }
   if (done && hipEventRecord(done, stream) != hipSuccess) return MGT_EHIP;
   return MGT_OK;
 }
@@ -1430,17 +1593,25 @@ int mgt_batch_graph_create(mgt_plan_t plan, const mgt_item* items, int32_t n_ite
   if (!out) return MGT_EINVAL;
   if (plan && (plan->flags & MGT_DEBUG_TIMING)) return MGT_EINVAL;
   std::vector<HostItem> hi;
-  int st = batch_items(plan, items, n_items, hi);
+  Tune tune;
+  int st = batch_items(plan, items, n_items, hi, tune);
   if (st != MGT_OK) return st;
   if (n_items == 0) return MGT_EINVAL;  // nothing to record
   if (!workspace || ((uintptr_t)workspace & 255u)) return MGT_EINVAL;
-  Layout y = make_layout(hi);
-  if (workspace_bytes < y.bytes) return MGT_ENOMEM;
+  BatchRun r;
+  plan_batch(plan, hi, tune, true, r);
+  if (workspace_bytes < r.bytes && !r.tiles.empty()) {
+    r = BatchRun();
+    plan_batch(plan, hi, tune, false, r);
+  }
+  if (workspace_bytes < r.bytes) return MGT_ENOMEM;
   mgt_graph_s* g = new (std::nothrow) mgt_graph_s();
   if (!g) return MGT_ENOMEM;
   {
     std::lock_guard<std::mutex> lock(plan->mu);
-    st = record_graph(plan, hi, y, workspace, d_status, g);
+    st = record_graph(batch_upload_bytes(r), g, [&](hipStream_t s) {
+      return run_batch(plan, r, workspace, d_status, s, (uint8_t*)g->staging, false);
+    });
   }
   if (st == MGT_OK && !g->exec) st = MGT_EINVAL;
   if (st != MGT_OK) {

@@ -68,6 +68,27 @@ __device__ __forceinline__ uint32_t opaque(uint32_t v) {
   return v;
 }
 
+// Batches: the item whose range of `base` (running totals) holds v, found by the
+// whole workgroup, and its arguments (uniform, so they load as scalars).
+__device__ __forceinline__ uint32_t coop_item(const uint32_t* base, uint32_t n, uint32_t v) {
+  uint32_t lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const uint32_t step = (hi - lo + kTh - 1) / kTh;
+    const uint32_t p = lo + threadIdx.x * step;
+    int c = __syncthreads_count(p < hi && gm(base)[p] <= v);
+    c = c < 1 ? 1 : c;
+    lo += (uint32_t)(c - 1) * step;
+    hi = min(lo + step, hi);
+  }
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+}
+typedef const __attribute__((address_space(4))) TileArgs* ItemPtr;
+__device__ __forceinline__ TileArgs load_item(const TileArgs* items, uint32_t i) {
+  TileArgs a;
+  __builtin_memcpy(&a, (ItemPtr)(items + i), sizeof(TileArgs));
+  return a;
+}
+
 // Whether the call's inputs were found invalid (MGT_VALIDATE): k_tile_sort left
 // a flag per tile. Every thread of the workgroup must call it.
 __device__ __forceinline__ bool any_bad(const TileArgs& a) {
@@ -208,13 +229,19 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
 // with three workgroups per CU in flight; the records are stored straight to
 // their place in the tile's own region (up to 80 KB, whole lines by the time
 // they leave the L2).
-template <bool kIdx>
-__global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs a) {
+template <bool kIdx, bool kBatch>
+__global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt) {
   constexpr int kWords = kIdx ? 4 : 3;
   __shared__ SortLds L;
+  uint32_t t = blockIdx.x;
+  TileArgs a = one;
+  if constexpr (kBatch) {
+    const uint32_t i = coop_item(bt.tile_base, bt.n_items, t);
+    a = load_item(bt.items, i);
+    t -= bt.tile_base[i];
+  }
   uint16_t* const wc = (uint16_t*)__builtin_assume_aligned(s_dyn, 16);
   uint32_t* const byt = (uint32_t*)(wc + a.n_buckets * kNW);
-  const uint32_t t = blockIdx.x;
   const uint32_t w = threadIdx.x / kWave, lane = lane_id();
   const uint64_t k0 = (uint64_t)t * a.tile_cells;
   const uint32_t n = (uint32_t)min((uint64_t)a.tile_cells, a.nnz - k0);
@@ -390,12 +417,24 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs a) {
 // X and B of a partitioned call: workgroups (s, j), j < gridDim.y, histogram
 // the owners of the columns of source partition s (its cells are consecutive
 // in the input), every gridDim.y-th chunk each, and add to its row of both.
-__global__ __launch_bounds__(kTh) void k_tile_xfer(TileArgs a, TileBounds b) {
+template <bool kBatch>
+__global__ __launch_bounds__(kTh) void k_tile_xfer(TileArgs one, TileBounds b, TileBatch bt) {
   __shared__ uint32_t cnt[kDirectParts], byt[kDirectParts];
   __shared__ int32_t lb[kDirectParts + 1];
-  if (any_bad(a)) return;
-  const uint32_t R = (uint32_t)a.n_parts, s = blockIdx.x, tid = threadIdx.x;
-  for (uint32_t i = tid; i <= R; i += kTh) lb[i] = b.bounds[i];
+  uint32_t s = blockIdx.x;
+  const uint32_t tid = threadIdx.x;
+  TileArgs a = one;
+  if constexpr (kBatch) {
+    const uint32_t i = coop_item(bt.part_base, bt.n_items, s);
+    a = load_item(bt.items, i);
+    s -= bt.part_base[i];
+    for (uint32_t j = tid; j <= (uint32_t)a.n_parts; j += kTh)
+      lb[j] = gm(bt.bounds)[(uint64_t)bt.part_item[i] * (kDirectParts + 1) + j];
+  } else {
+    if (any_bad(a)) return;
+    for (uint32_t j = tid; j <= (uint32_t)a.n_parts; j += kTh) lb[j] = b.bounds[j];
+  }
+  const uint32_t R = (uint32_t)a.n_parts;
   for (uint32_t i = tid; i < R; i += kTh) {
     cnt[i] = 0;
     byt[i] = 0;
@@ -568,26 +607,37 @@ __device__ __forceinline__ void cell_tiles(const uint32_t* ex, const uint32_t* t
 // tiles' records in its L2.
 // A bucket of more than kCap cells (skewed columns) is taken in chunks: column
 // totals first, then every chunk's cells to their column's running place.
-template <bool kIdx>
-__global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs a) {
+template <bool kIdx, bool kBatch>
+__global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch bt) {
   constexpr int kItems = kMergeItems;
   constexpr uint32_t kCap = kTileCap, kWaveCells = kMergeWave;
   constexpr uint32_t kWords = kIdx ? 4 : 3;
   __shared__ MergeLds L;
-  const bool bad = any_bad(a);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (a.d_status) *a.d_status = bad ? MGT_ERANGE : MGT_OK;
-    if (!bad) {
-      st_off(a.t_row_ptr, (uint64_t)a.n_cols, (int64_t)a.nnz, a.lg);
-      if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
-    }
+  // workgroups past the buckets', one per item: status, end offsets, and a
+  // partitioned item's offsets and displacements
+  const uint32_t g8 = kBatch ? (bt.n_buckets + 7u) & ~7u : one.g8;
+  const bool tail = blockIdx.x >= g8;
+  uint32_t g = (uint32_t)xcd_tile(blockIdx.x, g8);
+  TileArgs a = one;
+  if constexpr (kBatch) {
+    if (!tail && g >= bt.n_buckets) return;
+    const uint32_t i = tail ? blockIdx.x - g8 : coop_item(bt.bucket_base, bt.n_items, g);
+    a = load_item(bt.items, (uint32_t)__builtin_amdgcn_readfirstlane((int)i));
+    g -= bt.bucket_base[i];
   }
-  if (bad) return;
-  if (blockIdx.x == a.g8) {  // one more workgroup of a partitioned call
-    tile_tails(a, L.red64);
+  const bool bad = any_bad(a);
+  if (tail) {
+    if (threadIdx.x == 0) {
+      if (a.d_status) *a.d_status = bad ? MGT_ERANGE : MGT_OK;
+      if (!bad) {
+        st_off(a.t_row_ptr, (uint64_t)a.n_cols, (int64_t)a.nnz, a.lg);
+        if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
+      }
+    }
+    if (!bad && a.n_parts > 0) tile_tails(a, L.red64);
     return;
   }
-  const uint32_t g = (uint32_t)xcd_tile(blockIdx.x, a.g8);
+  if (bad) return;
   const uint32_t G = a.n_buckets, T = a.n_tiles;
   if (g >= G) return;
   const uint32_t col0 = a.lut ? gm(a.bcol)[g] : g * a.cpb;
@@ -842,22 +892,44 @@ static_assert(sizeof(tl::MergeLds) <= 80 * 1024, "two workgroups per CU");
 
 template <bool kIdx>
 static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStream_t s) {
+  const TileBatch none{};
   if (a.lut) hipLaunchKernelGGL(tl::k_tile_bounds, dim3(1), dim3(tl::kBoundTh), 0, s, a);
-  hipLaunchKernelGGL((tl::k_tile_sort<kIdx>), dim3(a.n_tiles), dim3(tl::kTh),
-                     tl::sort_dyn_bytes(a.n_buckets), s, a);
+  hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), dim3(tl::kTh),
+                     tl::sort_dyn_bytes(a.n_buckets), s, a, none);
   if (a.n_parts > 0) {
     // about 4,096 cells (two rounds of loads) per workgroup: the kernel is one
     // chain of latencies, and its adds are one per workgroup and partition pair
     const uint64_t per = std::min<uint64_t>(a.nnz / ((uint64_t)a.n_parts * 4096u) + 1, 65535);
-    hipLaunchKernelGGL(tl::k_tile_xfer, dim3((unsigned)a.n_parts, (unsigned)per), dim3(tl::kTh), 0, s, a, b);
+    hipLaunchKernelGGL((tl::k_tile_xfer<false>), dim3((unsigned)a.n_parts, (unsigned)per),
+                       dim3(tl::kTh), 0, s, a, b, none);
   }
-  hipLaunchKernelGGL((tl::k_tile_merge<kIdx>), dim3(a.g8 + (a.n_parts > 0 ? 1u : 0u)),
-                     dim3(tl::kTh), 0, s, a);
+  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
 }
 
 hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s) {
   if (a.perm) launch_tile_kernels<true>(a, b, s);
   else launch_tile_kernels<false>(a, b, s);
+  return hipGetLastError();
+}
+
+template <bool kIdx>
+static void launch_batch_kernels(const TileBatch& b, hipStream_t s) {
+  const TileArgs none{};
+  const TileBounds nob{};
+  hipLaunchKernelGGL((tl::k_tile_sort<kIdx, true>), dim3(b.n_tiles), dim3(tl::kTh),
+                     tl::sort_dyn_bytes(b.max_buckets), s, none, b);
+  if (b.n_parts) {
+    const uint64_t per = std::min<uint64_t>(b.max_part_cells / 4096u + 1, 65535);
+    hipLaunchKernelGGL((tl::k_tile_xfer<true>), dim3(b.n_parts, (unsigned)per), dim3(tl::kTh), 0, s,
+                       none, nob, b);
+  }
+  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, true>), dim3(((b.n_buckets + 7u) & ~7u) + b.n_items),
+                     dim3(tl::kTh), 0, s, none, b);
+}
+
+hipError_t launch_tile_batch(const TileBatch& b, hipStream_t s) {
+  if (b.idx) launch_batch_kernels<true>(b, s);
+  else launch_batch_kernels<false>(b, s);
   return hipGetLastError();
 }
 
