@@ -49,6 +49,12 @@ int floor_log2_u64(uint64_t x) {
 }
 uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
+// Column bits a finish bucket keeps when the last pass takes its extra bit.
+constexpr int kWideFinishMinBits = 5;
+// Mean cells per bucket up to which one pass is enough (the 1,024-thread
+// finish holds 10,240).
+constexpr uint64_t kOneSweepCells = 8192;
+
 // Digit schedule of one matrix.
 struct Sched {
   int n_levels = 1;
@@ -104,7 +110,7 @@ int passes_for(int B, int first_cap, int mb, int last_cap) {
 // more passes than that, instead of the one that needs the fewest.
 Sched make_sched_mb(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t R,
                     const int64_t* bounds, bool partitioned, int mb, int mf, bool spread,
-                    int force_fb, int last_cap, int level_budget = 0) {
+                    int force_fb, int last_cap, int level_budget = 0, bool split = false) {
   Sched s;
   uint64_t width = (uint64_t)std::max<int64_t>(n_cols, 1);
   if (partitioned) {
@@ -120,6 +126,10 @@ Sched make_sched_mb(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t 
   if (nnz > 0 && n_cols > 0) {
     const double per_col = (double)nnz / (double)n_cols;
     double target = (spread ? 2.0 : 4.0) * kSub;
+    // buckets of few columns carry the spread of single column degrees, so they
+    // aim for the 1,024-thread finish (2^27 cells over 256 uneven partitions,
+    // 512 cells per column: 8 columns 6.71 ms, 16 columns 6.23 ms)
+    if (spread && target / per_col < (double)(1 << (kWideFinishMinBits - 1))) target *= 2.0;
     if (spread)
       target = std::min(target, std::max(kSub / 8.0, (double)nnz / (double)kTargetBuckets));
     fb_ideal = floor_log2_u64((uint64_t)std::max(1.0, target / per_col));
@@ -135,15 +145,29 @@ Sched make_sched_mb(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t 
   // Fewest passes first, then the smallest finish width that achieves them
   // (within a level budget: the smallest finish width that fits it).
   int best_fb = fb_ideal, best_L = 1 << 30;
-  for (int fb = fb_ideal; fb <= std::min(mf, K); ++fb) {
-    const int L = passes_for(K - fb, first_cap, mb, last_cap);
-    if (level_budget > 0 && L <= level_budget) {
-      best_L = L;
-      best_fb = fb;
-      break;
+  auto choose = [&](int widest) {
+    best_fb = fb_ideal;
+    best_L = 1 << 30;
+    for (int fb = fb_ideal; fb <= std::min(widest, K); ++fb) {
+      const int L = passes_for(K - fb, first_cap, mb, last_cap);
+      if (level_budget > 0 && L <= level_budget) {
+        best_L = L;
+        best_fb = fb;
+        break;
+      }
+      if (L < best_L) { best_L = L; best_fb = fb; }
     }
-    if (L < best_L) { best_L = L; best_fb = fb; }
-  }
+  };
+  choose(mf);
+  // split: one pass only where its buckets fit the finish's LDS (kOneSweepCells on
+  // average): larger ones are sorted in 2,048-cell pieces by a workgroup each,
+  // and records-only passes are cheap beside that. Both ways: 2^27 fixed-width
+  // cells over 256 partitions 8.56 ms in one pass, 6.23 in two; 10 M cells of
+  // 8-16 bytes 812 and 543 us.
+  if (split && best_L == 1 && best_fb > fb_ideal && nnz > 0 && n_cols > 0 &&
+      (double)nnz / (double)n_cols * (double)(1ull << best_fb) > (double)kOneSweepCells)
+    choose(std::max(fb_ideal, floor_log2_u64((uint64_t)std::max(
+                                  1.0, (double)kOneSweepCells * (double)n_cols / (double)nnz))));
   if (K <= fb_ideal) { best_fb = K; best_L = 1; }
   if (force_fb >= 0) {  // a finish width set by the caller
     best_fb = std::min(force_fb, K);
@@ -168,23 +192,20 @@ Sched make_sched_mb(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t 
 
 uint32_t tile_cells_for(uint64_t nnz);
 
-// Column bits a finish bucket keeps when the last pass takes its extra bit.
-constexpr int kWideFinishMinBits = 5;
-
 // A single-matrix call whose tiles hold at least kWideSub cells runs its last
 // pass (records only) in the 512-thread form, which takes up to
 // kMaxLastPassBits bits when the pass cap is the full kMaxBitsPerPass.
 // The schedule a setting gives (it may need more than kMaxLevels passes).
 Sched make_sched_tuned(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t R,
                        const int64_t* bounds, bool partitioned, bool spread, const Tune* t,
-                       int level_budget = 0) {
+                       int level_budget = 0, bool split = false) {
   const int mb = (t && t->pass_bits > 0) ? t->pass_bits : max_pass_bits();
   const int ff = (t && t->finish_bits >= 0) ? t->finish_bits : -1;
   const uint32_t tile = (t && t->tile) ? t->tile : tile_cells_for((uint64_t)std::max<int64_t>(nnz, 0));
   const bool wide = spread && tile >= (uint32_t)kWideSub;
   const int last_cap = (wide && mb >= kMaxBitsPerPass) ? kMaxLastPassBits : mb;
   Sched s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, max_finish_bits(),
-                          spread, ff, last_cap, level_budget);
+                          spread, ff, last_cap, level_budget, split);
   // A finish bucket of fewer than 2^kWideFinishMinBits columns carries the
   // spread of single column degrees: on skewed inputs many such buckets
   // outgrow the 512-thread finish. The extra last-pass bit is kept only when
@@ -192,15 +213,15 @@ Sched make_sched_tuned(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32
   if (last_cap > mb && s.n_levels >= 2 && s.bits[s.n_levels - 1] > mb &&
       s.finish_bits < kWideFinishMinBits)
     s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, max_finish_bits(),
-                      spread, ff, mb, level_budget);
+                      spread, ff, mb, level_budget, split);
   return s;
 }
 
 Sched make_sched(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t R,
                  const int64_t* bounds, bool partitioned, bool spread, const Tune* t = nullptr,
-                 int level_budget = 0) {
+                 int level_budget = 0, bool split = false) {
   Sched s = make_sched_tuned(n_cols, nnz, payload_bytes, R, bounds, partitioned, spread, t,
-                             level_budget);
+                             level_budget, split);
   if (s.n_levels > kMaxLevels) {
     const uint32_t tile = (t && t->tile) ? t->tile : tile_cells_for((uint64_t)std::max<int64_t>(nnz, 0));
     const bool wide = spread && tile >= (uint32_t)kWideSub;
@@ -1073,8 +1094,12 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   HostItem& it = items[0];
   it.d = d;
   it.bounds = p->bounds.empty() ? nullptr : p->bounds.data();
-  it.s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, it.bounds, partitioned, true,
-                    &p->tune);
+  // A call of the two-launch form needs no second pass to fall back on; one
+  // whose workspace holds a single pass only makes that.
+  const TileGeo tg = tile_geo(d, partitioned, p->tune, crowded);
+  const int64_t* const bounds = it.bounds;
+  it.s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true,
+                    &p->tune, 0, !tg.ok);
   it.tile = p->tune.tile;
   if (!partitioned) it.d.n_parts = 1;
   fill_outputs(it.dev, row_ptr, col, payload_off, payload, t_row_ptr, t_col, t_payload_off, t_payload,
@@ -1089,9 +1114,12 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   }
   if (!partitioned) it.bounds = nullptr;
   Layout y = make_layout(Items(items, 1));
+  if (ws_bytes < y.bytes && !tg.ok) {
+    it.s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true, &p->tune);
+    y = make_layout(Items(items, 1));
+  }
   if (ws_bytes < y.bytes) return MGT_ENOMEM;
   const bool direct = use_direct(p, d, partitioned);
-  const TileGeo tg = tile_geo(d, partitioned, p->tune, crowded);
   // (a workspace that only the passes fit keeps them)
   const bool tiles = !direct && tg.ok && ws_bytes >= tg.bytes;
   if (graph)
@@ -1116,11 +1144,11 @@ size_t single_ws(const mgt_desc& d, const int64_t* bounds, bool partitioned, con
   items[0].d = d;
   if (!partitioned) items[0].d.n_parts = 1;
   items[0].bounds = bounds;
-  items[0].s =
-      make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true, &t);
+  const TileGeo tg = tile_geo(d, partitioned, t);
+  items[0].s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true, &t,
+                          0, !tg.ok);
   items[0].tile = t.tile;
   std::memset(&items[0].dev, 0, sizeof(ItemDev));
-  const TileGeo tg = tile_geo(d, partitioned, t);
   return std::max<uint64_t>(make_layout(items).bytes, tg.ok ? tg.bytes : 0);
 }
 
@@ -1661,8 +1689,8 @@ int mgt_plan_schedule(mgt_plan_t plan, int32_t partitioned, int32_t* out) {
   std::lock_guard<std::mutex> lock(plan->mu);
   const mgt_desc& d = plan->desc;
   const Sched s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, plan->bounds.data(),
-                             partitioned != 0,
-                             true, &plan->tune);  // as a call with these arguments makes it
+                             partitioned != 0, true, &plan->tune, 0,
+                             !tile_geo(d, partitioned != 0, plan->tune).ok);  // as a call makes it
   out[0] = s.n_levels;
   for (int l = 0; l < kMaxLevels; ++l) out[1 + l] = l < s.n_levels ? s.bits[l] : 0;
   out[5] = s.finish_bits;
