@@ -79,6 +79,37 @@ __device__ __forceinline__ T block_excl_scan(T v, T* scratch, T& total) {
   return inc - v + before;
 }
 
+// Two such scans sharing their barriers. `scratch` holds at least 2 NW values.
+template <int NW, class T, class U>
+__device__ __forceinline__ void block_excl_scan2(T& v, U& u, uint64_t* scratch, T& vtotal, U& utotal) {
+  const T vi = wave_incl_scan(v);
+  const U ui = wave_incl_scan(u);
+  const int w = threadIdx.x / kWave;
+  if (lane_id() == kWave - 1) {
+    scratch[2 * w] = vi;
+    scratch[2 * w + 1] = ui;
+  }
+  __syncthreads();
+  T vb = 0, va = 0;
+  U ub = 0, ua = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const T t = (T)scratch[2 * i];
+    const U x = (U)scratch[2 * i + 1];
+    if (i < w) {
+      vb += t;
+      ub += x;
+    }
+    va += t;
+    ua += x;
+  }
+  vtotal = va;
+  utotal = ua;
+  v = vi - v + vb;
+  u = ui - u + ub;
+  __syncthreads();
+}
+
 // Lanes of the wave whose `digit` equals the calling lane's digit, among the
 // lanes where `active` holds. `dbits` (wave-uniform) bounds the digit width.
 // A bit costs five vector instructions: the bit as a full mask, its ballot, and

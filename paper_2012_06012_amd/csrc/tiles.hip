@@ -521,8 +521,8 @@ constexpr int kMergeItems = kTileCap / kTh;  // cells per lane of a bucket held 
 constexpr uint32_t kMergeWave = kMergeItems * kWave;
 
 struct MergeLds {
-  // output order: row, payload offset (or payload), size then byte prefix. The
-  // tile of every cell, before that, in `row`.
+  // output order: row, payload offset (or payload), size then byte prefix.
+  // Before that, in `row`: the record of every cell, or its tile.
   uint32_t row[kTileCap], src[kTileCap], bp[kTileCap + 1];
   union {
     struct {
@@ -533,7 +533,7 @@ struct MergeLds {
   };
   alignas(16) uint16_t wc[kTileCols * kNW];  // (column, wave) counts, then first positions
   uint32_t red[kNW];
-  uint64_t red64[kNW];
+  uint64_t red64[2 * kNW];
 };
 
 // Size of a record's cell: from the offsets where the field cannot hold it
@@ -553,19 +553,27 @@ __device__ __forceinline__ uint32_t rec_size(const TileArgs& a, uint32_t key, ui
   return z;
 }
 
+// The words of record i (byte offsets stay below 2^32: 2^23 records of 16 bytes).
+template <uint32_t kWords>
+__device__ __forceinline__ const GMEM uint32_t* record(const TileArgs& a, uint32_t i) {
+  return (const GMEM uint32_t*)(gm((const uint8_t*)a.recs) + i * (4u * kWords));
+}
+
+// Cells of a run (or of a thread's share of one) up to which the threads list
+// them one by one.
+constexpr uint32_t kShortRun = 32;
+
 // The tile of every cell of bucket cells [q0, q0 + m), in tl[0..m): the tile
-// runs' starts marked and spread upwards. Ends with a barrier.
+// runs' starts marked and spread upwards (ex: every tile's first cell, n cells
+// in all). Ends with a barrier.
 template <int kItems>
-__device__ __forceinline__ void cell_tiles(const uint32_t* ex, const uint32_t* table_len, uint32_t t0,
-                                           uint32_t per, uint32_t T, uint32_t q0, uint32_t m,
-                                           uint32_t* tl, uint32_t* red) {
+__device__ __forceinline__ void cell_tiles(const uint32_t* ex, uint32_t T, uint32_t n, uint32_t q0,
+                                           uint32_t m, uint32_t* tl, uint32_t* red) {
   for (uint32_t i = threadIdx.x; i < m; i += kTh) tl[i] = 0;
   __syncthreads();
-  for (uint32_t j = 0; j < per; ++j) {
-    const uint32_t t = t0 + j;
-    if (t >= T) break;
-    const uint32_t e = ex[t], len = table_len[j];
-    if (len && e + len > q0 && e < q0 + m) tl[max(e, q0) - q0] = t + 1;
+  for (uint32_t t = threadIdx.x; t < T; t += kTh) {
+    const uint32_t e = ex[t], end = t + 1 < T ? ex[t + 1] : n;
+    if (end > e && end > q0 && e < q0 + m) tl[max(e, q0) - q0] = t + 1;
   }
   __syncthreads();
   // inclusive maximum: each thread's run, then over the threads
@@ -642,46 +650,74 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
   if (g >= G) return;
   const uint32_t col0 = a.lut ? gm(a.bcol)[g] : g * a.cpb;
   const uint32_t nc = a.lut ? gm(a.bcol)[g + 1] - col0 : min(a.cpb, (uint32_t)a.n_cols - col0);
-  // the bucket's column of the table: its place in the output, and its runs
+  // the bucket's column of the table: its place in the output, and its runs.
+  // `per` tiles per thread; with fewer tiles than threads, `lanes` threads per
+  // tile share its run.
   constexpr int kPerT = kTileTiles / kTh;
-  const uint32_t per = (T + kTh - 1) / kTh, t0 = threadIdx.x * per;
-  uint32_t len[kPerT];
+  const uint32_t per = (T + kTh - 1) / kTh;
+  const uint32_t lanes_lg = T * 2 > (uint32_t)kTh ? 0u : 31u - (uint32_t)__clz((uint32_t)kTh / T);
+  const uint32_t t0 = lanes_lg ? threadIdx.x >> lanes_lg : threadIdx.x * per;
+  const uint32_t sub = threadIdx.x & ((1u << lanes_lg) - 1u);
+  uint32_t len[kPerT], ex[kPerT], first[kPerT];  // a run: cells, first cell, first record
   uint32_t n, cell0;
   uint64_t byte0;
   {
-    uint32_t st[kPerT], sl = 0, sc = 0;
-    uint64_t sb = 0;
+    uint64_t s = 0, sb = 0;  // s: cells of the runs, and before them in their tiles << 32
+    uint32_t st[kPerT];
 #pragma unroll
     for (int j = 0; j < kPerT; ++j) {
       uint2 e = make_uint2(0u, 0u);
       if ((uint32_t)j < per && t0 + j < T) {
-        e.x = gm(a.table)[(uint64_t)(t0 + j) * G + g].x;
-        e.y = gm(a.table)[(uint64_t)(t0 + j) * G + g].y;
+        const GMEM uint2* const q = gm(a.table) + (uint64_t)(t0 + j) * G + g;
+        e.x = q->x;
+        e.y = q->y;
       }
       st[j] = e.x & 0xffffu;
       len[j] = e.x >> 16;
-      sl += len[j];
-      sc += st[j];
-      sb += e.y;
-    }
-    uint32_t e = block_excl_scan<kNW>(sl, L.red, n);
-    block_excl_scan<kNW>(sc, L.red, cell0);
-    block_excl_scan<kNW>(sb, L.red64, byte0);
-#pragma unroll
-    for (int j = 0; j < kPerT; ++j)
-      if ((uint32_t)j < per && t0 + j < T) {
-        L.ex[t0 + j] = e;
-        L.st[t0 + j] = (uint16_t)st[j];
-        e += len[j];
+      first[j] = (t0 + j) * a.tile_cells + st[j];
+      if (sub == 0) {
+        s += (uint64_t)len[j] | ((uint64_t)st[j] << 32);
+        sb += e.y;
       }
+    }
+    uint64_t tot;
+    block_excl_scan2<kNW>(s, sb, L.red64, tot, byte0);
+    n = (uint32_t)tot;
+    cell0 = (uint32_t)(tot >> 32);
+    uint32_t e = (uint32_t)s;
+    if (sub) e -= len[0];  // (the threads of one tile: the first one's run is in their prefix)
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j) {
+      ex[j] = e;
+      e += len[j];
+    }
   }
-  __syncthreads();
   if (n == 0) {
     for (uint32_t c = threadIdx.x; c < nc; c += kTh)
       st_off(a.t_row_ptr, (uint64_t)col0 + c, (int64_t)cell0, a.lg);
     return;
   }
   const bool multi = n > kCap;  // block-uniform
+  // Short runs: each thread lists its runs' records. Long ones (columns that
+  // crowd into few tiles) would leave one thread to it, so their starts are
+  // marked and spread instead (cell_tiles).
+  bool lng = multi;
+#pragma unroll
+  for (int j = 0; j < kPerT; ++j) lng |= (len[j] >> lanes_lg) > kShortRun;
+  lng = __syncthreads_or(lng) != 0;  // block-uniform
+  if (lng) {
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j)
+      if ((uint32_t)j < per && t0 + j < T && sub == 0) {
+        L.ex[t0 + j] = ex[j];
+        L.st[t0 + j] = (uint16_t)(first[j] - (t0 + j) * a.tile_cells);
+      }
+  } else {
+#pragma unroll
+    for (int j = 0; j < kPerT; ++j)
+      for (uint32_t i = sub; i < len[j]; i += 1u << lanes_lg) L.row[ex[j] + i] = first[j] + i;
+  }
+  __syncthreads();
   const int dbits = ceil_log2(nc);
   // chunked buckets: running first cell and byte of every column (bucket
   // relative), in the last words of `src` and `bp` of the chunk, which a chunk
@@ -697,11 +733,10 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     }
     for (uint32_t q0 = 0; q0 < n; q0 += chunk) {
       const uint32_t m = min(chunk, n - q0);
-      cell_tiles<kItems>(L.ex, len, t0, per, T, q0, m, L.row, L.red);
+      cell_tiles<kItems>(L.ex, T, n, q0, m, L.row, L.red);
       for (uint32_t i = threadIdx.x; i < m; i += kTh) {
         const uint32_t t = L.row[i] - 1u;
-        const GMEM uint32_t* const r =
-            gm(a.recs + ((uint64_t)t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t])) * kWords);
+        const GMEM uint32_t* const r = record<kWords>(a, t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t]));
         const uint32_t key = r[2], d = min(key >> 22, nc - 1u);
         atomicAdd(&run_c[d], 1u);
         atomicAdd(&run_b[d], rec_size(a, key, r[0]));
@@ -726,14 +761,17 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     const uint32_t w = tid / kWave, lane = tid % kWave;
     const uint32_t m = min(chunk, n - q0);
     __syncthreads();  // the previous chunk's positions have been read
-    cell_tiles<kItems>(L.ex, len, t0, per, T, q0, m, L.row, L.red);
+    if (lng) cell_tiles<kItems>(L.ex, T, n, q0, m, L.row, L.red);
     uint32_t x[kItems], row[kItems], key[kItems], idx[kIdx ? kItems : 1];
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
       const uint32_t i = min(w * kWaveCells + q * kWave + lane, m - 1u);
-      const uint32_t t = L.row[i] - 1u;
-      const GMEM uint32_t* const r =
-          gm(a.recs + ((uint64_t)t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t])) * kWords);
+      uint32_t ri = L.row[i];
+      if (lng) {
+        const uint32_t t = ri - 1u;
+        ri = t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t]);
+      }
+      const GMEM uint32_t* const r = record<kWords>(a, ri);
       x[q] = r[0];
       row[q] = r[1];
       key[q] = r[2];
