@@ -199,8 +199,9 @@ static_assert(sizeof(DirectArgs) <= 2048, "kernel argument size");
 hipError_t launch_direct(const DirectArgs& a, hipStream_t s);
 // A mid-size matrix in two launches (three for a partitioned call; see
 // tiles.hip): tiles sorted by column bucket, then one workgroup per bucket.
-constexpr uint32_t kTileMax = 4096;      // cells of a tile
-constexpr uint32_t kTileTiles = 2048;    // tiles of a call
+constexpr uint32_t kTileMax = 16384;     // cells of a tile
+constexpr uint32_t kTileSub = 4096;      // cells of a tile ranked at once
+constexpr uint32_t kTileTiles = 512;     // tiles of a call
 constexpr uint32_t kTileBuckets = 2048;  // buckets of a call
 constexpr uint32_t kTileCols = 512;      // columns of a bucket
 constexpr uint32_t kTileCap = 4608;      // cells of a bucket held at once

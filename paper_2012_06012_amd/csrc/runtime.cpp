@@ -445,9 +445,10 @@ struct TileGeo {
 constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
 
 // crowded: the caller knows some columns to hold far more cells than others.
-// batch: one of many items, whose workgroups fill the device together.
+// batch_cells: the cells of the batch it is an item of, whose workgroups fill
+// the device together (0: a call of its own).
 TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool crowded = false,
-                 bool batch = false) {
+                 uint64_t batch_cells = 0) {
   TileGeo t;
   const uint64_t nnz = (uint64_t)std::max<int64_t>(d.nnz, 0), cols = (uint64_t)std::max<int64_t>(d.n_cols, 0);
   if (nnz < 1 || nnz > (uint64_t)kTileMax * kTileTiles || cols < 1) return t;
@@ -458,7 +459,7 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   // buckets of at most 4/5 of what a workgroup holds, whole rounds of the
   // workgroups that run at once; small calls still fill one round
   uint64_t g = std::max<uint64_t>((5 * nnz + 4 * cap - 1) / (4 * cap), (cols + kTileCols - 1) / kTileCols);
-  if (batch) g = std::max<uint64_t>(g, 1);
+  if (batch_cells) g = std::max<uint64_t>(g, 1);
   else if (g > kTileSlots) g = align_up(g, kTileSlots);
   else g = std::max<uint64_t>(g, std::min<uint64_t>(kTileSlots, (nnz + 255) / 256));
   g = std::min<uint64_t>(g, cols);
@@ -478,11 +479,10 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
       t.n_buckets = (uint32_t)most;
     }
   }
-  uint64_t tiles = (nnz + kTileMax - 1) / kTileMax;
-  if (batch) {
-  } else if (tiles > kTileSlots) tiles = std::min<uint64_t>(align_up(tiles, kTileSlots), kTileTiles);
-  else tiles = std::max<uint64_t>(tiles, std::min<uint64_t>(kTileSlots, (nnz + 1023) / 1024));
-  t.tile_cells = (uint32_t)std::min<uint64_t>(align_up((nnz + tiles - 1) / tiles, 64), kTileMax);
+  // one round of tiles on the device, of 1,024 cells at least
+  const uint64_t all = batch_cells ? batch_cells : nnz;
+  t.tile_cells = (uint32_t)std::min<uint64_t>(
+      std::max<uint64_t>(align_up((all + kTileSlots - 1) / kTileSlots, 64), 1024), kTileMax);
   t.n_tiles = (uint32_t)((nnz + t.tile_cells - 1) / t.tile_cells);
   if (t.n_tiles > kTileTiles) return t;
   const uint64_t words = (d.flags & MGT_EMIT_PERM) ? 4 : 3;
@@ -1245,13 +1245,15 @@ void plan_batch(const mgt_plan_s* p, const std::vector<HostItem>& items, const T
                 bool tiles_too, BatchRun& r) {
   // device checks cancel a whole batch together: the passes' own business
   tiles_too = tiles_too && !(p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING));
+  uint64_t cells = 0;
+  for (const HostItem& it : items) cells += (uint64_t)it.d.nnz;
   for (size_t i = 0; i < items.size(); ++i) {
     const HostItem& it = items[i];
     TileGeo g;
     if (tiles_too) {
       mgt_desc d = it.d;
       d.flags |= p->flags & MGT_EMIT_PERM;
-      g = tile_geo(d, d.n_parts > 1, tune, false, true);
+      g = tile_geo(d, d.n_parts > 1, tune, false, std::max<uint64_t>(cells, 1));
     }
     (g.ok ? r.tiles : r.passes).push_back(it);
     if (g.ok) r.geo.push_back(g);

@@ -1,7 +1,7 @@
 // The two-launch transpose of mid-size matrices: tiles sorted by column bucket,
 // then one workgroup per bucket that collects its cells from every tile.
 //
-//   k_tile_sort   a workgroup sorts a tile of up to kTileMax consecutive cells
+//   k_tile_sort   a workgroup sorts a tile of up to 16,384 consecutive cells
 //                 by bucket (a run of `cpb` columns) and writes their records
 //                 in that order, with the tile's row of a table: for every
 //                 bucket, where its cells start in the tile, how many there
@@ -43,7 +43,7 @@ namespace tl {
 
 constexpr int kTh = 512;                 // threads of both kernels, two or more workgroups per CU
 constexpr int kNW = kTh / kWave;
-constexpr int kSortItems = kTileMax / kTh;  // cells per lane of k_tile_sort
+constexpr int kSortItems = kTileSub / kTh;  // cells per lane and piece of k_tile_sort
 constexpr int kSortWave = kSortItems * kWave;
 constexpr uint32_t kInline = 4;             // payload bytes a record holds itself
 constexpr uint32_t kSizeMask = (1u << 22) - 1u;  // size field; all ones: look it up
@@ -168,13 +168,13 @@ __global__ __launch_bounds__(kBoundTh) void k_tile_bounds(TileArgs a) {
 // ----------------------------------------------------------------------------- tile sort
 
 struct SortLds {
-  uint32_t incl[kTileMax];  // row starts per position, then their inclusive scan
-  uint32_t red[kNW];
+  uint32_t incl[kTileSub];  // row starts per position, then their inclusive scan
+  uint64_t red[2 * kNW];
 };
 // Beside it, sized by the call's buckets: 16-bit (bucket, wave) counts, then
-// first positions; payload bytes per bucket.
+// positions; the next position of every bucket; payload bytes per bucket.
 extern __shared__ uint16_t s_dyn[];
-inline uint32_t sort_dyn_bytes(uint32_t n_buckets) { return n_buckets * (2u * kNW + 4u); }
+inline uint32_t sort_dyn_bytes(uint32_t n_buckets) { return n_buckets * (2u * kNW + 8u); }
 
 // Row owning cell k: the last row starting at or before it, found by the whole
 // workgroup (each round probes kTh evenly spaced rows).
@@ -225,10 +225,13 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
 }
 
 // kIdx: the record carries the cell's input index (perm).
-// Bound by the latency of its steps (row search, loads, row expansion, ranks)
-// with three workgroups per CU in flight; the records are stored straight to
-// their place in the tile's own region (up to 80 KB, whole lines by the time
-// they leave the L2).
+// The tile's columns and sizes are read twice: counted first, which gives every
+// bucket its place in the tile, then ranked and stored in pieces of kTileSub
+// cells. Tiles of four pieces instead of one leave runs four times as long and
+// a quarter of the table for k_tile_merge, whose time goes with the number of
+// lines it reads. Bound by the latency of its steps with two workgroups per CU
+// in flight; the records are stored straight to their place in the tile's own
+// region (whole lines by the time they leave the L2).
 template <bool kIdx, bool kBatch>
 __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt) {
   constexpr int kWords = kIdx ? 4 : 3;
@@ -240,27 +243,17 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     a = load_item(bt.items, i);
     t -= bt.tile_base[i];
   }
+  const uint32_t G = a.n_buckets;
   uint16_t* const wc = (uint16_t*)__builtin_assume_aligned(s_dyn, 16);
-  uint32_t* const byt = (uint32_t*)(wc + a.n_buckets * kNW);
+  uint32_t* const next = (uint32_t*)(wc + G * kNW);
+  uint32_t* const byt = next + G;
   const uint32_t w = threadIdx.x / kWave, lane = lane_id();
   const uint64_t k0 = (uint64_t)t * a.tile_cells;
   const uint32_t n = (uint32_t)min((uint64_t)a.tile_cells, a.nnz - k0);
-  const uint32_t G = a.n_buckets, last = n - 1;
-  // the tile's columns and offsets first, so they fly during the row search
-  uint32_t col[kSortItems], off[kSortItems], end;
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t i = w * kSortWave + r * kWave + lane;
-    col[r] = (uint32_t)gm(a.col)[k0 + min(i, last)];
-    off[r] = a.fixed_w < 0 ? ld_lo(a.poff, k0 + min(i, n), a.lg) : (uint32_t)(k0 + min(i, n)) * (uint32_t)a.fixed_w;
+  for (uint32_t i = threadIdx.x; i < G; i += kTh) {
+    next[i] = 0;
+    byt[i] = 0;
   }
-  {
-    const uint32_t e = min(w * kSortWave + kSortWave, n);
-    end = a.fixed_w < 0 ? ld_lo(a.poff, k0 + e, a.lg) : (uint32_t)(k0 + e) * (uint32_t)a.fixed_w;
-  }
-  for (uint32_t i = threadIdx.x; i < (uint32_t)kTileMax; i += kTh) L.incl[i] = 0;
-  for (uint32_t i = threadIdx.x; i < (G * kNW + 1) / 2; i += kTh) ((uint32_t*)wc)[i] = 0;
-  for (uint32_t i = threadIdx.x; i < G; i += kTh) byt[i] = 0;
   if (a.validate) {
     const bool bad = __syncthreads_or(tile_bad(a, t)) != 0;
     if (threadIdx.x == 0) gm(a.bad)[t] = bad ? 1u : 0u;
@@ -272,57 +265,11 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
       gm(a.xfer_cells)[e] = 0;
       gm(a.xfer_bytes)[e] = 0;
     }
-  const uint32_t r0 = coop_row(a.row_ptr, a.lg, (uint64_t)a.n_rows, k0);
-  __syncthreads();
-  // rows of the tile's cells: row starts counted per position, then scanned
-  {
-    const uint64_t kend = k0 + n;
-    bool more = true;
-    for (uint64_t base = (uint64_t)r0 + 1; more; base += kTh) {
-      const uint64_t r = base + threadIdx.x;
-      bool stop = r >= (uint64_t)a.n_rows;
-      if (!stop) {
-        const uint64_t v = (uint64_t)ld_off(a.row_ptr, r, a.lg);
-        if (v >= k0 && v < kend) atomicAdd(&L.incl[v - k0], 1u);
-        stop = v >= kend;
-      }
-      more = !__syncthreads_or(stop);
-    }
-    constexpr int kPer = kTileMax / kTh;
-    const uint32_t p0 = threadIdx.x * kPer;
-    uint32_t v[kPer], s = 0;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      v[q] = L.incl[p0 + q];
-      s += v[q];
-    }
-    uint32_t tot;
-    uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      ex += v[q];
-      L.incl[p0 + q] = ex;
-    }
-    __syncthreads();
-  }
-  uint32_t rank[kSortItems], dig[kSortItems], size[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {  // each cell's size: the next cell's offset minus its own
-    uint32_t nx = (uint32_t)__shfl_down((int)off[r], 1);
-    const uint32_t wrap = r + 1 < kSortItems
-        ? (uint32_t)__builtin_amdgcn_readlane((int)off[r + 1 < kSortItems ? r + 1 : r], 0) : end;
-    if (lane == kWave - 1) nx = wrap;
-    size[r] = nx - off[r];
-  }
-  const int dbits = ceil_log2(G);
-  // ranks within the tile: stable per (bucket, wave), each wave in cell order
-  uint32_t at[kSortItems];
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t i = w * kSortWave + r * kWave + lane;
+  // bucket of a column, and the bucket's first column
+  auto bucket = [&](uint32_t col, uint32_t& first) {
     // (clamped: columns out of range are undefined input, but stay in bounds)
-    const uint32_t c = min(col[r], (uint32_t)a.n_cols - 1u);
-    uint32_t d, first;
+    const uint32_t c = min(col, (uint32_t)a.n_cols - 1u);
+    uint32_t d;
     if (a.lut) {  // uniform
       d = gm(a.lut)[c >> a.lut_shift];
       first = gm(a.bcol)[d];
@@ -331,83 +278,171 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
       if (d * a.cpb > c) --d;  // the reciprocal is rounded up
       first = d * a.cpb;
     }
-    dig[r] = d;
-    at[r] = d * kNW + w;
-    col[r] = c - first;
-    if (i < n && size[r]) atomicAdd(&byt[d], size[r]);
-  }
-  wave_ranks(wc, at, dig, n > w * kSortWave ? n - w * kSortWave : 0u, dbits, rank);
+    return d;
+  };
+  uint32_t r0 = coop_row(a.row_ptr, a.lg, (uint64_t)a.n_rows, k0);
   __syncthreads();
-  {  // bucket-major scan of the counters, and of the bytes per bucket
-    constexpr int kPer = kTileBuckets / kTh;  // buckets per thread
-    const uint32_t g0 = threadIdx.x * kPer;
-    uint32_t s = 0, sb = 0, b[kPer];
-    v4 c[kPer];  // eight 16-bit counters of a bucket
+  for (uint32_t c0 = 0; c0 < n; c0 += kTileSub) {  // cells per bucket
+    uint32_t col[kSortItems];
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      c[q] = v4{0u, 0u, 0u, 0u};
-      b[q] = 0;
-      if (g0 + q < G) {
-        c[q] = *(const v4*)&wc[(g0 + q) * kNW];
-        b[q] = byt[g0 + q];
+    for (int r = 0; r < kSortItems; ++r)
+      col[r] = (uint32_t)gm(a.col)[k0 + min(c0 + (uint32_t)r * kTh + threadIdx.x, n - 1)];
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+      uint32_t first;
+      if (c0 + (uint32_t)r * kTh + threadIdx.x < n) atomicAdd(&next[bucket(col[r], first)], 1u);
+    }
+  }
+  __syncthreads();
+  // every bucket's place in the tile (kPer consecutive buckets per thread)
+  constexpr int kPerG = kTileBuckets / kTh;
+  const uint32_t g0 = threadIdx.x * kPerG;
+  {
+    uint32_t s = 0, c[kPerG], tot;
+#pragma unroll
+    for (int q = 0; q < kPerG; ++q) {
+      c[q] = g0 + q < G ? next[g0 + q] : 0u;
+      s += c[q];
+    }
+    uint32_t ex = block_excl_scan<kNW>(s, (uint32_t*)L.red, tot);
+#pragma unroll
+    for (int q = 0; q < kPerG; ++q) {
+      if (g0 + q < G) next[g0 + q] = ex;
+      ex += c[q];
+    }
+  }
+  const int dbits = ceil_log2(G);
+  uint32_t* const rec = a.recs + k0 * kWords;
+  for (uint32_t c0 = 0; c0 < n; c0 += kTileSub) {
+    const uint32_t m = min(kTileSub, n - c0);
+    const uint64_t kb = k0 + c0;
+    // key: column within the bucket and size; at: the (bucket, wave) counter
+    uint32_t off[kSortItems], key[kSortItems], at[kSortItems], dig[kSortItems], end;
+    {
+      uint32_t col[kSortItems];
+#pragma unroll
+      for (int r = 0; r < kSortItems; ++r) {
+        const uint32_t i = w * kSortWave + r * kWave + lane;
+        col[r] = (uint32_t)gm(a.col)[kb + min(i, m - 1)];
+        off[r] = a.fixed_w < 0 ? ld_lo(a.poff, kb + min(i, m), a.lg)
+                               : (uint32_t)(kb + min(i, m)) * (uint32_t)a.fixed_w;
+      }
+      const uint32_t e = min(w * kSortWave + kSortWave, m);
+      end = a.fixed_w < 0 ? ld_lo(a.poff, kb + e, a.lg) : (uint32_t)(kb + e) * (uint32_t)a.fixed_w;
+      for (uint32_t i = threadIdx.x; i < kTileSub; i += kTh) L.incl[i] = 0;
+      for (uint32_t i = threadIdx.x; i < G * kNW / 2; i += kTh) ((uint32_t*)wc)[i] = 0;
+      __syncthreads();
+      // rows of the piece's cells: row starts counted per position, then scanned
+      bool more = true;
+      for (uint64_t base = (uint64_t)r0 + 1; more; base += kTh) {
+        const uint64_t r = base + threadIdx.x;
+        bool stop = r >= (uint64_t)a.n_rows;
+        if (!stop) {
+          const uint64_t v = (uint64_t)ld_off(a.row_ptr, r, a.lg);
+          if (v >= kb && v < kb + m) atomicAdd(&L.incl[v - kb], 1u);
+          stop = v >= kb + m;
+        }
+        more = !__syncthreads_or(stop);
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) s += (c[q][j] & 0xffffu) + (c[q][j] >> 16);
-      sb += b[q];
+      for (int r = 0; r < kSortItems; ++r) {  // a cell's size: the next cell's offset minus its own
+        uint32_t nx = (uint32_t)__shfl_down((int)off[r], 1);
+        const uint32_t wrap = r + 1 < kSortItems
+            ? (uint32_t)__builtin_amdgcn_readlane((int)off[r + 1 < kSortItems ? r + 1 : r], 0) : end;
+        if (lane == kWave - 1) nx = wrap;
+        uint32_t first;
+        const uint32_t z = nx - off[r];
+        dig[r] = bucket(col[r], first);
+        at[r] = dig[r] * kNW + w;
+        key[r] = ((min(col[r], (uint32_t)a.n_cols - 1u) - first) << 22) | min(z, kSizeMask);
+        if (w * kSortWave + r * kWave + lane < m && z) atomicAdd(&byt[dig[r]], z);
+      }
     }
-    uint32_t tot;
-    uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
-    uint32_t eb = block_excl_scan<kNW>(sb, L.red, tot);
+    uint32_t rank[kSortItems];
+    wave_ranks(wc, at, dig, m > w * kSortWave ? m - w * kSortWave : 0u, dbits, rank);
+    uint32_t rows;
+    {
+      constexpr int kPer = kTileSub / kTh;
+      const uint32_t p0 = threadIdx.x * kPer;
+      uint32_t v[kPer], s = 0;
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        v[q] = L.incl[p0 + q];
+        s += v[q];
+      }
+      uint32_t ex = block_excl_scan<kNW>(s, (uint32_t*)L.red, rows);  // (also: all counters are in)
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        ex += v[q];
+        L.incl[p0 + q] = ex;
+      }
+    }
+    // counts to positions: the bucket's next one, then wave by wave
+    for (uint32_t g = threadIdx.x; g < G; g += kTh) {
+      v4 c = *(const v4*)&wc[g * kNW];
+      uint32_t p = next[g];
+      v4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t lo = p;
+        p += c[j] & 0xffffu;
+        o[j] = lo | (p << 16);
+        p += c[j] >> 16;
+      }
+      *(v4*)&wc[g * kNW] = o;
+      next[g] = p;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSortItems; ++r) {
+      const uint32_t i = w * kSortWave + r * kWave + lane;
+      if (i >= m) continue;
+      const uint32_t z = key[r] & kSizeMask;
+      uint32_t x = off[r];
+      // a small payload goes in place of its offset: the aligned words that hold
+      // it (each holds one of its bytes; nothing is read past the payload array)
+      if (z && z <= kInline && (uint64_t)x + z <= a.payload_bytes) {
+        const uint8_t* const p = a.payload + x;
+        const uint32_t sh = 8u * ((uint32_t)(uintptr_t)p & 3u);
+        const GMEM uint32_t* const q = gm((const uint32_t*)((uintptr_t)p & ~(uintptr_t)3));
+        const uint32_t nb = ((uint32_t)(uintptr_t)p & 3u) + z;
+        const uint32_t w0 = q[0], w1 = nb > 4u ? q[1] : 0u;
+        x = (uint32_t)((((uint64_t)w1 << 32) | w0) >> sh);
+      }
+      const uint32_t row = r0 + L.incl[i];
+      const uint32_t p = (uint32_t)wc[at[r]] + rank[r];
+      GMEM uint32_t* const o = gm(rec + (uint64_t)p * kWords);
+      if constexpr (kWords == 3) {
+        o[0] = x;
+        o[1] = row;
+        o[2] = key[r];
+      } else {
+        typedef uint32_t r4 __attribute__((ext_vector_type(4), aligned(4)));
+        *(GMEM r4*)o = r4{x, row, key[r], (uint32_t)kb + i};
+      }
+    }
+    r0 += rows;    // the row of the piece's last cell; later rows start at the next piece or after
+    __syncthreads();  // rows and positions have been read
+  }
+  {  // the tile's row of the table: (start, cells) and the bytes of the earlier buckets
+    uint32_t s = 0, b[kPerG], tot;
+#pragma unroll
+    for (int q = 0; q < kPerG; ++q) {
+      b[q] = g0 + q < G ? byt[g0 + q] : 0u;
+      s += b[q];
+    }
+    uint32_t eb = block_excl_scan<kNW>(s, (uint32_t*)L.red, tot);
+    uint32_t start = g0 && g0 <= G ? next[g0 - 1] : 0u;  // (every bucket's end is in `next` by now)
     uint2* const row = a.table + (uint64_t)t * G;
 #pragma unroll
-    for (int q = 0; q < kPer; ++q) {
+    for (int q = 0; q < kPerG; ++q) {
       if (g0 + q < G) {
-        const uint32_t at = ex;
-        v4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint32_t lo = ex;
-          ex += c[q][j] & 0xffffu;
-          o[j] = lo | (ex << 16);
-          ex += c[q][j] >> 16;
-        }
-        *(v4*)&wc[(g0 + q) * kNW] = o;
-        // (start, cells) and the bytes of the tile's earlier buckets
-        gm(row)[g0 + q].x = at | ((ex - at) << 16);
+        const uint32_t end = next[g0 + q];
+        gm(row)[g0 + q].x = start | ((end - start) << 16);
         gm(row)[g0 + q].y = eb;
+        start = end;
       }
       eb += b[q];
-    }
-  }
-  __syncthreads();
-  uint32_t* const rec = a.recs + k0 * kWords;
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t i = w * kSortWave + r * kWave + lane;
-    if (i >= n) continue;
-    const uint32_t z = size[r];
-    uint32_t x = off[r];
-    // a small payload goes in place of its offset: the aligned words that hold
-    // it (each holds one of its bytes; nothing is read past the payload array)
-    if (z && z <= kInline && (uint64_t)x + z <= a.payload_bytes) {
-      const uint8_t* const p = a.payload + x;
-      const uint32_t sh = 8u * ((uint32_t)(uintptr_t)p & 3u);
-      const GMEM uint32_t* const q = gm((const uint32_t*)((uintptr_t)p & ~(uintptr_t)3));
-      const uint32_t nb = ((uint32_t)(uintptr_t)p & 3u) + z;
-      const uint32_t w0 = q[0], w1 = nb > 4u ? q[1] : 0u;
-      x = (uint32_t)((((uint64_t)w1 << 32) | w0) >> sh);
-    }
-    const uint32_t row = r0 + L.incl[i];
-    const uint32_t key = (col[r] << 22) | min(z, kSizeMask);
-    const uint32_t p = (uint32_t)wc[dig[r] * kNW + w] + rank[r];
-    GMEM uint32_t* const o = gm(rec + (uint64_t)p * kWords);
-    if constexpr (kWords == 3) {
-      o[0] = x;
-      o[1] = row;
-      o[2] = key;
-    } else {
-      typedef uint32_t r4 __attribute__((ext_vector_type(4), aligned(4)));
-      *(GMEM r4*)o = r4{x, row, key, (uint32_t)k0 + i};
     }
   }
 }
