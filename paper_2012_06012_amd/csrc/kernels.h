@@ -203,7 +203,8 @@ constexpr uint32_t kTileMax = 16384;     // cells of a tile
 constexpr uint32_t kTileSub = 4096;      // cells of a tile ranked at once
 constexpr uint32_t kTileTiles = 512;     // tiles of a call
 constexpr uint32_t kTileBuckets = 2048;  // buckets of a call
-constexpr uint32_t kTileCols = 512;      // columns of a bucket
+constexpr uint32_t kTileCols = 512;      // columns of a bucket ...
+constexpr uint32_t kTileWide = 4096;     // ... or of a wide one (many columns, few cells each)
 constexpr uint32_t kTileCap = 4608;      // cells of a bucket held at once
 constexpr uint32_t kTileBins = 4096;     // column runs of a table of uneven buckets
 struct TileArgs {
@@ -230,6 +231,7 @@ struct TileArgs {
                               // of every run of 2^lut_shift columns (k_tile_bounds)
   uint32_t* bcol;             // with lut: every bucket's first column, n_buckets + 1 entries
   uint32_t lut_shift, tile_target;  // with lut: and the cells a bucket aims for
+  const uint32_t* vval;       // view operations: the value of every cell, in place of its row
   uint64_t nnz, payload_bytes;  // payload_bytes < 2^32
   int64_t n_rows, n_cols;     // < 2^31
   uint32_t cpb;               // columns per bucket
@@ -240,6 +242,8 @@ struct TileArgs {
   int32_t fixed_w;            // bytes of every cell, or -1
   int32_t n_parts;            // 0: plain call; <= kDirectParts
   int32_t validate;
+  int32_t wide;               // cpb > kTileCols (calls of their own only)
+  uint32_t size_bits;         // of a record's size field: 22, or 20 beside a wide bucket's column
 };
 struct TileBounds {
   int32_t bounds[kDirectParts + 1];
@@ -247,6 +251,19 @@ struct TileBounds {
 // Single call: the item's arguments travel with the launches. perm decides the
 // record form.
 hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s);
+// A view operation's sort keys and carried values (as launch_view_keys, with
+// the arguments beside the launch); its tiles then take keys as columns and
+// the values as vval.
+struct TileView {
+  const void* row_ptr;        // over the virtual rows
+  const int32_t* col;
+  uint32_t* keys;
+  uint32_t* vals;
+  uint64_t nnz, n_virtual;    // cells; rows of the input CSR
+  int64_t n_rows, n_cols;     // of the matrix the views represent
+  int32_t op, column_view, n_parts, lg;
+};
+hipError_t launch_tile_keys(const TileView& v, const TileBounds& b, hipStream_t s);
 // Batch: the items' arguments lie in memory, with running totals of their
 // tiles, buckets, and source partitions of partitioned items (n_items + 1
 // entries each).

@@ -438,6 +438,7 @@ struct TileGeo {
   bool ok = false;
   uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
   bool uneven = false;  // bucket bounds from sampled columns (k_tile_bounds)
+  bool wide = false;    // buckets of more than kTileCols columns
   uint32_t lut_shift = 0, target = 0;
   uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_lut = 0, o_bcol = 0, bytes = 0;
 };
@@ -463,11 +464,17 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   else if (g > kTileSlots) g = align_up(g, kTileSlots);
   else g = std::max<uint64_t>(g, std::min<uint64_t>(kTileSlots, (nnz + 255) / 256));
   g = std::min<uint64_t>(g, cols);
+  if (g > kTileBuckets && !batch_cells && nnz <= kTileBuckets * cap * 4 / 5) {
+    // too many columns for buckets of kTileCols: wide ones, as many as the cells ask for
+    g = std::max<uint64_t>((5 * nnz + 4 * cap - 1) / (4 * cap), (cols + kTileWide - 1) / kTileWide);
+    if (g > kTileSlots) g = std::min<uint64_t>(align_up(g, kTileSlots), kTileBuckets);
+    t.wide = true;
+  }
   if (g > kTileBuckets) return t;
   t.cpb = (uint32_t)((cols + g - 1) / g);
   t.n_buckets = (uint32_t)((cols + t.cpb - 1) / t.cpb);
-  if (t.cpb > kTileCols || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
-  if (crowded && nnz >= 64 * 1024) {
+  if (t.cpb > (t.wide ? kTileWide : kTileCols) || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
+  if (crowded && !t.wide && nnz >= 64 * 1024) {
     // runs of up to 2^lut_shift columns; buckets aim for 3/5 of what a
     // workgroup holds, the samples' spread on top
     t.lut_shift = (uint32_t)std::max(0, ceil_log2_u64(cols) - ceil_log2_u64(kTileBins));
@@ -1056,6 +1063,9 @@ TileArgs tile_args(const HostItem& it, const TileGeo& t, bool partitioned, uint3
   a.lg = d.offset_width == 8 ? 3 : 2;
   a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
   a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
+  a.wide = t.wide ? 1 : 0;
+  a.size_bits = t.wide ? 20 : 22;
+  a.vval = v.vval;
   if (partitioned) a.n_parts = d.n_parts;
   return a;
 }
@@ -1362,6 +1372,16 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
   return MGT_OK;
 }
 
+// The two-launch form of a view operation: the keys are the columns (device
+// checks of the views' own invariants keep the passes).
+TileGeo view_geo(const mgt_plan_s* p) {
+  if ((p->flags & MGT_VALIDATE) || p->desc.n_parts > kDirectParts) return TileGeo();
+  return tile_geo(p->view_desc, false, p->tune);
+}
+uint64_t view_tiles_bytes(const TileGeo& t, int64_t nnz) {
+  return align_up(t.bytes, 256) + 2 * align_up(4ull * (uint64_t)nnz, 256);
+}
+
 }  // namespace
 
 namespace mgt {
@@ -1478,6 +1498,8 @@ int mgt_view_plan(const mgt_desc* desc, int32_t op, int32_t in_view, mgt_plan_t*
   items[0].s = make_sched(v.n_cols, v.nnz, v.payload_bytes, 1, nullptr, false, true);
   std::memset(&items[0].dev, 0, sizeof(ItemDev));
   p->ws_view = make_layout(items, (uint64_t)R + 1).bytes;
+  const TileGeo tg = view_geo(p);
+  if (tg.ok) p->ws_view = std::max<uint64_t>(p->ws_view, view_tiles_bytes(tg, v.nnz));
   *out = p;
   if (workspace_bytes) *workspace_bytes = p->ws_view;
   return MGT_OK;
@@ -1504,6 +1526,28 @@ int mgt_view_transform(mgt_plan_t p, const void* row_ptr, const int32_t* col,
   Layout y = make_layout(items, p->bounds.size());
   if (workspace_bytes < y.bytes) return MGT_ENOMEM;
   uint8_t* W = (uint8_t*)workspace;
+  const TileGeo tg = view_geo(p);
+  if (tg.ok && workspace_bytes >= view_tiles_bytes(tg, v.nnz)) {
+    TileView k{};
+    TileBounds b{};
+    k.row_ptr = row_ptr;
+    k.col = col;
+    k.keys = (uint32_t*)(W + align_up(tg.bytes, 256));
+    k.vals = (uint32_t*)((uint8_t*)k.keys + align_up(4ull * (uint64_t)v.nnz, 256));
+    k.nnz = (uint64_t)v.nnz;
+    k.n_virtual = (uint64_t)v.n_rows;
+    k.n_rows = p->desc.n_rows;
+    k.n_cols = p->desc.n_cols;
+    k.op = p->view_op;
+    k.column_view = p->column_view;
+    k.n_parts = p->desc.n_parts;
+    k.lg = v.offset_width == 8 ? 3 : 2;
+    for (int32_t r = 0; r <= p->desc.n_parts; ++r) b.bounds[r] = (int32_t)p->bounds[(size_t)r];
+    MGT_HIP(launch_tile_keys(k, b, stream));
+    it.dev.col = (const int32_t*)k.keys;
+    it.dev.vval = k.vals;
+    return run_tiles(it, tg, false, p->flags, workspace, d_status, stream);
+  }
   it.dev.col = (const int32_t*)(W + y.o_vkeys);  // the passes sort by the keys ...
   it.dev.vval = (const uint32_t*)(W + y.o_vvals);  // ... and carry the values
   ViewCall vc{col, p->bounds.data(), p->desc.n_rows, p->desc.n_cols, p->view_op, p->column_view};

@@ -25,8 +25,8 @@
 // travel with the launches.
 //
 // Record of a cell (3 words, a 4th for perm): payload offset (or the payload
-// itself, up to 4 bytes), row, column within the bucket << 22 | size, input
-// index. A size of 2^22 - 1 or more is looked up again in the offsets.
+// itself, up to 4 bytes), row, column within the bucket << size_bits | size,
+// input index. A size the field cannot hold is looked up again in the offsets.
 // (Payloads of up to 8 bytes in a word more were no faster: 4.3 M cells of 8
 // bytes 143 us, against 146 us for 9 bytes read from the input.)
 #include <hip/hip_runtime.h>
@@ -46,8 +46,7 @@ constexpr int kNW = kTh / kWave;
 constexpr int kSortItems = kTileSub / kTh;  // cells per lane and piece of k_tile_sort
 constexpr int kSortWave = kSortItems * kWave;
 constexpr uint32_t kInline = 4;             // payload bytes a record holds itself
-constexpr uint32_t kSizeMask = (1u << 22) - 1u;  // size field; all ones: look it up
-static_assert(kTileCols <= 1 << 10, "column field of a record");
+static_assert(kTileCols <= 1 << 10 && kTileWide <= 1 << 12, "column field of a record");
 
 __device__ __forceinline__ int64_t ld_off(const void* p, uint64_t i, int lg) {
   return lg == 2 ? (int64_t)gm((const int32_t*)p)[i] : gm((const int64_t*)p)[i];
@@ -192,6 +191,42 @@ __device__ __forceinline__ uint32_t coop_row(const void* rp, int lg, uint64_t n_
   return (uint32_t)lo;
 }
 
+// Rows of the cells [kb, kb + m), the first of which lies in row r0: the row
+// starts after it counted per position (incl zero before, and a barrier after
+// that), then scanned: cell kb + i lies in row r0 + incl[i]. Returns the rows
+// that start among them. Every thread must call both.
+__device__ __forceinline__ void mark_rows(const void* rp, int lg, uint64_t n_rows, uint64_t kb, uint32_t m,
+                                          uint32_t r0, uint32_t* incl) {
+  bool more = true;
+  for (uint64_t base = (uint64_t)r0 + 1; more; base += kTh) {
+    const uint64_t r = base + threadIdx.x;
+    bool stop = r >= n_rows;
+    if (!stop) {
+      const uint64_t v = (uint64_t)ld_off(rp, r, lg);
+      if (v >= kb && v < kb + m) atomicAdd(&incl[v - kb], 1u);
+      stop = v >= kb + m;
+    }
+    more = !__syncthreads_or(stop);
+  }
+}
+__device__ __forceinline__ uint32_t scan_rows(uint32_t* incl, uint32_t* red) {
+  constexpr int kPer = kTileSub / kTh;
+  const uint32_t p0 = threadIdx.x * kPer;
+  uint32_t v[kPer], s = 0, rows;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    v[q] = incl[p0 + q];
+    s += v[q];
+  }
+  uint32_t ex = block_excl_scan<kNW>(s, red, rows);
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    ex += v[q];
+    incl[p0 + q] = ex;
+  }
+  return rows;
+}
+
 // Device-side data checks of this tile's share of the inputs (as k_validate).
 __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
   bool bad = false;
@@ -232,7 +267,8 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
 // lines it reads. Bound by the latency of its steps with two workgroups per CU
 // in flight; the records are stored straight to their place in the tile's own
 // region (whole lines by the time they leave the L2).
-template <bool kIdx, bool kBatch>
+// kVal: every cell carries a value of its own (vval) in place of its row id.
+template <bool kIdx, bool kBatch, bool kVal = false>
 __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt) {
   constexpr int kWords = kIdx ? 4 : 3;
   __shared__ SortLds L;
@@ -280,7 +316,8 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     }
     return d;
   };
-  uint32_t r0 = coop_row(a.row_ptr, a.lg, (uint64_t)a.n_rows, k0);
+  uint32_t r0 = 0;
+  if constexpr (!kVal) r0 = coop_row(a.row_ptr, a.lg, (uint64_t)a.n_rows, k0);
   __syncthreads();
   for (uint32_t c0 = 0; c0 < n; c0 += kTileSub) {  // cells per bucket
     uint32_t col[kSortItems];
@@ -312,12 +349,14 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     }
   }
   const int dbits = ceil_log2(G);
+  const uint32_t size_mask = (1u << a.size_bits) - 1u;
   uint32_t* const rec = a.recs + k0 * kWords;
   for (uint32_t c0 = 0; c0 < n; c0 += kTileSub) {
     const uint32_t m = min(kTileSub, n - c0);
     const uint64_t kb = k0 + c0;
     // key: column within the bucket and size; at: the (bucket, wave) counter
     uint32_t off[kSortItems], key[kSortItems], at[kSortItems], dig[kSortItems], end;
+    uint32_t val[kVal ? kSortItems : 1];
     {
       uint32_t col[kSortItems];
 #pragma unroll
@@ -327,23 +366,17 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
         off[r] = a.fixed_w < 0 ? ld_lo(a.poff, kb + min(i, m), a.lg)
                                : (uint32_t)(kb + min(i, m)) * (uint32_t)a.fixed_w;
       }
+      if constexpr (kVal) {
+#pragma unroll
+        for (int r = 0; r < kSortItems; ++r)
+          val[r] = gm(a.vval)[kb + min(w * kSortWave + r * kWave + lane, m - 1)];
+      }
       const uint32_t e = min(w * kSortWave + kSortWave, m);
       end = a.fixed_w < 0 ? ld_lo(a.poff, kb + e, a.lg) : (uint32_t)(kb + e) * (uint32_t)a.fixed_w;
       for (uint32_t i = threadIdx.x; i < kTileSub; i += kTh) L.incl[i] = 0;
       for (uint32_t i = threadIdx.x; i < G * kNW / 2; i += kTh) ((uint32_t*)wc)[i] = 0;
       __syncthreads();
-      // rows of the piece's cells: row starts counted per position, then scanned
-      bool more = true;
-      for (uint64_t base = (uint64_t)r0 + 1; more; base += kTh) {
-        const uint64_t r = base + threadIdx.x;
-        bool stop = r >= (uint64_t)a.n_rows;
-        if (!stop) {
-          const uint64_t v = (uint64_t)ld_off(a.row_ptr, r, a.lg);
-          if (v >= kb && v < kb + m) atomicAdd(&L.incl[v - kb], 1u);
-          stop = v >= kb + m;
-        }
-        more = !__syncthreads_or(stop);
-      }
+      if constexpr (!kVal) mark_rows(a.row_ptr, a.lg, (uint64_t)a.n_rows, kb, m, r0, L.incl);
 #pragma unroll
       for (int r = 0; r < kSortItems; ++r) {  // a cell's size: the next cell's offset minus its own
         uint32_t nx = (uint32_t)__shfl_down((int)off[r], 1);
@@ -354,29 +387,15 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
         const uint32_t z = nx - off[r];
         dig[r] = bucket(col[r], first);
         at[r] = dig[r] * kNW + w;
-        key[r] = ((min(col[r], (uint32_t)a.n_cols - 1u) - first) << 22) | min(z, kSizeMask);
+        key[r] = ((min(col[r], (uint32_t)a.n_cols - 1u) - first) << a.size_bits) | min(z, size_mask);
         if (w * kSortWave + r * kWave + lane < m && z) atomicAdd(&byt[dig[r]], z);
       }
     }
     uint32_t rank[kSortItems];
     wave_ranks(wc, at, dig, m > w * kSortWave ? m - w * kSortWave : 0u, dbits, rank);
-    uint32_t rows;
-    {
-      constexpr int kPer = kTileSub / kTh;
-      const uint32_t p0 = threadIdx.x * kPer;
-      uint32_t v[kPer], s = 0;
-#pragma unroll
-      for (int q = 0; q < kPer; ++q) {
-        v[q] = L.incl[p0 + q];
-        s += v[q];
-      }
-      uint32_t ex = block_excl_scan<kNW>(s, (uint32_t*)L.red, rows);  // (also: all counters are in)
-#pragma unroll
-      for (int q = 0; q < kPer; ++q) {
-        ex += v[q];
-        L.incl[p0 + q] = ex;
-      }
-    }
+    uint32_t rows = 0;
+    if constexpr (kVal) __syncthreads();  // all counters are in
+    else rows = scan_rows(L.incl, (uint32_t*)L.red);  // (likewise)
     // counts to positions: the bucket's next one, then wave by wave
     for (uint32_t g = threadIdx.x; g < G; g += kTh) {
       v4 c = *(const v4*)&wc[g * kNW];
@@ -397,7 +416,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     for (int r = 0; r < kSortItems; ++r) {
       const uint32_t i = w * kSortWave + r * kWave + lane;
       if (i >= m) continue;
-      const uint32_t z = key[r] & kSizeMask;
+      const uint32_t z = key[r] & size_mask;
       uint32_t x = off[r];
       // a small payload goes in place of its offset: the aligned words that hold
       // it (each holds one of its bytes; nothing is read past the payload array)
@@ -409,7 +428,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
         const uint32_t w0 = q[0], w1 = nb > 4u ? q[1] : 0u;
         x = (uint32_t)((((uint64_t)w1 << 32) | w0) >> sh);
       }
-      const uint32_t row = r0 + L.incl[i];
+      const uint32_t row = kVal ? val[kVal ? r : 0] : r0 + L.incl[i];
       const uint32_t p = (uint32_t)wc[at[r]] + rank[r];
       GMEM uint32_t* const o = gm(rec + (uint64_t)p * kWords);
       if constexpr (kWords == 3) {
@@ -444,6 +463,59 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
       }
       eb += b[q];
     }
+  }
+}
+
+// ----------------------------------------------------------------------------- view keys
+
+// Sort key and carried value of every cell of a view operation (see k_view_keys
+// in kernels.hip for the four cases), kTileSub cells per workgroup.
+__global__ __launch_bounds__(kTh) void k_tile_keys(TileView v, TileBounds b) {
+  __shared__ uint32_t incl[kTileSub];
+  __shared__ int32_t lb[kDirectParts + 1];
+  __shared__ uint32_t red[kNW];
+  const uint32_t R = (uint32_t)v.n_parts;
+  for (uint32_t i = threadIdx.x; i <= R; i += kTh) lb[i] = b.bounds[i];
+  for (uint32_t i = threadIdx.x; i < kTileSub; i += kTh) incl[i] = 0;
+  const uint64_t k0 = (uint64_t)blockIdx.x * kTileSub;
+  const uint32_t m = (uint32_t)min((uint64_t)kTileSub, v.nnz - k0);
+  const uint32_t r0 = coop_row(v.row_ptr, v.lg, v.n_virtual, k0);
+  __syncthreads();
+  mark_rows(v.row_ptr, v.lg, v.n_virtual, k0, m, r0, incl);
+  scan_rows(incl, red);
+  __syncthreads();
+  // the last partition starting at or before x
+  auto owner = [&](int64_t x) {
+    uint32_t lo = 0, hi = R;
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (lb[mid] <= x) lo = mid;
+      else hi = mid;
+    }
+    return lo;
+  };
+  constexpr int kPer = kTileSub / kTh;
+  int32_t col[kPer];
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) col[r] = gm(v.col)[k0 + min((uint32_t)(r * kTh) + threadIdx.x, m - 1)];
+#pragma unroll
+  for (int r = 0; r < kPer; ++r) {
+    const uint32_t i = (uint32_t)(r * kTh) + threadIdx.x;
+    if (i >= m) break;
+    const uint32_t row = r0 + incl[i];
+    uint64_t key;
+    uint32_t val;
+    if (!v.column_view) {
+      key = v.op == 0 ? (uint64_t)owner(row) * (uint64_t)v.n_cols + (uint64_t)(int64_t)col[r]
+                      : (uint64_t)owner(col[r]) * (uint64_t)v.n_rows + row;
+      val = v.op == 0 ? row : (uint32_t)col[r];
+    } else {
+      const uint32_t i_row = row % (uint32_t)v.n_rows;
+      key = v.op == 0 ? (uint64_t)(int64_t)col[r] : i_row;
+      val = v.op == 0 ? i_row : (uint32_t)col[r];
+    }
+    gm(v.keys)[k0 + i] = (uint32_t)key;
+    gm(v.vals)[k0 + i] = val;
   }
 }
 
@@ -566,7 +638,9 @@ struct MergeLds {
     };
     alignas(16) uint8_t stage[kNW][kStage];  // after the records are read, single-chunk buckets only
   };
-  alignas(16) uint16_t wc[kTileCols * kNW];  // (column, wave) counts, then first positions
+  // (column, wave) counts, then first positions, and one for the cells outside
+  // a piece of a wide bucket
+  alignas(16) uint16_t wc[(kTileCols + 1) * kNW];
   uint32_t red[kNW];
   uint64_t red64[2 * kNW];
 };
@@ -574,8 +648,9 @@ struct MergeLds {
 // Size of a record's cell: from the offsets where the field cannot hold it
 // (its payload is not inline, so x is its offset: the last cell starting there).
 __device__ __forceinline__ uint32_t rec_size(const TileArgs& a, uint32_t key, uint32_t x) {
-  uint32_t z = key & kSizeMask;
-  if (z == kSizeMask) {
+  const uint32_t mask = (1u << a.size_bits) - 1u;
+  uint32_t z = key & mask;
+  if (z == mask) {
     if (a.fixed_w >= 0) return (uint32_t)a.fixed_w;
     uint64_t lo = 0, hi = a.nnz;
     while (hi - lo > 1) {
@@ -650,7 +725,10 @@ __device__ __forceinline__ void cell_tiles(const uint32_t* ex, uint32_t T, uint3
 // tiles' records in its L2.
 // A bucket of more than kCap cells (skewed columns) is taken in chunks: column
 // totals first, then every chunk's cells to their column's running place.
-template <bool kIdx, bool kBatch>
+// kWide: buckets of up to kTileWide columns, whose cells are ranked by the low
+// six column bits, then by the high ones (two small sets of counters instead of
+// one per column and wave); a chunked one is taken kTileCols columns at a time.
+template <bool kIdx, bool kBatch, bool kWide = false>
 __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch bt) {
   constexpr int kItems = kMergeItems;
   constexpr uint32_t kCap = kTileCap, kWaveCells = kMergeWave;
@@ -753,16 +831,25 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
       for (uint32_t i = sub; i < len[j]; i += 1u << lanes_lg) L.row[ex[j] + i] = first[j] + i;
   }
   __syncthreads();
-  const int dbits = ceil_log2(nc);
   // chunked buckets: running first cell and byte of every column (bucket
-  // relative), in the last words of `src` and `bp` of the chunk, which a chunk
-  // of kChunk cells leaves free
+  // relative), in the last words of `src` and `bp`, which chunks leave free
   const uint32_t chunk = multi ? kCap - kTileCols : kCap;
   uint32_t* const run_c = L.src + chunk;
   uint32_t* const run_b = L.bp + chunk + 1;
-  const uint32_t E = nc * kNW;
+  const bool two_step = kWide && !multi && nc > kTileCols;  // block-uniform
+  const uint32_t piece = kWide && multi ? kTileCols : nc;
+  for (uint32_t sub0 = 0; sub0 < nc; sub0 += piece) {
+  const uint32_t ncs = min(piece, nc - sub0);  // this piece's columns; ncs: any other (kWide)
+  auto column = [&](uint32_t key) {
+    const uint32_t d = key >> a.size_bits;
+    return kWide ? min(d - sub0, ncs) : min(d, nc - 1u);
+  };
+  const uint32_t E = (ncs + (kWide ? 1u : 0u)) * kNW;
+  const int dbits = ceil_log2(ncs + (kWide ? 1u : 0u));
+  uint32_t piece_cells = 0, piece_bytes = 0;
   if (multi) {
-    for (uint32_t c = threadIdx.x; c < nc; c += kTh) {
+    __syncthreads();  // (the previous piece has been written)
+    for (uint32_t c = threadIdx.x; c < ncs; c += kTh) {
       run_c[c] = 0;
       run_b[c] = 0;
     }
@@ -772,29 +859,29 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
       for (uint32_t i = threadIdx.x; i < m; i += kTh) {
         const uint32_t t = L.row[i] - 1u;
         const GMEM uint32_t* const r = record<kWords>(a, t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t]));
-        const uint32_t key = r[2], d = min(key >> 22, nc - 1u);
+        const uint32_t key = r[2], d = column(key);
+        if (kWide && d == ncs) continue;
         atomicAdd(&run_c[d], 1u);
         atomicAdd(&run_b[d], rec_size(a, key, r[0]));
       }
       __syncthreads();
     }
-    uint32_t v = 0, u = 0, tot;  // nc <= kTileCols == kTh
-    if (threadIdx.x < nc) {
+    uint32_t v = 0, u = 0;  // ncs <= kTileCols == kTh
+    if (threadIdx.x < ncs) {
       v = run_c[threadIdx.x];
       u = run_b[threadIdx.x];
     }
-    const uint32_t ev = block_excl_scan<kNW>(v, L.red, tot);
-    const uint32_t eu = block_excl_scan<kNW>(u, L.red, tot);
-    if (threadIdx.x < nc) {
-      run_c[threadIdx.x] = ev;
-      run_b[threadIdx.x] = eu;
-      st_off(a.t_row_ptr, (uint64_t)col0 + threadIdx.x, (int64_t)cell0 + ev, a.lg);
+    block_excl_scan2<kNW>(v, u, L.red64, piece_cells, piece_bytes);
+    if (threadIdx.x < ncs) {
+      run_c[threadIdx.x] = v;
+      run_b[threadIdx.x] = u;
+      st_off(a.t_row_ptr, (uint64_t)col0 + sub0 + threadIdx.x, (int64_t)cell0 + v, a.lg);
     }
   }
   for (uint32_t q0 = 0; q0 < n; q0 += chunk) {
     const uint32_t tid = opaque(threadIdx.x);
     const uint32_t w = tid / kWave, lane = tid % kWave;
-    const uint32_t m = min(chunk, n - q0);
+    uint32_t m = min(chunk, n - q0);
     __syncthreads();  // the previous chunk's positions have been read
     if (lng) cell_tiles<kItems>(L.ex, T, n, q0, m, L.row, L.red);
     uint32_t x[kItems], row[kItems], key[kItems], idx[kIdx ? kItems : 1];
@@ -812,28 +899,95 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
       key[q] = r[2];
       if constexpr (kIdx) idx[q] = r[3];
     }
-    for (uint32_t e = tid; e < (E + 1) / 2; e += kTh) ((uint32_t*)L.wc)[e] = 0;
-    __syncthreads();
-    uint32_t rank[kItems];
-    {
+    uint32_t pos[kItems];  // every cell's place in output order (bucket relative)
+    const uint32_t mine = m > w * kWaveCells ? m - w * kWaveCells : 0u;  // the wave's cells
+    if (two_step) {
+      // stable by the low six bits, then by the high ones; the columns' own
+      // counts give the row offsets
+      uint32_t* const hist = (uint32_t*)L.wc;         // two 16-bit counts per word
+      uint16_t* const dc = (uint16_t*)&L.stage[0][0];  // (digit, wave) counters
+      static_assert(64 * kNW == kTh, "one digit counter per thread");
+      for (uint32_t e = tid; e < kTileWide / 2; e += kTh) hist[e] = 0;
+      __syncthreads();  // (and every record has been read)
+      dc[tid] = 0;
+      __syncthreads();
+      uint32_t at[kItems], d[kItems], rank[kItems];
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        const uint32_t c = min(key[q] >> a.size_bits, nc - 1u);
+        d[q] = c & 63u;
+        at[q] = d[q] * kNW + w;
+        if ((uint32_t)q * kWave + lane < mine) atomicAdd(&hist[c >> 1], 1u << (16u * (c & 1u)));
+      }
+      wave_ranks(dc, at, d, mine, 6, rank);
+      __syncthreads();
+      {
+        v4 h = *(const v4*)&hist[tid * 4];  // eight columns
+        uint32_t s = 0, e = dc[tid], ts, te;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s += (h[j] & 0xffffu) + (h[j] >> 16);
+        block_excl_scan2<kNW>(s, e, L.red64, ts, te);
+        dc[tid] = (uint16_t)e;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const uint32_t c = tid * 8 + j;
+          if (c < nc) st_off(a.t_row_ptr, (uint64_t)col0 + c, (int64_t)cell0 + s, a.lg);
+          s += (h[j >> 1] >> (16 * (j & 1))) & 0xffffu;
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        const uint32_t i = w * kWaveCells + q * kWave + lane;
+        const uint32_t c = min(key[q] >> a.size_bits, nc - 1u);
+        if (i < m) L.bp[dc[at[q]] + rank[q]] = ((c >> 6) << 16) | i;
+      }
+      __syncthreads();
+      dc[tid] = 0;
+      uint32_t from[kItems];
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) {
+        const uint32_t v = L.bp[min(w * kWaveCells + q * kWave + lane, m - 1u)];
+        from[q] = v & 0xffffu;
+        d[q] = v >> 16;
+        at[q] = d[q] * kNW + w;
+      }
+      __syncthreads();
+      wave_ranks(dc, at, d, mine, 6, rank);
+      __syncthreads();
+      {
+        uint32_t tot;
+        const uint32_t e = block_excl_scan<kNW>((uint32_t)dc[tid], L.red, tot);
+        dc[tid] = (uint16_t)e;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kItems; ++q)
+        if ((uint32_t)q * kWave + lane < mine) L.src[from[q]] = dc[at[q]] + rank[q];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) pos[q] = L.src[min(w * kWaveCells + q * kWave + lane, m - 1u)];
+      __syncthreads();
+    } else {
+      for (uint32_t e = tid; e < E / 2; e += kTh) ((uint32_t*)L.wc)[e] = 0;
+      __syncthreads();
       uint32_t at[kItems], d[kItems];
 #pragma unroll
       for (int q = 0; q < kItems; ++q) {
-        d[q] = min(key[q] >> 22, nc - 1u);
+        d[q] = column(key[q]);
         at[q] = d[q] * kNW + w;
       }
-      wave_ranks(L.wc, at, d, m > w * kWaveCells ? m - w * kWaveCells : 0u, dbits, rank);
-    }
-    __syncthreads();
-    {  // column-major scan of the counters (eight per column, one column per thread)
+      wave_ranks(L.wc, at, d, mine, dbits, pos);
+      __syncthreads();
+      // column-major scan of the counters (eight per column, one column per thread)
       static_assert(kTileCols == kTh, "one column per thread");
       v4 c = v4{0u, 0u, 0u, 0u};
-      if (tid < nc) c = *(const v4*)&L.wc[tid * kNW];
+      if (tid < ncs) c = *(const v4*)&L.wc[tid * kNW];
       uint32_t s = 0, tot;
 #pragma unroll
       for (int j = 0; j < 4; ++j) s += (c[j] & 0xffffu) + (c[j] >> 16);
       uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
-      if (tid < nc) {
+      if (tid < ncs) {
         if (!multi) st_off(a.t_row_ptr, (uint64_t)col0 + tid, (int64_t)cell0 + ex, a.lg);
         v4 o;
 #pragma unroll
@@ -845,20 +999,29 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         }
         *(v4*)&L.wc[tid * kNW] = o;
       }
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < kItems; ++q) pos[q] += L.wc[at[q]];
+      if constexpr (kWide) {  // cells of other pieces' columns have no place
+#pragma unroll
+        for (int q = 0; q < kItems; ++q)
+          if (d[q] == ncs) pos[q] = ~0u;
+        m = tot;
+      }
     }
-    __syncthreads();
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      const uint32_t i = w * kWaveCells + q * kWave + lane;
-      if (i >= m) continue;
-      const uint32_t d = min(key[q] >> 22, nc - 1u);
-      const uint32_t p = (uint32_t)L.wc[d * kNW + w] + rank[q];
+      if ((uint32_t)q * kWave + lane >= mine || (kWide && pos[q] == ~0u)) continue;
+      const uint32_t p = pos[q];
       L.row[p] = row[q];
       L.src[p] = x[q];
       L.bp[p] = rec_size(a, key[q], x[q]);
       if constexpr (kIdx) {
         uint64_t at = (uint64_t)cell0 + p;
-        if (multi) at = (uint64_t)cell0 + run_c[d] + (p - L.wc[d * kNW]);
+        if (multi) {
+          const uint32_t d = column(key[q]);
+          at = (uint64_t)cell0 + run_c[d] + (p - L.wc[d * kNW]);
+        }
         gm(a.perm)[at] = idx[q];
       }
     }
@@ -909,7 +1072,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         if (g0 + q >= kItems || p >= m) continue;
         uint64_t at = (uint64_t)cell0 + p, bt = byte0 + b[q];
         if (multi) {
-          uint32_t lo = 0, hi = nc;  // the cell's column: the last one starting at or before p
+          uint32_t lo = 0, hi = ncs;  // the cell's column: the last one starting at or before p
           while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
             if ((uint32_t)L.wc[mid * kNW] <= p) lo = mid;
@@ -947,15 +1110,15 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     }
     if (multi) {
       __syncthreads();
-      uint32_t dc = 0, db = 0;
-      if (tid < nc) {
-        const uint32_t i0 = L.wc[tid * kNW], i1 = tid + 1 < nc ? (uint32_t)L.wc[(tid + 1) * kNW] : m;
-        dc = i1 - i0;
-        db = L.bp[i1] - L.bp[i0];
-        run_c[tid] += dc;
-        run_b[tid] += db;
+      if (tid < ncs) {
+        const uint32_t i0 = L.wc[tid * kNW], i1 = tid + 1 < ncs ? (uint32_t)L.wc[(tid + 1) * kNW] : m;
+        run_c[tid] += i1 - i0;
+        run_b[tid] += L.bp[i1] - L.bp[i0];
       }
     }
+  }
+  cell0 += piece_cells;
+  byte0 += piece_bytes;
   }
 }
 
@@ -967,8 +1130,12 @@ template <bool kIdx>
 static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStream_t s) {
   const TileBatch none{};
   if (a.lut) hipLaunchKernelGGL(tl::k_tile_bounds, dim3(1), dim3(tl::kBoundTh), 0, s, a);
-  hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), dim3(tl::kTh),
-                     tl::sort_dyn_bytes(a.n_buckets), s, a, none);
+  if (a.vval)
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, true>), dim3(a.n_tiles), dim3(tl::kTh),
+                       tl::sort_dyn_bytes(a.n_buckets), s, a, none);
+  else
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), dim3(tl::kTh),
+                       tl::sort_dyn_bytes(a.n_buckets), s, a, none);
   if (a.n_parts > 0) {
     // about 4,096 cells (two rounds of loads) per workgroup: the kernel is one
     // chain of latencies, and its adds are one per workgroup and partition pair
@@ -976,7 +1143,16 @@ static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStrea
     hipLaunchKernelGGL((tl::k_tile_xfer<false>), dim3((unsigned)a.n_parts, (unsigned)per),
                        dim3(tl::kTh), 0, s, a, b, none);
   }
-  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
+  if (a.wide)
+    hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false, true>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
+  else
+    hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
+}
+
+hipError_t launch_tile_keys(const TileView& v, const TileBounds& b, hipStream_t s) {
+  const uint64_t nb = (v.nnz + kTileSub - 1) / kTileSub;
+  hipLaunchKernelGGL(tl::k_tile_keys, dim3((unsigned)nb), dim3(tl::kTh), 0, s, v, b);
+  return hipGetLastError();
 }
 
 hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s) {
