@@ -11,6 +11,7 @@
 
 #include "../../include/mgt.h"
 #include "kernels.h"
+#include "payload.h"
 #include "prims.h"
 
 // Workgroup geometry of this copy of the device code. The library holds two:
@@ -847,193 +848,51 @@ __device__ __forceinline__ uint32_t expand_rows(const void* rp, int ow, uint64_t
   return r0 + tot + *s_extra;
 }
 
-// Payload copies of a lane's kItems cells, split in two so the caller can
-// put other work (the record stores) between the loads and the stores. When
-// every cell is dword aligned on both sides and at most 32 bytes, the words
-// are loaded into registers up front (`fast`) as at most three pieces per
-// cell (16, 16 or 8 + 4 bytes; dword-aligned multi-dword accesses are legal
-// on gfx950), so a wave moves a cell in up to three instructions instead of
-// up to eight. When every cell is at most 16 bytes at any alignment
-// (`small`), the loads take the one or two 16-byte-aligned blocks that hold
-// its bytes (an aligned block lies within one page, so reading all of it is
-// safe), and the stores write exactly the cell's bytes: bytes up to the first
-// dword boundary of the destination, the dwords after it (the source bytes
-// shifted into place in registers), then the remaining bytes. Otherwise the
-// cells are copied one by one in the store phase (up to 32 bytes the same
-// way, in two halves).
+// Payload copies of a lane's cells, split in two so the caller can put other
+// work (the record stores) between the loads and the stores. A cell of up to
+// 32 bytes, at any alignment, is one or two unaligned 16-byte loads into
+// registers and at most six exact stores (payload.h); longer ones are copied in
+// the store phase. begin, end: the bytes that may be read.
 constexpr int kPay = 4;  // cells per lane whose payload words are held at once
+#define kNoEnd ((const uint8_t*)~(uintptr_t)0)  // every cell is followed by 32 readable bytes
 
-typedef uint32_t u32x4a __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));  // 16-byte aligned record
-typedef uint32_t u32x2a __attribute__((ext_vector_type(2), aligned(4)));
 // A 12-byte packed record (a three-element vector type would be padded to 16).
 struct alignas(4) Rec12 {
   uint32_t x, y, z;
 };
 static_assert(sizeof(Rec12) == 12, "12-byte record");
+typedef v4 v4u;  // 16-byte aligned record
 template <int N>
 struct PayRegsT {
-  u32x4a v[N][2];
-  bool fast, small;
+  v4 a[N], b[N];
 };
-
-// The 4 bytes at byte b (0..3) of the 8-byte value hi:lo.
-__device__ __forceinline__ uint32_t funnel_bytes(uint32_t hi, uint32_t lo, uint32_t b) {
-  return (uint32_t)((((uint64_t)hi << 32) | lo) >> (8u * b));
-}
-// a_q for q in 0..4, without indexing registers by a lane value: a
-// multiplexer on the bits of q, on values (a chain of equality tests, or
-// selects between elements of one array, end up as loads from scratch memory).
-__device__ __forceinline__ uint32_t mux5(uint32_t q, uint32_t a0, uint32_t a1, uint32_t a2,
-                                         uint32_t a3, uint32_t a4) {
-  const uint32_t a = (q & 1u) ? a1 : a0;
-  const uint32_t b = (q & 1u) ? a3 : a2;
-  const uint32_t c = (q & 2u) ? b : a;
-  return (q & 4u) ? a4 : c;
-}
-// The dwords 0..5 of the window w0..w8 (w9 = 0) shifted down by q (0..4)
-// dwords, then the five dwords starting b (0..3) bytes into that.
-struct Shifted5 {
-  uint32_t m0, m1, m2, m3, m4;
-};
-__device__ __forceinline__ Shifted5 shift_window(uint32_t q, uint32_t b, uint32_t w0, uint32_t w1,
-                                                 uint32_t w2, uint32_t w3, uint32_t w4, uint32_t w5,
-                                                 uint32_t w6, uint32_t w7, uint32_t w8) {
-  const uint32_t t0 = mux5(q, w0, w1, w2, w3, w4), t1 = mux5(q, w1, w2, w3, w4, w5);
-  const uint32_t t2 = mux5(q, w2, w3, w4, w5, w6), t3 = mux5(q, w3, w4, w5, w6, w7);
-  const uint32_t t4 = mux5(q, w4, w5, w6, w7, w8), t5 = mux5(q, w5, w6, w7, w8, 0u);
-  return Shifted5{funnel_bytes(t1, t0, b), funnel_bytes(t2, t1, b), funnel_bytes(t3, t2, b),
-                  funnel_bytes(t4, t3, b), funnel_bytes(t5, t4, b)};
-}
-
-// Stores the n <= 16 bytes that start at byte o (0..15) of the 32-byte window
-// v (the source's aligned blocks) to dst, touching no byte outside
-// [dst, dst + n).
-__device__ __forceinline__ void store_small(uint8_t* dst, const u32x4a (&v)[2], uint32_t o,
-                                            uint32_t n) {
-  const uint32_t w0 = v[0].x, w1 = v[0].y, w2 = v[0].z, w3 = v[0].w;
-  const uint32_t w4 = v[1].x, w5 = v[1].y, w6 = v[1].z, w7 = v[1].w;
-  GMEM uint8_t* const d = gm(dst);
-  const uint32_t hd = min((4u - ((uint32_t)(uintptr_t)dst & 3u)) & 3u, n);  // bytes before a dword boundary
-  const uint32_t qh = o >> 2;
-  const uint32_t hv = funnel_bytes(mux5(qh, w1, w2, w3, w4, w5), mux5(qh, w0, w1, w2, w3, w4), o & 3u);
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-    if ((uint32_t)j < hd) d[j] = (uint8_t)(hv >> (8 * j));
-  const uint32_t x = o + hd;  // the dwords after the head
-  const Shifted5 m = shift_window(x >> 2, x & 3u, w0, w1, w2, w3, w4, w5, w6, w7, 0u);
-  const uint32_t nm = (n - hd) >> 2, nt = (n - hd) & 3u;
-  GMEM uint32_t* const da = (GMEM uint32_t*)(d + hd);
-  if (nm == 4u) {
-    *(GMEM u32x4a*)da = u32x4a{m.m0, m.m1, m.m2, m.m3};
-  } else {
-    if (nm & 2u) *(GMEM u32x2a*)da = u32x2a{m.m0, m.m1};
-    if (nm & 1u) da[nm & 2u] = (nm & 2u) ? m.m2 : m.m0;
-  }
-  const uint32_t tv = mux5(nm, m.m0, m.m1, m.m2, m.m3, m.m4);
-  GMEM uint8_t* const dt = (GMEM uint8_t*)(da + nm);
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-    if ((uint32_t)j < nt) dt[j] = (uint8_t)(tv >> (8 * j));
-}
 using PayRegs = PayRegsT<kPay>;
 
-// Copies n <= 32 bytes of any alignment the same way, in two halves: the
-// 16-byte-aligned blocks that hold the cell (up to three) are loaded first.
-__device__ __forceinline__ void copy_medium(uint8_t* dst, const uint8_t* src, uint32_t n) {
-  const uint32_t o = (uint32_t)(uintptr_t)src & 15u;
-  const GMEM v4u* const b = (const GMEM v4u*)gm(src - o);  // 16-byte aligned
-  u32x4a v[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    v[k] = u32x4a{0u, 0u, 0u, 0u};
-    if (o + n > 16u * (uint32_t)k) {  // block k holds a byte of the cell
-      const v4u x = b[k];
-      v[k] = u32x4a{x.x, x.y, x.z, x.w};
-    }
-  }
-  const u32x4a lo[2] = {v[0], v[1]}, hi[2] = {v[1], v[2]};
-  store_small(dst, lo, o, n < 16u ? n : 16u);
-  if (n > 16u) store_small(dst + 16, hi, o, n - 16u);
-}
-
 template <int N>
-__device__ __forceinline__ void pay_load(PayRegsT<N>& P, uint8_t* const (&dst)[N],
-                                         const uint8_t* const (&src)[N],
-                                         const uint32_t (&sz)[N]) {
-  bool fast = true, small = true;
+__device__ __forceinline__ void pay_load(PayRegsT<N>& P, const uint8_t* const (&src)[N],
+                                         const uint32_t (&sz)[N], const uint8_t* begin,
+                                         const uint8_t* end) {
 #pragma unroll
-  for (int r = 0; r < N; ++r) {
-    fast &= sz[r] == 0u ||
-            (sz[r] <= 32u && ((sz[r] | (uint32_t)(uintptr_t)src[r] | (uint32_t)(uintptr_t)dst[r]) & 3u) == 0);
-    small &= sz[r] <= 16u;
-  }
-  P.fast = fast;
-  P.small = !fast && small;
-  if (P.small) {
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-      const uint32_t z = sz[r];
-      const uint32_t o = (uint32_t)(uintptr_t)src[r] & 15u;
-      const GMEM v4u* const b = (const GMEM v4u*)gm(src[r] - o);  // 16-byte aligned
-      P.v[r][0] = u32x4a{0u, 0u, 0u, 0u};
-      P.v[r][1] = u32x4a{0u, 0u, 0u, 0u};
-      if (z) {
-        const v4u x = b[0];
-        P.v[r][0] = u32x4a{x.x, x.y, x.z, x.w};
-      }
-      if (o + z > 16u) {
-        const v4u y = b[1];
-        P.v[r][1] = u32x4a{y.x, y.y, y.z, y.w};
-      }
-    }
-  }
-  if (fast) {
-#pragma unroll
-    for (int r = 0; r < N; ++r) {
-      const GMEM uint8_t* s = gm(src[r]);
-      const uint32_t z = sz[r];
-      if (z >= 16u) P.v[r][0] = *(const GMEM u32x4a*)s;
-      const uint32_t o1 = z >= 16u ? 16u : 0u, rem = z - o1;
-      if (rem >= 16u) {
-        P.v[r][1] = *(const GMEM u32x4a*)(s + 16);
-      } else {
-        if (rem >= 8u) P.v[r][1].xy = *(const GMEM u32x2a*)(s + o1);
-        if (rem & 4u) P.v[r][1].z = *(const GMEM uint32_t*)(s + o1 + (rem & 8u));
-      }
-    }
-  }
+  for (int r = 0; r < N; ++r)
+    if (sz[r] - 1u < 32u) get_bytes(src[r], begin, end, sz[r], P.a[r], P.b[r]);
 }
 
 template <int N>
 __device__ __forceinline__ void pay_store(const PayRegsT<N>& P, uint8_t* const (&dst)[N],
                                           const uint8_t* const (&src)[N],
                                           const uint32_t (&sz)[N]) {
-  if (P.fast) {
+  bool dwords = true;
 #pragma unroll
-    for (int r = 0; r < N; ++r) {
-      GMEM uint8_t* d = gm(dst[r]);
-      const uint32_t z = sz[r];
-      if (z >= 16u) *(GMEM u32x4a*)d = P.v[r][0];
-      const uint32_t o1 = z >= 16u ? 16u : 0u, rem = z - o1;
-      if (rem >= 16u) {
-        *(GMEM u32x4a*)(d + 16) = P.v[r][1];
-      } else {
-        if (rem >= 8u) *(GMEM u32x2a*)(d + o1) = P.v[r][1].xy;
-        if (rem & 4u) *(GMEM uint32_t*)(d + o1 + (rem & 8u)) = P.v[r][1].z;
-      }
-    }
-  } else if (P.small) {
+  for (int r = 0; r < N; ++r) dwords &= sz[r] <= 32u && (sz[r] & 3u) == 0u;
+  if (__all(dwords)) {
 #pragma unroll
-    for (int r = 0; r < N; ++r)
-      if (sz[r]) store_small(dst[r], P.v[r], (uint32_t)(uintptr_t)src[r] & 15u, sz[r]);
-  } else {
+    for (int r = 0; r < N; ++r) put_global<true>(dst[r], P.a[r], P.b[r], sz[r]);
+    return;
+  }
 #pragma unroll
-    for (int r = 0; r < N; ++r) {
-      if (sz[r] == 0u) continue;
-      if (sz[r] <= 32u) copy_medium(dst[r], src[r], sz[r]);
-      else copy_cell(dst[r], src[r], sz[r]);
-    }
+  for (int r = 0; r < N; ++r) {
+    if (sz[r] <= 32u) put_global(dst[r], P.a[r], P.b[r], sz[r]);
+    else copy_long(dst[r], src[r], sz[r]);
   }
 }
 // ----------------------------------------------------------------------------- pass: scatter
@@ -1435,6 +1294,8 @@ __device__ __forceinline__ void scatter_body(const PassArgs& a, Lds& L, uint32_t
     }
 
     const uint8_t* src_base = pass0 ? i_pay + sub_base : a.pay_in + sub_base;
+    // (level buffers are followed by more of the workspace)
+    const uint8_t* const pay_end = pass0 ? i_pay + i_pbytes : kNoEnd;
     bool xfer_per_cell = false;
     uint32_t src_part = 0;
     if (track_xfer) {
@@ -1516,7 +1377,7 @@ __device__ __forceinline__ void scatter_body(const PassArgs& a, Lds& L, uint32_t
         }
       }
       PayRegsT<kPayN> P;
-      pay_load(P, pd, ps, pz);
+      pay_load(P, ps, pz, i_pay, pay_end);
 #pragma unroll
       for (int q = 0; q < kPayN; ++q) {
         const uint32_t i = (g + q) * kBlock + tid;
@@ -1944,7 +1805,7 @@ __device__ __forceinline__ void finish_body(const FinishArgs& a, SortLds& L, uin
         }
       }
       PayRegs P;
-      pay_load(P, pd, ps, pz);
+      pay_load(P, ps, pz, nullptr, kNoEnd);  // (more of the workspace follows)
 #pragma unroll
       for (int q = 0; q < kPay; ++q) {
         const uint32_t i = (g + q) * kBlock + threadIdx.x;
@@ -2267,8 +2128,7 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
       int32_t* const o_col = it->t_col;
       void* const o_poff = it->t_poff;
       const uint8_t* const src_base = a.pay_in + blo;
-      // (kept rolled: with its three copy paths the body is too large to
-      // unroll five times)
+      // (kept rolled: unrolled five times the body outgrows the instruction cache)
 #pragma unroll 1
       for (int g = 0; g < kBkItems; g += kBkPay) {
         uint8_t* pd[kBkPay];
@@ -2290,54 +2150,15 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
             ps[q] = src_base + L.src[p];
           }
         }
-        // Payloads of dword sizes up to 32 bytes at dword addresses (every cell
-        // of the large workloads) take the staged path: each lane loads its
-        // cell in whole 16-byte pieces (reading up to 12 bytes past it, inside
-        // the level buffer's padding), the wave packs its 64 cells' bytes in
-        // LDS in output order, and writes them back as 16 contiguous bytes
-        // per lane. Payloads of up to 16 bytes at any alignment (`ustaged`)
-        // pass through LDS too: each lane loads the 16-byte-aligned blocks
-        // that hold its cell, shifts its bytes to their place in the wave's
-        // run and ORs them into the zeroed stage, and the run is written back
-        // 16 bytes per lane, with dword and byte stores at its two ends.
-        // Other payloads are copied lane by lane.
+        // Payloads of up to 32 bytes are loaded in whole 16-byte pieces (what
+        // lies past a cell belongs to the workspace), the wave packs its 64
+        // cells' bytes in LDS in output order, and writes them back as 16
+        // contiguous bytes per lane. Longer ones are copied lane by lane.
         PayRegsT<kBkPay> P;
-        bool staged = true, small = true;
+        bool shorts = true;
 #pragma unroll
-        for (int q = 0; q < kBkPay; ++q) {
-          staged &= pz[q] == 0u ||
-                    (pz[q] <= 32u &&
-                     ((pz[q] | (uint32_t)(uintptr_t)ps[q] | (uint32_t)(uintptr_t)pd[q]) & 3u) == 0);
-          small &= pz[q] <= 16u;
-        }
-        staged = __all(staged);
-        const bool ustaged = !staged && __all(small);
-        if (staged) {
-#pragma unroll
-          for (int q = 0; q < kBkPay; ++q) {
-            const GMEM uint8_t* sp = gm(ps[q]);
-            if (pz[q]) P.v[q][0] = *(const GMEM u32x4a*)sp;
-            if (pz[q] > 16u) P.v[q][1] = *(const GMEM u32x4a*)(sp + 16);
-          }
-        } else if (ustaged) {
-#pragma unroll
-          for (int q = 0; q < kBkPay; ++q) {
-            const uint32_t o = (uint32_t)(uintptr_t)ps[q] & 15u;
-            const GMEM v4u* const bk = (const GMEM v4u*)gm(ps[q] - o);  // 16-byte aligned
-            P.v[q][0] = u32x4a{0u, 0u, 0u, 0u};
-            P.v[q][1] = u32x4a{0u, 0u, 0u, 0u};
-            if (pz[q]) {
-              const v4u x = bk[0];
-              P.v[q][0] = u32x4a{x.x, x.y, x.z, x.w};
-            }
-            if (o + pz[q] > 16u) {
-              const v4u y = bk[1];
-              P.v[q][1] = u32x4a{y.x, y.y, y.z, y.w};
-            }
-          }
-        } else {
-          pay_load(P, pd, ps, pz);
-        }
+        for (int q = 0; q < kBkPay; ++q) shorts &= pz[q] <= 32u;
+        pay_load(P, ps, pz, nullptr, kNoEnd);
 #pragma unroll
         for (int q = 0; q < kBkPay; ++q) {
           const uint32_t p = (uint32_t)(g + q) * kBkBlock + tid;
@@ -2346,10 +2167,10 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
             if (o_poff) st_off(o_poff, out_cell0 + p, (int64_t)(out_byte0 + pb[q]), ow);
           }
         }
-        if (staged) {
+        if (__all(shorts)) {
           // the counters' LDS is free once the column scan is done: 2 KB per
           // wave holds 64 payloads of up to 32 bytes
-          uint32_t* const stage = (uint32_t*)L.wc + w * (kWave * 8);
+          uint8_t* const stage = (uint8_t*)L.wc + w * 2048u;
 #pragma unroll
           for (int q = 0; q < kBkPay; ++q) {
             const uint32_t p = (uint32_t)(g + q) * kBkBlock + tid;
@@ -2360,82 +2181,7 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
             const uint32_t rel = pb[q] - b0;
             const uint32_t tot =
                 (uint32_t)__builtin_amdgcn_readlane((int)(rel + pz[q]), (int)last);
-            const uint32_t nw = pz[q] >> 2;
-            const uint32_t v[8] = {P.v[q][0].x, P.v[q][0].y, P.v[q][0].z, P.v[q][0].w,
-                                   P.v[q][1].x, P.v[q][1].y, P.v[q][1].z, P.v[q][1].w};
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-              if ((uint32_t)j < nw) stage[(rel >> 2) + j] = v[j];
-            GMEM uint8_t* const dst = gm(o_pay + out_byte0 + b0);
-            for (uint32_t o = lane * 16u; o < tot; o += kWave * 16u) {
-              const uint32_t* sw = stage + (o >> 2);
-              if (o + 16u <= tot) {
-                *(GMEM u32x4a*)(dst + o) = u32x4a{sw[0], sw[1], sw[2], sw[3]};
-              } else {
-                for (uint32_t j = 0; j < ((tot - o) >> 2); ++j) ((GMEM uint32_t*)(dst + o))[j] = sw[j];
-              }
-            }
-          }
-        } else if (ustaged) {
-          // stage dword 0 holds the dword-aligned address below the run's
-          // first byte; a run of 64 cells of up to 16 bytes spans at most 257
-          // of the wave's 512 stage dwords
-          uint32_t* const stage = (uint32_t*)L.wc + w * (kWave * 8);
-#pragma unroll
-          for (int q = 0; q < kBkPay; ++q) {
-            const uint32_t p = (uint32_t)(g + q) * kBkBlock + tid;
-            const uint64_t act = ballot(p < len);  // a prefix of the wave's lanes
-            if (act == 0) continue;                // wave-uniform
-            const uint32_t last = 63u - (uint32_t)__clzll(act);
-            const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)pb[q]);
-            const uint32_t rel = pb[q] - b0;
-            const uint32_t tot =
-                (uint32_t)__builtin_amdgcn_readlane((int)(rel + pz[q]), (int)last);
-            uint8_t* const run = o_pay + out_byte0 + b0;
-            const uint32_t sh = (uint32_t)(uintptr_t)run & 3u;
-            const uint32_t end = sh + tot;  // stage bytes [sh, end) are the run's
-            for (uint32_t e = lane; e < ((end + 3u) >> 2); e += kWave) stage[e] = 0u;
-            const uint32_t z = pz[q];
-            if (z) {
-              const uint32_t sb = sh + rel, r = sb & 3u, d0 = sb >> 2;
-              // the window with a zero dword in front, so the shift is >= 0
-              const uint32_t x = ((uint32_t)(uintptr_t)ps[q] & 15u) + 4u - r;  // 1..19
-              const Shifted5 m = shift_window(x >> 2, x & 3u, 0u, P.v[q][0].x, P.v[q][0].y,
-                                              P.v[q][0].z, P.v[q][0].w, P.v[q][1].x, P.v[q][1].y,
-                                              P.v[q][1].z, P.v[q][1].w);
-              const uint32_t mv[5] = {m.m0, m.m1, m.m2, m.m3, m.m4};
-              const uint32_t nd = (r + z + 3u) >> 2;
-#pragma unroll
-              for (int k = 0; k < 5; ++k) {
-                if ((uint32_t)k < nd) {
-                  const int lo = min(max((int)r - 4 * k, 0), 4);
-                  const int hi = min(max((int)(r + z) - 4 * k, 0), 4);
-                  const uint32_t mk = (hi >= 4 ? ~0u : (1u << (8 * hi)) - 1u) & ~((1u << (8 * lo)) - 1u);
-                  __hip_atomic_fetch_or(&stage[d0 + k], mv[k] & mk, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-              }
-            }
-            GMEM uint8_t* const base = gm(run - sh);  // dword aligned
-            for (uint32_t o = lane * 16u; o < end; o += kWave * 16u) {
-              const uint32_t* sw = stage + (o >> 2);
-              if (o >= sh && o + 16u <= end) {
-                *(GMEM u32x4a*)(base + o) = u32x4a{sw[0], sw[1], sw[2], sw[3]};
-              } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                  const uint32_t a0 = o + 4u * (uint32_t)j;
-                  if (a0 >= sh && a0 + 4u <= end) {
-                    *(GMEM uint32_t*)(base + a0) = sw[j];
-                  } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                      if (a0 + (uint32_t)i >= sh && a0 + (uint32_t)i < end)
-                        base[a0 + (uint32_t)i] = (uint8_t)(sw[j] >> (8 * i));
-                  }
-                }
-              }
-            }
+            write_run(stage, o_pay + out_byte0 + b0, rel, tot, P.a[q], P.b[q], pz[q]);
           }
         } else {
           pay_store(P, pd, ps, pz);
@@ -2544,7 +2290,7 @@ __device__ __forceinline__ void direct_place(const DirectArgs& a, DirectLds& L, 
   __builtin_amdgcn_wave_barrier();
   pd[0] = a.t_payload + bpos;
   PayRegsT<1> P;
-  pay_load(P, pd, ps, pz);
+  pay_load(P, ps, pz, a.payload, a.payload + a.payload_bytes);
   if (act) {
     gm(a.t_col)[pos] = (int32_t)lo;
     if (a.perm) gm(a.perm)[pos] = k;

@@ -187,69 +187,4 @@ __device__ __forceinline__ GMEM T* gm(T* p) { return (GMEM T*)p; }
 template <typename T>
 __device__ __forceinline__ const GMEM T* gm(const T* p) { return (const GMEM T*)p; }
 
-// Copies one cell's payload (any width, any alignment). Every chunk issues
-// all of its loads before its stores, so a lane waits for memory once per
-// chunk instead of once per word. Source and destination sharing their
-// alignment modulo 4 move as 4-byte words (up to 8 per chunk); otherwise as
-// bytes (up to 16 per chunk).
-__device__ __forceinline__ void copy_cell(uint8_t* __restrict__ dst_, const uint8_t* __restrict__ src_,
-                                          uint32_t n) {
-  GMEM uint8_t* dst = gm(dst_);
-  const GMEM uint8_t* src = gm(src_);
-  if ((((uintptr_t)dst_ ^ (uintptr_t)src_) & 3u) == 0) {
-    uint32_t h = (4u - ((uintptr_t)dst_ & 3u)) & 3u;
-    h = h < n ? h : n;
-    uint8_t hb[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      if ((uint32_t)j < h) hb[j] = src[j];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      if ((uint32_t)j < h) dst[j] = hb[j];
-    dst += h;
-    src += h;
-    n -= h;
-    const GMEM uint32_t* s4 = (const GMEM uint32_t*)src;
-    GMEM uint32_t* d4 = (GMEM uint32_t*)dst;
-    uint32_t w = n >> 2;
-    while (w) {
-      const uint32_t m = w < 8u ? w : 8u;
-      uint32_t v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if ((uint32_t)j < m) v[j] = s4[j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-        if ((uint32_t)j < m) d4[j] = v[j];
-      s4 += m;
-      d4 += m;
-      w -= m;
-    }
-    const uint32_t t = n & 3u;
-    const GMEM uint8_t* sb = (const GMEM uint8_t*)s4;
-    GMEM uint8_t* db = (GMEM uint8_t*)d4;
-    uint8_t tb[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      if ((uint32_t)j < t) tb[j] = sb[j];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      if ((uint32_t)j < t) db[j] = tb[j];
-  } else {
-    while (n) {
-      const uint32_t m = n < 16u ? n : 16u;
-      uint8_t v[16];
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if ((uint32_t)j < m) v[j] = src[j];
-#pragma unroll
-      for (int j = 0; j < 16; ++j)
-        if ((uint32_t)j < m) dst[j] = v[j];
-      src += m;
-      dst += m;
-      n -= m;
-    }
-  }
-}
-
 }  // namespace mgt

@@ -162,10 +162,10 @@ __global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a, uint32_t cell_blocks
   const uint64_t top = a.nnz;  // (> 0: S has a cell)
 #pragma unroll 1
   for (int g = 0; g < kFillPer; g += kPay) {
-    uint64_t ob[kPay], so[kPay];
+    uint64_t ob[kPay];
     uint32_t z[kPay];
     int32_t col[kPay];
-    const uint8_t* src[kPay];
+    const uint8_t *src[kPay], *from[kPay];
     v4 va[kPay], vb[kPay];
     bool ok = true;
 #pragma unroll
@@ -200,15 +200,15 @@ __global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a, uint32_t cell_blocks
       // (only offsets that decrease, in unvalidated inputs, can pass the end)
       if (ob[e] > a.cap_bytes || z[e] > a.cap_bytes - ob[e]) z[e] = 0;
       col[e] = gm(mir ? a.t_col : a.col)[k];
-      so[e] = o;
-      src[e] = (mir ? a.t_payload : a.payload) + o;
+      from[e] = mir ? a.t_payload : a.payload;
+      src[e] = from[e] + o;
       ok &= z[e] <= 32u;
     }
 #pragma unroll
     for (int e = 0; e < kPay; ++e) {
       va[e] = v4{0u, 0u, 0u, 0u};
       vb[e] = v4{0u, 0u, 0u, 0u};
-      if (z[e] && z[e] <= 32u) get_bytes(src[e], so[e] + 32u <= a.pbytes, z[e], va[e], vb[e]);
+      if (z[e] && z[e] <= 32u) get_bytes(src[e], from[e], from[e] + a.pbytes, z[e], va[e], vb[e]);
     }
 #pragma unroll
     for (int e = 0; e < kPay; ++e) {

@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         vb[q] = v4{0u, 0u, 0u, 0u};
         shorts &= z[q] <= 32u;
         if (z[q] > kInline && z[q] <= 32u)
-          get_bytes(a.payload + o[q], (uint64_t)o[q] + 32u <= a.payload_bytes, z[q], va[q], vb[q]);
+          get_bytes(a.payload + o[q], a.payload, a.payload + a.payload_bytes, z[q], va[q], vb[q]);
       }
 #pragma unroll
       for (int q = 0; q < kPay; ++q) {
