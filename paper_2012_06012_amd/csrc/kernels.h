@@ -203,8 +203,7 @@ constexpr uint32_t kTileMax = 16384;     // cells of a tile
 constexpr uint32_t kTileSub = 4096;      // cells of a tile ranked at once
 constexpr uint32_t kTileTiles = 512;     // tiles of a call
 constexpr uint32_t kTileBuckets = 2048;  // buckets of a call
-constexpr uint32_t kTileCols = 512;      // columns of a bucket ...
-constexpr uint32_t kTileWide = 4096;     // ... or of a wide one (many columns, few cells each)
+constexpr uint32_t kTileCols = 512;      // columns of a bucket
 constexpr uint32_t kTileCap = 4608;      // cells of a bucket held at once
 constexpr uint32_t kTileBins = 4096;     // column runs of a table of uneven buckets
 struct TileArgs {
@@ -242,8 +241,6 @@ struct TileArgs {
   int32_t fixed_w;            // bytes of every cell, or -1
   int32_t n_parts;            // 0: plain call; <= kDirectParts
   int32_t validate;
-  int32_t wide;               // cpb > kTileCols (calls of their own only)
-  uint32_t size_bits;         // of a record's size field: 22, or 20 beside a wide bucket's column
 };
 struct TileBounds {
   int32_t bounds[kDirectParts + 1];

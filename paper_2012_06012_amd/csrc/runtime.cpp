@@ -438,7 +438,6 @@ struct TileGeo {
   bool ok = false;
   uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
   bool uneven = false;  // bucket bounds from sampled columns (k_tile_bounds)
-  bool wide = false;    // buckets of more than kTileCols columns
   uint32_t lut_shift = 0, target = 0;
   uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_lut = 0, o_bcol = 0, bytes = 0;
 };
@@ -464,17 +463,11 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   else if (g > kTileSlots) g = align_up(g, kTileSlots);
   else g = std::max<uint64_t>(g, std::min<uint64_t>(kTileSlots, (nnz + 255) / 256));
   g = std::min<uint64_t>(g, cols);
-  if (g > kTileBuckets && !batch_cells && nnz <= kTileBuckets * cap * 4 / 5) {
-    // too many columns for buckets of kTileCols: wide ones, as many as the cells ask for
-    g = std::max<uint64_t>((5 * nnz + 4 * cap - 1) / (4 * cap), (cols + kTileWide - 1) / kTileWide);
-    if (g > kTileSlots) g = std::min<uint64_t>(align_up(g, kTileSlots), kTileBuckets);
-    t.wide = true;
-  }
   if (g > kTileBuckets) return t;
   t.cpb = (uint32_t)((cols + g - 1) / g);
   t.n_buckets = (uint32_t)((cols + t.cpb - 1) / t.cpb);
-  if (t.cpb > (t.wide ? kTileWide : kTileCols) || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
-  if (crowded && !t.wide && nnz >= 64 * 1024) {
+  if (t.cpb > kTileCols || nnz > (uint64_t)t.n_buckets * cap * 9 / 10) return t;
+  if (crowded && nnz >= 64 * 1024) {
     // runs of up to 2^lut_shift columns; buckets aim for 3/5 of what a
     // workgroup holds, the samples' spread on top
     t.lut_shift = (uint32_t)std::max(0, ceil_log2_u64(cols) - ceil_log2_u64(kTileBins));
@@ -1063,8 +1056,6 @@ TileArgs tile_args(const HostItem& it, const TileGeo& t, bool partitioned, uint3
   a.lg = d.offset_width == 8 ? 3 : 2;
   a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
   a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
-  a.wide = t.wide ? 1 : 0;
-  a.size_bits = t.wide ? 20 : 22;
   a.vval = v.vval;
   if (partitioned) a.n_parts = d.n_parts;
   return a;

@@ -25,7 +25,7 @@
 // travel with the launches.
 //
 // Record of a cell (3 words, a 4th for perm): payload offset (or the payload
-// itself, up to 4 bytes), row, column within the bucket << size_bits | size,
+// itself, up to 4 bytes), row, column within the bucket << 22 | size,
 // input index. A size the field cannot hold is looked up again in the offsets.
 // (Payloads of up to 8 bytes in a word more were no faster: 4.3 M cells of 8
 // bytes 143 us, against 146 us for 9 bytes read from the input.)
@@ -46,7 +46,9 @@ constexpr int kNW = kTh / kWave;
 constexpr int kSortItems = kTileSub / kTh;  // cells per lane and piece of k_tile_sort
 constexpr int kSortWave = kSortItems * kWave;
 constexpr uint32_t kInline = 4;             // payload bytes a record holds itself
-static_assert(kTileCols <= 1 << 10 && kTileWide <= 1 << 12, "column field of a record");
+constexpr uint32_t kSizeBits = 22;          // of a record's size field; all ones: look it up
+constexpr uint32_t kSizeMask = (1u << kSizeBits) - 1u;
+static_assert(kTileCols <= 1 << 10, "column field of a record");
 
 __device__ __forceinline__ int64_t ld_off(const void* p, uint64_t i, int lg) {
   return lg == 2 ? (int64_t)gm((const int32_t*)p)[i] : gm((const int64_t*)p)[i];
@@ -349,7 +351,6 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     }
   }
   const int dbits = ceil_log2(G);
-  const uint32_t size_mask = (1u << a.size_bits) - 1u;
   uint32_t* const rec = a.recs + k0 * kWords;
   for (uint32_t c0 = 0; c0 < n; c0 += kTileSub) {
     const uint32_t m = min(kTileSub, n - c0);
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
         const uint32_t z = nx - off[r];
         dig[r] = bucket(col[r], first);
         at[r] = dig[r] * kNW + w;
-        key[r] = ((min(col[r], (uint32_t)a.n_cols - 1u) - first) << a.size_bits) | min(z, size_mask);
+        key[r] = ((min(col[r], (uint32_t)a.n_cols - 1u) - first) << kSizeBits) | min(z, kSizeMask);
         if (w * kSortWave + r * kWave + lane < m && z) atomicAdd(&byt[dig[r]], z);
       }
     }
@@ -416,7 +417,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     for (int r = 0; r < kSortItems; ++r) {
       const uint32_t i = w * kSortWave + r * kWave + lane;
       if (i >= m) continue;
-      const uint32_t z = key[r] & size_mask;
+      const uint32_t z = key[r] & kSizeMask;
       uint32_t x = off[r];
       // a small payload goes in place of its offset: the aligned words that hold
       // it (each holds one of its bytes; nothing is read past the payload array)
@@ -638,9 +639,7 @@ struct MergeLds {
     };
     alignas(16) uint8_t stage[kNW][kStage];  // after the records are read, single-chunk buckets only
   };
-  // (column, wave) counts, then first positions, and one for the cells outside
-  // a piece of a wide bucket
-  alignas(16) uint16_t wc[(kTileCols + 1) * kNW];
+  alignas(16) uint16_t wc[kTileCols * kNW];  // (column, wave) counts, then first positions
   uint32_t red[kNW];
   uint64_t red64[2 * kNW];
 };
@@ -648,9 +647,8 @@ struct MergeLds {
 // Size of a record's cell: from the offsets where the field cannot hold it
 // (its payload is not inline, so x is its offset: the last cell starting there).
 __device__ __forceinline__ uint32_t rec_size(const TileArgs& a, uint32_t key, uint32_t x) {
-  const uint32_t mask = (1u << a.size_bits) - 1u;
-  uint32_t z = key & mask;
-  if (z == mask) {
+  uint32_t z = key & kSizeMask;
+  if (z == kSizeMask) {
     if (a.fixed_w >= 0) return (uint32_t)a.fixed_w;
     uint64_t lo = 0, hi = a.nnz;
     while (hi - lo > 1) {
@@ -725,10 +723,7 @@ __device__ __forceinline__ void cell_tiles(const uint32_t* ex, uint32_t T, uint3
 // tiles' records in its L2.
 // A bucket of more than kCap cells (skewed columns) is taken in chunks: column
 // totals first, then every chunk's cells to their column's running place.
-// kWide: buckets of up to kTileWide columns, whose cells are ranked by the low
-// six column bits, then by the high ones (two small sets of counters instead of
-// one per column and wave); a chunked one is taken kTileCols columns at a time.
-template <bool kIdx, bool kBatch, bool kWide = false>
+template <bool kIdx, bool kBatch>
 __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch bt) {
   constexpr int kItems = kMergeItems;
   constexpr uint32_t kCap = kTileCap, kWaveCells = kMergeWave;
@@ -795,8 +790,8 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     }
     uint64_t tot;
     block_excl_scan2<kNW>(s, sb, L.red64, tot, byte0);
-    n = (uint32_t)tot;
-    cell0 = (uint32_t)(tot >> 32);
+    n = (uint32_t)__builtin_amdgcn_readfirstlane((int)tot);
+    cell0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tot >> 32));
     uint32_t e = (uint32_t)s;
     if (sub) e -= len[0];  // (the threads of one tile: the first one's run is in their prefix)
 #pragma unroll
@@ -836,20 +831,9 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
   const uint32_t chunk = multi ? kCap - kTileCols : kCap;
   uint32_t* const run_c = L.src + chunk;
   uint32_t* const run_b = L.bp + chunk + 1;
-  const bool two_step = kWide && !multi && nc > kTileCols;  // block-uniform
-  const uint32_t piece = kWide && multi ? kTileCols : nc;
-  for (uint32_t sub0 = 0; sub0 < nc; sub0 += piece) {
-  const uint32_t ncs = min(piece, nc - sub0);  // this piece's columns; ncs: any other (kWide)
-  auto column = [&](uint32_t key) {
-    const uint32_t d = key >> a.size_bits;
-    return kWide ? min(d - sub0, ncs) : min(d, nc - 1u);
-  };
-  const uint32_t E = (ncs + (kWide ? 1u : 0u)) * kNW;
-  const int dbits = ceil_log2(ncs + (kWide ? 1u : 0u));
-  uint32_t piece_cells = 0, piece_bytes = 0;
+  auto column = [&](uint32_t key) { return min(key >> kSizeBits, nc - 1u); };
   if (multi) {
-    __syncthreads();  // (the previous piece has been written)
-    for (uint32_t c = threadIdx.x; c < ncs; c += kTh) {
+    for (uint32_t c = threadIdx.x; c < nc; c += kTh) {
       run_c[c] = 0;
       run_b[c] = 0;
     }
@@ -860,28 +844,27 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         const uint32_t t = L.row[i] - 1u;
         const GMEM uint32_t* const r = record<kWords>(a, t * a.tile_cells + L.st[t] + (q0 + i - L.ex[t]));
         const uint32_t key = r[2], d = column(key);
-        if (kWide && d == ncs) continue;
         atomicAdd(&run_c[d], 1u);
         atomicAdd(&run_b[d], rec_size(a, key, r[0]));
       }
       __syncthreads();
     }
-    uint32_t v = 0, u = 0;  // ncs <= kTileCols == kTh
-    if (threadIdx.x < ncs) {
+    uint32_t v = 0, u = 0, vt, ut;  // nc <= kTileCols == kTh
+    if (threadIdx.x < nc) {
       v = run_c[threadIdx.x];
       u = run_b[threadIdx.x];
     }
-    block_excl_scan2<kNW>(v, u, L.red64, piece_cells, piece_bytes);
-    if (threadIdx.x < ncs) {
+    block_excl_scan2<kNW>(v, u, L.red64, vt, ut);
+    if (threadIdx.x < nc) {
       run_c[threadIdx.x] = v;
       run_b[threadIdx.x] = u;
-      st_off(a.t_row_ptr, (uint64_t)col0 + sub0 + threadIdx.x, (int64_t)cell0 + v, a.lg);
+      st_off(a.t_row_ptr, (uint64_t)col0 + threadIdx.x, (int64_t)cell0 + v, a.lg);
     }
   }
   for (uint32_t q0 = 0; q0 < n; q0 += chunk) {
     const uint32_t tid = opaque(threadIdx.x);
     const uint32_t w = tid / kWave, lane = tid % kWave;
-    uint32_t m = min(chunk, n - q0);
+    const uint32_t m = min(chunk, n - q0);
     __syncthreads();  // the previous chunk's positions have been read
     if (lng) cell_tiles<kItems>(L.ex, T, n, q0, m, L.row, L.red);
     uint32_t x[kItems], row[kItems], key[kItems], idx[kIdx ? kItems : 1];
@@ -901,117 +884,42 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     }
     uint32_t pos[kItems];  // every cell's place in output order (bucket relative)
     const uint32_t mine = m > w * kWaveCells ? m - w * kWaveCells : 0u;  // the wave's cells
-    if (two_step) {
-      // stable by the low six bits, then by the high ones; the columns' own
-      // counts give the row offsets
-      uint32_t* const hist = (uint32_t*)L.wc;         // two 16-bit counts per word
-      uint16_t* const dc = (uint16_t*)&L.stage[0][0];  // (digit, wave) counters
-      static_assert(64 * kNW == kTh, "one digit counter per thread");
-      for (uint32_t e = tid; e < kTileWide / 2; e += kTh) hist[e] = 0;
-      __syncthreads();  // (and every record has been read)
-      dc[tid] = 0;
-      __syncthreads();
-      uint32_t at[kItems], d[kItems], rank[kItems];
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) {
-        const uint32_t c = min(key[q] >> a.size_bits, nc - 1u);
-        d[q] = c & 63u;
-        at[q] = d[q] * kNW + w;
-        if ((uint32_t)q * kWave + lane < mine) atomicAdd(&hist[c >> 1], 1u << (16u * (c & 1u)));
-      }
-      wave_ranks(dc, at, d, mine, 6, rank);
-      __syncthreads();
-      {
-        v4 h = *(const v4*)&hist[tid * 4];  // eight columns
-        uint32_t s = 0, e = dc[tid], ts, te;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s += (h[j] & 0xffffu) + (h[j] >> 16);
-        block_excl_scan2<kNW>(s, e, L.red64, ts, te);
-        dc[tid] = (uint16_t)e;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const uint32_t c = tid * 8 + j;
-          if (c < nc) st_off(a.t_row_ptr, (uint64_t)col0 + c, (int64_t)cell0 + s, a.lg);
-          s += (h[j >> 1] >> (16 * (j & 1))) & 0xffffu;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) {
-        const uint32_t i = w * kWaveCells + q * kWave + lane;
-        const uint32_t c = min(key[q] >> a.size_bits, nc - 1u);
-        if (i < m) L.bp[dc[at[q]] + rank[q]] = ((c >> 6) << 16) | i;
-      }
-      __syncthreads();
-      dc[tid] = 0;
-      uint32_t from[kItems];
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) {
-        const uint32_t v = L.bp[min(w * kWaveCells + q * kWave + lane, m - 1u)];
-        from[q] = v & 0xffffu;
-        d[q] = v >> 16;
-        at[q] = d[q] * kNW + w;
-      }
-      __syncthreads();
-      wave_ranks(dc, at, d, mine, 6, rank);
-      __syncthreads();
-      {
-        uint32_t tot;
-        const uint32_t e = block_excl_scan<kNW>((uint32_t)dc[tid], L.red, tot);
-        dc[tid] = (uint16_t)e;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kItems; ++q)
-        if ((uint32_t)q * kWave + lane < mine) L.src[from[q]] = dc[at[q]] + rank[q];
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) pos[q] = L.src[min(w * kWaveCells + q * kWave + lane, m - 1u)];
-      __syncthreads();
-    } else {
-      for (uint32_t e = tid; e < E / 2; e += kTh) ((uint32_t*)L.wc)[e] = 0;
-      __syncthreads();
-      uint32_t at[kItems], d[kItems];
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) {
-        d[q] = column(key[q]);
-        at[q] = d[q] * kNW + w;
-      }
-      wave_ranks(L.wc, at, d, mine, dbits, pos);
-      __syncthreads();
-      // column-major scan of the counters (eight per column, one column per thread)
-      static_assert(kTileCols == kTh, "one column per thread");
-      v4 c = v4{0u, 0u, 0u, 0u};
-      if (tid < ncs) c = *(const v4*)&L.wc[tid * kNW];
-      uint32_t s = 0, tot;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s += (c[j] & 0xffffu) + (c[j] >> 16);
-      uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
-      if (tid < ncs) {
-        if (!multi) st_off(a.t_row_ptr, (uint64_t)col0 + tid, (int64_t)cell0 + ex, a.lg);
-        v4 o;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const uint32_t lo = ex;
-          ex += c[j] & 0xffffu;
-          o[j] = lo | (ex << 16);
-          ex += c[j] >> 16;
-        }
-        *(v4*)&L.wc[tid * kNW] = o;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < kItems; ++q) pos[q] += L.wc[at[q]];
-      if constexpr (kWide) {  // cells of other pieces' columns have no place
-#pragma unroll
-        for (int q = 0; q < kItems; ++q)
-          if (d[q] == ncs) pos[q] = ~0u;
-        m = tot;
-      }
-    }
+    for (uint32_t e = tid; e < nc * (kNW / 2); e += kTh) ((uint32_t*)L.wc)[e] = 0;
+    __syncthreads();
+    uint32_t at[kItems], d[kItems];
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-      if ((uint32_t)q * kWave + lane >= mine || (kWide && pos[q] == ~0u)) continue;
+      d[q] = column(key[q]);
+      at[q] = d[q] * kNW + w;
+    }
+    wave_ranks(L.wc, at, d, mine, ceil_log2(nc), pos);
+    __syncthreads();
+    // column-major scan of the counters (eight per column, one column per thread)
+    static_assert(kTileCols == kTh, "one column per thread");
+    v4 c = v4{0u, 0u, 0u, 0u};
+    if (tid < nc) c = *(const v4*)&L.wc[tid * kNW];
+    uint32_t s = 0, tot;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s += (c[j] & 0xffffu) + (c[j] >> 16);
+    uint32_t ex = block_excl_scan<kNW>(s, L.red, tot);
+    if (tid < nc) {
+      if (!multi) st_off(a.t_row_ptr, (uint64_t)col0 + tid, (int64_t)cell0 + ex, a.lg);
+      v4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t lo = ex;
+        ex += c[j] & 0xffffu;
+        o[j] = lo | (ex << 16);
+        ex += c[j] >> 16;
+      }
+      *(v4*)&L.wc[tid * kNW] = o;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) pos[q] += L.wc[at[q]];
+#pragma unroll
+    for (int q = 0; q < kItems; ++q) {
+      if ((uint32_t)q * kWave + lane >= mine) continue;
       const uint32_t p = pos[q];
       L.row[p] = row[q];
       L.src[p] = x[q];
@@ -1072,7 +980,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         if (g0 + q >= kItems || p >= m) continue;
         uint64_t at = (uint64_t)cell0 + p, bt = byte0 + b[q];
         if (multi) {
-          uint32_t lo = 0, hi = ncs;  // the cell's column: the last one starting at or before p
+          uint32_t lo = 0, hi = nc;  // the cell's column: the last one starting at or before p
           while (hi - lo > 1) {
             const uint32_t mid = (lo + hi) >> 1;
             if ((uint32_t)L.wc[mid * kNW] <= p) lo = mid;
@@ -1110,15 +1018,12 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     }
     if (multi) {
       __syncthreads();
-      if (tid < ncs) {
-        const uint32_t i0 = L.wc[tid * kNW], i1 = tid + 1 < ncs ? (uint32_t)L.wc[(tid + 1) * kNW] : m;
+      if (tid < nc) {
+        const uint32_t i0 = L.wc[tid * kNW], i1 = tid + 1 < nc ? (uint32_t)L.wc[(tid + 1) * kNW] : m;
         run_c[tid] += i1 - i0;
         run_b[tid] += L.bp[i1] - L.bp[i0];
       }
     }
-  }
-  cell0 += piece_cells;
-  byte0 += piece_bytes;
   }
 }
 
@@ -1143,10 +1048,7 @@ static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStrea
     hipLaunchKernelGGL((tl::k_tile_xfer<false>), dim3((unsigned)a.n_parts, (unsigned)per),
                        dim3(tl::kTh), 0, s, a, b, none);
   }
-  if (a.wide)
-    hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false, true>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
-  else
-    hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
+  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
 }
 
 hipError_t launch_tile_keys(const TileView& v, const TileBounds& b, hipStream_t s) {
