@@ -197,8 +197,7 @@ struct DirectArgs {
 };
 static_assert(sizeof(DirectArgs) <= 2048, "kernel argument size");
 hipError_t launch_direct(const DirectArgs& a, hipStream_t s);
-// A mid-size matrix in two launches (three for a partitioned call; see
-// tiles.hip): tiles sorted by column bucket, then one workgroup per bucket.
+// A mid-size matrix in two launches (see tiles.hip): tiles sorted by column bucket, then one workgroup per bucket.
 constexpr uint32_t kTileMax = 16384;     // cells of a tile
 constexpr uint32_t kTileSub = 4096;      // cells of a tile ranked at once
 constexpr uint32_t kTileTiles = 512;     // tiles of a call
@@ -241,6 +240,8 @@ struct TileArgs {
   int32_t fixed_w;            // bytes of every cell, or -1
   int32_t n_parts;            // 0: plain call; <= kDirectParts
   int32_t validate;
+  uint64_t* xpart;            // partitioned calls of their own: workspace for X and B by xper
+  uint32_t xper;              // workgroups per source partition (0: k_tile_xfer adds in place)
 };
 struct TileBounds {
   int32_t bounds[kDirectParts + 1];

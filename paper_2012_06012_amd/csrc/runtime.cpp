@@ -439,7 +439,8 @@ struct TileGeo {
   uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
   bool uneven = false;  // bucket bounds from sampled columns (k_tile_bounds)
   uint32_t lut_shift = 0, target = 0;
-  uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_lut = 0, o_bcol = 0, bytes = 0;
+  uint32_t xper = 0;    // workgroups per source partition that count the transfer matrices
+  uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_xpart = 0, o_lut = 0, o_bcol = 0, bytes = 0;
 };
 
 constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
@@ -489,7 +490,14 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   t.o_table = 0;
   t.o_recs = align_up(8ull * t.n_tiles * t.n_buckets, 256);
   t.o_bad = t.o_recs + align_up(4 * words * nnz, 256);
-  t.o_lut = t.o_bad + align_up(4ull * t.n_tiles, 256);
+  t.o_xpart = t.o_bad + align_up(4ull * t.n_tiles, 256);
+  t.o_lut = t.o_xpart;
+  if (partitioned && !batch_cells) {
+    // about 4,096 cells (two rounds of loads) per workgroup, one chain of latencies
+    const uint64_t R = (uint64_t)d.n_parts;
+    t.xper = (uint32_t)(nnz / (R * 4096u) + 1);
+    t.o_lut += align_up(8 * t.xper * R * R, 256);
+  }
   t.o_bcol = t.o_lut + align_up(2ull * kTileBins, 256);
   t.bytes = t.uneven ? t.o_bcol + align_up(4ull * (t.n_buckets + 1), 256) : t.o_lut;
   t.ok = max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
@@ -1057,6 +1065,8 @@ TileArgs tile_args(const HostItem& it, const TileGeo& t, bool partitioned, uint3
   a.fixed_w = (d.flags & MGT_FIXED_WIDTH) ? (int32_t)(d.payload_bytes / d.nnz) : -1;
   a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
   a.vval = v.vval;
+  a.xpart = (uint64_t*)(W + t.o_xpart);
+  a.xper = t.xper;
   if (partitioned) a.n_parts = d.n_parts;
   return a;
 }

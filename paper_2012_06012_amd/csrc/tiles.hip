@@ -12,10 +12,13 @@
 //                 order), ranks them by column in LDS and writes the outputs
 //                 in final order, each payload read from the input.
 //
+// A partitioned call's transfer matrices are counted by workgroups of their own
+// beside the tiles, and added up by one beside the buckets.
+//
 // us per call, this form and the passes (8-byte offsets; 1-8 floats per cell):
 // 100 K cells 28 and 54, 300 K 36 and 65, 1 M 49 and 120, 4 M 151 and 414; 4.3 M
-// cells of 23 bytes over 37 partitions 210 and 850; 6 M cells of 0 to 7 bytes
-// with perm and device checks 214 and 557.
+// cells of 23 bytes over 37 partitions 181 and 850; 6 M cells of 0 to 7 bytes
+// with perm and device checks 181 and 557.
 //
 // Against the passes of kernels.hip: no histogram launches, no scans of
 // (digit, tile) counts and no segment tables between launches; records move
@@ -261,6 +264,135 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
   return bad;
 }
 
+// ----------------------------------------------------------------------------- transfer matrices
+
+struct NoBounds {};
+struct XferLds {
+  uint32_t cnt[kDirectParts], byt[kDirectParts];
+  int32_t lb[kDirectParts + 1];
+};
+
+// Rows of X and B of a partitioned call: workgroups (s, j), j < per, histogram
+// the owners of the columns of source partition s (its cells are consecutive in
+// the input), every per-th chunk each, into L.cnt and L.byt. L.lb holds the
+// partition bounds. Ends with a barrier.
+__device__ __forceinline__ void xfer_count(const TileArgs& a, uint32_t s, uint32_t j, uint32_t per,
+                                           XferLds& L) {
+  const uint32_t R = (uint32_t)a.n_parts, tid = threadIdx.x;
+  for (uint32_t i = tid; i < R; i += kTh) {
+    L.cnt[i] = 0;
+    L.byt[i] = 0;
+  }
+  __syncthreads();
+  const uint64_t kb = min((uint64_t)ld_off(a.row_ptr, (uint32_t)L.lb[s], a.lg), a.nnz);
+  const uint64_t ke = min((uint64_t)ld_off(a.row_ptr, (uint32_t)L.lb[s + 1], a.lg), a.nnz);
+  constexpr uint64_t kQ = 4, kChunk = kTh * kQ;
+  for (uint64_t c0 = kb + j * kChunk; c0 < ke; c0 += per * kChunk) {
+    uint32_t c[kQ], p0[kQ], p1[kQ];
+#pragma unroll
+    for (uint32_t q = 0; q < kQ; ++q) {
+      const uint64_t k = min(c0 + q * kTh + tid, ke - 1);
+      c[q] = (uint32_t)gm(a.col)[k];
+      p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : 0u;
+      p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, k + 1, a.lg) : (uint32_t)a.fixed_w;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kQ; ++q) {
+      const bool act = c0 + q * kTh + tid < ke;
+      uint32_t lo = 0, hi = R;  // the last partition starting at or before the column
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (L.lb[mid] <= (int32_t)c[q]) lo = mid;
+        else hi = mid;
+      }
+      // runs of equal owners in consecutive lanes add up first (sorted rows
+      // give a wave few owners), one atomic pair per run
+      const uint32_t d = act ? lo : 0xffffffffu, z = act ? p1[q] - p0[q] : 0u;
+      const uint32_t lane = lane_id();
+      const uint32_t prev = __shfl_up(d, 1, kWave), next = __shfl_down(d, 1, kWave);
+      const uint64_t heads = ballot(lane == 0 || prev != d);
+      const bool tail = lane == kWave - 1 || next != d;
+      const uint32_t incl = wave_incl_scan_u32(z);
+      const int h = 63 - (int)__clzll(heads & ((2ull << lane) - 1ull));
+      const uint32_t base = __shfl(incl - z, h, kWave);
+      if (act && tail) {
+        atomicAdd(&L.cnt[d], lane - (uint32_t)h + 1u);
+        atomicAdd(&L.byt[d], incl - base);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// A batch's partitioned items: the rows are added to X and B, which the sort
+// has cleared.
+__global__ __launch_bounds__(kTh) void k_tile_xfer(TileBatch bt) {
+  __shared__ XferLds L;
+  uint32_t s = blockIdx.x;
+  const uint32_t i = coop_item(bt.part_base, bt.n_items, s);
+  const TileArgs a = load_item(bt.items, i);
+  s -= bt.part_base[i];
+  for (uint32_t j = threadIdx.x; j <= (uint32_t)a.n_parts; j += kTh)
+    L.lb[j] = gm(bt.bounds)[(uint64_t)bt.part_item[i] * (kDirectParts + 1) + j];
+  xfer_count(a, s, blockIdx.y, gridDim.y, L);
+  const uint32_t R = (uint32_t)a.n_parts;
+  for (uint32_t d = threadIdx.x; d < R; d += kTh) {
+    if (!L.cnt[d]) continue;
+    const uint64_t e = (uint64_t)s * R + d;
+    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_cells + e), (unsigned long long)L.cnt[d],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_bytes + e), (unsigned long long)L.byt[d],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// X and B from the workgroups' rows, by one workgroup (all zero for an input
+// that failed its checks). Ends with a barrier.
+__device__ void xfer_sum(const TileArgs& a, bool bad) {
+  const uint32_t rr = (uint32_t)a.n_parts * (uint32_t)a.n_parts;
+  for (uint32_t e = threadIdx.x; e < rr; e += kTh) {
+    uint64_t cells = 0, bytes = 0;
+    if (!bad) {
+#pragma unroll 8
+      for (uint32_t j = 0; j < a.xper; ++j) {
+        const uint64_t v = gm(a.xpart)[(uint64_t)j * rr + e];
+        cells += v & 0xffffffffu;
+        bytes += v >> 32;
+      }
+    }
+    gm(a.xfer_cells)[e] = (int64_t)cells;
+    gm(a.xfer_bytes)[e] = (int64_t)bytes;
+  }
+  __syncthreads();
+}
+
+// Partition offsets and displacements from X and B, by one workgroup.
+__device__ void tile_tails(const TileArgs& a, uint64_t* red) {
+  const uint32_t R = (uint32_t)a.n_parts, d = threadIdx.x;
+  uint64_t cells = 0, bytes = 0, sent = 0;
+  if (d < R) {
+#pragma unroll 8
+    for (uint32_t r = 0; r < R; ++r) {
+      if (a.rdispls) a.rdispls[(uint64_t)d * R + r] = (int64_t)cells;
+      if (a.sdispls) a.sdispls[(uint64_t)d * R + r] = (int64_t)sent;
+      cells += (uint64_t)a.xfer_cells[(uint64_t)r * R + d];
+      bytes += (uint64_t)a.xfer_bytes[(uint64_t)r * R + d];
+      sent += (uint64_t)a.xfer_cells[(uint64_t)d * R + r];
+    }
+  }
+  uint64_t tc, tb;
+  const uint64_t ec = block_excl_scan<kNW>(cells, red, tc);
+  const uint64_t eb = block_excl_scan<kNW>(bytes, red, tb);
+  if (d < R) {
+    a.part_cell_off[d] = (int64_t)ec;
+    a.part_byte_off[d] = (int64_t)eb;
+  }
+  if (d == 0) {
+    a.part_cell_off[R] = (int64_t)tc;
+    a.part_byte_off[R] = (int64_t)tb;
+  }
+}
+
 // kIdx: the record carries the cell's input index (perm).
 // The tile's columns and sizes are read twice: counted first, which gives every
 // bucket its place in the tile, then ranked and stored in pieces of kTileSub
@@ -270,11 +402,32 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
 // in flight; the records are stored straight to their place in the tile's own
 // region (whole lines by the time they leave the L2).
 // kVal: every cell carries a value of its own (vval) in place of its row id.
-template <bool kIdx, bool kBatch, bool kVal = false>
-__global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt) {
+// kParts: a partitioned call of its own; the workgroups past the tiles count its
+// transfer matrices, (s, j) its s-th source partition's j-th share, into xpart
+// for the merge's first workgroup to add up. In a launch between the two
+// kernels, with atomic adds, the calls took (137 K cells, 13 partitions) 30.3 us, now
+// 24.0; (1 M, 64) 71.5, now 67; (4.3 M, 37) 185, now 181.
+template <bool kIdx, bool kBatch, bool kVal = false, bool kParts = false>
+__global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt,
+                                                      std::conditional_t<kParts, TileBounds, NoBounds> pb) {
   constexpr int kWords = kIdx ? 4 : 3;
-  __shared__ SortLds L;
+  __shared__ union {
+    SortLds sort;
+    XferLds xfer;
+  } U;
+  SortLds& L = U.sort;
   uint32_t t = blockIdx.x;
+  if constexpr (kParts) {
+    if (t >= one.n_tiles) {
+      const uint32_t R = (uint32_t)one.n_parts, s = (t - one.n_tiles) / one.xper,
+                     j = (t - one.n_tiles) % one.xper;
+      for (uint32_t i = threadIdx.x; i <= R; i += kTh) U.xfer.lb[i] = pb.bounds[i];
+      xfer_count(one, s, j, one.xper, U.xfer);
+      for (uint32_t d = threadIdx.x; d < R; d += kTh)
+        gm(one.xpart)[((uint64_t)j * R + s) * R + d] = U.xfer.cnt[d] | (uint64_t)U.xfer.byt[d] << 32;
+      return;
+    }
+  }
   TileArgs a = one;
   if constexpr (kBatch) {
     const uint32_t i = coop_item(bt.tile_base, bt.n_items, t);
@@ -296,8 +449,8 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
     const bool bad = __syncthreads_or(tile_bad(a, t)) != 0;
     if (threadIdx.x == 0) gm(a.bad)[t] = bad ? 1u : 0u;
   }
-  // the transfer matrices of a partitioned call start at zero (k_tile_xfer adds to them)
-  if (a.n_parts > 0)
+  // the transfer matrices of a batch's item start at zero (k_tile_xfer adds to them)
+  if (kBatch && a.n_parts > 0)
     for (uint64_t e = (uint64_t)t * kTh + threadIdx.x; e < (uint64_t)a.n_parts * a.n_parts;
          e += (uint64_t)a.n_tiles * kTh) {
       gm(a.xfer_cells)[e] = 0;
@@ -520,113 +673,11 @@ __global__ __launch_bounds__(kTh) void k_tile_keys(TileView v, TileBounds b) {
   }
 }
 
-// ----------------------------------------------------------------------------- transfer matrices
-
-// X and B of a partitioned call: workgroups (s, j), j < gridDim.y, histogram
-// the owners of the columns of source partition s (its cells are consecutive
-// in the input), every gridDim.y-th chunk each, and add to its row of both.
-template <bool kBatch>
-__global__ __launch_bounds__(kTh) void k_tile_xfer(TileArgs one, TileBounds b, TileBatch bt) {
-  __shared__ uint32_t cnt[kDirectParts], byt[kDirectParts];
-  __shared__ int32_t lb[kDirectParts + 1];
-  uint32_t s = blockIdx.x;
-  const uint32_t tid = threadIdx.x;
-  TileArgs a = one;
-  if constexpr (kBatch) {
-    const uint32_t i = coop_item(bt.part_base, bt.n_items, s);
-    a = load_item(bt.items, i);
-    s -= bt.part_base[i];
-    for (uint32_t j = tid; j <= (uint32_t)a.n_parts; j += kTh)
-      lb[j] = gm(bt.bounds)[(uint64_t)bt.part_item[i] * (kDirectParts + 1) + j];
-  } else {
-    if (any_bad(a)) return;
-    for (uint32_t j = tid; j <= (uint32_t)a.n_parts; j += kTh) lb[j] = b.bounds[j];
-  }
-  const uint32_t R = (uint32_t)a.n_parts;
-  for (uint32_t i = tid; i < R; i += kTh) {
-    cnt[i] = 0;
-    byt[i] = 0;
-  }
-  __syncthreads();
-  const uint64_t kb = min((uint64_t)ld_off(a.row_ptr, (uint32_t)lb[s], a.lg), a.nnz);
-  const uint64_t ke = min((uint64_t)ld_off(a.row_ptr, (uint32_t)lb[s + 1], a.lg), a.nnz);
-  constexpr uint64_t kQ = 4, kChunk = kTh * kQ;
-  for (uint64_t c0 = kb + blockIdx.y * kChunk; c0 < ke; c0 += gridDim.y * kChunk) {
-    uint32_t c[kQ], p0[kQ], p1[kQ];
-#pragma unroll
-    for (uint32_t q = 0; q < kQ; ++q) {
-      const uint64_t k = min(c0 + q * kTh + tid, ke - 1);
-      c[q] = (uint32_t)gm(a.col)[k];
-      p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : 0u;
-      p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, k + 1, a.lg) : (uint32_t)a.fixed_w;
-    }
-#pragma unroll
-    for (uint32_t q = 0; q < kQ; ++q) {
-      const bool act = c0 + q * kTh + tid < ke;
-      uint32_t lo = 0, hi = R;  // the last partition starting at or before the column
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (lb[mid] <= (int32_t)c[q]) lo = mid;
-        else hi = mid;
-      }
-      // runs of equal owners in consecutive lanes add up first (sorted rows
-      // give a wave few owners), one atomic pair per run
-      const uint32_t d = act ? lo : 0xffffffffu, z = act ? p1[q] - p0[q] : 0u;
-      const uint32_t lane = lane_id();
-      const uint32_t prev = __shfl_up(d, 1, kWave), next = __shfl_down(d, 1, kWave);
-      const uint64_t heads = ballot(lane == 0 || prev != d);
-      const bool tail = lane == kWave - 1 || next != d;
-      const uint32_t incl = wave_incl_scan_u32(z);
-      const int h = 63 - (int)__clzll(heads & ((2ull << lane) - 1ull));
-      const uint32_t base = __shfl(incl - z, h, kWave);
-      if (act && tail) {
-        atomicAdd(&cnt[d], lane - (uint32_t)h + 1u);
-        atomicAdd(&byt[d], incl - base);
-      }
-    }
-  }
-  __syncthreads();
-  for (uint32_t i = tid; i < R; i += kTh) {
-    if (!cnt[i]) continue;
-    const uint64_t e = (uint64_t)s * R + i;
-    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_cells + e), (unsigned long long)cnt[i],
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_add(gm((unsigned long long*)a.xfer_bytes + e), (unsigned long long)byt[i],
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// Partition offsets and displacements from X and B, by one workgroup.
-__device__ void tile_tails(const TileArgs& a, uint64_t* red) {
-  const uint32_t R = (uint32_t)a.n_parts, d = threadIdx.x;
-  uint64_t cells = 0, bytes = 0, sent = 0;
-  if (d < R) {
-#pragma unroll 8
-    for (uint32_t r = 0; r < R; ++r) {
-      if (a.rdispls) a.rdispls[(uint64_t)d * R + r] = (int64_t)cells;
-      if (a.sdispls) a.sdispls[(uint64_t)d * R + r] = (int64_t)sent;
-      cells += (uint64_t)a.xfer_cells[(uint64_t)r * R + d];
-      bytes += (uint64_t)a.xfer_bytes[(uint64_t)r * R + d];
-      sent += (uint64_t)a.xfer_cells[(uint64_t)d * R + r];
-    }
-  }
-  uint64_t tc, tb;
-  const uint64_t ec = block_excl_scan<kNW>(cells, red, tc);
-  const uint64_t eb = block_excl_scan<kNW>(bytes, red, tb);
-  if (d < R) {
-    a.part_cell_off[d] = (int64_t)ec;
-    a.part_byte_off[d] = (int64_t)eb;
-  }
-  if (d == 0) {
-    a.part_cell_off[R] = (int64_t)tc;
-    a.part_byte_off[R] = (int64_t)tb;
-  }
-}
-
 // ----------------------------------------------------------------------------- bucket merge
 
 constexpr int kMergeItems = kTileCap / kTh;  // cells per lane of a bucket held at once
 constexpr uint32_t kMergeWave = kMergeItems * kWave;
+constexpr uint32_t kMergeLead = 8;  // one workgroup per XCD, so the buckets' own mapping stays
 
 struct MergeLds {
   // output order: row, payload offset (or payload), size then byte prefix.
@@ -729,11 +780,14 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
   constexpr uint32_t kCap = kTileCap, kWaveCells = kMergeWave;
   constexpr uint32_t kWords = kIdx ? 4 : 3;
   __shared__ MergeLds L;
-  // workgroups past the buckets', one per item: status, end offsets, and a
-  // partitioned item's offsets and displacements
+  // one workgroup per item besides the buckets': status, end offsets, and a
+  // partitioned item's matrices, offsets and displacements. A batch's are the
+  // last ones; a single call's is the first of the first eight (the others leave),
+  // so that a long sum over the partitions runs beside the buckets.
   const uint32_t g8 = kBatch ? (bt.n_buckets + 7u) & ~7u : one.g8;
-  const bool tail = blockIdx.x >= g8;
-  uint32_t g = (uint32_t)xcd_tile(blockIdx.x, g8);
+  const bool tail = kBatch ? blockIdx.x >= g8 : blockIdx.x < kMergeLead;
+  if (!kBatch && tail && blockIdx.x) return;
+  uint32_t g = (uint32_t)xcd_tile(kBatch ? blockIdx.x : blockIdx.x - kMergeLead, g8);
   TileArgs a = one;
   if constexpr (kBatch) {
     if (!tail && g >= bt.n_buckets) return;
@@ -750,6 +804,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
       }
     }
+    if (!kBatch && a.n_parts > 0) xfer_sum(a, bad);
     if (!bad && a.n_parts > 0) tile_tails(a, L.red64);
     return;
   }
@@ -1035,20 +1090,17 @@ template <bool kIdx>
 static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStream_t s) {
   const TileBatch none{};
   if (a.lut) hipLaunchKernelGGL(tl::k_tile_bounds, dim3(1), dim3(tl::kBoundTh), 0, s, a);
+  const dim3 th(tl::kTh);
+  const uint32_t dyn = tl::sort_dyn_bytes(a.n_buckets);
+  const tl::NoBounds nob{};
   if (a.vval)
-    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, true>), dim3(a.n_tiles), dim3(tl::kTh),
-                       tl::sort_dyn_bytes(a.n_buckets), s, a, none);
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, true>), dim3(a.n_tiles), th, dyn, s, a, none, nob);
+  else if (a.n_parts > 0)
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, false, true>),
+                       dim3(a.n_tiles + (uint32_t)a.n_parts * a.xper), th, dyn, s, a, none, b);
   else
-    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), dim3(tl::kTh),
-                       tl::sort_dyn_bytes(a.n_buckets), s, a, none);
-  if (a.n_parts > 0) {
-    // about 4,096 cells (two rounds of loads) per workgroup: the kernel is one
-    // chain of latencies, and its adds are one per workgroup and partition pair
-    const uint64_t per = std::min<uint64_t>(a.nnz / ((uint64_t)a.n_parts * 4096u) + 1, 65535);
-    hipLaunchKernelGGL((tl::k_tile_xfer<false>), dim3((unsigned)a.n_parts, (unsigned)per),
-                       dim3(tl::kTh), 0, s, a, b, none);
-  }
-  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(a.g8 + 1), dim3(tl::kTh), 0, s, a, none);
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), th, dyn, s, a, none, nob);
+  hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(tl::kMergeLead + a.g8), th, 0, s, a, none);
 }
 
 hipError_t launch_tile_keys(const TileView& v, const TileBounds& b, hipStream_t s) {
@@ -1066,13 +1118,11 @@ hipError_t launch_tiles(const TileArgs& a, const TileBounds& b, hipStream_t s) {
 template <bool kIdx>
 static void launch_batch_kernels(const TileBatch& b, hipStream_t s) {
   const TileArgs none{};
-  const TileBounds nob{};
   hipLaunchKernelGGL((tl::k_tile_sort<kIdx, true>), dim3(b.n_tiles), dim3(tl::kTh),
-                     tl::sort_dyn_bytes(b.max_buckets), s, none, b);
+                     tl::sort_dyn_bytes(b.max_buckets), s, none, b, tl::NoBounds{});
   if (b.n_parts) {
     const uint64_t per = std::min<uint64_t>(b.max_part_cells / 4096u + 1, 65535);
-    hipLaunchKernelGGL((tl::k_tile_xfer<true>), dim3(b.n_parts, (unsigned)per), dim3(tl::kTh), 0, s,
-                       none, nob, b);
+    hipLaunchKernelGGL(tl::k_tile_xfer, dim3(b.n_parts, (unsigned)per), dim3(tl::kTh), 0, s, b);
   }
   hipLaunchKernelGGL((tl::k_tile_merge<kIdx, true>), dim3(((b.n_buckets + 7u) & ~7u) + b.n_items),
                      dim3(tl::kTh), 0, s, none, b);
