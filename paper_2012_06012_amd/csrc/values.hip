@@ -43,7 +43,7 @@ __device__ __forceinline__ uint64_t gstride() { return (uint64_t)gridDim.x * blo
 //   k_emit       heads to their slots, run lengths, output row offsets
 // The bound is memory: col twice, the payload offsets once (every line holds
 // a head unless runs are long), the outputs once. 24 M cells in runs of two
-// on average (8-byte offsets): 346 -> 144 us against the form before (4-byte
+// on average (8-byte offsets): 346 -> 122 us against the form before (4-byte
 // flags, 8-byte slots and a 4-byte array of run starts, all in memory); k_emit
 // takes 81 of them, at 5.7 TB/s.
 constexpr int kChunkWords = 4 * kB;  // words per workgroup of k_head_sums / k_head_pref
@@ -74,13 +74,27 @@ __global__ __launch_bounds__(kB) void k_heads(const int32_t* col, uint64_t nnz, 
   }
 }
 
+// The starts of neighbouring rows fall into the same words: a wave ORs them
+// together first, one atomic per word and wave, as the number of atomics
+// bounds the kernel (1 M rows of 23 cells: 27.1 us with one atomic per row, now 6.9).
 __global__ __launch_bounds__(kB) void k_row_heads(const void* rp, int ow, uint64_t n_rows,
                                                   uint64_t nnz, uint64_t* words) {
-  for (uint64_t i = gtid(); i < n_rows; i += gstride()) {
+  const uint32_t lane = lane_id();
+  for (uint64_t i0 = gtid() - lane; i0 < n_rows; i0 += gstride()) {  // whole waves
+    const uint64_t i = min(i0 + lane, n_rows - 1);  // (the last row's bit again, past the end)
     const uint64_t a = min(ld_o(rp, i, ow), nnz), b = min(ld_o(rp, i + 1, ow), nnz);
-    if (a < b)
-      __hip_atomic_fetch_or(gm((unsigned long long*)words + (a >> 6)), 1ull << (a & 63),
-                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t w = (uint32_t)(a >> 6);
+    uint64_t m = a < b ? 1ull << (a & 63) : 0ull;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const uint64_t v = __shfl_down((unsigned long long)m, o, kWave);
+      const uint32_t u = (uint32_t)__shfl_down((int)w, o, kWave);
+      if (lane + o < kWave && u == w) m |= v;
+    }
+    const uint32_t prev = (uint32_t)__shfl_up((int)w, 1, kWave);
+    if (m && (lane == 0 || prev != w))
+      __hip_atomic_fetch_or(gm((unsigned long long*)words + w), m, __ATOMIC_RELAXED,
+                            __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
