@@ -128,8 +128,8 @@ def profiler_kernel_name(stage: str, pass_idx: int, n_passes: int, partitioned: 
 
 # The sources that build the transpose's kernels and launches (the value-list
 # conversions in values.hip are not part of it).
-TRANSPOSE_SOURCES = ("kernels.h", "kernels.hip", "kernels_wide.hip", "mgt_internal.h", "prims.h",
-                     "runtime.cpp")
+TRANSPOSE_SOURCES = ("kernels.h", "kernels.hip", "kernels_wide.hip", "mgt_internal.h", "payload.h", "prims.h",
+                     "runtime.cpp", "tiles.hip")
 
 
 def kernel_sources_digest() -> str:

@@ -121,24 +121,24 @@ def test_payload_alignment():
 
 
 @pytest.mark.parametrize("n_cols,nnz,law,ow", [
-    ((1 << 20) + 1, 60013, "uniform", 8), (3 << 20, 200003, "uniform", 4),
-    (8 << 20, 1000, "few", 8),             # the most columns of this form
-    ((8 << 20) + 1, 1000, "few", 8),       # past it: the passes
-    (2 << 20, 70001, "hot", 8),            # a wide bucket taken in chunks
+    (1 << 20, 60013, "uniform", 8),        # the most columns of this form
+    ((1 << 20) + 1, 60013, "uniform", 8),  # past it: the passes
+    (3 << 20, 200003, "uniform", 4), (8 << 20, 1000, "few", 8), ((8 << 20) + 1, 1000, "few", 8),
+    (2 << 20, 70001, "hot", 8),
 ])
 @pytest.mark.parametrize("perm", [False, True])
-def test_wide_buckets(n_cols, nnz, law, ow, perm, monkeypatch):
+def test_many_columns(n_cols, nnz, law, ow, perm, monkeypatch):
     _both(_matrix(500, n_cols, nnz, law, nnz, 0, 20, ow), monkeypatch, False, perm=perm)
 
 
-def test_wide_buckets_all_crowded(monkeypatch):
-    """Every cell in one bucket's columns: all of its pieces and chunks."""
+def test_many_columns_all_crowded(monkeypatch):
+    """Every cell in a few neighbouring columns."""
     a = _matrix(500, 3 << 20, 30000, "uniform", 1, 0, 9, 8)
     a.col[:] = 5000 + a.col % 1500
     _both(a, monkeypatch, False)
 
 
-def test_sizes_past_a_wide_record_field(monkeypatch):
+def test_long_cells_of_many_columns(monkeypatch):
     w = np.full(3000, 3)
     w[[0, 1500, 2999]] = [(1 << 20) - 2, (1 << 20) - 1, (1 << 20) + 5]
     rng = np.random.default_rng(0)

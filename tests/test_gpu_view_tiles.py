@@ -1,6 +1,6 @@
 """View operations in the two-launch form (keys as columns, values as rows)
-against oracle/views.py: few and many keys (wide buckets), crowded columns,
-both views and operations, and 257 partitions (the passes)."""
+against oracle/views.py: few and many keys (past 1,048,576: the passes), crowded
+columns, both views and operations, and 257 partitions (the passes)."""
 import numpy as np
 import pytest
 
