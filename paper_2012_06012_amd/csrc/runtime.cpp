@@ -960,18 +960,21 @@ int record_graph(size_t staging_bytes, mgt_graph_s* g, Call call) {
   return st;
 }
 
-// Small calls take k_direct: one launch that reads every column id in every
-// workgroup. us per call, direct, tiles and passes (1-8 floats per cell, 8-byte
-// offsets): 5 K cells 16, 22 and 44; 20 K 16, 24 and 46; 50 K 26, 25 and 51;
-// 100 K 41, 28 and 54; partitioned (R = 37, 23 bytes): 20 K 22, 30 and 104,
-// 50 K 32, 31 and 104.
-constexpr int64_t kDirectCells = 45000;
+// Small calls take k_direct: one launch (two for a partitioned call) that reads
+// every column id in every workgroup. us per call, direct and tiles: plain (1-8
+// floats per cell) 10 K cells 12.8 and 20.2, 30 K 17.7 and 21.3, 40 K 20.2 and
+// 21.2, 45 K 22.5 and 21.2; over 4 partitions 10 K 17.1 and 19.0, 20 K 21.7 and
+// 20.1 (recorded and replayed 22.2 and 23.7), 30 K 24.4 and 20.2, 40 K 28.1 and
+// 20.4; over 13 partitions 20 K 21.0 and 20.3, 30 K 23.1 and 20.6; over 37
+// partitions 20 K 21.1 and 23.6, 30 K 22.7 and 23.6, 40 K 25.1 and 23.9. (The
+// passes: 46 at 20 K plain, 104 over 37 partitions.)
+constexpr int64_t kDirectCells = 45000, kDirectCellsParts = 25000;
 
 // Whether a single-matrix call runs directly. Calls that ask for the passes'
 // own stages keep them: device-side checks and stage times, a schedule set by
 // the caller or by the environment.
 bool use_direct(const mgt_plan_s* p, const mgt_desc& d, bool partitioned) {
-  if (d.nnz < 1 || d.nnz > kDirectCells) return false;
+  if (d.nnz < 1 || d.nnz > (partitioned ? kDirectCellsParts : kDirectCells)) return false;
   if (d.n_cols > (int64_t)kDirectCols * kDirectWgs || d.payload_bytes >= (1ll << 32)) return false;
   if (partitioned && d.n_parts > kDirectParts) return false;
   if (p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING)) return false;
