@@ -40,6 +40,15 @@ def test_shares(parts, nnz, crowded):
     assert_matches_oracle(a, h, partitioned=True)
 
 
+@pytest.mark.parametrize("nnz", [25000, 25001])  # the last direct partitioned size, the first past it
+def test_edge_of_the_direct_form(nnz, monkeypatch):
+    monkeypatch.delenv("MGT_NO_DIRECT")
+    a = _matrix(1500, nnz, equal_bounds(1500, 13), nnz)
+    h, st = gpu_transpose(a, partitioned=True, perm=True)
+    assert st == 0
+    assert_matches_oracle(a, h, partitioned=True)
+
+
 def test_failed_check_leaves_zero():
     from paper_2012_06012_amd import mgt
     a = _matrix(900, 50021, equal_bounds(900, 7), 5)
