@@ -221,6 +221,12 @@ __device__ __forceinline__ void raise_status(int32_t* item_status, int32_t* abor
 __device__ __forceinline__ bool aborted(const int32_t* abort_flag) {
   return __hip_atomic_load(abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 }
+// The same for a whole workgroup, in kernels whose own workgroups may raise the
+// flag: without it some waves would leave while the others went on with shared
+// state that the first were to fill. Every thread must call it.
+__device__ __forceinline__ bool aborted_all(const int32_t* abort_flag) {
+  return __syncthreads_or(aborted(abort_flag)) != 0;
+}
 // Whether this call's records are packed: the host allows it (pk_on) and the
 // first histogram found every payload size within 32 - pk_shift bits (it sets
 // no_pack otherwise). Uniform over the grid.
@@ -493,7 +499,7 @@ __global__ __launch_bounds__(kBlock) void k_pass_hist(PassArgs a) {
   __shared__ Seg s_seg;
   __shared__ uint32_t s_si;
   __shared__ uint64_t s_red[kNW + 1];
-  if (aborted(a.abort_flag)) return;
+  if (aborted_all(a.abort_flag)) return;
   const uint64_t tile = xcd_tile(blockIdx.x, a.g8);
   if (tile >= a.tstart[a.nseg]) return;
   {
@@ -1522,7 +1528,7 @@ __global__ __launch_bounds__(kBlock) void k_view_keys(ViewArgs a) {
   __shared__ uint16_t s_ot[kOwnerT + 1];
   __shared__ uint32_t s_extra;
   __shared__ uint32_t s_red[kNW + 1];
-  if (aborted(a.abort_flag)) return;
+  if (aborted_all(a.abort_flag)) return;
   const ItemDev& it = a.items[0];
   const uint32_t R = (uint32_t)a.n_parts;
   for (uint32_t i = threadIdx.x; i <= R; i += kBlock) s_lb[i] = (int32_t)gm(a.bounds)[i];
