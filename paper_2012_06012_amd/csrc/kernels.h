@@ -277,6 +277,8 @@ struct TileBatch {
   uint32_t max_buckets;       // of one item
   uint64_t max_part_cells;    // cells per source partition, the largest item's mean
   int32_t idx;                // every item has perm
+  const int32_t* abort_flag;  // of the batch's items that make the passes, launched before: set if
+                              // one of them failed, which cancels these too (null: there are none)
 };
 hipError_t launch_tile_batch(const TileBatch& b, hipStream_t s);
 // mgt_symmetrize's stages after the transpose of the stored triangle

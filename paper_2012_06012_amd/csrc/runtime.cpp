@@ -1241,7 +1241,8 @@ void pad_passes(std::vector<HostItem>& items, const Tune& tune) {
 }
 
 // How a batch runs: items whose size fits the two-launch form take it together,
-// the others make the passes together.
+// after the others made the passes together (an item that fails there cancels
+// both kinds).
 struct BatchRun {
   std::vector<HostItem> passes;  // (out: their indexes in the batch)
   Layout y;                      // of the passes' part, at the start of the workspace
@@ -1372,6 +1373,7 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
   b.n_tiles = (uint32_t)tiles;
   b.n_buckets = (uint32_t)buckets;
   b.n_parts = (uint32_t)parts;
+  if (!r.passes.empty()) b.abort_flag = (const int32_t*)(W + r.y.o_abort);
   MGT_HIP(launch_tile_batch(b, s));
   return MGT_OK;
 }

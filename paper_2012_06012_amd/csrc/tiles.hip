@@ -795,10 +795,12 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
     a = load_item(bt.items, (uint32_t)__builtin_amdgcn_readfirstlane((int)i));
     g -= bt.bucket_base[i];
   }
-  const bool bad = any_bad(a);
+  // (set by an earlier launch or not at all: the same for every workgroup)
+  const bool cancelled = kBatch && bt.abort_flag && gm(bt.abort_flag)[0] != 0;
+  const bool bad = any_bad(a) || cancelled;
   if (tail) {
     if (threadIdx.x == 0) {
-      if (a.d_status) *a.d_status = bad ? MGT_ERANGE : MGT_OK;
+      if (a.d_status) *a.d_status = cancelled ? MGT_ECANCELED : bad ? MGT_ERANGE : MGT_OK;
       if (!bad) {
         st_off(a.t_row_ptr, (uint64_t)a.n_cols, (int64_t)a.nnz, a.lg);
         if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
