@@ -82,7 +82,11 @@ __global__ __launch_bounds__(kB) void k_sym_count(SymArgs a) {
 
 // S by output cells, kFillCells per workgroup, whatever the rows' lengths: the
 // workgroup finds the row of its first cell, counts in LDS where the rows after
-// it start and scans the counts. Cell j of row i comes from the stored row or
+// it start and scans the counts. A workgroup walks about kFillRows rows at most:
+// where more lie between two of its cells (a long stretch of empty ones), it
+// searches the cells' rows instead (2^24 vertices, edges among 8,000 of them: 97
+// ms for the call with one workgroup walking the rest, now 55, of which the
+// transpose takes 49). Cell j of row i comes from the stored row or
 // from T's row, both read in order, so every access runs along its array; a
 // wave's 64 payloads are one run of output bytes and go out through LDS.
 // Bound by the loads of the rows' fields (about ten per cell, nearly all from
@@ -90,6 +94,7 @@ __global__ __launch_bounds__(kB) void k_sym_count(SymArgs a) {
 // cells of 8 bytes on average in rows of 32 (8 M cells of S); this takes 134.
 constexpr int kFillCells = 2048;
 constexpr int kFillPer = kFillCells / kB;
+constexpr uint64_t kFillRows = 8 * kFillCells;
 
 __global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a, uint32_t cell_blocks) {
   __shared__ uint32_t incl[kFillCells];
@@ -141,6 +146,28 @@ __global__ __launch_bounds__(kB) void k_sym_fill(SymArgs a, uint32_t cell_blocks
       stop = v >= q0 + m;
     }
     more = !__syncthreads_or(stop);
+    if (more && base > r0 + kFillRows) {  // (block-uniform)
+      // the last row starting at or before each cell, and what it is past the
+      // one of the cell before
+#pragma unroll 1
+      for (uint32_t i = threadIdx.x; i < m; i += kB) {
+        uint64_t row[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const uint64_t q = q0 + (i > (uint32_t)e ? i - e : 0u);
+          uint64_t first = r0, end = a.n;
+          while (end - first > 1) {
+            const uint64_t mid = (first + end) >> 1;
+            if (a.ocnt[mid] <= q) first = mid;
+            else end = mid;
+          }
+          row[e] = first;
+        }
+        incl[i] = (uint32_t)(i ? row[0] - row[1] : row[0] - r0);
+      }
+      __syncthreads();
+      more = false;
+    }
   }
   {
     const uint32_t p0 = threadIdx.x * kFillPer;
