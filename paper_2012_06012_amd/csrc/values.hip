@@ -230,6 +230,19 @@ __global__ __launch_bounds__(kB) void k_expand_rows(const void* rp, const void* 
     st_o(o_rp, i, ld_o(poff, min(ld_o(rp, i, ow), nnz), ow) / w, ow);
 }
 
+// Whether an offset of the workgroup's share (nnz + 1 over the grid, rounded up)
+// is not a whole number of values.
+__device__ __forceinline__ bool share_bad(const void* poff, int ow, uint64_t nnz, uint32_t w) {
+  bool bad = false;
+  const uint64_t per = (nnz + gridDim.x) / gridDim.x;
+  const uint64_t k1 = min(nnz + 1, (blockIdx.x + 1) * per);
+  for (uint64_t k = blockIdx.x * per + threadIdx.x; k < k1; k += kB) {
+    const uint64_t v = ld_o(poff, k, ow);
+    bad |= (v >> 32) ? (v % w) != 0 : ((uint32_t)v % w) != 0;
+  }
+  return bad;
+}
+
 // The last cells of [0, hi) whose payload offsets are at most b0 and at most
 // b1 >= b0 (cell 0 if none), found by the whole workgroup: each round probes kB
 // evenly spaced cells for both, their loads in flight together.
@@ -257,29 +270,24 @@ __device__ __forceinline__ void coop_last_le(const void* poff, int ow, uint64_t 
 // between them start, and scans the counts: the payload offsets are read once,
 // in order, where a binary search per value read about 23 of them one after
 // another. A range of more than kExCells cells (long runs of empty cells)
-// is searched per value instead, so no input makes one workgroup walk it.
+// is searched per value instead, so no input makes one workgroup walk it (600 K
+// values in the first and the last of 300 K cells: 28.9 us by plain binary searches,
+// 20.6 by way of samples in LDS).
 // Bound by the latency of its steps (search, walk, scan, store), with 4 + ow
-// bytes stored per value. 24 M values of 6 M cells, 8-byte offsets: 536 -> 129
+// bytes stored per value. 24 M values of 6 M cells, 8-byte offsets: 536 -> 122
 // us against the binary search per value.
 // Each workgroup also checks its share of the offsets (status only).
 constexpr int kExVals = 2048;
 constexpr uint64_t kExCells = 8 * kExVals;
+constexpr int kExSamples = 1024;
 
 __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const void* poff, int ow,
                                                      uint64_t nnz, uint64_t nvals, uint32_t w,
                                                      int32_t* o_col, void* o_poff,
                                                      int32_t* d_status) {
-  __shared__ uint32_t incl[kExVals];
+  __shared__ uint32_t incl[kExVals], samples[kExSamples];
   __shared__ uint32_t red[kB / kWave];
-  bool bad = false;
-  {
-    const uint64_t per = (nnz + gridDim.x) / gridDim.x;  // nnz + 1 offsets over the grid, rounded up
-    const uint64_t k1 = min(nnz + 1, (blockIdx.x + 1) * per);
-    for (uint64_t k = blockIdx.x * per + threadIdx.x; k < k1; k += kB) {
-      const uint64_t v = ld_o(poff, k, ow);
-      bad |= (v >> 32) ? (v % w) != 0 : ((uint32_t)v % w) != 0;
-    }
-  }
+  const bool bad = share_bad(poff, ow, nnz, w);
   for (uint64_t q0 = (uint64_t)blockIdx.x * kExVals; q0 < nvals; q0 += (uint64_t)gridDim.x * kExVals) {
     const uint32_t n = (uint32_t)min((uint64_t)kExVals, nvals - q0);
     const uint64_t b0 = q0 * w, b1 = (q0 + n) * w;
@@ -314,23 +322,49 @@ __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const v
       }
       __syncthreads();
     }
+    if (!walk) {
+      // the starts of kExSamples evenly spaced cells of the range in LDS, in bytes
+      // past b0: each value's place among them, then among the cells between two,
+      // kSide values of a thread at a time (more take registers that the walk
+      // misses). Values of 2^32 bytes and more per workgroup do without samples.
+      const uint32_t last = (uint32_t)(c1 - c0), step = last / kExSamples + 1u;
+      const bool fits = (uint64_t)n * w < ~0u;
+      for (uint32_t i = threadIdx.x; i < (uint32_t)kExSamples; i += kB) {
+        const uint64_t o = ld_o(poff, c0 + min((uint64_t)i * step, (uint64_t)last), ow);
+        samples[i] = (uint32_t)min(o > b0 ? o - b0 : 0, (uint64_t)~0u);
+      }
+      __syncthreads();
+      constexpr int kSide = 2;
+      static_assert(kExVals % (kSide * kB) == 0, "whole rounds");
+#pragma unroll 1
+      for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kSide * kB) {
+        uint32_t f[kSide] = {};  // the last cell starting at or before the value (the first one does)
+#pragma unroll 1
+        for (uint32_t d = fits ? kExSamples / 2 : 0; d; d >>= 1) {
+#pragma unroll
+          for (int j = 0; j < kSide; ++j) f[j] += samples[f[j] + d] <= (i0 + j * kB) * w ? d : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kSide; ++j) f[j] = (uint32_t)min((uint64_t)f[j] * step, (uint64_t)last);
+#pragma unroll 1
+        for (uint32_t d = 1u << (31 - __clz((int)(fits ? step : last))); d; d >>= 1) {
+#pragma unroll
+          for (int j = 0; j < kSide; ++j) {
+            const uint32_t k = (uint32_t)min((uint64_t)f[j] + d, (uint64_t)last);
+            f[j] = ld_o(poff, c0 + k, ow) <= (q0 + i0 + j * kB) * w ? k : f[j];
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < kSide; ++j) incl[i0 + j * kB] = f[j];
+      }
+      __syncthreads();
+    }
     constexpr int kOut = kExVals / kB;  // values per thread, their columns in flight together
     int32_t c[kOut];
 #pragma unroll
     for (int j = 0; j < kOut; ++j) {
       const uint32_t i = min((uint32_t)(j * kB) + threadIdx.x, n - 1);
-      uint64_t cell;
-      if (walk) {
-        cell = min(c0 + incl[i], nnz - 1);
-      } else {
-        uint64_t lo = c0, hi = c1 + 1;
-        while (hi - lo > 1) {
-          const uint64_t mid = (lo + hi) >> 1;
-          if (ld_o(poff, mid, ow) <= (q0 + i) * w) lo = mid;
-          else hi = mid;
-        }
-        cell = lo;
-      }
+      const uint64_t cell = min(c0 + incl[i], nnz - 1);
       c[j] = gm(col)[cell];
     }
 #pragma unroll
@@ -343,6 +377,34 @@ __global__ __launch_bounds__(kB) void k_expand_cells(const int32_t* col, const v
     __syncthreads();  // incl is reused
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && o_poff) st_o(o_poff, nvals, nvals * w, ow);
+  if (bad && d_status) *d_status = MGT_ERANGE;
+}
+
+// The same with one value per thread, searched among all the cells, for calls of
+// few values, alone (kExFew) or beside the cells: there the workgroups of k_expand_cells are
+// too few to hide their steps. us per call, this and k_expand_cells: 300 K cells,
+// a value in each 11.0 and 12.3, in every 8th 11.0 and 25.9; 1 M, each 18.2 and 16.6,
+// every 2nd 14.8 and 16.4; 5 M, every 4th 42 and 33, every 6th 35 and 38, every 100th
+// 16 and 32; 20 M, every 8th 97 and 85, every 12th 74 and 94.
+constexpr uint64_t kExFew = 1 << 19;
+inline bool expand_far(uint64_t nnz, uint64_t nvals) { return nvals <= kExFew + nnz / 12; }
+
+__global__ __launch_bounds__(kB) void k_expand_far(const int32_t* col, const void* poff, int ow,
+                                                   uint64_t nnz, uint64_t nvals, uint32_t w,
+                                                   int32_t* o_col, void* o_poff, int32_t* d_status) {
+  const bool bad = share_bad(poff, ow, nnz, w);
+  for (uint64_t q = gtid(); q < nvals; q += gstride()) {
+    const uint64_t b = q * w;
+    uint64_t lo = 0, hi = nnz;
+    while (hi - lo > 1) {
+      const uint64_t mid = (lo + hi) >> 1;
+      if (ld_o(poff, mid, ow) <= b) lo = mid;
+      else hi = mid;
+    }
+    gm(o_col)[q] = gm(col)[lo];
+    if (o_poff) st_o(o_poff, q, b, ow);
+  }
+  if (gtid() == 0 && o_poff) st_o(o_poff, nvals, nvals * w, ow);
   if (bad && d_status) *d_status = MGT_ERANGE;
 }
 
@@ -447,11 +509,17 @@ int mgt_expand(int64_t n_rows, int64_t nnz, int64_t payload_bytes, int32_t offse
   hipLaunchKernelGGL(vl::k_expand_rows, vl::grid_for(r + 1), dim3(vl::kB), 0, stream, row_ptr,
                      payload_off, ow, r, n, w, o_row_ptr, d_status);
   // at least one workgroup (for the status), and enough to check the offsets side by side
-  const uint64_t blocks = std::max<uint64_t>((nvals + vl::kExVals - 1) / vl::kExVals,
+  const bool far = vl::expand_far(n, nvals);
+  const uint64_t vals = far ? vl::kB : vl::kExVals;
+  const uint64_t blocks = std::max<uint64_t>((nvals + vals - 1) / vals,
                                              (n + 1 + 8 * vl::kB - 1) / (8 * vl::kB));
-  hipLaunchKernelGGL(vl::k_expand_cells, dim3((unsigned)std::min<uint64_t>(blocks, 1u << 20)),
-                     dim3(vl::kB), 0, stream, col, payload_off, ow, n, nvals, w, o_col, o_payload_off,
-                     d_status);
+  const dim3 grid((unsigned)std::min<uint64_t>(blocks, 1u << 20));
+  if (far)
+    hipLaunchKernelGGL(vl::k_expand_far, grid, dim3(vl::kB), 0, stream, col, payload_off, ow, n, nvals, w,
+                       o_col, o_payload_off, d_status);
+  else
+    hipLaunchKernelGGL(vl::k_expand_cells, grid, dim3(vl::kB), 0, stream, col, payload_off, ow, n, nvals, w,
+                       o_col, o_payload_off, d_status);
   MGT_VL_HIP(hipGetLastError());
   return MGT_OK;
 }
