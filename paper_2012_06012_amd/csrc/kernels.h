@@ -240,9 +240,14 @@ struct TileArgs {
   int32_t fixed_w;            // bytes of every cell, or -1
   int32_t n_parts;            // 0: plain call; <= kDirectParts
   int32_t validate;
-  uint64_t* xpart;            // partitioned calls of their own: workspace for X and B by xper
-  uint32_t xper;              // workgroups per source partition (0: k_tile_xfer adds in place)
+  uint64_t* xpart;            // partitioned calls of their own: workspace for X and B by pieces
 };
+// The counting of a partitioned call's transfer matrices (tiles.hip) goes by
+// shares of 2^kXferLg cells, cut into pieces at the partitions.
+constexpr int kXferLg = 12;
+inline uint32_t xfer_pieces(uint64_t nnz, int32_t n_parts) {
+  return (uint32_t)((nnz + (1ull << kXferLg) - 1) >> kXferLg) + (uint32_t)n_parts - 1u;
+}
 struct TileBounds {
   int32_t bounds[kDirectParts + 1];
 };
@@ -263,19 +268,18 @@ struct TileView {
 };
 hipError_t launch_tile_keys(const TileView& v, const TileBounds& b, hipStream_t s);
 // Batch: the items' arguments lie in memory, with running totals of their
-// tiles, buckets, and source partitions of partitioned items (n_items + 1
+// tiles, buckets, and pieces of the counting of partitioned items (n_items + 1
 // entries each).
 struct TileBatch {
   const TileArgs* items;
   const uint32_t* tile_base;
   const uint32_t* bucket_base;
-  const uint32_t* part_base;
+  const uint32_t* piece_base;
   const int32_t* bounds;      // kDirectParts + 1 per partitioned item, in order
   const uint32_t* part_item;  // per item: its index among the partitioned ones
   uint32_t n_items;
-  uint32_t n_tiles, n_buckets, n_parts;  // the totals
+  uint32_t n_tiles, n_buckets, n_pieces;  // the totals
   uint32_t max_buckets;       // of one item
-  uint64_t max_part_cells;    // cells per source partition, the largest item's mean
   int32_t idx;                // every item has perm
   const int32_t* abort_flag;  // of the batch's items that make the passes, launched before: set if
                               // one of them failed, which cancels these too (null: there are none)

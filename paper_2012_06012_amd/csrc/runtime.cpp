@@ -439,7 +439,6 @@ struct TileGeo {
   uint32_t cpb = 1, n_buckets = 0, n_tiles = 0, tile_cells = 0;
   bool uneven = false;  // bucket bounds from sampled columns (k_tile_bounds)
   uint32_t lut_shift = 0, target = 0;
-  uint32_t xper = 0;    // workgroups per source partition that count the transfer matrices
   uint64_t o_table = 0, o_recs = 0, o_bad = 0, o_xpart = 0, o_lut = 0, o_bcol = 0, bytes = 0;
 };
 
@@ -492,12 +491,8 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
   t.o_bad = t.o_recs + align_up(4 * words * nnz, 256);
   t.o_xpart = t.o_bad + align_up(4ull * t.n_tiles, 256);
   t.o_lut = t.o_xpart;
-  if (partitioned && !batch_cells) {
-    // about 4,096 cells (two rounds of loads) per workgroup, one chain of latencies
-    const uint64_t R = (uint64_t)d.n_parts;
-    t.xper = (uint32_t)(nnz / (R * 4096u) + 1);
-    t.o_lut += align_up(8 * t.xper * R * R, 256);
-  }
+  if (partitioned && !batch_cells)
+    t.o_lut += align_up(8ull * (uint64_t)d.n_parts * (xfer_pieces(nnz, d.n_parts) + 1ull), 256);
   t.o_bcol = t.o_lut + align_up(2ull * kTileBins, 256);
   t.bytes = t.uneven ? t.o_bcol + align_up(4ull * (t.n_buckets + 1), 256) : t.o_lut;
   t.ok = max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
@@ -1069,7 +1064,6 @@ TileArgs tile_args(const HostItem& it, const TileGeo& t, bool partitioned, uint3
   a.validate = (flags & MGT_VALIDATE) ? 1 : 0;
   a.vval = v.vval;
   a.xpart = (uint64_t*)(W + t.o_xpart);
-  a.xper = t.xper;
   if (partitioned) a.n_parts = d.n_parts;
   return a;
 }
@@ -1251,7 +1245,7 @@ struct BatchRun {
   std::vector<uint64_t> at;      // their workspaces
   uint64_t n_partitioned = 0;
   uint64_t o_up = 0;             // the tiles' uploaded tables
-  uint64_t o_items = 0, o_tile = 0, o_bucket = 0, o_part = 0, o_pidx = 0, o_bounds = 0, up_bytes = 0;
+  uint64_t o_items = 0, o_tile = 0, o_bucket = 0, o_piece = 0, o_pidx = 0, o_bounds = 0, up_bytes = 0;
   uint64_t bytes = 0;
 };
 
@@ -1292,7 +1286,7 @@ void plan_batch(const mgt_plan_s* p, const std::vector<HostItem>& items, const T
     r.o_items = take(sizeof(TileArgs) * n);
     r.o_tile = take(4 * (n + 1));
     r.o_bucket = take(4 * (n + 1));
-    r.o_part = take(4 * (n + 1));
+    r.o_piece = take(4 * (n + 1));
     r.o_pidx = take(4 * n);
     r.o_bounds = take(4ull * (kDirectParts + 1) * r.n_partitioned);
     r.up_bytes = o - r.o_up;
@@ -1324,11 +1318,11 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
   TileArgs* const items = (TileArgs*)(H + r.o_items);
   uint32_t* const tb = (uint32_t*)(H + r.o_tile);
   uint32_t* const bb = (uint32_t*)(H + r.o_bucket);
-  uint32_t* const pb = (uint32_t*)(H + r.o_part);
+  uint32_t* const pb = (uint32_t*)(H + r.o_piece);
   uint32_t* const pi = (uint32_t*)(H + r.o_pidx);
   int32_t* const bounds = (int32_t*)(H + r.o_bounds);
   TileBatch b{};
-  uint64_t tiles = 0, buckets = 0, parts = 0, np = 0;
+  uint64_t tiles = 0, buckets = 0, pieces = 0, np = 0;
   for (size_t i = 0; i < n; ++i) {
     const HostItem& it = r.tiles[i];
     const bool part = it.d.n_parts > 1;
@@ -1336,7 +1330,7 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
     std::memcpy(&items[i], &a, sizeof(a));
     tb[i] = (uint32_t)tiles;
     bb[i] = (uint32_t)buckets;
-    pb[i] = (uint32_t)parts;
+    pb[i] = (uint32_t)pieces;
     pi[i] = (uint32_t)np;
     tiles += a.n_tiles;
     buckets += a.n_buckets;
@@ -1346,14 +1340,13 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
       for (int32_t q = 0; q <= it.d.n_parts; ++q)
         bounds[np * (kDirectParts + 1) + q] = (int32_t)it.bounds[q];
       ++np;
-      parts += (uint64_t)it.d.n_parts;
-      b.max_part_cells = std::max<uint64_t>(b.max_part_cells, (uint64_t)it.d.nnz / (uint64_t)it.d.n_parts);
+      pieces += xfer_pieces(a.nnz, a.n_parts);
     }
   }
   tb[n] = (uint32_t)tiles;
   bb[n] = (uint32_t)buckets;
-  pb[n] = (uint32_t)parts;
-  if (tiles >= (1ull << 31) || buckets + n >= (1ull << 31)) return MGT_EUNSUPPORTED;
+  pb[n] = (uint32_t)pieces;
+  if (tiles >= (1ull << 31) || buckets + n >= (1ull << 31) || pieces >= (1ull << 31)) return MGT_EUNSUPPORTED;
   uint8_t* const U = W + r.o_up;
   MGT_HIP(hipMemcpyAsync(U, H, r.up_bytes, hipMemcpyHostToDevice, s));
   if (!r.passes.empty()) {
@@ -1366,13 +1359,13 @@ int run_batch(mgt_plan_s* p, BatchRun& r, void* ws, int32_t* d_status, hipStream
   b.items = (const TileArgs*)(U + r.o_items);
   b.tile_base = (const uint32_t*)(U + r.o_tile);
   b.bucket_base = (const uint32_t*)(U + r.o_bucket);
-  b.part_base = (const uint32_t*)(U + r.o_part);
+  b.piece_base = (const uint32_t*)(U + r.o_piece);
   b.part_item = (const uint32_t*)(U + r.o_pidx);
   b.bounds = (const int32_t*)(U + r.o_bounds);
   b.n_items = (uint32_t)n;
   b.n_tiles = (uint32_t)tiles;
   b.n_buckets = (uint32_t)buckets;
-  b.n_parts = (uint32_t)parts;
+  b.n_pieces = (uint32_t)pieces;
   if (!r.passes.empty()) b.abort_flag = (const int32_t*)(W + r.y.o_abort);
   MGT_HIP(launch_tile_batch(b, s));
   return MGT_OK;

@@ -284,25 +284,44 @@ __device__ bool tile_bad(const TileArgs& a, uint32_t t) {
 struct NoBounds {};
 struct XferLds {
   uint32_t cnt[kDirectParts], byt[kDirectParts];
-  int32_t lb[kDirectParts + 1];
+  int32_t lb[kDirectParts + 1];      // the partition bounds
+  uint32_t start[kDirectParts + 1];  // the first cell of every source partition
 };
 
-// Rows of X and B of a partitioned call: workgroups (s, j), j < per, histogram
-// the owners of the columns of source partition s (its cells are consecutive in
-// the input), every per-th chunk each, into L.cnt and L.byt. L.lb holds the
-// partition bounds. Ends with a barrier.
-__device__ __forceinline__ void xfer_count(const TileArgs& a, uint32_t s, uint32_t j, uint32_t per,
-                                           XferLds& L) {
+// The cells are counted in shares of 2^kXferLg, each cut where a source partition
+// starts: share w's cells of source s are piece w + s (pieces follow the cells, a
+// step in w or in s each, so a piece is one pair). A workgroup takes a piece, two
+// rounds of loads, so its time does not hang on how the partitions share the cells
+// (1 M cells, 64 partitions, all cells in one: 410 us with as many workgroups for
+// each partition, now 78; 8 such items of 300 K in a batch 490 and 126).
+// The first piece of source s:
+__device__ __forceinline__ uint32_t xfer_first(const XferLds& L, uint32_t s) {
+  return (L.start[s] >> kXferLg) + s;
+}
+
+// Counts piece p by the owners of its cells' columns into L.cnt and L.byt;
+// bounds: the item's partition bounds. Returns its source partition. Ends with a
+// barrier.
+__device__ __forceinline__ uint32_t xfer_count(const TileArgs& a, uint32_t p, const int32_t* bounds,
+                                               XferLds& L) {
   const uint32_t R = (uint32_t)a.n_parts, tid = threadIdx.x;
-  for (uint32_t i = tid; i < R; i += kTh) {
-    L.cnt[i] = 0;
-    L.byt[i] = 0;
+  static_assert(kDirectParts < kTh, "a partition bound per thread");
+  if (tid <= R) {
+    const int32_t b = bounds[tid];
+    L.lb[tid] = b;
+    L.start[tid] = (uint32_t)min((uint64_t)ld_off(a.row_ptr, (uint32_t)b, a.lg), a.nnz);
+  }
+  if (tid < R) {
+    L.cnt[tid] = 0;
+    L.byt[tid] = 0;
   }
   __syncthreads();
-  const uint64_t kb = min((uint64_t)ld_off(a.row_ptr, (uint32_t)L.lb[s], a.lg), a.nnz);
-  const uint64_t ke = min((uint64_t)ld_off(a.row_ptr, (uint32_t)L.lb[s + 1], a.lg), a.nnz);
+  // the last source whose first piece is p or before (at least the first one, as its is 0)
+  const uint32_t s = (uint32_t)max(__syncthreads_count(tid < R && xfer_first(L, tid) <= p), 1) - 1u;
+  const uint64_t w = p > s ? p - s : 0u;
+  const uint64_t kb = max((uint64_t)L.start[s], w << kXferLg), ke = min((uint64_t)L.start[s + 1], (w + 1) << kXferLg);
   constexpr uint64_t kQ = 4, kChunk = kTh * kQ;
-  for (uint64_t c0 = kb + j * kChunk; c0 < ke; c0 += per * kChunk) {
+  for (uint64_t c0 = kb; c0 < ke; c0 += kChunk) {
     uint32_t c[kQ], p0[kQ], p1[kQ];
 #pragma unroll
     for (uint32_t q = 0; q < kQ; ++q) {
@@ -311,18 +330,19 @@ __device__ __forceinline__ void xfer_count(const TileArgs& a, uint32_t s, uint32
       p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : 0u;
       p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, k + 1, a.lg) : (uint32_t)a.fixed_w;
     }
+    uint32_t owner[kQ] = {};  // the last partition starting at or before the column
+    for (uint32_t len = R; len > 1; len -= len / 2) {
+#pragma unroll
+      for (uint32_t q = 0; q < kQ; ++q)
+        owner[q] += L.lb[owner[q] + len / 2] <= (int32_t)c[q] ? len / 2 : 0u;
+    }
 #pragma unroll
     for (uint32_t q = 0; q < kQ; ++q) {
+      if (c0 + q * kTh >= ke) break;  // (block-uniform)
       const bool act = c0 + q * kTh + tid < ke;
-      uint32_t lo = 0, hi = R;  // the last partition starting at or before the column
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (L.lb[mid] <= (int32_t)c[q]) lo = mid;
-        else hi = mid;
-      }
       // runs of equal owners in consecutive lanes add up first (sorted rows
       // give a wave few owners), one atomic pair per run
-      const uint32_t d = act ? lo : 0xffffffffu, z = act ? p1[q] - p0[q] : 0u;
+      const uint32_t d = act ? owner[q] : 0xffffffffu, z = act ? p1[q] - p0[q] : 0u;
       const uint32_t lane = lane_id();
       const uint32_t prev = __shfl_up(d, 1, kWave), next = __shfl_down(d, 1, kWave);
       const uint64_t heads = ballot(lane == 0 || prev != d);
@@ -337,19 +357,17 @@ __device__ __forceinline__ void xfer_count(const TileArgs& a, uint32_t s, uint32
     }
   }
   __syncthreads();
+  return s;
 }
 
-// A batch's partitioned items: the rows are added to X and B, which the sort
+// A batch's partitioned items: the counts are added to X and B, which the sort
 // has cleared.
 __global__ __launch_bounds__(kTh) void k_tile_xfer(TileBatch bt) {
   __shared__ XferLds L;
-  uint32_t s = blockIdx.x;
-  const uint32_t i = coop_item(bt.part_base, bt.n_items, s);
+  const uint32_t i = coop_item(bt.piece_base, bt.n_items, blockIdx.x);
   const TileArgs a = load_item(bt.items, i);
-  s -= bt.part_base[i];
-  for (uint32_t j = threadIdx.x; j <= (uint32_t)a.n_parts; j += kTh)
-    L.lb[j] = gm(bt.bounds)[(uint64_t)bt.part_item[i] * (kDirectParts + 1) + j];
-  xfer_count(a, s, blockIdx.y, gridDim.y, L);
+  const uint32_t s = xfer_count(a, blockIdx.x - bt.piece_base[i],
+                                bt.bounds + (uint64_t)bt.part_item[i] * (kDirectParts + 1), L);
   const uint32_t R = (uint32_t)a.n_parts;
   for (uint32_t d = threadIdx.x; d < R; d += kTh) {
     if (!L.cnt[d]) continue;
@@ -361,22 +379,64 @@ __global__ __launch_bounds__(kTh) void k_tile_xfer(TileBatch bt) {
   }
 }
 
-// X and B from the workgroups' rows, by one workgroup (all zero for an input
-// that failed its checks). Ends with a barrier.
-__device__ void xfer_sum(const TileArgs& a, bool bad) {
-  const uint32_t rr = (uint32_t)a.n_parts * (uint32_t)a.n_parts;
-  for (uint32_t e = threadIdx.x; e < rr; e += kTh) {
-    uint64_t cells = 0, bytes = 0;
-    if (!bad) {
-#pragma unroll 8
-      for (uint32_t j = 0; j < a.xper; ++j) {
-        const uint64_t v = gm(a.xpart)[(uint64_t)j * rr + e];
-        cells += v & 0xffffffffu;
-        bytes += v >> 32;
-      }
+// A call of its own: piece p's counts to its row of xpart (cells | bytes << 32
+// by destination), which start after every source's pieces (first | number << 32).
+__device__ __forceinline__ void xfer_piece(const TileArgs& a, uint32_t p, const int32_t* bounds, XferLds& L) {
+  xfer_count(a, p, bounds, L);
+  const uint32_t R = (uint32_t)a.n_parts, d = threadIdx.x;
+  if (d >= R) return;
+  gm(a.xpart)[((uint64_t)p + 1) * R + d] = L.cnt[d] | (uint64_t)L.byt[d] << 32;
+  if (p == 0) {
+      const uint32_t c0 = L.start[d], c1 = L.start[d + 1];
+    const uint32_t n = c1 > c0 ? ((c1 - 1u) >> kXferLg) - (c0 >> kXferLg) + 1u : 0u;
+    gm(a.xpart)[d] = xfer_first(L, d) | (uint64_t)n << 32;
+  }
+}
+
+// X and B from the pieces, by one workgroup (all zero for an input that failed
+// its checks), kEntries entries of a thread and two pieces of each in flight. src:
+// LDS for kDirectParts words. Ends with a barrier.
+__device__ void xfer_sum(const TileArgs& a, bool bad, uint64_t* src) {
+  const uint32_t R = (uint32_t)a.n_parts, rr = R * R;
+  constexpr int kEntries = 4;
+  const GMEM uint64_t* const part = gm(a.xpart);
+  for (uint32_t s = threadIdx.x; s < R; s += kTh) src[s] = bad ? 0ull : part[s];
+  __syncthreads();
+  for (uint32_t e0 = threadIdx.x; e0 < rr; e0 += kEntries * kTh) {
+    uint32_t n[kEntries], row[kEntries];
+    uint64_t v[kEntries][2];
+#pragma unroll
+    for (int q = 0; q < kEntries; ++q) {
+      const uint32_t e = min(e0 + q * kTh, rr - 1u), s = e / R;
+      n[q] = e0 + q * kTh < rr ? (uint32_t)(src[s] >> 32) : 0u;
+      row[q] = n[q] ? ((uint32_t)src[s] + 1u) * R + (e - s * R) : 0u;
+      v[q][0] = part[row[q]];
+      v[q][1] = part[row[q] + (n[q] > 1u ? R : 0u)];
     }
-    gm(a.xfer_cells)[e] = (int64_t)cells;
-    gm(a.xfer_bytes)[e] = (int64_t)bytes;
+#pragma unroll
+    for (int q = 0; q < kEntries; ++q) {
+      uint64_t cells = 0, bytes = 0;
+      auto add = [&](bool in, uint64_t x) {
+        cells += in ? x & 0xffffffffu : 0u;
+        bytes += in ? x >> 32 : 0u;
+      };
+      add(n[q] > 0u, v[q][0]);
+      add(n[q] > 1u, v[q][1]);
+      auto more = [&](auto k, uint32_t j) {  // k of them from j on
+        uint64_t x[k()];
+#pragma unroll
+        for (uint32_t i = 0; i < k(); ++i) x[i] = part[row[q] + min(j + i, n[q] - 1u) * R];
+#pragma unroll
+        for (uint32_t i = 0; i < k(); ++i) add(j + i < n[q], x[i]);
+      };
+      uint32_t j = 2;
+      for (; j + 4u < n[q]; j += 16) more(std::integral_constant<uint32_t, 16>{}, j);
+      if (j < n[q]) more(std::integral_constant<uint32_t, 4>{}, j);
+      const uint32_t e = e0 + q * kTh;
+      if (e >= rr) break;
+      gm(a.xfer_cells)[e] = (int64_t)cells;
+      gm(a.xfer_bytes)[e] = (int64_t)bytes;
+    }
   }
   __syncthreads();
 }
@@ -418,10 +478,10 @@ __device__ void tile_tails(const TileArgs& a, uint64_t* red) {
 // region (whole lines by the time they leave the L2).
 // kVal: every cell carries a value of its own (vval) in place of its row id.
 // kParts: a partitioned call of its own; the workgroups past the tiles count its
-// transfer matrices, (s, j) its s-th source partition's j-th share, into xpart
-// for the merge's first workgroup to add up. In a launch between the two
-// kernels, with atomic adds, the calls took (137 K cells, 13 partitions) 30.3 us, now
-// 24.0; (1 M, 64) 71.5, now 67; (4.3 M, 37) 185, now 181.
+// transfer matrices, a piece each, into xpart for the merge's first workgroup to
+// add up. In a launch between the two kernels, with atomic adds, the calls took
+// (137 K cells, 13 partitions) 30.3 us, beside the tiles 24.0; (1 M, 64) 71.5 and 67;
+// (4.3 M, 37) 185 and 181.
 template <bool kIdx, bool kBatch, bool kVal = false, bool kParts = false>
 __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt,
                                                       std::conditional_t<kParts, TileBounds, NoBounds> pb) {
@@ -434,12 +494,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
   uint32_t t = blockIdx.x;
   if constexpr (kParts) {
     if (t >= one.n_tiles) {
-      const uint32_t R = (uint32_t)one.n_parts, s = (t - one.n_tiles) / one.xper,
-                     j = (t - one.n_tiles) % one.xper;
-      for (uint32_t i = threadIdx.x; i <= R; i += kTh) U.xfer.lb[i] = pb.bounds[i];
-      xfer_count(one, s, j, one.xper, U.xfer);
-      for (uint32_t d = threadIdx.x; d < R; d += kTh)
-        gm(one.xpart)[((uint64_t)j * R + s) * R + d] = U.xfer.cnt[d] | (uint64_t)U.xfer.byt[d] << 32;
+      xfer_piece(one, t - one.n_tiles, pb.bounds, U.xfer);
       return;
     }
   }
@@ -821,7 +876,7 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_merge(TileArgs one, TileBatch b
         if (a.t_poff) st_off(a.t_poff, a.nnz, (int64_t)a.payload_bytes, a.lg);
       }
     }
-    if (!kBatch && a.n_parts > 0) xfer_sum(a, bad);
+    if (!kBatch && a.n_parts > 0) xfer_sum(a, bad, (uint64_t*)L.row);
     if (!bad && a.n_parts > 0) tile_tails(a, L.red64);
     return;
   }
@@ -1113,8 +1168,8 @@ static void launch_tile_kernels(const TileArgs& a, const TileBounds& b, hipStrea
   if (a.vval)
     hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, true>), dim3(a.n_tiles), th, dyn, s, a, none, nob);
   else if (a.n_parts > 0)
-    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, false, true>),
-                       dim3(a.n_tiles + (uint32_t)a.n_parts * a.xper), th, dyn, s, a, none, b);
+    hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false, false, true>), dim3(a.n_tiles + xfer_pieces(a.nnz, a.n_parts)), th,
+                       dyn, s, a, none, b);
   else
     hipLaunchKernelGGL((tl::k_tile_sort<kIdx, false>), dim3(a.n_tiles), th, dyn, s, a, none, nob);
   hipLaunchKernelGGL((tl::k_tile_merge<kIdx, false>), dim3(tl::kMergeLead + a.g8), th, 0, s, a, none);
@@ -1137,10 +1192,7 @@ static void launch_batch_kernels(const TileBatch& b, hipStream_t s) {
   const TileArgs none{};
   hipLaunchKernelGGL((tl::k_tile_sort<kIdx, true>), dim3(b.n_tiles), dim3(tl::kTh),
                      tl::sort_dyn_bytes(b.max_buckets), s, none, b, tl::NoBounds{});
-  if (b.n_parts) {
-    const uint64_t per = std::min<uint64_t>(b.max_part_cells / 4096u + 1, 65535);
-    hipLaunchKernelGGL(tl::k_tile_xfer, dim3(b.n_parts, (unsigned)per), dim3(tl::kTh), 0, s, b);
-  }
+  if (b.n_pieces) hipLaunchKernelGGL(tl::k_tile_xfer, dim3(b.n_pieces), dim3(tl::kTh), 0, s, b);
   hipLaunchKernelGGL((tl::k_tile_merge<kIdx, true>), dim3(((b.n_buckets + 7u) & ~7u) + b.n_items),
                      dim3(tl::kTh), 0, s, none, b);
 }
