@@ -2218,11 +2218,15 @@ __global__ __launch_bounds__(kBkBlock, 4) void k_finish_bucket(FinishArgs a) {
 // The work grows with cells times workgroups, so it pays up to about
 // kDirectCells cells (runtime.cpp: use_direct, where both sides are given). A
 // wave whose cells outgrow its list (kDirList; skewed columns) reads its share
-// of the input again instead.
+// of the input again instead, 256 cells at a time. What crowds into few columns is
+// placed by few workgroups, so what a wave does one after another counts there:
+// four rounds of 64 share their row searches and payload loads, and the bytes of
+// equal columns come from a scan per column (45 K cells in one column 158 us, 470 one
+// round at a time with a shuffle per equal cell; half of them in one 101 and 253).
 constexpr int kDirThreads = 1024;
 constexpr int kDirNW = kDirThreads / kWave;
 constexpr int kDirRows = 8192;   // row offsets kept in LDS
-constexpr int kDirList = 256;    // listed cells per wave
+constexpr int kDirList = 384;    // listed cells per wave
 constexpr int kDirBatch = 8;     // rounds of 64 cells in flight per wave
 
 struct DirectLds {
@@ -2236,73 +2240,95 @@ struct DirectLds {
   uint32_t below[kDirNW], bytes[kDirNW];
   uint32_t red[kDirNW];
 };
-static_assert(sizeof(DirectLds) <= 128 * 1024, "one workgroup per CU");
+static_assert(sizeof(DirectLds) <= 160 * 1024, "one workgroup per CU");
 
-// Places the wave's first n <= 64 listed cells.
+// Places n <= 64 N of the wave's listed cells, from the at-th on, 64 at a time
+// with their row searches and payload loads side by side.
+template <int N>
 __device__ __forceinline__ void direct_place(const DirectArgs& a, DirectLds& L, uint32_t w, uint32_t n,
-                                             uint32_t at, uint32_t nc, uint32_t cell0, uint32_t byte0,
-                                             bool rows_lds, int dbits) {
+                                             uint32_t at, uint32_t cell0, uint32_t byte0, bool rows_lds,
+                                             int dbits) {
   const uint32_t lane = lane_id();
-  const bool act = lane < n;
-  const uint32_t i = at + (act ? lane : 0u);
-  const uint32_t k = L.k[w][i], c = L.c[w][i];
-  const uint32_t z = act ? L.z[w][i] : 0u, o = L.o[w][i];
-  uint8_t* pd[1] = {a.t_payload};
-  const uint8_t* ps[1] = {a.payload + o};
-  const uint32_t pz[1] = {z};
+  uint32_t k[N], c[N], z[N], o[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const bool act = q * kWave + lane < n;
+    const uint32_t i = at + (act ? q * kWave + lane : 0u);
+    k[q] = L.k[w][i];
+    c[q] = L.c[w][i];
+    z[q] = act ? L.z[w][i] : 0u;
+    o[q] = L.o[w][i];
+  }
   // row of the cell: the last row starting at or before it
-  uint32_t lo = 0, hi = (uint32_t)a.n_rows;
+  uint32_t row[N] = {};
   if (rows_lds) {
-    while (ballot(hi - lo > 1)) {
-      const uint32_t mid = (lo + hi) >> 1;
-      const bool up = L.rp[mid] <= k;
-      if (hi - lo > 1) {
-        lo = up ? mid : lo;
-        hi = up ? hi : mid;
-      }
+    for (uint32_t len = (uint32_t)a.n_rows; len > 1; len -= len / 2) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) row[q] += L.rp[row[q] + len / 2] <= k[q] ? len / 2 : 0u;
     }
   } else {
-    while (ballot(hi - lo > 1)) {
-      const uint32_t mid = (lo + hi) >> 1;
-      const bool up = ld_lo(a.row_ptr, mid, a.lg) <= k;
-      if (hi - lo > 1) {
-        lo = up ? mid : lo;
-        hi = up ? hi : mid;
-      }
+    for (uint32_t len = (uint32_t)a.n_rows; len > 1; len -= len / 2) {
+#pragma unroll
+      for (int q = 0; q < N; ++q) row[q] += ld_lo(a.row_ptr, row[q] + len / 2, a.lg) <= k[q] ? len / 2 : 0u;
     }
   }
-  const uint64_t peers = match_peers(c, act, dbits);
-  const uint32_t rank = popc_below(peers);
-  uint32_t pre = 0;  // bytes of the equal columns in the lanes below
-  uint64_t rem = act ? peers & ((1ull << lane) - 1ull) : 0ull;
-  while (ballot(rem != 0)) {
-    const int b = rem ? __ffsll((unsigned long long)rem) - 1 : (int)lane;
-    const uint32_t zz = (uint32_t)__shfl((int)z, b, kWave);
-    if (rem) pre += zz;
-    rem &= rem - 1ull;
+  uint32_t pos[N], bpos[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const bool act = q * kWave + lane < n;
+    pos[q] = 0;
+    bpos[q] = 0;
+    if (N > 1 && q * kWave >= n) continue;  // (wave-uniform)
+    const uint64_t peers = match_peers(c[q], act, dbits);
+    const uint32_t rank = popc_below(peers), size = (uint32_t)__popcll(peers);
+    // bytes of the equal columns in the lanes below: a scan for each column of
+    // many cells, the others one by one
+    constexpr uint32_t kFew = 4;
+    uint32_t pre = 0;
+    for (uint64_t many = ballot(act && rank == 0 && size > kFew); many; many &= many - 1ull) {
+      const int b = __ffsll((unsigned long long)many) - 1;
+      const uint32_t mlo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)peers, b);
+      const uint32_t mhi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(peers >> 32), b);
+      const bool in = ((((uint64_t)mhi << 32) | mlo) >> lane) & 1ull;
+      const uint32_t incl = wave_incl_scan_u32(in ? z[q] : 0u);
+      if (in) pre = incl - z[q];
+    }
+    uint64_t rem = act && size <= kFew ? peers & ((1ull << lane) - 1ull) : 0ull;
+    while (ballot(rem != 0)) {
+      const int b = rem ? __ffsll((unsigned long long)rem) - 1 : (int)lane;
+      const uint32_t zz = (uint32_t)__shfl((int)z[q], b, kWave);
+      if (rem) pre += zz;
+      rem &= rem - 1ull;
+    }
+    const uint32_t e = c[q] * kDirNW + w;
+    if (act) {
+      pos[q] = cell0 + L.cnt[e] + rank;
+      bpos[q] = byte0 + L.byt[e] + pre;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (act && rank + 1u == size) {  // the column's last cell moves its place on
+      L.cnt[e] += rank + 1u;
+      L.byt[e] += pre + z[q];
+    }
+    __builtin_amdgcn_wave_barrier();
   }
-  uint32_t pos = 0, bpos = 0;
-  if (act) {
-    const uint32_t e = c * kDirNW + w;
-    pos = cell0 + L.cnt[e] + rank;
-    bpos = byte0 + L.byt[e] + pre;
+  uint8_t* pd[N];
+  const uint8_t* ps[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    pd[q] = a.t_payload + bpos[q];
+    ps[q] = a.payload + o[q];
   }
-  __builtin_amdgcn_wave_barrier();
-  if (act && rank + 1u == (uint32_t)__popcll(peers)) {  // the column's last cell moves its place on
-    const uint32_t e = c * kDirNW + w;
-    L.cnt[e] += rank + 1u;
-    L.byt[e] += pre + z;
+  PayRegsT<N> P;
+  pay_load(P, ps, z, a.payload, a.payload + a.payload_bytes);
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    if (q * kWave + lane >= n) continue;
+    gm(a.t_col)[pos[q]] = (int32_t)row[q];
+    if (a.perm) gm(a.perm)[pos[q]] = k[q];
+    if (a.t_poff) st_off(a.t_poff, pos[q], (int64_t)bpos[q], a.lg == 3 ? 8 : 4);
   }
-  __builtin_amdgcn_wave_barrier();
-  pd[0] = a.t_payload + bpos;
-  PayRegsT<1> P;
-  pay_load(P, ps, pz, a.payload, a.payload + a.payload_bytes);
-  if (act) {
-    gm(a.t_col)[pos] = (int32_t)lo;
-    if (a.perm) gm(a.perm)[pos] = k;
-    if (a.t_poff) st_off(a.t_poff, pos, (int64_t)bpos, a.lg == 3 ? 8 : 4);
-  }
-  pay_store(P, pd, ps, pz);
+  pay_store(P, pd, ps, z);
 }
 
 __global__ __launch_bounds__(kDirThreads) void k_direct(DirectArgs a) {
@@ -2440,42 +2466,49 @@ __global__ __launch_bounds__(kDirThreads) void k_direct(DirectArgs a) {
   // starts above: wave 0's, whose first batch waits for this barrier)
   __syncthreads();
   const int dbits = ceil_log2(nc);
-  if (nsel <= (uint32_t)kDirList) {
-    for (uint32_t at = 0; at < nsel; at += kWave)
-      direct_place(a, L, w, min((uint32_t)kWave, nsel - at), at, nc, cell0, byte0, rows_lds, dbits);
+  if (nsel <= (uint32_t)kWave) {
+    if (nsel) direct_place<1>(a, L, w, nsel, 0, cell0, byte0, rows_lds, dbits);
     return;
   }
-  // more cells than the list holds: read the share again, a full batch at a time
-  uint32_t n = 0;
-  for (uint32_t k0 = kb; k0 < ke; k0 += kWave) {
-    const uint32_t k = min(k0 + lane, last);
-    const uint32_t c = (uint32_t)gm(a.col)[k];
-    const bool sel = k0 + lane < ke && c >= col0 && c - col0 < nc;
-    const uint64_t m = ballot(sel);
-    if (m == 0) continue;
-    if (sel) {
-      const uint32_t at = n + popc_below(m);  // under 128
-      const uint32_t p0 = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : k * (uint32_t)a.fixed_w;
-      const uint32_t p1 = a.fixed_w < 0 ? ld_lo(a.poff, (uint64_t)k + 1, a.lg) : p0 + (uint32_t)a.fixed_w;
-      L.k[w][at] = k;
-      L.z[w][at] = p1 - p0;
-      L.o[w][at] = p0;
-      L.c[w][at] = (uint16_t)(c - col0);
-    }
-    n += (uint32_t)__popcll(m);
-    __builtin_amdgcn_wave_barrier();
-    if (n < (uint32_t)kWave) continue;
-    direct_place(a, L, w, kWave, 0, nc, cell0, byte0, rows_lds, dbits);
-    n -= kWave;
-    if (lane < n) {  // the rest to the front
-      L.k[w][lane] = L.k[w][kWave + lane];
-      L.z[w][lane] = L.z[w][kWave + lane];
-      L.o[w][lane] = L.o[w][kWave + lane];
-      L.c[w][lane] = L.c[w][kWave + lane];
-    }
-    __builtin_amdgcn_wave_barrier();
+  constexpr uint32_t kSide = 4, kFlush = kDirList - kSide * kWave;
+  if (nsel <= (uint32_t)kDirList) {
+    for (uint32_t at = 0; at < nsel; at += kSide * kWave)
+      direct_place<kSide>(a, L, w, min(kSide * kWave, nsel - at), at, cell0, byte0, rows_lds, dbits);
+    return;
   }
-  if (n) direct_place(a, L, w, n, 0, nc, cell0, byte0, rows_lds, dbits);
+  // more cells than the list holds: read the share again, the list placed whenever
+  // another step might not fit
+  uint32_t n = 0;
+  for (uint32_t k0 = kb; k0 < ke; k0 += kSide * kWave) {
+    uint32_t c[kSide], p0[kSide], p1[kSide];
+#pragma unroll
+    for (uint32_t q = 0; q < kSide; ++q) {
+      const uint32_t k = min(k0 + q * kWave + lane, last);
+      c[q] = (uint32_t)gm(a.col)[k];
+      p0[q] = a.fixed_w < 0 ? ld_lo(a.poff, k, a.lg) : k * (uint32_t)a.fixed_w;
+      p1[q] = a.fixed_w < 0 ? ld_lo(a.poff, (uint64_t)k + 1, a.lg) : p0[q] + (uint32_t)a.fixed_w;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kSide; ++q) {
+      const uint32_t k = k0 + q * kWave + lane, cc = c[q] - col0;
+      const bool sel = k < ke && c[q] >= col0 && cc < nc;
+      const uint64_t m = ballot(sel);
+      if (sel) {
+        const uint32_t at = n + popc_below(m);
+        L.k[w][at] = k;
+        L.z[w][at] = p1[q] - p0[q];
+        L.o[w][at] = p0[q];
+        L.c[w][at] = (uint16_t)cc;
+      }
+      n += (uint32_t)__popcll(m);
+    }
+    if (n <= kFlush && k0 + kSide * kWave < ke) continue;
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t at = 0; at < n; at += kSide * kWave)
+      direct_place<kSide>(a, L, w, min(kSide * kWave, n - at), at, cell0, byte0, rows_lds, dbits);
+    __builtin_amdgcn_wave_barrier();
+    n = 0;
+  }
 }
 
 // X and B of a small partitioned call (Section 2 step 2): one workgroup per

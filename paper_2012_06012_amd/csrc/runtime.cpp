@@ -957,8 +957,10 @@ int record_graph(size_t staging_bytes, mgt_graph_s* g, Call call) {
 
 // Small calls take k_direct: one launch (two for a partitioned call) that reads
 // every column id in every workgroup. us per call, direct and tiles: plain (1-8
-// floats per cell) 10 K cells 12.8 and 20.2, 30 K 17.7 and 21.3, 40 K 20.2 and
-// 21.2, 45 K 22.5 and 21.2; over 4 partitions 10 K 17.1 and 19.0, 20 K 21.7 and
+// floats per cell) 10 K cells 11.8 and 20.6, 30 K 17.4 and 21.1, 40 K 19.9 and
+// 21.2, 45 K 22.1 and 21.2; a tenth of the cells in one column 20 K 17.9 and 24.0,
+// 45 K 31.6 and 50.0; half of them 49.7 and 78.8, 101 and 153; columns by a power
+// law 20 K 18.4 and 24.2, 45 K 32.1 and 27.8. Over 4 partitions 10 K 17.1 and 19.0, 20 K 21.7 and
 // 20.1 (recorded and replayed 22.2 and 23.7), 30 K 24.4 and 20.2, 40 K 28.1 and
 // 20.4; over 13 partitions 20 K 21.0 and 20.3, 30 K 23.1 and 20.6; over 37
 // partitions 20 K 21.1 and 23.6, 30 K 22.7 and 23.6, 40 K 25.1 and 23.9. (The
