@@ -71,6 +71,7 @@ struct Tune {
   int pass_bits = 0;     // 1..8, 0: the environment cap / default
   int finish_bits = -1;  // 0..10, -1: the rule's choice
   uint32_t tile = 0;     // 2048..16384 cells, 0: sized for the call
+  int finish_cap = -1;   // the environment's cap on finish widths, where the caller has read it
 };
 
 // Schedule caps from the environment: MGT_MAX_PASS_BITS (1..8) bounds the bits
@@ -200,11 +201,12 @@ Sched make_sched_tuned(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32
                        const int64_t* bounds, bool partitioned, bool spread, const Tune* t,
                        int level_budget = 0, bool split = false) {
   const int mb = (t && t->pass_bits > 0) ? t->pass_bits : max_pass_bits();
+  const int mf = (t && t->finish_cap >= 0) ? t->finish_cap : max_finish_bits();
   const int ff = (t && t->finish_bits >= 0) ? t->finish_bits : -1;
   const uint32_t tile = (t && t->tile) ? t->tile : tile_cells_for((uint64_t)std::max<int64_t>(nnz, 0));
   const bool wide = spread && tile >= (uint32_t)kWideSub;
   const int last_cap = (wide && mb >= kMaxBitsPerPass) ? kMaxLastPassBits : mb;
-  Sched s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, max_finish_bits(),
+  Sched s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, mf,
                           spread, ff, last_cap, level_budget, split);
   // A finish bucket of fewer than 2^kWideFinishMinBits columns carries the
   // spread of single column degrees: on skewed inputs many such buckets
@@ -212,7 +214,7 @@ Sched make_sched_tuned(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32
   // the buckets it buys span that many columns.
   if (last_cap > mb && s.n_levels >= 2 && s.bits[s.n_levels - 1] > mb &&
       s.finish_bits < kWideFinishMinBits)
-    s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, max_finish_bits(),
+    s = make_sched_mb(n_cols, nnz, payload_bytes, R, bounds, partitioned, mb, mf,
                       spread, ff, mb, level_budget, split);
   return s;
 }
@@ -444,9 +446,16 @@ struct TileGeo {
 
 constexpr uint64_t kTileSlots = 512;  // workgroups of either kernel that run at once
 
+// Whether the environment leaves calls to that form (caps on the passes' schedules
+// ask for the passes).
+bool tiles_on() {
+  return max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
+         !env_cap("MGT_NO_PACK", 0, 1, 0) && !env_cap("MGT_NO_TILES", 0, 1, 0);
+}
+
 // crowded: the caller knows some columns to hold far more cells than others.
 // batch_cells: the cells of the batch it is an item of, whose workgroups fill
-// the device together (0: a call of its own).
+// the device together (0: a call of its own); its caller has asked tiles_on().
 TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool crowded = false,
                  uint64_t batch_cells = 0) {
   TileGeo t;
@@ -495,8 +504,7 @@ TileGeo tile_geo(const mgt_desc& d, bool partitioned, const Tune& tune, bool cro
     t.o_lut += align_up(8ull * (uint64_t)d.n_parts * (xfer_pieces(nnz, d.n_parts) + 1ull), 256);
   t.o_bcol = t.o_lut + align_up(2ull * kTileBins, 256);
   t.bytes = t.uneven ? t.o_bcol + align_up(4ull * (t.n_buckets + 1), 256) : t.o_lut;
-  t.ok = max_pass_bits() == kMaxBitsPerPass && max_finish_bits() == kMaxFinishBits &&
-         !env_cap("MGT_NO_PACK", 0, 1, 0) && !env_cap("MGT_NO_TILES", 0, 1, 0);
+  t.ok = batch_cells || tiles_on();
   return t;
 }
 
@@ -1179,6 +1187,9 @@ int batch_items(mgt_plan_s* p, const mgt_item* in, int32_t n, std::vector<HostIt
     tune = p->tune;
   }
   items.resize((size_t)n);
+  Tune caps = tune;  // the environment's caps, read once for all items
+  if (caps.pass_bits == 0) caps.pass_bits = max_pass_bits();
+  caps.finish_cap = max_finish_bits();
   int64_t tn = 0, tc = 0, tr = 0, tp = 0;
   for (int32_t i = 0; i < n; ++i) {
     const mgt_item& m = in[i];
@@ -1200,7 +1211,7 @@ int batch_items(mgt_plan_s* p, const mgt_item* in, int32_t n, std::vector<HostIt
     it.d = m.desc;
     it.bounds = m.desc.part_bounds;
     it.s = make_sched(m.desc.n_cols, m.desc.nnz, m.desc.payload_bytes, m.desc.n_parts,
-                      m.desc.part_bounds, part, false, &tune);
+                      m.desc.part_bounds, part, false, &caps);
     it.tile = tune.tile;
     fill_outputs(it.dev, m.row_ptr, m.col, m.payload_off, m.payload, m.t_row_ptr, m.t_col,
                  m.t_payload_off, m.t_payload, m.perm);
@@ -1255,7 +1266,9 @@ struct BatchRun {
 void plan_batch(const mgt_plan_s* p, const std::vector<HostItem>& items, const Tune& tune,
                 bool tiles_too, BatchRun& r) {
   // device checks cancel a whole batch together: the passes' own business
-  tiles_too = tiles_too && !(p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING));
+  tiles_too = tiles_too && !(p->flags & (MGT_VALIDATE | MGT_DEBUG_TIMING)) && tiles_on();
+  (tiles_too ? r.tiles : r.passes).reserve(items.size());
+  if (tiles_too) r.geo.reserve(items.size());
   uint64_t cells = 0;
   for (const HostItem& it : items) cells += (uint64_t)it.d.nnz;
   for (size_t i = 0; i < items.size(); ++i) {
