@@ -54,6 +54,9 @@ constexpr int kWideFinishMinBits = 5;
 // Mean cells per bucket up to which one pass is enough (the 1,024-thread
 // finish holds 10,240).
 constexpr uint64_t kOneSweepCells = 8192;
+// Bytes of a call's arrays (8-byte offsets, perm) and of its two-pass workspace up
+// to which one pass may become two.
+constexpr uint64_t kSplitBytes = 192ull << 30;
 
 // Digit schedule of one matrix.
 struct Sched {
@@ -164,11 +167,18 @@ Sched make_sched_mb(int64_t n_cols, int64_t nnz, int64_t payload_bytes, int32_t 
   // average): larger ones are sorted in 2,048-cell pieces by a workgroup each,
   // and records-only passes are cheap beside that. Both ways: 2^27 fixed-width
   // cells over 256 partitions 8.56 ms in one pass, 6.23 in two; 10 M cells of
-  // 8-16 bytes 812 and 543 us.
-  if (split && best_L == 1 && best_fb > fb_ideal && nnz > 0 && n_cols > 0 &&
-      (double)nnz / (double)n_cols * (double)(1ull << best_fb) > (double)kOneSweepCells)
+  // 8-16 bytes 812 and 543 us. A second pass takes 24 bytes of workspace per cell
+  // more (a third one, which calls of over 2^30 cells would need, a copy of the
+  // payload besides), so calls whose arrays and workspace would pass kSplitBytes
+  // keep the one pass they fit the device with.
+  const uint64_t split_bytes =
+      (uint64_t)std::max<int64_t>(nnz, 0) * 84u + 3u * (uint64_t)std::max<int64_t>(payload_bytes, 0);
+  if (split && best_L == 1 && best_fb > fb_ideal && nnz > 0 && n_cols > 0 && split_bytes <= kSplitBytes &&
+      (double)nnz / (double)n_cols * (double)(1ull << best_fb) > (double)kOneSweepCells) {
     choose(std::max(fb_ideal, floor_log2_u64((uint64_t)std::max(
                                   1.0, (double)kOneSweepCells * (double)n_cols / (double)nnz))));
+    if (best_L > 2) choose(mf);
+  }
   if (K <= fb_ideal) { best_fb = K; best_L = 1; }
   if (force_fb >= 0) {  // a finish width set by the caller
     best_fb = std::min(force_fb, K);
