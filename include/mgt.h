@@ -154,8 +154,10 @@ int mgt_transpose_partitioned(mgt_plan_t plan, const void* row_ptr, const int32_
 /*
  * Schedule of a single-matrix plan, for tuning (host only). The transpose is
  * a few stable partition passes over the column bits followed by a per-bucket
- * sort; by default the library picks the fewest passes, then the narrowest
- * finish buckets of about 4,096 cells, and tiles sized for the call.
+ * sort (small and mid-size calls take forms of one or two launches instead, unless
+ * a schedule is set); by default the library picks the fewest passes, or two
+ * where one would leave buckets that the sort cannot hold at once, then the
+ * narrowest finish buckets of about 4,096 cells, and tiles sized for the call.
  *   pass_bits   largest digit of a bits-mode pass, 1..8 (0: default)
  *   finish_bits column bits of a finish bucket, 0..10, exactly (-1: default)
  *   tile_cells  cells per tile: 2048, 4096, 8192 or 16384 (0: default)
@@ -167,13 +169,14 @@ int mgt_transpose_partitioned(mgt_plan_t plan, const void* row_ptr, const int32_
  * later submits (finish_bits capped by each item's column bits; an item whose
  * schedule would need more than four passes keeps the rule's), the tile size
  * to the whole batch, *workspace_bytes receives the plan's estimate again,
- * and mgt_batch_workspace gives a batch's exact need. View plans give
+ * and mgt_batch_workspace gives a batch's need. View plans give
  * MGT_EINVAL.
  */
 int mgt_plan_set_schedule(mgt_plan_t plan, int32_t pass_bits, int32_t finish_bits,
                           int32_t tile_cells, size_t* workspace_bytes);
 
-/* The schedule a call on this single-matrix plan uses (host only): out[0] passes,
+/* The schedule a call on this single-matrix plan uses where it makes the passes
+ * (host only): out[0] passes,
  * out[1..4] bits of each pass (partition passes: sub-bits below the
  * partition), out[5] finish bits, out[6] tile cells, out[7] 1 for a
  * partition-mode first pass. partitioned selects mgt_transpose_partitioned. */
@@ -264,19 +267,23 @@ typedef struct {
 } mgt_item;
 
 /* Creates a batch plan. *workspace_bytes receives an estimate for a batch at
- * the limits (payload bytes excluded); mgt_batch_workspace gives the exact
+ * the limits (payload bytes excluded); mgt_batch_workspace gives the
  * requirement of a particular batch. */
 int mgt_batch_plan(const mgt_batch_limits* limits, mgt_plan_t* out, size_t* workspace_bytes);
 
-/* Exact device workspace that mgt_batch_submit needs for these items. Host only. */
+/* Device workspace that mgt_batch_submit runs these items best with. (Smaller ones
+ * are accepted down to what the partition passes take for all of them.) Host only. */
 int mgt_batch_workspace(mgt_plan_t batch_plan, const mgt_item* items, int32_t n_items,
                         size_t* workspace_bytes);
 
 /*
- * Transposes every item of the batch with one fixed sequence of stage kernels
- * whose grids cover all items at once (the item count does not change the
- * number of launches). Items may differ in size, payload width and partition
- * count. The descriptor table is copied to the device through the plan's
+ * Transposes every item of the batch with at most two fixed sequences of stage
+ * kernels, one for the items whose size fits the two-launch form and one, before
+ * it, for the others, whose grids cover all of their items at once (the item
+ * count does not change the number of launches). Items may differ in size, payload
+ * width and partition count. An item that fails (MGT_EUNSUPPORTED, or MGT_ERANGE
+ * with MGT_VALIDATE) cancels all others (MGT_ECANCELED), which may then be
+ * submitted again. The descriptor table is copied to the device through the plan's
  * pinned staging buffer; the call returns once the copy is queued. d_status
  * (may be NULL) receives one status word per item. If `done` is not NULL it
  * is recorded on `stream` after the last stage.
@@ -392,9 +399,10 @@ int mgt_symmetrize(mgt_plan_t plan, int32_t triangle, const void* row_ptr, const
  * MGT_EINVAL). Nothing runs at creation. Each mgt_graph_launch runs the whole
  * call on `stream`, reading the inputs as they are at that time; the buffers
  * must stay allocated while the graph exists, and launches that overlap on
- * one workspace race. The plan may be destroyed after creation. Each replay
- * re-uploads the graph's descriptor copy (status words and first-pass tables
- * included) and clears counters with kernel stores (it records no memset).
+ * one workspace race. The plan may be destroyed after creation. A call of the
+ * passes re-uploads the graph's descriptor copy (status words and first-pass
+ * tables included) at each replay and clears counters with kernel stores (it
+ * records no memset); the one- and two-launch forms carry their arguments.
  */
 typedef struct mgt_graph_s* mgt_graph_t;
 
@@ -427,9 +435,9 @@ int mgt_graph_destroy(mgt_graph_t graph);
  * runs on holds its own until the process ends). The call allocates nothing
  * (no device or pinned memory, no events) and hands the plan's descriptor to
  * the device through kernel arguments.
- *   - A plan whose transpose needs more workspace than that (the size
- *     mgt_plan reported for this form) gives MGT_ENOMEM before anything is
- *     launched; plans with MGT_DEBUG_TIMING give MGT_EINVAL.
+ *   - A plan whose transpose cannot run in that gives MGT_ENOMEM before anything
+ *     is launched (the size mgt_plan reports may lie above what it can run in);
+ *     plans with MGT_DEBUG_TIMING give MGT_EINVAL.
  *   - Every call on one GPU shares that GPU's array, and the array keeps the
  *     last call's contents (no call relies on it starting at zero). Calls whose
  *     device work may overlap on one GPU (several streams, several threads)

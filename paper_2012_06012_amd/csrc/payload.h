@@ -54,9 +54,9 @@ __device__ __forceinline__ void put_global(uint8_t* dst, const v4& a, const v4& 
              [&](uint32_t o, uint8_t x) { d[o] = x; }, a, b, z);
 }
 // The z <= 32 bytes at src (any alignment) as two 16-byte values (what follows
-// them is not cleared), from an array at [begin, end): whole 16-byte loads where
-// 32 bytes follow; at the array's end its last 32 bytes, shifted down; in an
-// array shorter than that, byte by byte.
+// them is not cleared), from an array at [begin, end), no byte outside it: whole
+// 16-byte loads where 32 bytes follow; at the array's end its last 32 bytes,
+// shifted down; in an array shorter than that, byte by byte.
 __device__ __forceinline__ void get_bytes(const uint8_t* src, const uint8_t* begin, const uint8_t* end,
                                           uint32_t z, v4& a, v4& b) {
   const GMEM uint8_t* const s = gm(src);

@@ -17,15 +17,18 @@
 //
 // us per call, this form and the passes (8-byte offsets; 1-8 floats per cell):
 // 100 K cells 28 and 54, 300 K 36 and 65, 1 M 49 and 120, 4 M 151 and 414; 4.3 M
-// cells of 23 bytes over 37 partitions 181 and 850; 6 M cells of 0 to 7 bytes
-// with perm and device checks 181 and 557.
+// cells of 23 bytes over 37 partitions 189 and 869; 6 M cells of 0 to 7 bytes
+// with perm and device checks 218 and 571. Columns that crowd leave some buckets
+// to one workgroup for long, as they do in the passes: half of the cells in one
+// column 300 K 950 and 1,019, 4 M 13,115 and 16,354.
 //
 // Against the passes of kernels.hip: no histogram launches, no scans of
 // (digit, tile) counts and no segment tables between launches; records move
 // once, payloads go from the input to their place. It takes one level of up to
 // kTileBuckets buckets, so it ends where buckets outgrow the LDS of a
-// workgroup. Neither launch needs anything prepared in memory: the arguments
-// travel with the launches.
+// workgroup. A single call with equal buckets needs nothing prepared in memory: its
+// arguments travel with the launches (uneven buckets take a launch before them,
+// batches an uploaded table of items).
 //
 // Record of a cell (3 words, a 4th for perm): payload offset (or the payload
 // itself, up to 4 bytes), row, column within the bucket << 22 | size,
@@ -642,8 +645,9 @@ __global__ __launch_bounds__(kTh, 4) void k_tile_sort(TileArgs one, TileBatch bt
       if (i >= m) continue;
       const uint32_t z = key[r] & kSizeMask;
       uint32_t x = off[r];
-      // a small payload goes in place of its offset: the aligned words that hold
-      // it (each holds one of its bytes; nothing is read past the payload array)
+      // a small payload goes in place of its offset, from the aligned words that hold
+      // it (each holds one of its bytes; the array's first and last word may hold up
+      // to three bytes of its neighbours, no further word is read)
       if (z && z <= kInline && (uint64_t)x + z <= a.payload_bytes) {
         const uint8_t* const p = a.payload + x;
         const uint32_t sh = 8u * ((uint32_t)(uintptr_t)p & 3u);
