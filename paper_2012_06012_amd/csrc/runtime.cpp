@@ -1167,17 +1167,23 @@ int single_call(mgt_plan_s* p, bool partitioned, const void* row_ptr, const int3
   return run(p, Items(items, 1), y, ws, d_status, s);
 }
 
-size_t single_ws(const mgt_desc& d, const int64_t* bounds, bool partitioned, const Tune& t) {
+// Workspace of a single call by the passes (split: two where one would leave
+// buckets past the finish's LDS).
+size_t passes_ws(const mgt_desc& d, const int64_t* bounds, bool partitioned, const Tune& t, bool split) {
   std::vector<HostItem> items(1);
   items[0].d = d;
   if (!partitioned) items[0].d.n_parts = 1;
   items[0].bounds = bounds;
-  const TileGeo tg = tile_geo(d, partitioned, t);
   items[0].s = make_sched(d.n_cols, d.nnz, d.payload_bytes, d.n_parts, bounds, partitioned, true, &t,
-                          0, !tg.ok);
+                          0, split);
   items[0].tile = t.tile;
   std::memset(&items[0].dev, 0, sizeof(ItemDev));
-  return std::max<uint64_t>(make_layout(items).bytes, tg.ok ? tg.bytes : 0);
+  return make_layout(items).bytes;
+}
+
+size_t single_ws(const mgt_desc& d, const int64_t* bounds, bool partitioned, const Tune& t) {
+  const TileGeo tg = tile_geo(d, partitioned, t);
+  return std::max<uint64_t>(passes_ws(d, bounds, partitioned, t, !tg.ok), tg.ok ? tg.bytes : 0);
 }
 
 // Workspace estimate for a batch at the limits; mgt_batch_workspace gives the
@@ -1780,14 +1786,21 @@ struct SymLayout {
   uint64_t bytes;
 };
 
-SymLayout sym_layout(const mgt_plan_s* p) {
+// least: with the smallest workspace that the transpose accepts.
+SymLayout sym_layout(const mgt_plan_s* p, bool least = false) {
   const mgt_desc& d = p->desc;
   const uint64_t n = (uint64_t)d.n_rows, nnz = (uint64_t)d.nnz, ow = (uint64_t)d.offset_width;
   SymLayout y{};
-  // (the transpose of a triangle takes uneven buckets, which a plan made for
-  // any matrix does not count)
-  const TileGeo tg = tile_geo(d, false, p->tune, true);
-  uint64_t o = align_up(std::max<uint64_t>(p->ws_plain, tg.ok ? tg.bytes : 0), 256);
+  uint64_t o;
+  if (least) {
+    o = passes_ws(d, p->bounds.data(), false, p->tune, false);
+  } else {
+    // (the transpose of a triangle takes uneven buckets, which a plan made for
+    // any matrix does not count)
+    const TileGeo tg = tile_geo(d, false, p->tune, true);
+    o = std::max<uint64_t>(p->ws_plain, tg.ok ? tg.bytes : 0);
+  }
+  o = align_up(o, 256);
   auto take = [&](uint64_t bytes) {
     const uint64_t at = o;
     o = align_up(o + bytes, 256);
@@ -1850,6 +1863,7 @@ int mgt_symmetrize(mgt_plan_t plan, int32_t triangle, const void* row_ptr, const
   {
     std::lock_guard<std::mutex> lock(plan->mu);
     y = sym_layout(plan);
+    if (workspace_bytes < y.bytes) y = sym_layout(plan, true);
   }
   if (workspace_bytes < y.bytes) return MGT_ENOMEM;
   uint8_t* W = (uint8_t*)workspace;
